@@ -56,6 +56,117 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 }  // namespace
 
+// ------------------------------------------------------------------ work of a sweep
+// A sweep's blocks of degrees, each swept from its top order down, cut into pieces and
+// dealt to slots of about equal length (s2mi_sweep.hip).
+struct Work {
+    int nblk = 1;                       // blocks (inverse) or degree groups (forward)
+    int tiles = 1, per_item = 1;        // ring tiles (inverse) or ring blocks (forward); workgroups per run: tiles x slots
+    int cb = 1, nk = 1;                 // inverse: chunks per block; forward: four-ring steps per wave
+    int rp = 0;                         // ring stride of a cut's state
+    int nslot = 1, quota = 1, pieces = 1;
+    std::vector<int4> seg;
+    std::vector<int> first;             // [nslot + 1]
+    std::vector<int> cfirst;            // [nblk + 1] first cut of each block
+    std::vector<int2> cuts;             // {order c, cut index}, descending in a block
+    int4 *seg_d = nullptr;
+    int *first_d = nullptr;
+};
+
+namespace {
+
+// Orders per piece that a slot's fixed cost (state load, start of the pipeline)
+// amounts to, and the shortest piece worth a cut.
+constexpr int PIECE_COST = 10, PIECE_MIN = 16;
+
+// (Measured, pair of MW L = 64 spin 2: 342 us with one workgroup per run over all orders,
+// 136 us with the orders in four pieces and both runs in one launch.)
+// Fills seg / first / cuts for blocks of `orders[b]` orders (largest work last), so
+// that `items` runs sharing a launch of `tiles` ring tiles each fill `ncu` compute
+// units: the slot count that minimises (rounds of workgroups) x (orders per slot +
+// fixed cost).  force > 0: every block in `force` pieces (as far as 16 orders go).
+void deal_work(Work &W, const std::vector<int> &orders, int items, int ncu, int force)
+{
+    const int nb = (int)orders.size();
+    long long total = 0;
+    for (int o : orders) total += o;
+    W.nblk = nb;
+    W.seg.clear();
+    W.first.assign(1, 0);
+    W.cuts.clear();
+    std::vector<std::vector<int>> cut_of(nb);
+    if (force > 0) {
+        for (int b = nb - 1; b >= 0; --b) {
+            const int k = std::max(1, std::min(force, orders[b] / PIECE_MIN));
+            int hi = orders[b] - 1;
+            for (int j = k - 1; j >= 0; --j) {
+                const int lo = j == 0 ? 0 : orders[b] * j / k / 4 * 4;
+                if (lo > hi) continue;
+                W.seg.push_back(make_int4(b, hi, lo, hi == orders[b] - 1 ? -1 : 0));
+                if (lo > 0) cut_of[b].push_back(lo);
+                W.first.push_back((int)W.seg.size());
+                hi = lo - 1;
+            }
+        }
+        W.quota = (int)((total + W.first.size() - 2) / std::max<size_t>(1, W.first.size() - 1));
+    } else {
+        const long long wg1 = (long long)W.tiles * items;
+        int best = 1;
+        double cost = 1e300;
+        for (int s = 1; s <= 4096 && (s == 1 || total / s >= PIECE_MIN); ++s) {
+            const double c = (double)((wg1 * s + ncu - 1) / ncu) * ((double)total / s + PIECE_COST);
+            if (c < cost * 0.999) { cost = c; best = s; }
+        }
+        W.quota = std::max(PIECE_MIN, (int)((total + best - 1) / best + 3) / 4 * 4);
+        int room = W.quota;
+        for (int b = nb - 1; b >= 0; --b) {
+            int hi = orders[b] - 1;
+            while (hi >= 0) {
+                int lo = hi + 1 - room;
+                lo = lo <= 7 ? 0 : (lo + 3) / 4 * 4;     // cuts at multiples of 4; no short rest
+                if (lo > hi) lo = hi / 4 * 4;
+                W.seg.push_back(make_int4(b, hi, lo, hi == orders[b] - 1 ? -1 : 0));
+                if (lo > 0) cut_of[b].push_back(lo);
+                room -= hi - lo + 1;
+                hi = lo - 1;
+                if (room <= 7) {
+                    W.first.push_back((int)W.seg.size());
+                    room = W.quota;
+                }
+            }
+        }
+        if (W.first.back() != (int)W.seg.size()) W.first.push_back((int)W.seg.size());
+    }
+    W.nslot = (int)W.first.size() - 1;
+    W.cfirst.assign(1, 0);
+    W.pieces = 1;
+    for (int b = 0; b < nb; ++b) {
+        for (int c : cut_of[b]) W.cuts.push_back(make_int2(c, (int)W.cuts.size()));
+        W.cfirst.push_back((int)W.cuts.size());
+        W.pieces = std::max(W.pieces, (int)cut_of[b].size() + 1);
+    }
+    for (int4 &g : W.seg)
+        if (g.w == 0)
+            for (int q = W.cfirst[g.x]; q < W.cfirst[g.x + 1]; ++q)
+                if (W.cuts[q].x == g.y + 1) g.w = W.cuts[q].y;
+}
+
+// Consecutive slots that one workgroup runs when `items` runs share the launch.
+int merge_slots(const Work &W, long long items, int ncu)
+{
+    int best = 1;
+    double cost = 1e300;
+    for (int k = 1; k <= W.nslot; ++k) {
+        const long long nt = (W.nslot + k - 1) / k, wg = nt * W.tiles * items;
+        // a slot that continues the same block saves its state load
+        const double c = (double)((wg + ncu - 1) / ncu) * ((double)k * W.quota + PIECE_COST);
+        if (c < cost * 0.999) { cost = c; best = k; }
+    }
+    return best;
+}
+
+}  // namespace
+
 // ------------------------------------------------------------------ plan
 struct s2_plan_s {
     int L = 0, spin = 0, N = 1, sampling = 0, nside = 0, max_batch = 1, prec = 0;
@@ -66,6 +177,7 @@ struct s2_plan_s {
                                           // half when mirror rings come from the symmetry)
     long long nsamp = 0;                  // samples per slice map
     std::vector<Run> runs;
+    int ncu = 256;                        // compute units of the plan's device
 
     // device memory owned by the plan
     std::vector<void *> allocs;
@@ -80,12 +192,12 @@ struct s2_plan_s {
     // recursion tables
     double *kap = nullptr, *gtab = nullptr;
     std::vector<double *> lbin;   // per run
-    std::vector<double *> lam;    // per run [L][hstride]
     std::vector<double2 *> init;  // per run [nreg][L]: start values of Eq. 27
-    // per-slice weights: SHT (Eqs. 30, 33), SO(3) inverse (Eq. 13), SO(3) forward (Eq. 14)
-    std::vector<double *> w_sht, w_so3i, w_so3f;
+    int *spin_d = nullptr;        // spin of every slice (device)
+    // weights [slice][L]: SHT (Eqs. 30, 33), SO(3) inverse (Eq. 13), SO(3) forward (Eq. 14)
+    double *w_sht = nullptr, *w_so3i = nullptr, *w_so3f = nullptr;
     double *w_so3f_n1 = nullptr;          // one-slice Wigner forward on the matrix cores: w_so3f times the gamma rule 2 pi
-    std::vector<double *> w_fadj;         // HEALPix: (4 pi / Npix) w_l, the adjoint of the forward quadrature
+    double *w_fadj = nullptr;             // HEALPix: (4 pi / Npix) w_l, the adjoint of the forward quadrature
     // FFT
     std::vector<FftArgs> ffts_h;
     FftArgs *ffts = nullptr;
@@ -102,22 +214,23 @@ struct s2_plan_s {
     // orders -(|n|-1) and supplies the other run's orders |m| < |n| there
     int nxp = 0;                           // max |n| over the runs (orders below it are remedied)
     int nx = 0;                            // negative orders held in the tables: max(0, nxp - 1)
-    int inv_nblk = 1, inv_waves = 4;
-    int *lslot = nullptr, *lchunk = nullptr, *mtop = nullptr;
-    int fwd_nblk = 1, fwd_waves = 4, G = 1;
+    Work inv, fwd;                         // work of the inverse and forward sweeps
+    int *mtop = nullptr;                   // top order of each inverse block
+    bool one = false;                      // runs feed one side each (spin-s sphere plans)
     // forward sweep over the northern rings (spin 0, symmetric samplings: nsw < nreg)
     bool fwd_pair = false;
-    int fwdp_nblk = 1, fwdp_waves = 4, Gp = 1, pstride = 0;
+    int pstride = 0;
     size_t off_Fp = 0;                    // workspace: sums and differences of mirror-ring spectra
     int hstride = 0;                       // ring stride of the forward spectra (padded to the sweep's slots)
-    // order tiles of the FP64 sweeps and, per run, the recursion state at their cuts
-    OrderTiles tiles{};
-    std::vector<double *> ck;
+    SweepRun *runs_d = nullptr;            // the runs as the sweeps read them
+    int order_tiles = 1;                   // most pieces that one block of degrees is cut into
+    int group = 1;                         // maps of a batch that share the launches (FP64)
+    size_t ws1 = 0;                        // workspace bytes of one map
     // workspace layout (bytes)
     size_t off_C = 0, off_P = 0, off_maps = 0, off_F = 0, off_Q = 0, off_hpole = 0, ws_bytes = 0;
     size_t off_fscr = 0, sz_fscr = 0;      // split-Bluestein scratch: FFT_SCRATCH complex per FFT workgroup
     size_t off_hsym = 0;                   // spin-0 S2 plans: Hermitian part of a coefficient cotangent
-    size_t szC = 0, szP = 0, szF = 0, szQ = 0;
+    size_t szC = 0, szP = 0, szF = 0, szQ = 0;   // C per run, others per slice
     size_t off_Hx = 0, off_Qx = 0, szHx = 0, szQx = 0;
 
     // matrix-core contraction path (precision FP32 / split BF16): batched over maps
@@ -177,6 +290,7 @@ struct Staging {
     std::deque<std::vector<double>> d;
     std::deque<std::vector<int>> i;
     std::deque<std::vector<long long>> ll;
+    std::vector<SweepRun> sr;
 };
 
 template <typename T>
@@ -308,7 +422,7 @@ int s2_plan_info(s2_plan_t P, s2_plan_info_t *info)
     info->workspace_bytes = P->ws_bytes;
     info->plan_device_bytes = P->plan_bytes;
     info->swept_rings = P->nsw;
-    info->order_tiles = P->ck.empty() ? 1 : P->tiles.nt;
+    info->order_tiles = P->order_tiles;
     return S2_OK;
 }
 
@@ -518,15 +632,19 @@ static int plan_create_impl(s2_plan_t *out, int L, int spin, int N, s2_sampling_
         if ((rc = upload(P, &lb, stg.d.back(), st, "log2 binomials"))) return bail(rc);
         P->lbin.push_back(lb);
     }
-    for (int k = 0; k < P->nslice; ++k) {
-        for (int kind = 0; kind < 3; ++kind) {
-            stg.d.emplace_back();
-            host_weights(L, kind, P->slice_spin[k], &stg.d.back());
-            double *a;
-            if ((rc = upload(P, &a, stg.d.back(), st, "weights"))) return bail(rc);
-            (kind == 0 ? P->w_sht : kind == 1 ? P->w_so3i : P->w_so3f).push_back(a);
+    for (int kind = 0; kind < 3; ++kind) {
+        stg.d.emplace_back();
+        std::vector<double> &all = stg.d.back();
+        for (int k = 0; k < P->nslice; ++k) {
+            std::vector<double> w;
+            host_weights(L, kind, P->slice_spin[k], &w);
+            all.insert(all.end(), w.begin(), w.begin() + L);
         }
+        if ((rc = upload(P, kind == 0 ? &P->w_sht : kind == 1 ? &P->w_so3i : &P->w_so3f, all, st, "weights")))
+            return bail(rc);
     }
+    stg.i.emplace_back(P->slice_spin);
+    if ((rc = upload(P, &P->spin_d, stg.i.back(), st, "slice spins"))) return bail(rc);
     if (!so3 && sampling == S2_MW && spin == 0 && prec != S2_FP64) {
         // so3_forward with N = 1 on the matrix-core path folds the gamma rule 2 pi/(2N-1) = 2 pi
         // (Eq. 16) into the finish's weights instead of scaling a copy of the samples
@@ -536,151 +654,87 @@ static int plan_create_impl(s2_plan_t *out, int L, int spin, int N, s2_sampling_
         if ((rc = upload(P, &P->w_so3f_n1, stg.d.back(), st, "one-slice Wigner forward weights"))) return bail(rc);
     }
 
-    // inverse d-stage assignment: waves of INV_NCH 8-degree chunks, W a multiple of 4.
-    // Spin-0 plans of the N/S-symmetric samplings sweep only the northern rings and
-    // produce each mirror ring from d^l_{m,0}(pi - theta) = (-1)^{l+m} d^l_{m,0}(theta),
-    // when the halved grid still has a workgroup for every compute unit (splitting the
-    // l-range over more blocks instead does not pay: the per-order reduction dominates
-    // sparsely filled waves).
+    // Sweep work.  Spin-0 plans of the N/S-symmetric samplings sweep only the northern
+    // rings and produce each mirror ring from d^l_{m,0}(pi - theta) = (-1)^{l+m}
+    // d^l_{m,0}(theta), halving the recursion and the products.
+    // S2MI_RING_PAIRING=0 / 1 turns that off / on wherever it applies (tests, tuning).
+    P->one = !so3 && spin != 0;
+    const int nrun = (int)P->runs.size();
     {
-        const int nch = (L + 7) / 8;
-        const int per_blk = DSTAGE_MAX_WAVES * INV_NCH;
-        P->inv_nblk = (nch + per_blk - 1) / per_blk;
-        const int wneed = (nch + INV_NCH * P->inv_nblk - 1) / (INV_NCH * P->inv_nblk);
-        P->inv_waves = std::min(DSTAGE_MAX_WAVES, std::max(4, (wneed + 3) / 4 * 4));
-        // S2MI_RING_PAIRING=0 / 1 turns the mirror-ring sweep off / on wherever it applies
-        // (tests, tuning); unset, the plan decides from the grid size.
-        P->nsw = P->nreg;
-        int dev = 0, ncu = 0;
+        int dev = 0;
         PLANCHK(hipGetDevice(&dev), "hipGetDevice");
-        PLANCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev), "CU count");
+        PLANCHK(hipDeviceGetAttribute(&P->ncu, hipDeviceAttributeMultiprocessorCount, dev), "CU count");
+        P->nsw = P->nreg;
         const bool sym = sampling == S2_DH || sampling == S2_GL || sampling == S2_MWSS || sampling == S2_HEALPIX;
         const char *pm = std::getenv("S2MI_RING_PAIRING");
         const int mode = pm && pm[0] == '0' ? 0 : pm && pm[0] == '1' ? 1 : -1;
-        if (sym && spin == 0 && !so3 && prec == S2_FP64 && mode != 0) {
-            const int half_rings = (P->nreg + 1) / 2;
-            if (mode == 1 || (half_rings + 63) / 64 * P->inv_nblk >= ncu) P->nsw = half_rings;
-        }
-        // Order tiles (FP64 sweeps; see OrderTiles): a grid of fewer than two waves per
-        // SIMD is run as nt tiles aiming at four (more, shorter workgroups also even out
-        // the tail), at most one per 64 orders (128 for the mirror-ring sweeps, whose
-        // forward degree groups span 128).  Measured, MW L = 1024 spin 0: sweeps 0.90 +
-        // 1.00 ms untiled, 0.46 + 0.58 ms in 8 tiles; at L = 2048, where the grid already
-        // holds two waves per SIMD, 2 tiles made the forward sweep slower (3.05 -> 3.5 ms).
-        // If the tiled grid still holds fewer than two waves per SIMD, four-wave
-        // workgroups over twice the l-blocks (MW L = 512: inverse 0.206 -> 0.193 ms; at
-        // L = 1024 in 8 tiles the eight-wave form is faster, 0.72 -> 0.46 ms, its l-blocks
-        // writing half the partial sums).  S2MI_ORDER_TILES=k forces k tiles (1: none),
-        // S2MI_INV_WAVES=4 / 8 the inverse workgroup size (tests, tuning).
-        {
-            const long long base = (long long)((P->nsw + 63) / 64) * P->inv_nblk * P->inv_waves;
-            const long long two = 8LL * ncu, four = 16LL * ncu;
-            const int q = P->nsw < P->nreg ? 128 : 64;
-            int nt = base >= two ? 1 : (int)std::min<long long>(MAX_ORDER_TILES, (four + base - 1) / base);
-            if (const char *ev = std::getenv("S2MI_ORDER_TILES"))
-                nt = std::max(1, std::min(MAX_ORDER_TILES, std::atoi(ev)));
-            if (prec != S2_FP64) nt = 1;                     // the matrix-core path has no FP64 sweeps
-            nt = std::min(nt, std::max(1, L / q));
-            P->tiles.nt = nt;
-            const char *iw = std::getenv("S2MI_INV_WAVES");
-            if (P->inv_waves == DSTAGE_MAX_WAVES && (iw ? iw[0] == '4' : base * nt < two)) {
-                P->inv_waves = 4;
-                P->inv_nblk *= 2;
-            }
-        }
-        stg.i.emplace_back(); std::vector<int> &lch = stg.i.back();
-        stg.i.emplace_back(); std::vector<int> &ls = stg.i.back();
+        if (sym && spin == 0 && !so3 && prec == S2_FP64 && mode != 0 && (mode == 1 || P->nreg >= PAIR_MIN_RINGS))
+            P->nsw = (P->nreg + 1) / 2;
+        P->fwd_pair = P->nsw < P->nreg;
+        // S2MI_ORDER_TILES=k cuts every block into k pieces (1: none)
+        int force = 0;
+        if (const char *ev = std::getenv("S2MI_ORDER_TILES")) force = std::max(1, std::min(8, std::atoi(ev)));
+        if (prec != S2_FP64) force = 1;                  // the matrix-core path has no FP64 sweeps
+        // inverse: blocks of at most 256 degrees, of equal size
+        const int nb = (L + INV_BLK - 1) / INV_BLK, nq = (L + 7) / 8;
+        P->inv.cb = (nq + nb - 1) / nb;
+        P->inv.tiles = std::max(1, (P->nsw + 63) / 64);
+        P->inv.rp = P->inv.tiles * 64;
+        std::vector<int> orders;
+        for (int q = 0; q < nq; q += P->inv.cb) orders.push_back(std::min(L, 8 * (q + P->inv.cb)));
+        deal_work(P->inv, orders, nrun, P->ncu, force);
         stg.i.emplace_back(); std::vector<int> &mt = stg.i.back();
-        assign_inverse(L, P->inv_nblk, P->inv_waves, INV_NCH, lch, ls, mt);
-        if ((rc = upload(P, &P->lchunk, lch, st, "inverse chunks"))) return bail(rc);
-        if ((rc = upload(P, &P->lslot, ls, st, "inverse slots"))) return bail(rc);
+        for (int o : orders) mt.push_back(o - 1);
         if ((rc = upload(P, &P->mtop, mt, st, "inverse mtop"))) return bail(rc);
-    }
-    // forward d-stage assignment: wave w of block b sweeps rings (b W + w) FWD_R ..
-    // + FWD_R - 1; rings past the last regular ring are inert padding.  W is 4, 8
-    // or 16 (rotating groups of four reducer waves); larger workgroups mean fewer
-    // ring blocks and so fewer partial sums to write and add up in the finish.  At
-    // most 16 ring blocks where the waves allow (MW L = 1024 in 8 order tiles: 32
-    // blocks of 4 waves 0.62 ms, 16 blocks of 8 waves 0.58 ms, finish 0.15 -> 0.07 ms).
-    {
-        P->G = (L + 63) / 64;
-        const int pairs = (P->G + 1) / 2;
-        int nb = std::max(1, std::min({16, 256 / pairs, (P->nreg + 4 * FWD_R - 1) / (4 * FWD_R)}));
-        int W = (P->nreg + nb * FWD_R - 1) / (nb * FWD_R);
-        while (W > FWD_MAX_WAVES) { ++nb; W = (P->nreg + nb * FWD_R - 1) / (nb * FWD_R); }
-        W = W <= 4 ? 4 : W <= 8 ? 8 : 16;                    // 1, 2 or 4 groups of four waves
-        if (W > FWD_MAX_WAVES) W = FWD_MAX_WAVES;
-        if (const char *fw = std::getenv("S2MI_FWD_WAVES")) {   // 4, 8 or 16 forced (tuning)
-            const int Wf = std::atoi(fw);
-            if (Wf == 4 || Wf == 8 || Wf == 16) {
-                W = Wf;
-                nb = (P->nreg + W * FWD_R - 1) / (W * FWD_R);
-            }
+        // forward: groups of 64 degrees (mirror-ring sweep: of one parity), ring blocks of
+        // equal size
+        P->fwd.tiles = std::max(1, (P->nsw + FWD_BLK - 1) / FWD_BLK);
+        P->fwd.nk = std::max(1, (P->nsw + P->fwd.tiles * 4 * SW_WAVES - 1) / (P->fwd.tiles * 4 * SW_WAVES));
+        const int slots = P->fwd.tiles * 4 * SW_WAVES * P->fwd.nk;
+        P->fwd.rp = (P->nsw + 3) / 4 * 4;
+        P->hstride = std::max(P->nring, P->fwd_pair ? 0 : slots);
+        if (P->fwd_pair) P->pstride = slots;
+        orders.clear();
+        const int ng = P->fwd_pair ? 2 * ((L + 127) / 128) : (L + 63) / 64;
+        for (int g = 0; g < ng; ++g)
+            {
+            const int lmin = P->fwd_pair ? 128 * (g >> 1) + (g & 1) : 64 * g;
+            orders.push_back(lmin < L ? std::min(L, lmin + (P->fwd_pair ? 127 : 64)) : 0);
         }
-        P->fwd_nblk = nb;
-        P->fwd_waves = W;
-        P->hstride = std::max(nb * W * FWD_R, P->nring);
-        // the mirror-ring form sweeps nsw rings with groups of 64 degrees of one parity
-        // (Gp groups), on the same rule
-        if (P->nsw < P->nreg) {
-            P->fwd_pair = true;
-            P->Gp = 2 * ((L + 127) / 128);
-            const int pp = (P->Gp + 1) / 2;
-            int nbp = std::max(1, std::min({16, 256 / pp, (P->nsw + 4 * FWD_R - 1) / (4 * FWD_R)}));
-            int Wp = (P->nsw + nbp * FWD_R - 1) / (nbp * FWD_R);
-            while (Wp > FWD_MAX_WAVES) { ++nbp; Wp = (P->nsw + nbp * FWD_R - 1) / (nbp * FWD_R); }
-            Wp = Wp <= 4 ? 4 : Wp <= 8 ? 8 : 16;
-            if (Wp > FWD_MAX_WAVES) Wp = FWD_MAX_WAVES;
-            P->fwdp_nblk = nbp;
-            P->fwdp_waves = Wp;
-            P->pstride = nbp * Wp * FWD_R;
-            P->hstride = std::max(P->hstride, P->pstride);  // the lambda table's columns cover every slot
-        }
+        deal_work(P->fwd, orders, nrun, P->ncu, force);
+        P->order_tiles = P->inv.pieces;
     }
 
+    std::vector<SweepRun> &sr = stg.sr;
     for (size_t ri = 0; ri < P->runs.size(); ++ri) {
         const Run &r = P->runs[ri];
-        double *lam;
         double2 *ini;
-        if ((rc = P->dalloc(&lam, (size_t)(L + P->nx) * P->hstride, "lambda table"))) return bail(rc);
-        lam += (size_t)P->nx * P->hstride;                 // rows m in [-nx, L)
-        PLANCHK(launch_lambda_table(st, L, P->nx, P->nreg, P->hstride, r.n, P->cot, P->csc, lam), "lambda table");
         if ((rc = P->dalloc(&ini, (size_t)L * P->nreg, "start values"))) return bail(rc);
         PLANCHK(launch_init_table(st, L, P->nreg, r.n, P->lsin, P->lcos, P->lbin[ri], ini), "start values");
-        P->lam.push_back(lam);
         P->init.push_back(ini);
+        sr.push_back(SweepRun{r.n, r.sliceA, r.sliceB, 0, ini, nullptr, nullptr});
     }
-
-    // order-tile cuts (tile count chosen with the inverse geometry above): tiles of about
-    // equal work (the work above order m grows like (L - m)^2), cut at whole forward
-    // degree groups, and per run the recursion state at each cut
-    if (P->tiles.nt > 1) {
-        const int q = P->fwd_pair ? 128 : 64;
-        const int nt = P->tiles.nt;
-        OrderTiles &ot = P->tiles;
-        ot.c[0] = L;
-        int k = 1;
-        for (int j = 1; j < nt; ++j) {
-            const double c = (double)L * (1.0 - std::sqrt((double)j / nt));
-            int cq = (int)std::lround(c / q) * q;
-            cq = std::max(q, std::min(cq, (L - 1) / q * q));
-            if (cq < ot.c[k - 1]) ot.c[k++] = cq;
-        }
-        ot.nt = k;
-        ot.rp = (P->nreg + 63) / 64 * 64;
-        size_t tot = 0;
-        for (int j = 1; j < ot.nt; ++j) {
-            ot.off[j] = (long long)tot;
-            tot += (size_t)(L - ot.c[j]) * 3 * ot.rp;
-        }
-        for (size_t ri = 0; ri < P->runs.size() && ot.nt > 1; ++ri) {
+    // the work tables and, per run, the recursion state at each cut
+    for (int f = 0; f < 2 && prec == S2_FP64; ++f) {
+        Work &W = f ? P->fwd : P->inv;
+        const int D = f ? FWD_L : 8 * W.cb;
+        if ((rc = upload(P, &W.seg_d, W.seg, st, "work pieces"))) return bail(rc);
+        if ((rc = upload(P, &W.first_d, W.first, st, "work slots"))) return bail(rc);
+        if (W.cuts.empty()) continue;
+        int *cf;
+        int2 *cu;
+        if ((rc = upload(P, &cf, W.cfirst, st, "cuts"))) return bail(rc);
+        if ((rc = upload(P, &cu, W.cuts, st, "cuts"))) return bail(rc);
+        for (size_t ri = 0; ri < P->runs.size(); ++ri) {
             double *ck;
-            if ((rc = P->dalloc(&ck, tot, "order-tile states"))) return bail(rc);
-            PLANCHK(launch_order_ckpt(st, L, P->nreg, P->runs[ri].n, P->cot, P->csc, P->init[ri], P->kap, ot, ck),
-                    "order-tile states");
-            P->ck.push_back(ck);
+            if ((rc = P->dalloc(&ck, W.cuts.size() * D * 3 * (size_t)W.rp, "recursion states"))) return bail(rc);
+            PLANCHK(launch_cut_state(st, f == 1, L, P->nsw, W.rp, D, W.nblk, P->fwd_pair, P->runs[ri].n, P->cot, P->csc,
+                                     P->init[ri], P->kap, cf, cu, ck),
+                    "recursion states");
+            (f ? sr[ri].ckF : sr[ri].ckI) = ck;
         }
     }
+    if ((rc = upload(P, &P->runs_d, sr, st, "runs"))) return bail(rc);
 
     // S2MI_DEBUG_CHECKS=1: check sum_{|m| <= l} (d^l_{m,n})^2 = 1 (d^l is orthogonal) on
     // sampled rings, for every degree and every run whose partner -n is in the plan,
@@ -731,33 +785,48 @@ static int plan_create_impl(s2_plan_t *out, int L, int spin, int N, s2_sampling_
     // workspace layout
     {
         const size_t S = P->nslice;
-        P->szC = (size_t)P->inv_nblk * P->inv_waves * INV_J * (L + P->nx) * 5 * sizeof(double);
-        P->szP = (size_t)P->inv_nblk * P->nreg * L * 4 * sizeof(double);
-        P->szF = (size_t)L * P->hstride * 4 * sizeof(double);
+        const size_t nq = (L + 7) / 8;
+        P->szC = align256((nq * P->nx + 4 * nq * (nq + 1)) * (P->one ? 24 : 40) * sizeof(double));
+        P->szP = (size_t)P->inv.nblk * P->nreg * L * 4 * sizeof(double);
+        // (the forward sweep's operand loads run up to 28 rings past a row's end)
+        P->szF = ((size_t)L * P->hstride + 32) * 4 * sizeof(double);
         // forward partials [blk][l][m][4]; the adjoint of the MW / MWSS forward reuses the
         // buffer for ring partials [nring][m][4] (nring = L + 1 for MWSS)
         const int adj_rows = (sampling == S2_MW || sampling == S2_MWSS) ? P->nring : 0;
-        P->szQ = (size_t)std::max({P->fwd_nblk * L, P->fwdp_nblk * L, adj_rows}) * L * 4 * sizeof(double);
+        P->szQ = std::max((size_t)P->fwd.tiles * L, (size_t)adj_rows) * L * 4 * sizeof(double);
         size_t o = 0;
-        P->off_C = o; o += align256(P->szC * P->runs.size());
+        P->off_C = o; o += P->szC * P->runs.size();
         P->off_P = o; o += align256(P->szP * S);
         P->off_maps = o; o += (sampling == S2_MW && spin == 0) ? align256((size_t)P->nsamp * S * sizeof(double2)) : 0;
         P->off_F = o; o += align256(P->szF * S);
         P->off_Q = o; o += align256(P->szQ * S);
         P->off_hpole = o; o += align256((size_t)(2 * L - 1) * S * 2 * sizeof(double2));   // south, north
         // low-order machinery of runs with n != 0: masked spectra copies per run, continuation sums per slice
-        P->szHx = (size_t)std::max(P->nxp, 1) * P->hstride * 4 * sizeof(double);
-        P->szQx = (size_t)P->fwd_nblk * L * std::max(P->nxp, 1) * 4 * sizeof(double);
+        P->szHx = ((size_t)std::max(P->nxp, 1) * P->hstride + 32) * 4 * sizeof(double);
+        P->szQx = (size_t)P->fwd.tiles * L * std::max(P->nxp, 1) * 4 * sizeof(double);
         P->off_Hx = o; o += P->nxp > 0 ? align256(2 * P->szHx * P->runs.size()) : 0;
         P->off_Qx = o; o += P->nxp > 0 ? align256(P->szQx * S) : 0;
+        P->off_hsym = o; o += (spin == 0 && !so3) ? align256((size_t)L * (2 * L - 1) * sizeof(double2)) : 0;
+        P->off_Fp = o; o += P->fwd_pair ? align256((2 * (size_t)L * P->pstride + 32) * 4 * sizeof(double)) : 0;
+        P->ws1 = o;
+        // Maps of a batch that share the launches: enough to give every compute unit about
+        // GROUP_ORDERS orders of work (fixed costs are then a few per cent), within
+        // GROUP_BYTES of workspace.
+        if (prec == S2_FP64) {
+            long long ord = 0;
+            for (const int4 &g : P->inv.seg) ord += g.y - g.z + 1;
+            const double per = (double)ord * P->inv.tiles * P->runs.size() / P->ncu;
+            const double want = std::ceil(GROUP_ORDERS / std::max(per, 1e-3));
+            P->group = (int)std::max(1.0, std::min({(double)max_batch, want, std::floor((double)GROUP_BYTES / (double)o),
+                                                               32768.0 / (double)std::max(S, P->runs.size())}));
+        }
+        o *= P->group;
         bool split = false;
         for (const FftArgs &f : P->ffts_h) split = split || (f.blue && f.split);
         // one FFT_SCRATCH slice per workgroup of the phi-DFT (hstride), inverse phi-DFT
-        // (nring) and MW filter (L) launches
+        // (nring) and MW filter (L) launches of one item (items then run one by one)
         P->sz_fscr = split ? (size_t)std::max({P->hstride, P->nring, L}) * FFT_SCRATCH * sizeof(double2) : 0;
         P->off_fscr = o; o += align256(P->sz_fscr);
-        P->off_hsym = o; o += (spin == 0 && !so3) ? align256((size_t)L * (2 * L - 1) * sizeof(double2)) : 0;
-        P->off_Fp = o; o += P->fwd_pair ? align256(2 * (size_t)L * P->pstride * 4 * sizeof(double)) : 0;
         P->ws_bytes = o;
     }
 
@@ -774,7 +843,7 @@ static int plan_create_impl(s2_plan_t *out, int L, int spin, int N, s2_sampling_
             for (double &v : stg.d.back()) v *= 4.0 * M_PI / (double)P->nsamp;
         double *a;
         if ((rc = upload(P, &a, stg.d.back(), st, "forward-adjoint weights"))) return bail(rc);
-        P->w_fadj.push_back(a);
+        P->w_fadj = a;
     }
 
     // matrix-core path: generator assignment, {kappa, g} table, batched workspace
@@ -826,7 +895,7 @@ static int plan_create_impl(s2_plan_t *out, int L, int spin, int N, s2_sampling_
         P->off_mP = o; o += align256(B * S * nP1 * sizeof(double));
         P->off_mF = o; o += align256(B * S * P->szF);
         P->off_mQ = o; o += align256(B * S * nQ1 * sizeof(double));
-        P->off_mhp = o; o += align256(B * S * (2 * L - 1) * 2 * sizeof(double2));        // south, north
+        P->off_mhp = o; o += align256(B * S * (2 * L - 1) * 2 * sizeof(double2));        // [south, north][b][slice]
         P->off_mmaps = o; o += (S > 1) ? align256(B * S * (size_t)P->nsamp * sizeof(double2)) : 0;
         P->off_mQx = o; o += P->nxp > 0 ? align256(B * S * (size_t)L * P->nxp * 4 * sizeof(double)) : 0;
         P->ws_bytes = o;
@@ -895,15 +964,6 @@ int check_call(const char *fn, s2_plan_t P, const void *in, const void *out, int
     return S2_OK;
 }
 
-// the order tiles of run ri (one tile where the plan has no state tables)
-OrderTiles run_tiles(const s2_plan_s *P, size_t ri)
-{
-    OrderTiles ot = P->tiles;
-    if (ri < P->ck.size()) ot.ck = P->ck[ri];
-    else ot.nt = 1;
-    return ot;
-}
-
 // the theta filter's convolution form: its FFT, kernel spectra and length (none: nullptr)
 #define CONV_ARGS(P) ((P)->conv_idx >= 0 ? (P)->ffts + (P)->conv_idx : nullptr)
 
@@ -913,200 +973,215 @@ double2 *fft_scratch(const s2_plan_s *P, char *ws)
     return P->sz_fscr ? reinterpret_cast<double2 *>(ws + P->off_fscr) : nullptr;
 }
 
-// inverse d-stage of one (map, all slices): flm slices [S][L][2L-1] -> partials P[slice][blk][ring][m][4]
-// (half: real signal of a spin-0 plan, orders m >= 0 and components 0,1 only)
-int run_inverse_dstage(s2_plan_t P, const double2 *flm, const std::vector<double *> &wl, char *ws, hipStream_t st,
+Items all_slices(const s2_plan_s *P) { return Items{P->nslice, 0, P->spin_d}; }
+// strides of the workspace's per-map buffers (doubles), of coefficients and of maps
+long long wsd(const s2_plan_s *P) { return (long long)(P->ws1 / sizeof(double)); }
+long long coef_n(const s2_plan_s *P) { return (long long)P->L * (2 * P->L - 1); }
+Strides coef_strides(const s2_plan_s *P) { return Strides{P->nslice * coef_n(P), coef_n(P)}; }
+// complex entries between the slice maps of consecutive maps in the workspace
+long long tmp_stride(const s2_plan_s *P) { return (long long)(P->ws1 / sizeof(double2)); }
+Strides map_strides(const s2_plan_s *P) { return Strides{P->nslice * P->nsamp, P->nsamp}; }
+Strides ws_strides(const s2_plan_s *P, size_t slice_bytes)
+{
+    return Strides{wsd(P), (long long)(slice_bytes / sizeof(double))};
+}
+// pole lines: [south, north][slice][2L-1] complex per map
+Strides pole_strides(const s2_plan_s *P) { return Strides{(long long)(P->ws1 / sizeof(double2)), 2 * P->L - 1}; }
+
+// inverse d-stage of nm maps, all slices: flm [nm][S][L][2L-1] (fstride per map) ->
+// partials P[map][slice][blk][ring][m][4]  (half: real signal of a spin-0 plan, orders
+// m >= 0 and components 0,1 only)
+int run_inverse_dstage(s2_plan_t P, const double2 *flm, long long fstride, int nm, const double *wl, char *ws,
+                       hipStream_t st, int half = 0)
+{
+    InvArgs a{};
+    a.L = P->L; a.nx = P->nx; a.nreg = P->nreg; a.nsw = P->nsw; a.nrun = (int)P->runs.size(); a.half = half;
+    a.rt = P->inv.tiles; a.nslot = P->inv.nslot; a.cb = P->inv.cb; a.rp = P->inv.rp;
+    a.merge = merge_slots(P->inv, (long long)nm * a.nrun, P->ncu);
+    a.wsd = wsd(P); a.nC = (long long)(P->szC / sizeof(double)); a.nP = (long long)(P->szP / sizeof(double));
+    a.runs = P->runs_d; a.seg = P->inv.seg_d; a.first = P->inv.first_d;
+    a.C = (double *)(ws + P->off_C); a.P = (double *)(ws + P->off_P);
+    const bool one = P->one || half;
+    {
+        TIMED(S2_STAGE_PACK);
+        HIPCHK(launch_pack_inv(st, a, nm, one, flm, fstride, wl, P->kap, P->gtab), "pack");
+    }
+    if (P->nreg < 1) return S2_OK;
+    TIMED(S2_STAGE_DSTAGE_INV);
+    HIPCHK(launch_sweep_inv(st, a, nm, one, P->cot, P->csc), "inverse d-stage");
+    return S2_OK;
+}
+
+// inverse of nm maps, all slices: flm -> slice maps [nm][S][nsamp] (strides sm)
+// (tight: one map on a workspace of inverse_extent bytes, the DFT scratch right behind
+// its partial sums)
+int run_inverse(s2_plan_t P, const double2 *flm, double2 *maps, Strides sm, int nm, const double *wl, char *ws,
+                hipStream_t st, bool tight = false)
+{
+    const Strides sf = coef_strides(P);
+    int rc = run_inverse_dstage(P, flm, sf.map, nm, wl, ws, st);
+    if (rc) return rc;
+    TIMED(S2_STAGE_PHI_INV);
+    HIPCHK(launch_phi_inv(st, P->fft_threads, P->fft_lds, P->nring, P->L, P->nreg, P->inv.nblk, all_slices(P),
+                          nm * P->nslice, ws_strides(P, P->szP), sf, sm, (const double *)(ws + P->off_P), P->mtop, flm,
+                          wl, P->ring_nphi, P->ring_start, P->ring_shift, P->ring_fft, P->ffts, maps,
+                          tight && P->sz_fscr ? (double2 *)(ws + align256(P->off_P + P->szP * P->nslice))
+                                              : fft_scratch(P, ws)),
+           "inverse phi-DFT");
+    return S2_OK;
+}
+
+// the theta filter (adj: its adjoint) of nm maps in place on F, or the pole lines alone
+int run_theta(s2_plan_t P, int nm, char *ws, hipStream_t st, int half, int adj)
+{
+    const int L = P->L, ss = P->sampling == S2_MWSS;
+    double2 *hp = (double2 *)(ws + P->off_hpole);
+    double2 *hpN = ss ? hp + (size_t)P->nslice * (2 * L - 1) : nullptr;
+    HIPCHK(launch_mw_filter(st, P->fft_threads, P->fft_lds, L, ss, P->hstride, all_slices(P), nm * P->nslice,
+                            ws_strides(P, P->szF), pole_strides(P), P->ffts, P->wq, P->ph, (double *)(ws + P->off_F), hp,
+                            hpN, fft_scratch(P, ws), half, adj, CONV_ARGS(P)), "MW theta filter");
+    return S2_OK;
+}
+
+int run_pole_lines(s2_plan_t P, int nm, char *ws, hipStream_t st)
+{
+    const int L = P->L;
+    double2 *hp = (double2 *)(ws + P->off_hpole);
+    const double *F = (const double *)(ws + P->off_F);
+    HIPCHK(launch_pole_from_F(st, L, P->hstride, L - 1, all_slices(P), nm * P->nslice, ws_strides(P, P->szF),
+                              pole_strides(P), F, hp), "pole line");
+    if (P->sampling == S2_MWSS)
+        HIPCHK(launch_pole_from_F(st, L, P->hstride, L, all_slices(P), nm * P->nslice, ws_strides(P, P->szF),
+                                  pole_strides(P), F, hp + (size_t)P->nslice * (2 * L - 1)), "north pole line");
+    return S2_OK;
+}
+
+// the partials of an adjoint's inverse-type sweep through the theta filter's adjoint,
+// into the ring partials Q[map][slice][ring][m][4] of the phi-DFT
+int run_theta_adjoint(s2_plan_t P, const double2 *G, Strides sf, int nm, const double *wl, char *ws, hipStream_t st,
+                      int half)
+{
+    const int L = P->L, ss = P->sampling == S2_MWSS;
+    double *F = (double *)(ws + P->off_F), *Q = (double *)(ws + P->off_Q);
+    double2 *hp = (double2 *)(ws + P->off_hpole);
+    double2 *hpN = ss ? hp + (size_t)P->nslice * (2 * L - 1) : nullptr;
+    const double q = 2.0 * M_PI / (double)(ss ? 2 * L : 2 * L - 1);
+    TIMED(S2_STAGE_MW_THETA);
+    HIPCHK(launch_fadj_gather(st, L, ss, P->inv.nblk, all_slices(P), nm * P->nslice, ws_strides(P, P->szP), sf,
+                              ws_strides(P, P->szF), (const double *)(ws + P->off_P), P->mtop, G, wl, P->hstride, F),
+           "adjoint gather");
+    int rc = run_theta(P, nm, ws, st, half, 1);
+    if (rc) return rc;
+    HIPCHK(launch_fadj_scatter(st, L, ss, P->hstride, q, all_slices(P), nm * P->nslice, ws_strides(P, P->szF),
+                               pole_strides(P), ws_strides(P, P->szQ), F, hp, hpN, Q), "adjoint scatter");
+    return S2_OK;
+}
+
+// adjoint of the MW / MWSS forward of nm maps, all slices (finish weights wl, spin
+// slice_spin[k]): coefficient cotangents -> slice maps.  MWSS adds the north-pole row
+// and runs the adjoint form of its theta filter.
+int run_forward_adjoint_mw(s2_plan_t P, const double2 *G, double2 *maps, Strides sm, int nm, const double *wl, char *ws,
+                           hipStream_t st)
+{
+    const Strides sf = coef_strides(P);
+    int rc = run_inverse_dstage(P, G, sf.map, nm, wl, ws, st);
+    if (rc || (rc = run_theta_adjoint(P, G, sf, nm, wl, ws, st, 0))) return rc;
+    TIMED(S2_STAGE_PHI_INV);
+    HIPCHK(launch_phi_inv(st, P->fft_threads, P->fft_lds, P->nring, P->L, P->nring, 1, all_slices(P), nm * P->nslice,
+                          ws_strides(P, P->szQ), sf, sm, (const double *)(ws + P->off_Q), P->mtop1, G, wl, P->ring_nphi,
+                          P->ring_start, P->ring_shift, P->ring_fft, P->ffts, maps, fft_scratch(P, ws)),
+           "adjoint phi-DFT");
+    return S2_OK;
+}
+
+// forward d-stage of nm maps from the (filtered) ring spectra F -> flm
+int run_forward_dstage(s2_plan_t P, bool poles, double2 *flm, int nm, const double *wl, char *ws, hipStream_t st,
                        int half = 0)
 {
     const int L = P->L;
-    const size_t slab = (size_t)L * (2 * L - 1);
-    double *C0 = (double *)(ws + P->off_C);
-    double *P0 = (double *)(ws + P->off_P);
-    const size_t nP = P->szP / sizeof(double), nC = P->szC / sizeof(double);
-    for (size_t ri = 0; ri < P->runs.size(); ++ri) {
-        const Run &r = P->runs[ri];
-        const double2 *fa = r.sliceA >= 0 ? flm + r.sliceA * slab : nullptr;
-        const double2 *fb = r.sliceB >= 0 ? flm + r.sliceB * slab : nullptr;
-        // a run that feeds one side only (spin-s sphere plans) sweeps that side alone
-        const int side = half ? 1 : (fa && fb) ? 0 : (fa ? 1 : 2);
-        double *C = C0 + ri * nC;
-        {
-        TIMED(S2_STAGE_PACK);
-        HIPCHK(launch_pack_inv(st, L, P->nx, r.n, P->inv_nblk, P->inv_waves * INV_J, P->lslot, fa, fb,
-                               r.sliceA >= 0 ? wl[r.sliceA] : nullptr, r.sliceB >= 0 ? wl[r.sliceB] : nullptr, P->kap,
-                               P->gtab, C, side), "pack");
-        }
-        TIMED(S2_STAGE_DSTAGE_INV);
-        HIPCHK(launch_dstage_inv(st, P->inv_waves, P->inv_nblk, L, P->nx, P->nreg, r.n, P->cot, P->csc, P->init[ri], C,
-                                 P->lchunk, P->mtop,
-                                 r.sliceA >= 0 ? P0 + r.sliceA * nP : nullptr,
-                                 r.sliceB >= 0 ? P0 + r.sliceB * nP : nullptr, side, P->nsw, run_tiles(P, ri)),
-               "inverse d-stage");
-    }
-    return S2_OK;
-}
-
-// inverse of one (map, all slices): flm slices [S][L][2L-1] -> slice maps
-int run_inverse(s2_plan_t P, const double2 *flm, double2 *const *slice_maps, const std::vector<double *> &wl,
-                char *ws, hipStream_t st)
-{
-    const int L = P->L;
-    const size_t slab = (size_t)L * (2 * L - 1);
-    double *P0 = (double *)(ws + P->off_P);
-    const size_t nP = P->szP / sizeof(double);
-    int rc = run_inverse_dstage(P, flm, wl, ws, st);
-    if (rc) return rc;
-    for (int k = 0; k < P->nslice; ++k) {
-        TIMED(S2_STAGE_PHI_INV);
-        HIPCHK(launch_phi_inv(st, P->fft_threads, P->fft_lds, P->nring, L, P->nreg, P->inv_nblk, P->slice_spin[k],
-                              P0 + k * nP, P->mtop, flm + k * slab, wl[k], P->ring_nphi, P->ring_start,
-                              P->ring_shift, P->ring_fft, P->ffts, slice_maps[k], fft_scratch(P, ws)), "inverse phi-DFT");
-    }
-    return S2_OK;
-}
-
-// adjoint of the MW / MWSS forward of one map, all slices (finish weights wl[k],
-// spin slice_spin[k]): coefficient cotangent slices -> slice maps.  The slices
-// share one gather / filter / scatter buffer in turn.  MWSS adds the north-pole
-// row and runs the adjoint form of its theta filter.
-int run_forward_adjoint_mw(s2_plan_t P, const double2 *G, double2 *const *slice_maps,
-                           const std::vector<double *> &wl, char *ws, hipStream_t st)
-{
-    const int L = P->L;
-    const int ss = P->sampling == S2_MWSS;
-    const size_t slab = (size_t)L * (2 * L - 1);
-    int rc = run_inverse_dstage(P, G, wl, ws, st);
-    if (rc) return rc;
-    double *P0 = (double *)(ws + P->off_P);
-    const size_t nP = P->szP / sizeof(double);
-    double *F0 = (double *)(ws + P->off_F);
-    double2 *hp0 = (double2 *)(ws + P->off_hpole);
-    double2 *hpN0 = ss ? hp0 + (size_t)P->nslice * (2 * L - 1) : nullptr;
-    double *Q0 = (double *)(ws + P->off_Q);
-    const double q = 2.0 * M_PI / (double)(ss ? 2 * L : 2 * L - 1);
-    for (int k = 0; k < P->nslice; ++k) {
-        const int s = P->slice_spin[k];
-        const double2 *Gk = G + k * slab;
-        {
-        TIMED(S2_STAGE_MW_THETA);
-        HIPCHK(launch_fadj_gather(st, L, ss, P->inv_nblk, s, P0 + k * nP, P->mtop, Gk, wl[k], P->hstride, F0),
-               "adjoint gather");
-        HIPCHK(launch_mw_filter(st, P->fft_threads, P->fft_lds, L, ss, P->hstride, s, P->ffts, P->wq, P->ph, F0, hp0,
-                                hpN0, fft_scratch(P, ws), 0, 1, CONV_ARGS(P)), "adjoint theta filter");
-        HIPCHK(launch_fadj_scatter(st, L, ss, P->hstride, q, F0, hp0, hpN0, Q0), "adjoint scatter");
-        }
-        TIMED(S2_STAGE_PHI_INV);
-        HIPCHK(launch_phi_inv(st, P->fft_threads, P->fft_lds, P->nring, L, P->nring, 1, s, Q0, P->mtop1, Gk, wl[k],
-                              P->ring_nphi, P->ring_start, P->ring_shift, P->ring_fft, P->ffts, slice_maps[k],
-                              fft_scratch(P, ws)), "adjoint phi-DFT");
-    }
-    return S2_OK;
-}
-
-// forward d-stage of one map from the filtered ring spectra H (slices) -> flm slices
-int run_forward_dstage(s2_plan_t P, double *H0, const double2 *hpole0, const double2 *hpoleN0, double2 *flm,
-                       const std::vector<double *> &wl,
-                       char *ws, hipStream_t st, int half = 0)
-{
-    const int L = P->L;
-    const size_t slab = (size_t)L * (2 * L - 1);
-    const size_t nF = P->szF / sizeof(double), nQ = P->szQ / sizeof(double);
-    const size_t nHx = P->szHx / sizeof(double), nQx = P->szQx / sizeof(double);
-    double *Q0 = (double *)(ws + P->off_Q);
-    double *Hx0 = P->nxp > 0 ? (double *)(ws + P->off_Hx) : nullptr;
-    double *Qx0 = P->nxp > 0 ? (double *)(ws + P->off_Qx) : nullptr;
-    if (Qx0) HIPCHK(launch_zero(st, Qx0, P->szQx * P->nslice), "continuation sums clear");
-    if (P->fwd_pair) {
-        // spin-0 S2 plan (one slice, run n = 0): sweep the northern rings on the sums and
-        // differences of each ring's and its mirror's spectra
-        double *S = (double *)(ws + P->off_Fp);
-        double *D = S + (size_t)L * P->pstride * 4;
+    FwdArgs a{};
+    a.L = L; a.nxp = std::max(P->nxp, 1); a.nreg = P->nsw; a.hstride = P->fwd_pair ? P->pstride : P->hstride;
+    a.nrun = (int)P->runs.size(); a.half = half ? 1 : 0;
+    a.rb = P->fwd.tiles; a.nk = P->fwd.nk; a.nslot = P->fwd.nslot; a.rp = P->fwd.rp;
+    a.merge = merge_slots(P->fwd, (long long)nm * a.nrun, P->ncu);
+    a.wsd = wsd(P);
+    a.nF = (long long)(P->szF / sizeof(double)); a.nQ = (long long)(P->szQ / sizeof(double));
+    a.nHx = (long long)(P->szHx / sizeof(double)); a.nQx = (long long)(P->szQx / sizeof(double));
+    a.runs = P->runs_d; a.seg = P->fwd.seg_d; a.first = P->fwd.first_d;
+    a.F = (const double *)(ws + P->off_F);
+    a.Q = (double *)(ws + P->off_Q);
+    double *Hx = P->nxp > 0 ? (double *)(ws + P->off_Hx) : nullptr;
+    a.Hx = Hx;
+    a.Qx = P->nxp > 0 ? (double *)(ws + P->off_Qx) : nullptr;
+    if (a.Qx) HIPCHK(launch_zero_maps(st, nm, a.wsd, a.Qx, P->szQx * P->nslice / sizeof(double)), "continuation sums clear");
+    const bool one = P->one || half;
+    {
         TIMED(S2_STAGE_DSTAGE_FWD);
-        HIPCHK(launch_pair_spectra(st, L, P->nreg, P->nsw, P->hstride, P->pstride, H0, S, D), "mirror spectra");
-        HIPCHK(launch_dstage_fwd(st, P->fwdp_waves, P->fwdp_nblk, P->Gp, L, 1, P->nsw, P->pstride, P->hstride, 0,
-                                 P->lam[0], P->init[0], P->kap, P->gtab, S, D, nullptr, nullptr, Q0, Q0, nullptr,
-                                 nullptr, half, 1, run_tiles(P, 0)), "forward d-stage");
+        if (P->fwd_pair) {
+            // spin-0 S2 plan (one slice, run n = 0): sweep the northern rings on the sums and
+            // differences of each ring's and its mirror's spectra
+            double *S = (double *)(ws + P->off_Fp), *D = S + (size_t)L * P->pstride * 4;
+            HIPCHK(launch_pair_spectra(st, nm, a.wsd, L, P->nreg, P->nsw, P->hstride, P->pstride, a.F, S, D),
+                   "mirror spectra");
+            a.S = S;
+            a.D = D;
+        } else if (P->nxp > 0) {
+            HIPCHK(launch_mask_low(st, nm, a.nrun, P->runs_d, P->nxp, P->nreg, P->hstride, P->cot, P->csc, a.F, Hx,
+                                   a.wsd, a.nF, a.nHx), "low-order spectra");
+        }
+        HIPCHK(launch_sweep_fwd(st, a, nm, one, P->cot, P->csc, P->kap), "forward d-stage");
     }
-    for (size_t ri = 0; ri < P->runs.size() && !P->fwd_pair; ++ri) {
-        const Run &r = P->runs[ri];
-        const int an = r.n < 0 ? -r.n : r.n;
-        const double *HA = r.sliceA >= 0 ? H0 + r.sliceA * nF : H0 + r.sliceB * nF;
-        const double *HB = r.sliceB >= 0 ? H0 + r.sliceB * nF : HA;
-        double *HxA = an > 0 ? Hx0 + 2 * ri * nHx : nullptr;
-        double *HxB = an > 0 ? HxA + nHx : nullptr;
-        const int side = half ? 1 : (r.sliceA >= 0 && r.sliceB >= 0) ? 0 : (r.sliceA >= 0 ? 1 : 2);
-        TIMED(S2_STAGE_DSTAGE_FWD);
-        if (an > 0)
-            HIPCHK(launch_mask_low(st, an, r.n, P->nreg, P->hstride, P->cot, P->csc, HA, HB, HxA, HxB),
-                   "low-order spectra");
-        HIPCHK(launch_dstage_fwd(st, P->fwd_waves, P->fwd_nblk, P->G, L, std::max(P->nxp, 1), P->nreg, P->hstride,
-                                 P->hstride, r.n, P->lam[ri], P->init[ri], P->kap, P->gtab, HA, HB, HxA, HxB,
-                                 r.sliceA >= 0 ? Q0 + r.sliceA * nQ : nullptr,
-                                 r.sliceB >= 0 ? Q0 + r.sliceB * nQ : nullptr,
-                                 (an > 0 && r.sliceA >= 0) ? Qx0 + r.sliceA * nQx : nullptr,
-                                 (an > 0 && r.sliceB >= 0) ? Qx0 + r.sliceB * nQx : nullptr, side, 0,
-                                 run_tiles(P, ri)), "forward d-stage");
-    }
-    for (int k = 0; k < P->nslice; ++k) {
-        const int s = P->slice_spin[k];
-        TIMED(S2_STAGE_FINISH);
-        HIPCHK(launch_finish_fwd(st, L, P->fwd_pair ? P->fwdp_nblk : P->fwd_nblk, s, s, Q0 + k * nQ,
-                                 Qx0 ? Qx0 + k * nQx : nullptr,
-                                 std::max(P->nxp, 1), wl[k], hpole0 ? hpole0 + k * (2 * L - 1) : nullptr,
-                                 hpoleN0 ? hpoleN0 + k * (2 * L - 1) : nullptr, flm + k * slab, half),
-               "forward finish");
-    }
+    TIMED(S2_STAGE_FINISH);
+    const double2 *hp = poles ? (const double2 *)(ws + P->off_hpole) : nullptr;
+    const double2 *hpN = poles && P->sampling == S2_MWSS ? hp + (size_t)P->nslice * (2 * L - 1) : nullptr;
+    HIPCHK(launch_finish_fwd(st, L, P->fwd.tiles, all_slices(P), nm * P->nslice, ws_strides(P, P->szQ),
+                             ws_strides(P, P->szQx), pole_strides(P), coef_strides(P), P->gtab, a.Q, a.Qx, a.nxp, wl, hp,
+                             hpN, flm, half),
+           "forward finish");
     return S2_OK;
 }
 
-// forward of one map: slice maps -> flm slices.  adjoint: unit phi weight, no theta filter.
-int run_forward(s2_plan_t P, const double2 *const *slice_maps, double2 *flm, const std::vector<double *> &wl,
-                char *ws, hipStream_t st, bool adjoint)
+// phi weight of the forward (adjoint: unit)
+double phi_weight(const s2_plan_s *P, bool adjoint)
 {
-    const int L = P->L;
-    const size_t nF = P->szF / sizeof(double);
-    double *F0 = (double *)(ws + P->off_F);
-    double2 *hp0 = (double2 *)(ws + P->off_hpole);
+    if (adjoint) return 1.0;
+    if (P->sampling == S2_MW) return 2.0 * M_PI / (double)(2 * P->L - 1);
+    if (P->sampling == S2_MWSS) return 2.0 * M_PI / (double)(2 * P->L);
+    return 4.0 * M_PI / (double)P->nsamp;                 // HEALPix (DH / GL: per-ring weights)
+}
+
+// forward of nm maps: slice maps (strides sm) -> flm.  adjoint: unit phi weight, no theta filter.
+int run_forward(s2_plan_t P, const double2 *maps, Strides sm, double2 *flm, int nm, const double *wl, char *ws,
+                hipStream_t st, bool adjoint)
+{
     const bool mw = P->sampling == S2_MW || P->sampling == S2_MWSS;   // theta-torus samplings
-    const int ss = P->sampling == S2_MWSS;
-    double2 *hpN0 = ss ? hp0 + (size_t)P->nslice * (2 * L - 1) : nullptr;
-    double q;
-    if (adjoint) q = 1.0;
-    else if (mw) q = 2.0 * M_PI / (double)(ss ? 2 * L : 2 * L - 1);
-    else q = 4.0 * M_PI / (double)P->nsamp;
-    for (int k = 0; k < P->nslice; ++k) {
-        double *F = F0 + k * nF;
-        {
+    {
         TIMED(S2_STAGE_PHI_FWD);
-        HIPCHK(launch_phi_fwd(st, P->fft_threads, P->fft_lds, P->nring, P->hstride, L, q, slice_maps[k], P->ring_nphi,
-                              P->ring_start, P->ring_shift, P->ring_fft, P->ffts, adjoint ? nullptr : P->ringq, F,
-                              fft_scratch(P, ws)),
-                   "forward phi-DFT");
-        }
-        TIMED(S2_STAGE_MW_THETA);
-        if (mw && !adjoint)
-            HIPCHK(launch_mw_filter(st, P->fft_threads, P->fft_lds, L, ss, P->hstride, P->slice_spin[k], P->ffts, P->wq,
-                                    P->ph, F, hp0 + k * (2 * L - 1), ss ? hpN0 + k * (2 * L - 1) : nullptr,
-                                    fft_scratch(P, ws), 0, 0, CONV_ARGS(P)), "MW theta filter");
-        else if (mw) {
-            HIPCHK(launch_pole_from_F(st, L, P->hstride, L - 1, F, hp0 + k * (2 * L - 1)), "pole line");
-            if (ss) HIPCHK(launch_pole_from_F(st, L, P->hstride, L, F, hpN0 + k * (2 * L - 1)), "north pole line");
-        }
+        HIPCHK(launch_phi_fwd(st, P->fft_threads, P->fft_lds, P->nring, P->hstride, P->L, phi_weight(P, adjoint),
+                              all_slices(P), nm * P->nslice, sm, ws_strides(P, P->szF), maps, P->ring_nphi,
+                              P->ring_start, P->ring_shift, P->ring_fft, P->ffts, adjoint ? nullptr : P->ringq,
+                              (double *)(ws + P->off_F), fft_scratch(P, ws)), "forward phi-DFT");
     }
-    return run_forward_dstage(P, F0, mw ? hp0 : nullptr, hpN0, flm, wl, ws, st);
+    if (mw) {
+        TIMED(S2_STAGE_MW_THETA);
+        int rc = adjoint ? run_pole_lines(P, nm, ws, st) : run_theta(P, nm, ws, st, 0, 0);
+        if (rc) return rc;
+    }
+    return run_forward_dstage(P, mw, flm, nm, wl, ws, st);
 }
 
 // Real signals (spin-0 S2 plan, Hermitian symmetry of the coefficients): the
 // sweeps carry the orders m >= 0 only and pairs of rings share a phi-DFT.
-int run_inverse_real(s2_plan_t P, const double2 *flm, double *map, char *ws, hipStream_t st)
+int run_inverse_real(s2_plan_t P, const double2 *flm, long long fstride, double *map, int nm, const double *wl,
+                     char *ws, hipStream_t st)
 {
-    int rc = run_inverse_dstage(P, flm, P->w_sht, ws, st, 1);
+    int rc = run_inverse_dstage(P, flm, fstride, nm, wl, ws, st, 1);
     if (rc) return rc;
     TIMED(S2_STAGE_PHI_INV);
-    HIPCHK(launch_phi_inv_real(st, P->fft_threads, P->fft_lds, P->npair, P->L, P->nreg, P->inv_nblk, P->ring_pairs,
-                               (const double *)(ws + P->off_P), P->mtop, flm, P->w_sht[0], P->ring_nphi,
-                               P->ring_start, P->ring_shift, P->ring_fft, P->ffts, map, fft_scratch(P, ws)),
-           "real inverse phi-DFT");
+    HIPCHK(launch_phi_inv_real(st, P->fft_threads, P->fft_lds, P->npair, P->L, P->nreg, P->inv.nblk, nm, wsd(P),
+                               fstride, P->nsamp, P->ring_pairs, (const double *)(ws + P->off_P), P->mtop, flm, wl,
+                               P->ring_nphi, P->ring_start, P->ring_shift, P->ring_fft, P->ffts, map,
+                               fft_scratch(P, ws)), "real inverse phi-DFT");
     return S2_OK;
 }
 
@@ -1114,35 +1189,22 @@ int run_inverse_real(s2_plan_t P, const double2 *flm, double *map, char *ws, hip
 // real map cotangent: 2 A^H g at m > 0 and Re (A^H g) at m = 0 (A the complex
 // inverse), i.e. the unnormalised phi-DFT, no theta filter, the forward-type
 // sweep with the SHT weights, and the finish in its gradient mode.
-int run_forward_real(s2_plan_t P, const double *map, double2 *flm, char *ws, hipStream_t st, bool vjp = false)
+int run_forward_real(s2_plan_t P, const double *map, double2 *flm, int nm, char *ws, hipStream_t st, bool vjp = false)
 {
-    const int L = P->L;
     const bool mw = P->sampling == S2_MW || P->sampling == S2_MWSS;   // theta-torus samplings
-    const int ss = P->sampling == S2_MWSS;
-    double *F0 = (double *)(ws + P->off_F);
-    double2 *hp0 = (double2 *)(ws + P->off_hpole);
-    double2 *hpN0 = ss ? hp0 + (size_t)P->nslice * (2 * L - 1) : nullptr;
-    double q;
-    if (vjp) q = 1.0;
-    else if (mw) q = 2.0 * M_PI / (double)(ss ? 2 * L : 2 * L - 1);
-    else q = 4.0 * M_PI / (double)P->nsamp;               // HEALPix (DH / GL: per-ring weights)
     {
-    TIMED(S2_STAGE_PHI_FWD);
-    HIPCHK(launch_phi_fwd_real(st, P->fft_threads, P->fft_lds, P->nring, P->hstride, P->npair, L, q, P->ring_pairs,
-                               map, P->ring_nphi, P->ring_start, P->ring_shift, P->ring_fft, P->ffts,
-                               vjp ? nullptr : P->ringq, F0, fft_scratch(P, ws)), "real forward phi-DFT");
+        TIMED(S2_STAGE_PHI_FWD);
+        HIPCHK(launch_phi_fwd_real(st, P->fft_threads, P->fft_lds, P->nring, P->hstride, P->npair, P->L,
+                                   phi_weight(P, vjp), nm, P->nsamp, wsd(P), P->ring_pairs, map, P->ring_nphi,
+                                   P->ring_start, P->ring_shift, P->ring_fft, P->ffts, vjp ? nullptr : P->ringq,
+                                   (double *)(ws + P->off_F), fft_scratch(P, ws)), "real forward phi-DFT");
     }
     if (mw) {
         TIMED(S2_STAGE_MW_THETA);
-        if (!vjp) {
-            HIPCHK(launch_mw_filter(st, P->fft_threads, P->fft_lds, L, ss, P->hstride, 0, P->ffts, P->wq, P->ph, F0,
-                                    hp0, hpN0, fft_scratch(P, ws), 1, 0, CONV_ARGS(P)), "MW theta filter");
-        } else {
-            HIPCHK(launch_pole_from_F(st, L, P->hstride, L - 1, F0, hp0), "pole line");
-            if (ss) HIPCHK(launch_pole_from_F(st, L, P->hstride, L, F0, hpN0), "north pole line");
-        }
+        int rc = vjp ? run_pole_lines(P, nm, ws, st) : run_theta(P, nm, ws, st, 1, 0);
+        if (rc) return rc;
     }
-    return run_forward_dstage(P, F0, mw ? hp0 : nullptr, hpN0, flm, P->w_sht, ws, st, vjp ? 2 : 1);
+    return run_forward_dstage(P, mw, flm, nm, P->w_sht, ws, st, vjp ? 2 : 1);
 }
 
 // The adjoint of the forward transform restricted to real maps: Re(F^H G) =
@@ -1150,53 +1212,44 @@ int run_forward_real(s2_plan_t P, const double *map, double2 *flm, char *ws, hip
 // MW / MWSS as the complex adjoint (gather, adjoint theta filter on one side,
 // scatter) ending in the paired real phi-DFT; DH / GL / HEALPix the real
 // inverse with the forward-adjoint weights, then the ring weights (DH / GL).
-int run_forward_real_adjoint(s2_plan_t P, const double2 *G, double *map, char *ws, hipStream_t st)
+int run_forward_real_adjoint(s2_plan_t P, const double2 *G, double *map, int nm, char *ws, hipStream_t st)
 {
-    const int L = P->L;
-    const int ss = P->sampling == S2_MWSS;
     double2 *H = (double2 *)(ws + P->off_hsym);
-    HIPCHK(launch_hermitian_part(st, L, G, H), "Hermitian part");
+    const long long hs = (long long)(P->ws1 / sizeof(double2));
+    HIPCHK(launch_hermitian_part(st, nm, coef_n(P), hs, P->L, G, H), "Hermitian part");
+    int rc;
     if (P->sampling != S2_MW && P->sampling != S2_MWSS) {
-        int rc = run_inverse_dstage(P, H, P->w_fadj, ws, st, 1);
-        if (rc) return rc;
-        {
-        TIMED(S2_STAGE_PHI_INV);
-        HIPCHK(launch_phi_inv_real(st, P->fft_threads, P->fft_lds, P->npair, L, P->nreg, P->inv_nblk, P->ring_pairs,
-                                   (const double *)(ws + P->off_P), P->mtop, H, P->w_fadj[0], P->ring_nphi,
-                                   P->ring_start, P->ring_shift, P->ring_fft, P->ffts, map, fft_scratch(P, ws)),
-               "real inverse phi-DFT");
-        }
+        if ((rc = run_inverse_real(P, H, hs, map, nm, P->w_fadj, ws, st))) return rc;
         if (P->ringq)
-            HIPCHK(launch_ring_scale_real(st, P->nring, P->ring_start, P->ring_nphi, P->ringq, map), "ring weights");
+            HIPCHK(launch_ring_scale_real(st, nm, P->nsamp, P->nring, P->ring_start, P->ring_nphi, P->ringq, map),
+                   "ring weights");
         return S2_OK;
     }
-    int rc = run_inverse_dstage(P, H, P->w_sht, ws, st, 1);
-    if (rc) return rc;
-    double *P0 = (double *)(ws + P->off_P);
-    double *F0 = (double *)(ws + P->off_F);
-    double2 *hp0 = (double2 *)(ws + P->off_hpole);
-    double2 *hpN0 = ss ? hp0 + (size_t)P->nslice * (2 * L - 1) : nullptr;
-    double *Q0 = (double *)(ws + P->off_Q);
-    const double q = 2.0 * M_PI / (double)(ss ? 2 * L : 2 * L - 1);
-    {
-    TIMED(S2_STAGE_MW_THETA);
     // side B of the gathered rows is not produced by the half sweep and is never read
-    HIPCHK(launch_fadj_gather(st, L, ss, P->inv_nblk, 0, P0, P->mtop, H, P->w_sht[0], P->hstride, F0),
-           "adjoint gather");
-    HIPCHK(launch_mw_filter(st, P->fft_threads, P->fft_lds, L, ss, P->hstride, 0, P->ffts, P->wq, P->ph, F0, hp0,
-                            hpN0, fft_scratch(P, ws), 1, 1, CONV_ARGS(P)), "adjoint theta filter");
-    HIPCHK(launch_fadj_scatter(st, L, ss, P->hstride, q, F0, hp0, hpN0, Q0), "adjoint scatter");
-    }
+    if ((rc = run_inverse_dstage(P, H, hs, nm, P->w_sht, ws, st, 1))) return rc;
+    if ((rc = run_theta_adjoint(P, H, Strides{hs, 0}, nm, P->w_sht, ws, st, 1))) return rc;
     TIMED(S2_STAGE_PHI_INV);
-    HIPCHK(launch_phi_inv_real(st, P->fft_threads, P->fft_lds, P->npair, L, P->nring, 1, P->ring_pairs, Q0, P->mtop1,
-                               H, P->w_sht[0], P->ring_nphi, P->ring_start, P->ring_shift, P->ring_fft, P->ffts, map,
-                               fft_scratch(P, ws)), "real adjoint phi-DFT");
+    HIPCHK(launch_phi_inv_real(st, P->fft_threads, P->fft_lds, P->npair, P->L, P->nring, 1, nm, wsd(P), hs, P->nsamp,
+                               P->ring_pairs, (const double *)(ws + P->off_Q), P->mtop1, H, P->w_sht, P->ring_nphi,
+                               P->ring_start, P->ring_shift, P->ring_fft, P->ffts, map, fft_scratch(P, ws)),
+           "real adjoint phi-DFT");
+    return S2_OK;
+}
+
+// maps [0, batch) in groups that share the launches: go(first map, maps of the group)
+template <typename F>
+int over_groups(int batch, int group, F go)
+{
+    for (int b = 0; b < batch; b += group) {
+        const int rc = go(b, std::min(group, batch - b));
+        if (rc) return rc;
+    }
     return S2_OK;
 }
 
 // ---------------------------------------------------------------- matrix-core path
 // Batched inverse: flm [B][S][L][2L-1] -> slice maps [B][S][nsamp].
-int run_inverse_mfma(s2_plan_t P, const double2 *flm, int B, double2 *maps, const std::vector<double *> &wl, char *ws,
+int run_inverse_mfma(s2_plan_t P, const double2 *flm, int B, double2 *maps, const double *wl, char *ws,
                      hipStream_t st)
 {
     const int L = P->L, S = P->nslice, fmt = P->prec;
@@ -1228,7 +1281,8 @@ int run_inverse_mfma(s2_plan_t P, const double2 *flm, int B, double2 *maps, cons
             {
             TIMED(S2_STAGE_PACK);
             HIPCHK(launch_pack_a(st, fmt, g, r.n, mlo, mcn, B, (long long)(S * slab), fa, fb,
-                                 r.sliceA >= 0 ? wl[r.sliceA] : nullptr, r.sliceB >= 0 ? wl[r.sliceB] : nullptr, A),
+                                 r.sliceA >= 0 ? wl + (size_t)r.sliceA * L : nullptr,
+                                 r.sliceB >= 0 ? wl + (size_t)r.sliceB * L : nullptr, A),
                    "coefficient pack");
             }
             TIMED(S2_STAGE_MFMA);
@@ -1236,19 +1290,16 @@ int run_inverse_mfma(s2_plan_t P, const double2 *flm, int B, double2 *maps, cons
                    "inverse contraction");
         }
     }
-    for (int b = 0; b < B; ++b)
-        for (int k = 0; k < S; ++k) {
-            TIMED(S2_STAGE_PHI_INV);
-            HIPCHK(launch_phi_inv(st, P->fft_threads, P->fft_lds, P->nring, L, P->nreg, 1, P->slice_spin[k],
-                                  Pm + ((size_t)b * S + k) * nP1, P->mtop1, flm + ((size_t)b * S + k) * slab, wl[k],
-                                  P->ring_nphi, P->ring_start, P->ring_shift, P->ring_fft, P->ffts,
-                                  maps + ((size_t)b * S + k) * P->nsamp, fft_scratch(P, ws)), "inverse phi-DFT");
-        }
+    TIMED(S2_STAGE_PHI_INV);
+    HIPCHK(launch_phi_inv(st, P->fft_threads, P->fft_lds, P->nring, L, P->nreg, 1, all_slices(P), B * S,
+                          Strides{(long long)(S * nP1), (long long)nP1}, coef_strides(P), map_strides(P), Pm, P->mtop1, flm,
+                          wl, P->ring_nphi, P->ring_start, P->ring_shift, P->ring_fft, P->ffts, maps,
+                          fft_scratch(P, ws)), "inverse phi-DFT");
     return S2_OK;
 }
 
 // Batched forward (adjoint: unit phi weight, no theta filter): slice maps [B][S][nsamp] -> flm [B][S][L][2L-1].
-int run_forward_mfma(s2_plan_t P, const double2 *maps, int B, double2 *flm, const std::vector<double *> &wl, char *ws,
+int run_forward_mfma(s2_plan_t P, const double2 *maps, int B, double2 *flm, const double *wl, char *ws,
                      hipStream_t st, bool adjoint)
 {
     const int L = P->L, S = P->nslice, fmt = P->prec;
@@ -1265,38 +1316,32 @@ int run_forward_mfma(s2_plan_t P, const double2 *maps, int B, double2 *flm, cons
     double *Fm = (double *)(ws + P->off_mF);
     double *Qm = (double *)(ws + P->off_mQ);
     double2 *hp = (double2 *)(ws + P->off_mhp);
-    double2 *hpN = ss ? hp + (size_t)B * S * (2 * L - 1) : nullptr;
+    double2 *hpN = mw && ss ? hp + (size_t)B * S * (2 * L - 1) : nullptr;
     const int nxp1 = std::max(P->nxp, 1);
     const size_t nQx1 = (size_t)L * nxp1 * 4;
     double *Qxm = P->nxp > 0 ? (double *)(ws + P->off_mQx) : nullptr;
     if (Qxm) HIPCHK(launch_zero(st, Qxm, (size_t)B * S * nQx1 * sizeof(double)), "continuation sums clear");
-    double q;
-    if (adjoint) q = 1.0;
-    else if (mw) q = 2.0 * M_PI / (double)(ss ? 2 * L : 2 * L - 1);
-    else q = 4.0 * M_PI / (double)P->nsamp;
-    for (int b = 0; b < B; ++b)
-        for (int k = 0; k < S; ++k) {
-            const size_t bk = (size_t)b * S + k;
-            double *F = Fm + bk * nF;
-            {
-            TIMED(S2_STAGE_PHI_FWD);
-            HIPCHK(launch_phi_fwd(st, P->fft_threads, P->fft_lds, P->nring, P->hstride, L, q, maps + bk * P->nsamp,
-                                  P->ring_nphi, P->ring_start, P->ring_shift, P->ring_fft, P->ffts,
-                                  adjoint ? nullptr : P->ringq, F,
-                                  fft_scratch(P, ws)),
-                   "forward phi-DFT");
-            }
-            TIMED(S2_STAGE_MW_THETA);
-            if (mw && !adjoint)
-                HIPCHK(launch_mw_filter(st, P->fft_threads, P->fft_lds, L, ss, P->hstride, P->slice_spin[k], P->ffts,
-                                        P->wq, P->ph, F, hp + bk * (2 * L - 1), ss ? hpN + bk * (2 * L - 1) : nullptr,
-                                        fft_scratch(P, ws), 0, 0, CONV_ARGS(P)),
+    const Strides sF{(long long)(S * nF), (long long)nF}, sh{(long long)S * (2 * L - 1), 2 * L - 1};
+    {
+        TIMED(S2_STAGE_PHI_FWD);
+        HIPCHK(launch_phi_fwd(st, P->fft_threads, P->fft_lds, P->nring, P->hstride, L, phi_weight(P, adjoint),
+                              all_slices(P), B * S, map_strides(P), sF, maps, P->ring_nphi, P->ring_start, P->ring_shift,
+                              P->ring_fft, P->ffts, adjoint ? nullptr : P->ringq, Fm, fft_scratch(P, ws)),
+               "forward phi-DFT");
+    }
+    if (mw) {
+        TIMED(S2_STAGE_MW_THETA);
+        if (!adjoint) {
+            HIPCHK(launch_mw_filter(st, P->fft_threads, P->fft_lds, L, ss, P->hstride, all_slices(P), B * S, sF, sh,
+                                    P->ffts, P->wq, P->ph, Fm, hp, hpN, fft_scratch(P, ws), 0, 0, CONV_ARGS(P)),
                    "MW theta filter");
-            else if (mw) {
-                HIPCHK(launch_pole_from_F(st, L, P->hstride, L - 1, F, hp + bk * (2 * L - 1)), "pole line");
-                if (ss) HIPCHK(launch_pole_from_F(st, L, P->hstride, L, F, hpN + bk * (2 * L - 1)), "north pole line");
-            }
+        } else {
+            HIPCHK(launch_pole_from_F(st, L, P->hstride, L - 1, all_slices(P), B * S, sF, sh, Fm, hp), "pole line");
+            if (ss)
+                HIPCHK(launch_pole_from_F(st, L, P->hstride, L, all_slices(P), B * S, sF, sh, Fm, hpN),
+                       "north pole line");
         }
+    }
     for (size_t ri = 0; ri < P->runs.size(); ++ri) {
         const Run &r = P->runs[ri];
         const double *FA = r.sliceA >= 0 ? Fm + r.sliceA * nF : Fm + r.sliceB * nF;
@@ -1325,15 +1370,10 @@ int run_forward_mfma(s2_plan_t P, const double2 *maps, int B, double2 *flm, cons
                                    (long long)(S * nQx1)), "forward contraction");
         }
     }
-    for (int b = 0; b < B; ++b)
-        for (int k = 0; k < S; ++k) {
-            const size_t bk = (size_t)b * S + k;
-            const int s = P->slice_spin[k];
-            TIMED(S2_STAGE_FINISH);
-            HIPCHK(launch_finish_fwd(st, L, 1, s, s, Qm + bk * nQ1, Qxm ? Qxm + bk * nQx1 : nullptr, nxp1, wl[k],
-                                     mw ? hp + bk * (2 * L - 1) : nullptr, ss ? hpN + bk * (2 * L - 1) : nullptr,
-                                     flm + bk * slab), "forward finish");
-        }
+    TIMED(S2_STAGE_FINISH);
+    HIPCHK(launch_finish_fwd(st, L, 1, all_slices(P), B * S, Strides{(long long)(S * nQ1), (long long)nQ1},
+                             Strides{(long long)(S * nQx1), (long long)nQx1}, sh, coef_strides(P), nullptr, Qm, Qxm, nxp1,
+                             wl, mw ? hp : nullptr, hpN, flm), "forward finish");
     return S2_OK;
 }
 
@@ -1350,11 +1390,10 @@ int s2_inverse(s2_plan_t P, const void *flm, void *f, int batch, void *workspace
     hipStream_t st = (hipStream_t)hip_stream;
     const size_t slab = (size_t)P->L * (2 * P->L - 1);
     if (P->mfma) return run_inverse_mfma(P, (const double2 *)flm, batch, (double2 *)f, P->w_sht, (char *)workspace, st);
-    for (int b = 0; b < batch; ++b) {
-        double2 *out = (double2 *)f + (size_t)b * P->nsamp;
-        if ((rc = run_inverse(P, (const double2 *)flm + b * slab, &out, P->w_sht, (char *)workspace, st))) return rc;
-    }
-    return S2_OK;
+    return over_groups(batch, P->group, [&](int b, int nm) {
+        return run_inverse(P, (const double2 *)flm + b * slab, (double2 *)f + (size_t)b * P->nsamp, map_strides(P), nm,
+                           P->w_sht, (char *)workspace, st);
+    });
 }
 
 }  // extern "C"
@@ -1393,8 +1432,7 @@ int scratch_on_current_device(void **out)
 // split-Bluestein scratch when a ring DFT needs it)
 size_t inverse_extent(const s2_plan_s *P)
 {
-    if (P->sz_fscr) return P->off_fscr + P->sz_fscr;
-    return P->off_P + P->szP * P->nslice;
+    return P->off_P + P->szP * P->nslice + (P->sz_fscr ? 256 + P->sz_fscr : 0);
 }
 
 }  // namespace
@@ -1419,10 +1457,9 @@ int s2_inverse_noalloc(s2_plan_t P, const void *flm, void *f, int batch, void *h
     hipStream_t st = (hipStream_t)hip_stream;
     const size_t slab = (size_t)P->L * (2 * P->L - 1);
     g_no_timing = true;
-    for (int b = 0; b < batch && rc == S2_OK; ++b) {
-        double2 *out = (double2 *)f + (size_t)b * P->nsamp;
-        rc = run_inverse(P, (const double2 *)flm + b * slab, &out, P->w_sht, (char *)ws, st);
-    }
+    for (int b = 0; b < batch && rc == S2_OK; ++b)       // one map's workspace at a time
+        rc = run_inverse(P, (const double2 *)flm + b * slab, (double2 *)f + (size_t)b * P->nsamp, map_strides(P), 1,
+                         P->w_sht, (char *)ws, st, true);
     g_no_timing = false;
     return rc;
 }
@@ -1437,11 +1474,10 @@ int s2_forward(s2_plan_t P, const void *f, void *flm, int batch, void *workspace
     const size_t slab = (size_t)P->L * (2 * P->L - 1);
     if (P->mfma)
         return run_forward_mfma(P, (const double2 *)f, batch, (double2 *)flm, P->w_sht, (char *)workspace, st, false);
-    for (int b = 0; b < batch; ++b) {
-        const double2 *in = (const double2 *)f + (size_t)b * P->nsamp;
-        if ((rc = run_forward(P, &in, (double2 *)flm + b * slab, P->w_sht, (char *)workspace, st, false))) return rc;
-    }
-    return S2_OK;
+    return over_groups(batch, P->group, [&](int b, int nm) {
+        return run_forward(P, (const double2 *)f + (size_t)b * P->nsamp, map_strides(P), (double2 *)flm + b * slab, nm,
+                           P->w_sht, (char *)workspace, st, false);
+    });
 }
 
 int s2_inverse_adjoint(s2_plan_t P, const void *g, void *g_flm, int batch, void *workspace, void *hip_stream)
@@ -1454,11 +1490,10 @@ int s2_inverse_adjoint(s2_plan_t P, const void *g, void *g_flm, int batch, void 
     const size_t slab = (size_t)P->L * (2 * P->L - 1);
     if (P->mfma)
         return run_forward_mfma(P, (const double2 *)g, batch, (double2 *)g_flm, P->w_sht, (char *)workspace, st, true);
-    for (int b = 0; b < batch; ++b) {
-        const double2 *in = (const double2 *)g + (size_t)b * P->nsamp;
-        if ((rc = run_forward(P, &in, (double2 *)g_flm + b * slab, P->w_sht, (char *)workspace, st, true))) return rc;
-    }
-    return S2_OK;
+    return over_groups(batch, P->group, [&](int b, int nm) {
+        return run_forward(P, (const double2 *)g + (size_t)b * P->nsamp, map_strides(P), (double2 *)g_flm + b * slab, nm,
+                           P->w_sht, (char *)workspace, st, true);
+    });
 }
 
 int s2_forward_adjoint(s2_plan_t P, const void *g_flm, void *g, int batch, void *workspace, void *hip_stream)
@@ -1470,17 +1505,17 @@ int s2_forward_adjoint(s2_plan_t P, const void *g_flm, void *g, int batch, void 
     if (batch == 0) return S2_OK;
     hipStream_t st = (hipStream_t)hip_stream;
     const size_t slab = (size_t)P->L * (2 * P->L - 1);
-    for (int b = 0; b < batch; ++b) {
+    return over_groups(batch, P->group, [&](int b, int nm) {
         const double2 *G = (const double2 *)g_flm + b * slab;
         double2 *out = (double2 *)g + (size_t)b * P->nsamp;
         if (P->sampling == S2_MW || P->sampling == S2_MWSS)
-            rc = run_forward_adjoint_mw(P, G, &out, P->w_sht, (char *)workspace, st);
-        else rc = run_inverse(P, G, &out, P->w_fadj, (char *)workspace, st);
+            return run_forward_adjoint_mw(P, G, out, map_strides(P), nm, P->w_sht, (char *)workspace, st);
+        int rc = run_inverse(P, G, out, map_strides(P), nm, P->w_fadj, (char *)workspace, st);
         if (rc) return rc;
         if (P->ringq)
-            HIPCHK(launch_ring_scale(st, P->nring, 2 * P->L - 1, P->ringq, out), "quadrature weights");
-    }
-    return S2_OK;
+            HIPCHK(launch_ring_scale(st, nm, P->nsamp, P->nring, 2 * P->L - 1, P->ringq, out), "quadrature weights");
+        return S2_OK;
+    });
 }
 
 int so3_inverse(s2_plan_t P, const void *flmn, void *f, int batch, void *workspace, void *hip_stream)
@@ -1495,27 +1530,24 @@ int so3_inverse(s2_plan_t P, const void *flmn, void *f, int batch, void *workspa
     if (P->mfma) {
         double2 *tmp = (S > 1) ? (double2 *)((char *)workspace + P->off_mmaps) : (double2 *)f;
         if ((rc = run_inverse_mfma(P, (const double2 *)flmn, batch, tmp, P->w_so3i, (char *)workspace, st))) return rc;
-        if (S > 1)
-            for (int b = 0; b < batch; ++b) {
-                TIMED(S2_STAGE_GAMMA);
-                HIPCHK(launch_gamma_dft(st, P->N, P->nsamp, +1, 1.0, P->groots, tmp + (size_t)b * S * P->nsamp,
-                                        (double2 *)f + (size_t)b * S * P->nsamp), "gamma DFT");
-            }
-        return S2_OK;
-    }
-    for (int b = 0; b < batch; ++b) {
-        double2 *out = (double2 *)f + (size_t)b * S * P->nsamp;
-        std::vector<double2 *> maps(S);
-        double2 *tmp = (S > 1) ? (double2 *)((char *)workspace + P->off_maps) : out;
-        for (int k = 0; k < S; ++k) maps[k] = tmp + (size_t)k * P->nsamp;
-        if ((rc = run_inverse(P, (const double2 *)flmn + (size_t)b * S * slab, maps.data(), P->w_so3i,
-                              (char *)workspace, st))) return rc;
         if (S > 1) {
             TIMED(S2_STAGE_GAMMA);
-            HIPCHK(launch_gamma_dft(st, P->N, P->nsamp, +1, 1.0, P->groots, tmp, out), "gamma DFT");
+            HIPCHK(launch_gamma_dft(st, batch, S * P->nsamp, S * P->nsamp, P->N, P->nsamp, +1, 1.0, P->groots, tmp,
+                                    (double2 *)f), "gamma DFT");
         }
+        return S2_OK;
     }
-    return S2_OK;
+    return over_groups(batch, P->group, [&](int b, int nm) {
+        double2 *out = (double2 *)f + (size_t)b * S * P->nsamp;
+        double2 *tmp = S > 1 ? (double2 *)((char *)workspace + P->off_maps) : out;
+        const Strides sm = S > 1 ? Strides{tmp_stride(P), P->nsamp} : map_strides(P);
+        int rc = run_inverse(P, (const double2 *)flmn + (size_t)b * S * slab, tmp, sm, nm, P->w_so3i,
+                             (char *)workspace, st);
+        if (rc || S == 1) return rc;
+        TIMED(S2_STAGE_GAMMA);
+        HIPCHK(launch_gamma_dft(st, nm, sm.map, S * P->nsamp, P->N, P->nsamp, +1, 1.0, P->groots, tmp, out), "gamma DFT");
+        return S2_OK;
+    });
 }
 
 int so3_forward(s2_plan_t P, const void *f, void *flmn, int batch, void *workspace, void *hip_stream)
@@ -1531,32 +1563,27 @@ int so3_forward(s2_plan_t P, const void *f, void *flmn, int batch, void *workspa
         const double2 *src = (const double2 *)f;
         if (S > 1) {
             double2 *tmp = (double2 *)((char *)workspace + P->off_mmaps);
-            for (int b = 0; b < batch; ++b) {
-                TIMED(S2_STAGE_GAMMA);
-                HIPCHK(launch_gamma_dft(st, P->N, P->nsamp, -1, 2.0 * M_PI / (double)S, P->groots,
-                                        (const double2 *)f + (size_t)b * S * P->nsamp, tmp + (size_t)b * S * P->nsamp),
-                       "gamma DFT");
-            }
+            TIMED(S2_STAGE_GAMMA);
+            HIPCHK(launch_gamma_dft(st, batch, S * P->nsamp, S * P->nsamp, P->N, P->nsamp, -1, 2.0 * M_PI / (double)S,
+                                    P->groots, src, tmp), "gamma DFT");
             src = tmp;
         }
         // one slice (N = 1): the gamma rule is the weight 2 pi alone, folded into the finish
-        const std::vector<double *> w1 = {P->w_so3f_n1};
-        return run_forward_mfma(P, src, batch, (double2 *)flmn, S > 1 ? P->w_so3f : w1, (char *)workspace, st, false);
+        return run_forward_mfma(P, src, batch, (double2 *)flmn, S > 1 ? P->w_so3f : P->w_so3f_n1, (char *)workspace, st,
+                                false);
     }
-    for (int b = 0; b < batch; ++b) {
+    return over_groups(batch, P->group, [&](int b, int nm) {
         const double2 *in = (const double2 *)f + (size_t)b * S * P->nsamp;
-        std::vector<const double2 *> maps(S);
         double2 *tmp = (double2 *)((char *)workspace + P->off_maps);
         // f_n = 2pi/(2N-1) sum_k f(gamma_k) e^{-i n gamma_k}  (Eq. 16, exact equispaced rule)
         {
-        TIMED(S2_STAGE_GAMMA);
-        HIPCHK(launch_gamma_dft(st, P->N, P->nsamp, -1, 2.0 * M_PI / (double)S, P->groots, in, tmp), "gamma DFT");
+            TIMED(S2_STAGE_GAMMA);
+            HIPCHK(launch_gamma_dft(st, nm, S * P->nsamp, tmp_stride(P), P->N, P->nsamp, -1, 2.0 * M_PI / (double)S,
+                                    P->groots, in, tmp), "gamma DFT");
         }
-        for (int k = 0; k < S; ++k) maps[k] = tmp + (size_t)k * P->nsamp;
-        if ((rc = run_forward(P, maps.data(), (double2 *)flmn + (size_t)b * S * slab, P->w_so3f, (char *)workspace,
-                              st, false))) return rc;
-    }
-    return S2_OK;
+        return run_forward(P, tmp, Strides{tmp_stride(P), P->nsamp}, (double2 *)flmn + (size_t)b * S * slab, nm,
+                           P->w_so3f, (char *)workspace, st, false);
+    });
 }
 
 static int check_real(const char *fn, s2_plan_t P)
@@ -1574,10 +1601,10 @@ int s2_inverse_real(s2_plan_t P, const void *flm, void *f, int batch, void *work
     if (batch == 0) return S2_OK;
     hipStream_t st = (hipStream_t)hip_stream;
     const size_t slab = (size_t)P->L * (2 * P->L - 1);
-    for (int b = 0; b < batch; ++b)
-        if ((rc = run_inverse_real(P, (const double2 *)flm + b * slab, (double *)f + (size_t)b * P->nsamp,
-                                   (char *)workspace, st))) return rc;
-    return S2_OK;
+    return over_groups(batch, P->group, [&](int b, int nm) {
+        return run_inverse_real(P, (const double2 *)flm + b * slab, (long long)slab, (double *)f + (size_t)b * P->nsamp,
+                                nm, P->w_sht, (char *)workspace, st);
+    });
 }
 
 int s2_forward_real(s2_plan_t P, const void *f, void *flm, int batch, void *workspace, void *hip_stream)
@@ -1587,10 +1614,10 @@ int s2_forward_real(s2_plan_t P, const void *f, void *flm, int batch, void *work
     if (batch == 0) return S2_OK;
     hipStream_t st = (hipStream_t)hip_stream;
     const size_t slab = (size_t)P->L * (2 * P->L - 1);
-    for (int b = 0; b < batch; ++b)
-        if ((rc = run_forward_real(P, (const double *)f + (size_t)b * P->nsamp, (double2 *)flm + b * slab,
-                                   (char *)workspace, st))) return rc;
-    return S2_OK;
+    return over_groups(batch, P->group, [&](int b, int nm) {
+        return run_forward_real(P, (const double *)f + (size_t)b * P->nsamp, (double2 *)flm + b * slab, nm,
+                                (char *)workspace, st);
+    });
 }
 
 int s2_inverse_real_adjoint(s2_plan_t P, const void *g, void *g_flm, int batch, void *workspace, void *hip_stream)
@@ -1600,10 +1627,10 @@ int s2_inverse_real_adjoint(s2_plan_t P, const void *g, void *g_flm, int batch, 
     if (batch == 0) return S2_OK;
     hipStream_t st = (hipStream_t)hip_stream;
     const size_t slab = (size_t)P->L * (2 * P->L - 1);
-    for (int b = 0; b < batch; ++b)
-        if ((rc = run_forward_real(P, (const double *)g + (size_t)b * P->nsamp, (double2 *)g_flm + b * slab,
-                                   (char *)workspace, st, true))) return rc;
-    return S2_OK;
+    return over_groups(batch, P->group, [&](int b, int nm) {
+        return run_forward_real(P, (const double *)g + (size_t)b * P->nsamp, (double2 *)g_flm + b * slab, nm,
+                                (char *)workspace, st, true);
+    });
 }
 
 int s2_forward_real_adjoint(s2_plan_t P, const void *g_flm, void *g, int batch, void *workspace, void *hip_stream)
@@ -1613,10 +1640,10 @@ int s2_forward_real_adjoint(s2_plan_t P, const void *g_flm, void *g, int batch, 
     if (batch == 0) return S2_OK;
     hipStream_t st = (hipStream_t)hip_stream;
     const size_t slab = (size_t)P->L * (2 * P->L - 1);
-    for (int b = 0; b < batch; ++b)
-        if ((rc = run_forward_real_adjoint(P, (const double2 *)g_flm + b * slab, (double *)g + (size_t)b * P->nsamp,
-                                           (char *)workspace, st))) return rc;
-    return S2_OK;
+    return over_groups(batch, P->group, [&](int b, int nm) {
+        return run_forward_real_adjoint(P, (const double2 *)g_flm + b * slab, (double *)g + (size_t)b * P->nsamp, nm,
+                                        (char *)workspace, st);
+    });
 }
 
 int so3_inverse_adjoint(s2_plan_t P, const void *g, void *g_flmn, int batch, void *workspace, void *hip_stream)
@@ -1635,31 +1662,27 @@ int so3_inverse_adjoint(s2_plan_t P, const void *g, void *g_flmn, int batch, voi
         const double2 *src = (const double2 *)g;
         if (S > 1) {
             double2 *tmp = (double2 *)((char *)workspace + P->off_mmaps);
-            for (int b = 0; b < batch; ++b) {
-                TIMED(S2_STAGE_GAMMA);
-                HIPCHK(launch_gamma_dft(st, P->N, P->nsamp, -1, 1.0, P->groots,
-                                        (const double2 *)g + (size_t)b * S * P->nsamp, tmp + (size_t)b * S * P->nsamp),
-                       "gamma DFT");
-            }
+            TIMED(S2_STAGE_GAMMA);
+            HIPCHK(launch_gamma_dft(st, batch, S * P->nsamp, S * P->nsamp, P->N, P->nsamp, -1, 1.0, P->groots, src, tmp),
+                   "gamma DFT");
             src = tmp;
         }
         return run_forward_mfma(P, src, batch, (double2 *)g_flmn, P->w_so3i, (char *)workspace, st, true);
     }
-    for (int b = 0; b < batch; ++b) {
-        const double2 *in = (const double2 *)g + (size_t)b * S * P->nsamp;
-        const double2 *src = in;
+    return over_groups(batch, P->group, [&](int b, int nm) {
+        const double2 *src = (const double2 *)g + (size_t)b * S * P->nsamp;
+        Strides sm = map_strides(P);
         if (S > 1) {
             double2 *tmp = (double2 *)((char *)workspace + P->off_maps);
             TIMED(S2_STAGE_GAMMA);
-            HIPCHK(launch_gamma_dft(st, P->N, P->nsamp, -1, 1.0, P->groots, in, tmp), "gamma DFT");
+            HIPCHK(launch_gamma_dft(st, nm, sm.map, tmp_stride(P), P->N, P->nsamp, -1, 1.0, P->groots, src, tmp),
+                   "gamma DFT");
             src = tmp;
+            sm.map = tmp_stride(P);
         }
-        std::vector<const double2 *> maps(S);
-        for (int k = 0; k < S; ++k) maps[k] = src + (size_t)k * P->nsamp;
-        if ((rc = run_forward(P, maps.data(), (double2 *)g_flmn + (size_t)b * S * slab, P->w_so3i, (char *)workspace,
-                              st, true))) return rc;
-    }
-    return S2_OK;
+        return run_forward(P, src, sm, (double2 *)g_flmn + (size_t)b * S * slab, nm, P->w_so3i, (char *)workspace, st,
+                           true);
+    });
 }
 
 int so3_forward_adjoint(s2_plan_t P, const void *g_flmn, void *g, int batch, void *workspace, void *hip_stream)
@@ -1676,16 +1699,15 @@ int so3_forward_adjoint(s2_plan_t P, const void *g_flmn, void *g, int batch, voi
     // so3_forward = per-n MW forwards after the gamma analysis (sign -1, weight 2pi/(2N-1)), so
     // its adjoint is the per-n forward adjoints followed by the gamma synthesis with that weight.
     double2 *tmp = (double2 *)((char *)workspace + P->off_maps);
-    std::vector<double2 *> maps(S);
-    for (int k = 0; k < S; ++k) maps[k] = tmp + (size_t)k * P->nsamp;
-    for (int b = 0; b < batch; ++b) {
-        if ((rc = run_forward_adjoint_mw(P, (const double2 *)g_flmn + (size_t)b * S * slab, maps.data(), P->w_so3f,
-                                         (char *)workspace, st))) return rc;
+    return over_groups(batch, P->group, [&](int b, int nm) {
+        int rc = run_forward_adjoint_mw(P, (const double2 *)g_flmn + (size_t)b * S * slab, tmp,
+                                        Strides{tmp_stride(P), P->nsamp}, nm, P->w_so3f, (char *)workspace, st);
+        if (rc) return rc;
         TIMED(S2_STAGE_GAMMA);
-        HIPCHK(launch_gamma_dft(st, P->N, P->nsamp, +1, 2.0 * M_PI / (double)S, P->groots, tmp,
-                                (double2 *)g + (size_t)b * S * P->nsamp), "gamma DFT");
-    }
-    return S2_OK;
+        HIPCHK(launch_gamma_dft(st, nm, tmp_stride(P), S * P->nsamp, P->N, P->nsamp, +1, 2.0 * M_PI / (double)S,
+                                P->groots, tmp, (double2 *)g + (size_t)b * S * P->nsamp), "gamma DFT");
+        return S2_OK;
+    });
 }
 
 int s2_plan_set_timing(s2_plan_t P, int enable)

@@ -59,28 +59,16 @@ struct FftArgs {
 };
 
 // ----------------------------------------------------------------- d-stage geometry
-constexpr int INV_NCH = 4;              // 8-degree chunks per wave, inverse d-stage
-constexpr int INV_J = 8 * INV_NCH;      // l-slots per wave
-constexpr int FWD_NCH = 1;              // 8-ring chunks per wave, forward d-stage
-constexpr int FWD_R = 8 * FWD_NCH;      // ring-slots per wave
+constexpr int SW_WAVES = 8;             // waves of a sweep workgroup (two per SIMD at 256 registers)
+constexpr int INV_BLK = 256;            // degrees of an inverse block at most (8 waves x 4 chunks of 8)
+constexpr int FWD_L = 64;               // degrees of a forward group
+constexpr int FWD_KS = 8;               // four-ring steps of a forward wave at most
+constexpr int FWD_BLK = 4 * FWD_KS * SW_WAVES;   // rings of a forward block at most
+constexpr int PAIR_MIN_RINGS = 64;      // mirror-ring sweeps from this many rings on
+constexpr double GROUP_ORDERS = 1024;   // a batch's maps share launches up to this much work per compute unit ..
+constexpr size_t GROUP_BYTES = (size_t)2 << 30;   // .. and this much workspace
 constexpr int GEN_NCH = 2;              // 8-degree chunks per wave, d-tile generator (matrix-core path)
-constexpr int DSTAGE_MAX_WAVES = 8;     // inverse sweep / d-tile generator workgroups: at most 512 threads
-constexpr int FWD_MAX_WAVES = 16;       // forward sweep workgroups: at most 1024 threads (4, 8 or 16 waves)
-
-// Order tiles of the sweeps.  Tile k runs the orders c[k] - 1 down to c[k+1]
-// (c[0] = L; the last tile runs down to the run's lowest order), so that more
-// workgroups share one run without adding partial sums (each order stays in one
-// tile).  A tile k > 0 starts from the recursion state after order c[k], held per
-// run in ck at offset off[k] as rows (l - c[k]), l >= c[k], of 3 x rp doubles:
-// {e_{c[k]}[ring], e_{c[k]+1}[ring], E[ring]} (a recursion slot state; see renorm).
-constexpr int MAX_ORDER_TILES = 8;
-struct OrderTiles {
-    int nt = 1;                             // tiles (1: the whole order range)
-    int rp = 0;                             // ring stride of a state row
-    int c[MAX_ORDER_TILES + 1] = {};
-    long long off[MAX_ORDER_TILES] = {};
-    const double *ck = nullptr;             // the run's state table (nt > 1)
-};
+constexpr int DSTAGE_MAX_WAVES = 8;     // d-tile generator workgroups: at most 512 threads
 
 // One recursion run: fixed second index n of d^l_{m,n}; its A side feeds the
 // slice of spin -n at orders +m, its B side the slice of spin +n at orders -m.

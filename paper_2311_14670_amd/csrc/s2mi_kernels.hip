@@ -1,26 +1,17 @@
-// s2mi_kernels.hip -- gfx950 kernels of the spin SHT / Wigner transforms.
+// s2mi_kernels.hip -- gfx950 kernels of the spin SHT / Wigner transforms outside
+// the Wigner sweeps (s2mi_sweep.hip).
 //
 // Paper: Price & McEwen, arXiv 2311.14670.
-//   d-stage   Wigner d^l_{m,n}(theta) by the descending-m recursion (Sec. 3.3,
-//             Eqs. 25-26) started from Eq. 27 in log space, renormalised as it
-//             runs (Sec. 3.4), fused with the l-contraction of Eq. 33 (inverse)
-//             or the theta-contraction of Eq. 30 (forward) -- Sec. 4.4.
+//   start     d^l_{l,n} of Eq. 27 in log space, once per plan.
 //   phi-DFT   Eqs. 31-32 per isolatitude ring; HEALPix rings repeat / fold the
 //             Fourier line (Sec. 4.2, HEALPix).
 //   MW theta  the exact MW theta integral (Sec. 4.2, MW): torus extension,
 //             band-limited sin(theta) weight, evaluated on the L rings.
+//   finish    block sums, weights and layout of the forward; glue of the adjoints.
 //
-// Recursion in rescaled form.  With alpha_k = sqrt((l+k)(l-k+1)) and
-// d_m = e_m g_m (g from the plan tables), Eq. 25 becomes
-//     e_{m-1} = kappa_m lambda_m e_m - e_{m+1},  lambda_m = (n - m cos th)/sin th,
-// two FP64 operations per step.  Each (ring, l) carries (e_m, e_{m+1}, E) with
-// d = e g 2^E.  While the value is below 2^-600 (E < 0) the pair is held scaled near
-// 2^-600 and renormalised by an exact power of two every RN orders; the contraction
-// uses e as it stands, so such a slot adds a negligible amount (below 2^-279 of its
-// record) with no per-step scaling.  Once the value is within 2^-600 of unit scale
-// it is realised (E = 0, d = e g): |d| <= 1 and the recursion runs downhill in m, so
-// it can no longer overflow or meaningfully underflow.  A chunk whose lanes are all
-// realised skips the renormalisation.
+// Transforms of several maps and slices share one launch: blockIdx.y is the item
+// item0 + y = map * nslice + slice, and every buffer has a stride per map and one per
+// slice (Items).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -76,7 +67,12 @@ __device__ __forceinline__ void d_init(int l, int n, DD lbin, DD ls, DD lc, doub
     if ((l - n) & 1) v = -v;
     int ex = (int)fl;
     if (ex >= -RT) { v = ldexp(v, ex); ex = 0; }
-    else { v = ldexp(v, -RT); ex += RT; }
+    else {
+        v = ldexp(v, -RT);
+        ex += RT;
+        v = ldexp(v, ex & 3);                            // multiples of 4 (see renorm)
+        ex &= ~3;
+    }
     e = v;
     E = ex;
 }
@@ -98,954 +94,16 @@ __global__ void k_init_table(int L, int nreg, int n, const double *__restrict__ 
     init[i] = make_double2(e, (double)E);
 }
 
-// ------------------------------------------------------------------ inverse pack
-// Records in the inverse sweep's slot order, C[blk][m + nx][wave][slot] = 5 doubles
-//   {kappa_{m+1}^l, wA_l g_m^l flmA[l][m], wB_l g_m^l (-1)^{m-n} flmB[l][-m]}
-// for l = lslot[blk][wave][slot] and orders m in [-nx, L); zeros where the run
-// does not reach (l < max(m, |n|), empty slot) or the side is absent.  The
-// B record is used at m > 0 and, for n != 0, at m <= 0 by the continuation of
-// the run below m = 0 (orders m <= 0 then feed the B slice at -m >= 0 and the
-// A slice at m < 0).  A wave reads the records of one order at fixed offsets
-// from a single base address.  One side (rs = 3): the records hold kappa and the
-// A side (real signals: the B side is its conjugate) or, with flmA absent, the
-// B side (a spin-s sphere run that feeds only the orders -m of its slice).
-__global__ void k_pack_inv(int L, int nx, int n, int nslot, int S, int rs, const int *__restrict__ lslot,
-                           const double2 *__restrict__ flmA, const double2 *__restrict__ flmB,
-                           const double *__restrict__ wA, const double *__restrict__ wB,
-                           const double *__restrict__ kap, const double *__restrict__ gtab, double *__restrict__ C)
-{
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;   // i = (blk, slot-in-block)
-    const int m = (int)blockIdx.y - nx;
-    if (i >= (size_t)nslot) return;
-    const int M = 2 * L - 1;
-    const int an = n < 0 ? -n : n;
-    const int l = lslot[i];
-    double rec[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    if (l >= 0 && l >= m && l >= an) {
-        const double g = gtab[(ptrdiff_t)m * L + l];
-        if (l > m) rec[0] = kap[(ptrdiff_t)m * L + l];
-        if (flmA) {
-            const double2 a = flmA[(size_t)l * M + (L - 1) + m];
-            const double sa = wA[l] * g;
-            rec[1] = sa * a.x;
-            rec[2] = sa * a.y;
-        }
-        if (flmB && (m > 0 || an > 0)) {
-            const double2 b = flmB[(size_t)l * M + (L - 1) - m];
-            double sb = wB[l] * g;
-            if ((m - n) & 1) sb = -sb;
-            rec[3] = sb * b.x;
-            rec[4] = sb * b.y;
-        }
-    }
-    // slot index i = blk * S + s (S slots per block); record at ((blk * (L + nx) + m + nx) * S + s)
-    const int blk = (int)(i / S), s = (int)(i % S);
-    double *o = C + (((size_t)blk * (L + nx) + (m + nx)) * S + s) * rs;
-    if (rs == 3) {
-        o[0] = rec[0];
-        o[1] = flmA ? rec[1] : rec[3];
-        o[2] = flmA ? rec[2] : rec[4];
-    } else {
-#pragma unroll
-        for (int q = 0; q < 5; ++q) o[q] = rec[q];
-    }
-}
-
-// ------------------------------------------------------------------ inverse d-stage
-// Lanes = 64 rings.  Each wave owns two chunks of SG = 8 consecutive l (a high
-// and a low chunk, for balance; slot j of a chunk holds l = base + SG-1-j),
-// waves of a workgroup share the rings and split the l-range.  A slot whose l
-// has not started (l < m) has zero state and zero records, so chunks need no
-// per-slot activity test: a chunk is skipped until its top l is reached, its
-// SG starts happen in SG consecutive "ramp" orders, and afterwards it runs the
-// branch-free step
-//   e_{m-1} = (kappa lambda) e_m - e_{m+1};  acc += e * C[m][slot].{A,B}.
-// The two state registers of a slot alternate roles between consecutive
-// orders (PAR), so the recursion needs no register moves.  Per order, each
-// wave's partial sums are reduced over the waves in LDS by a rotating group of
-// four waves and written to partA/partB[blk][ring][m].
-// Renormalisation pass over chunks that are not yet realised, every RN orders (see
-// s2mi_recur.h); a chunk whose lanes all reached E = 0 stays realised while no degree
-// starts in it.  (Passes every 8 orders: MW L = 2048 inverse 2.70 ms, forward 2.78 ms;
-// every 16: 2.62 and 2.71-2.76 ms.)
-// Orders of record / spectra prefetch ahead of use (both sweeps, every run).  Measured
-// at MW L = 2048 spin 0 with the unscaled contraction and passes every 16 orders:
-// inverse 2.61 / 2.60 / 2.62 ms and forward 2.72 / 2.68 / 2.74 ms at 3 / 2 / 4 orders
-// ahead.
-constexpr int PFD = 2;
-
-// ------------------------------------------------------------------ order-tile states
-// State of the descending recursion (Eq. 25 in the rescaled form of the sweeps)
-// after order c of every order-tile cut c = ot.c[k], k >= 1, for ring r and degree
-// l >= c: thread (r, l) starts at order l from d^l_{l,n} (Eq. 27) and steps down
-// with the sweeps' operations (kappa lambda, then one fma), renormalising every RN
-// orders by exact powers of two at the same orders as the sweeps, so a tile that
-// starts from this state holds exactly the state of the uninterrupted sweep.  Rings past nreg and degrees below |n| (never started)
-// hold zeros.
-__global__ void k_order_ckpt(int L, int nreg, int n, const double *__restrict__ cot, const double *__restrict__ csc,
-                             const double2 *__restrict__ init, const double *__restrict__ kap, OrderTiles ot,
-                             double *__restrict__ ck)
-{
-    const int r = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    const int l = (int)blockIdx.y;
-    if (r >= ot.rp) return;
-    const int an = n < 0 ? -n : n;
-    const bool live = r < nreg && l >= an;
-    double cur = 0.0, prev = 0.0;                        // e_m, e_{m+1}
-    int E = 0;
-    double ct = 0.0, ncs = 0.0;
-    if (live) {
-        const double2 v = init[(size_t)r * L + l];
-        cur = v.x;
-        E = (int)v.y;
-        ct = cot[r];
-        ncs = (double)n * csc[r];
-    }
-    int m = l;
-    for (int k = 1; k < ot.nt; ++k) {
-        const int c = ot.c[k];
-        if (c > l) continue;
-        if (live) {
-            for (int mm = m - 1; mm >= c; --mm) {
-                const double lam = fma(-(double)(mm + 1), ct, ncs);
-                const double p = kap[(ptrdiff_t)mm * L + l] * lam;
-                const double nw = fma(p, cur, -prev);
-                prev = cur;
-                cur = nw;
-                if ((mm & (RN - 1)) == 0) renorm(cur, prev, E);
-            }
-            m = c;
-        }
-        double *q = ck + ot.off[k] + (size_t)(l - c) * 3 * ot.rp + r;
-        q[0] = cur;
-        q[ot.rp] = prev;
-        q[2 * ot.rp] = (double)E;
-    }
-}
-
-// Workgroups of the sweeps hold W = 4, 8 or 16 waves; the 4 x 64 outputs of an
-// order are reduced by one group of four waves, rotating with the order.
-__device__ __forceinline__ int reducer_group(int m, int W)
-{
-    return m & ((W >> 2) - 1);                            // positive residue, also for m < 0
-}
-
-// Sum over the W waves of one output's partials in LDS (NC components of 64 per
-// wave).  The reads of all MAXW slots are issued together; slots of absent waves
-// are read (inside the buffer) but selected away, so stale contents never enter
-// the sum.  The sum is a pairwise tree (depth log2 MAXW instead of a chain of MAXW
-// dependent adds).
-template <int MAXW, int NC = 4>
-__device__ __forceinline__ double wave_sum(const double *rb, int comp, int i, int W)
-{
-    double v[MAXW];
-#pragma unroll
-    for (int ww = 0; ww < MAXW; ++ww) v[ww] = ww < W ? rb[(ww * NC + comp) * 64 + i] : 0.0;
-#pragma unroll
-    for (int h = MAXW / 2; h >= 1; h /= 2)
-#pragma unroll
-        for (int ww = 0; ww < h; ++ww) v[ww] += v[ww + h];
-    return v[0];
-}
-
-template <int NCH>
-__device__ __forceinline__ void renorm_chunks(double (&X)[NCH][SG], double (&Y)[NCH][SG], int (&E)[NCH][SG], int p,
-                                              uint32_t &real)
-{
-#pragma unroll
-    for (int g = 0; g < NCH; ++g) {
-        if (g >= p || ((real >> g) & 1u)) continue;
-        bool z = true;
-#pragma unroll
-        for (int j = 0; j < SG; ++j) {
-            renorm(X[g][j], Y[g][j], E[g][j]);
-            z = z && (E[g][j] == 0);
-        }
-        if (__all(z)) real |= (1u << g);
-    }
-}
-
-// One order of one chunk: e_{m-1} = (kappa lambda) e_m - e_{m+1}, plus the
-// contribution e times the records (unscaled: a slot not yet realised holds e near
-// 2^-RT, so its contribution is negligible; see renorm).
-// SIDE 1 / 2 (one side present: real signals, or a spin-s sphere run, which
-// feeds only the orders +m or only -m of its slice): records of RS = 3 doubles,
-// {kappa, that side's coefficient}.  ac[0..3] are the sums {Re A, Im A, Re B,
-// Im B}; PAIR: ac[0..3] over the even and ac[4..7] over the odd degrees (slot j
-// of a chunk holds l = base + SG-1-j, base a multiple of SG, so l is odd
-// exactly when j is even).
-template <int PAR, int SIDE = 0, bool PAIR = false>
-__device__ __forceinline__ void inv_chunk(double (&X)[SG], double (&Y)[SG], const double *__restrict__ rec, double lam,
-                                          double (&ac)[PAIR ? 8 : 4])
-{
-    constexpr int RS = SIDE ? 3 : 5;
-    // GROUPED: all kappa-lambda products, then all recurrence updates, then the
-    // contractions, so that dependent FP64 operations issue several apart (the
-    // operations and the summation order are those of one slot after another).
-    // Measured at L = 2048, this pays only for the two-sided unpaired sweep (MW
-    // inverse 3.62 -> 3.36 ms); the one-sided and the paired sweeps keep the
-    // slot-by-slot order, which is faster for them (the paired form spills when
-    // grouped).
-    constexpr bool GROUPED = SIDE == 0 && !PAIR;
-    double tt[SG];
-    if constexpr (GROUPED) {
-        double p[SG];
-#pragma unroll
-        for (int j = 0; j < SG; ++j) p[j] = rec[j * RS] * lam;
-#pragma unroll
-        for (int j = 0; j < SG; ++j) {
-            double &nw = PAR == 0 ? Y[j] : X[j];          // receives order m
-            double &od = PAR == 0 ? X[j] : Y[j];          // holds order m+1
-            nw = fma(p[j], od, -nw);
-            tt[j] = nw;
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < SG; ++j) {
-        const int o = (PAIR && (j & 1) == 0) ? 4 : 0;
-        const double *c = rec + j * RS;
-        double t = tt[j];
-        if constexpr (!GROUPED) {
-            double &nw = PAR == 0 ? Y[j] : X[j];
-            double &od = PAR == 0 ? X[j] : Y[j];
-            nw = fma(c[0] * lam, od, -nw);
-            t = nw;
-        }
-        if constexpr (SIDE == 2) {
-            ac[o + 2] = fma(t, c[1], ac[o + 2]);
-            ac[o + 3] = fma(t, c[2], ac[o + 3]);
-        } else {
-            ac[o + 0] = fma(t, c[1], ac[o + 0]);
-            ac[o + 1] = fma(t, c[2], ac[o + 1]);
-            if constexpr (SIDE == 0) {
-                ac[o + 2] = fma(t, c[3], ac[o + 2]);
-                ac[o + 3] = fma(t, c[4], ac[o + 3]);
-            }
-        }
-    }
-}
-
-// A degree l starts at order m = l from its start value (e0, E0) (Eq. 27) with
-// e_{l+1} = 0.  Its slot holds zero state until then and its record at l == m
-// has kappa = 0, so writing -e0 into the register that receives order m lets the
-// ordinary step produce e_m = fma(0, 0, e0) = e0: every chunk runs one step form.
-// jin is wave-uniform.
-template <int PAR>
-__device__ __forceinline__ void inv_preset(double (&X)[SG], double (&Y)[SG], int (&E)[SG], int jin, double e0, int E0)
-{
-#pragma unroll
-    for (int j = 0; j < SG; ++j)
-        if (j == jin) {
-            (PAR == 0 ? Y[j] : X[j]) = -e0;
-            E[j] = E0;
-        }
-}
-
-// PAIR (spin 0, N/S-symmetric sampling): the lanes sweep the northern rings
-// (nsw of nreg) and also produce the mirror ring nreg-1-r, using
-// d^l_{m,0}(pi - theta) = (-1)^{l+m} d^l_{m,0}(theta): with E and O the sums
-// over the even and odd degrees, ring r gets E + O and its mirror (-1)^m (E - O).
-template <int SIDE, bool PAIR>
-__device__ __forceinline__ void inv_reduce(int m, int L, int W, bool good, int ms, int ring0, int nreg, int nsw,
-                                           const double *rb, int blk, double *__restrict__ partA,
-                                           double *__restrict__ partB);
-
-// One order of the inverse sweep: its partial sums go to LDS buffer m mod 8 (paired:
-// m mod 4) and the caller reduces four orders (paired: two) after one barrier.
-template <int NCH, int PAR, int SIDE = 0, bool PAIR = false>
-__device__ __forceinline__ void inv_step(int m, int L, int nx, int n, int an, bool good, int ms, int ring0, int nreg,
-                                         int nsw, int lane,
-                                         int w, int W,
-                                         const int (&lb)[NCH], double (&X)[NCH][SG], double (&Y)[NCH][SG],
-                                         int (&E)[NCH][SG], uint32_t &fast, double ct, double ncs,
-                                         const double2 *__restrict__ initr, const double *__restrict__ C, double *red,
-                                         int blk, double *__restrict__ partA, double *__restrict__ partB)
-{
-    constexpr int RS = SIDE ? 3 : 5;
-    constexpr int NA = PAIR ? 8 : 4;                     // sums per lane
-    const double lam = fma(-(double)(m + 1), ct, ncs);   // lambda_{m+1}: produces order m
-    double ac[NA];
-#pragma unroll
-    for (int c = 0; c < NA; ++c) ac[c] = 0.0;
-    const double *Cw = C + (((size_t)blk * (L + nx) + (m + nx)) * W + w) * (NCH * SG) * RS;   // records at order m
-
-#pragma unroll
-    for (int g = 0; g < NCH; ++g) {
-        const int base = lb[g];
-        if (base < 0 || m > base + SG - 1) continue;     // chunk not started
-        const double *rec = Cw + g * SG * RS;
-        if (m >= base) {                                  // ramp: slot base + SG-1 - m starts at this order
-            if (m >= an) {
-                const double2 iv = initr[m];             // d^m_{m,n}(theta_ring) as (mantissa, exponent)
-                inv_preset<PAR>(X[g], Y[g], E[g], base + SG - 1 - m, iv.x, (int)iv.y);
-            }
-            fast &= ~(1u << g);
-        }
-        inv_chunk<PAR, SIDE, PAIR>(X[g], Y[g], rec, lam, ac);
-    }
-    // renormalisation pass every RN orders over the started chunks not yet realised
-    if ((m & (RN - 1)) == 0) {
-#pragma unroll
-        for (int g = 0; g < NCH; ++g) {
-            const int base = lb[g];
-            if (base < 0 || m > base + SG - 1 || ((fast >> g) & 1u)) continue;
-            bool z = true;
-#pragma unroll
-            for (int j = 0; j < SG; ++j) {
-                renorm(X[g][j], Y[g][j], E[g][j]);
-                z = z && (E[g][j] == 0);
-            }
-            if (__all(z)) fast |= (1u << g);
-        }
-    }
-    constexpr int NBUF = PAIR ? 4 : 8;
-    double *rb = red + (size_t)(m & (NBUF - 1)) * DSTAGE_MAX_WAVES * NA * 64;
-#pragma unroll
-    for (int c = 0; c < NA; ++c)
-        if (SIDE == 0 || (SIDE == 1) == ((c & 3) < 2)) rb[(w * NA + c) * 64 + lane] = ac[c];
-}
-
-// Sum of one order's partials over the waves (LDS buffer rb) and its store.
-template <int SIDE, bool PAIR>
-__device__ __forceinline__ void inv_reduce(int m, int L, int W, bool good, int ms, int ring0, int nreg, int nsw,
-                                           const double *rb, int blk, double *__restrict__ partA,
-                                           double *__restrict__ partB)
-{
-    constexpr int NA = PAIR ? 8 : 4;
-    // four waves, rotating with the order, reduce the 4 x 64 outputs over the waves
-    // (only the present side's 2 x 64 for SIDE 1 / 2)
-    const int tr = (int)threadIdx.x - 256 * reducer_group(m, W);
-    if (tr >= 0 && tr < 256 && (SIDE == 0 || (SIDE == 1) == (tr < 128))) {
-        const int rl = tr & 63, comp = tr >> 6;         // rl == lane: this thread's ring
-        double s = 0.0, s2 = 0.0;                       // a plain loop: fewer scalar registers than wave_sum
-        if (PAIR) {
-            double se = 0.0, so = 0.0;
-            for (int ww = 0; ww < W; ++ww) {
-                se += rb[(ww * NA + comp) * 64 + rl];
-                so += rb[(ww * NA + 4 + comp) * 64 + rl];
-            }
-            s = se + so;                                // ring ring0 + rl
-            s2 = (m & 1) ? so - se : se - so;           // its mirror
-        } else {
-            for (int ww = 0; ww < W; ++ww) s += rb[(ww * NA + comp) * 64 + rl];
-        }
-        // Orders below the ring's switch order ms come from the run that is stable
-        // there (n cos(theta) < 0): it writes its own sides at m >= 0 and, from its
-        // continuation to m > -ms, the A slice at order m < 0 (components 2,3 at |m|)
-        // and the B slice at order -m >= 0 (components 0,1 at |m|).  The other run
-        // writes nothing below ms.
-        double *dst = nullptr;
-        int mo = m, co = comp;
-        const bool ext_ok = good && m <= 0 && -m < ms;   // continuation output of the stable run
-        if (comp < 2) {
-            if (m >= 0 && (good || m >= ms)) dst = partA;                      // A slice at order m
-            else if (m < 0 && ext_ok) { dst = partA; mo = -m; co = comp + 2; }  // A slice at order m < 0
-        } else {
-            if (m > 0 && (good || m >= ms)) dst = partB;                       // B slice at order -m
-            else if (ext_ok) { dst = partB; mo = -m; co = comp - 2; }          // B slice at order -m >= 0
-        }
-        const int rr = ring0 + rl;
-        if (dst && rr < nsw) {
-            dst[(((size_t)blk * nreg + rr) * L + mo) * 4 + co] = s;
-            if (PAIR && nreg - 1 - rr != rr) dst[(((size_t)blk * nreg + (nreg - 1 - rr)) * L + mo) * 4 + co] = s2;
-        }
-    }
-}
-
-template <int NCH, int WT, int SIDE = 0, bool PAIR = false>
-__global__ __launch_bounds__(64 * WT) void k_dstage_inv(
-    int L, int nx, int nreg, int nsw, int n, const double *__restrict__ cot, const double *__restrict__ csc,
-    const double2 *__restrict__ init, const double *__restrict__ C, const int *__restrict__ lchunk,
-    const int *__restrict__ mtop, double *__restrict__ partA, double *__restrict__ partB, OrderTiles ot)
-{
-    // unpaired sweeps reduce four orders per barrier (eight 16 KB buffers); the paired
-    // sweep, with twice the sums, two orders per barrier (four 32 KB buffers)
-    constexpr int DORD = PAIR ? 2 : 4;                   // orders per barrier
-    __shared__ double red[2 * DORD * DSTAGE_MAX_WAVES * (PAIR ? 8 : 4) * 64];
-    const int an = n < 0 ? -n : n;
-    const int lane = threadIdx.x & 63;
-    const int w = ufl(threadIdx.x >> 6);
-    constexpr int W = WT;                                // waves per workgroup (== blockDim.x / 64)
-    const int blk = blockIdx.y;
-    const int ring0 = blockIdx.x * 64;
-    const int ring = min(ring0 + lane, nsw - 1);        // swept rings 0 .. nsw-1 (nsw == nreg unless PAIR)
-    const double ct = cot[ring], cs = csc[ring];
-    const double ncs = (double)n * cs;
-    const bool good = ring_good(n, ct);                 // this run is the stable one at this ring
-    const int ms = switch_order(n, ct, cs);
-    const int mend = an > 1 ? -(an - 1) : 0;            // continuation below m = 0
-    const double2 *initr = init + (size_t)ring * L;
-
-    int lb[NCH];
-#pragma unroll
-    for (int g = 0; g < NCH; ++g) lb[g] = ufl(lchunk[((size_t)blk * W + w) * NCH + g]);
-    double X[NCH][SG], Y[NCH][SG];
-    int E[NCH][SG];
-#pragma unroll
-    for (int g = 0; g < NCH; ++g)
-#pragma unroll
-        for (int j = 0; j < SG; ++j) { X[g][j] = 0.0; Y[g][j] = 0.0; E[g][j] = 0; }
-    uint32_t fast = 0;
-
-    // order tile blockIdx.z: orders ctop - 1 .. bot; the slots whose degree started
-    // above the tile (l >= ctop) resume from the stored state after order ctop
-    const int tile = blockIdx.z;
-    const int ctop = tile == 0 ? L : ot.c[tile];
-    const int bot = tile + 1 < ot.nt ? ot.c[tile + 1] : mend;
-    const int mt = min(ufl(mtop[blk]), ctop - 1);
-    if (mt < bot) return;                               // no degree of this block reaches the tile
-    if (tile > 0) {
-        const double *ck = ot.ck + ot.off[tile] + ring;
-#pragma unroll
-        for (int g = 0; g < NCH; ++g)
-#pragma unroll
-            for (int j = 0; j < SG; ++j) {
-                const int l = lb[g] + SG - 1 - j;
-                if (lb[g] >= 0 && l >= ctop && l < L) {   // PAR 0 at order ctop - 1: X holds e_{ctop}
-                    const double *q = ck + (size_t)(l - ctop) * 3 * ot.rp;
-                    X[g][j] = q[0];
-                    Y[g][j] = q[ot.rp];
-                    E[g][j] = (int)q[2 * ot.rp];
-                }
-            }
-    }
-    int pf = 0;
-    constexpr int RS = SIDE ? 3 : 5;                     // doubles per record
-    constexpr int ROWB = NCH * SG * RS * 8;              // bytes of one wave's records per order
-    static_assert(ROWB % 128 == 0, "a wave's record row spans whole cache lines");
-    // Pull the records of orders mm - PFD and mm - PFD - 1 toward the caches (one
-    // dword per 128-byte line); the result is consumed only at the next pair of
-    // orders, so the load latency overlaps this pair's work.
-    auto prefetch = [&](int mm) {
-        asm volatile("" ::"v"(pf));
-        if (mm - PFD - 1 >= -nx && lane < 2 * ROWB / 128) {
-            const int row = mm - PFD - (lane >= ROWB / 128 ? 1 : 0);
-            const int *Cp = reinterpret_cast<const int *>(C + (((size_t)blk * (L + nx) + (row + nx)) * W + w) *
-                                                                  (NCH * SG) * RS);
-            pf = Cp[(lane % (ROWB / 128)) * 32];
-        }
-    };
-    // DORD orders per barrier, their sums in LDS buffers m mod 2 DORD; with 8 waves
-    // the two reducer groups take DORD / 2 orders each.  An order's buffer is next
-    // written two iterations on, after the next barrier, which every reducer
-    // reaches only once done here.
-    constexpr int NBUF = 2 * DORD;
-    constexpr size_t SL = (size_t)DSTAGE_MAX_WAVES * (PAIR ? 8 : 4) * 64;
-    for (int m = mt; m >= bot; m -= DORD) {
-        prefetch(m);
-        inv_step<NCH, 0, SIDE, PAIR>(m, L, nx, n, an, good, ms, ring0, nreg, nsw, lane, w, W, lb, X, Y, E, fast, ct,
-                                     ncs, initr, C, red, blk, partA, partB);
-        if (m - 1 >= bot)
-            inv_step<NCH, 1, SIDE, PAIR>(m - 1, L, nx, n, an, good, ms, ring0, nreg, nsw, lane, w, W, lb, X, Y, E, fast,
-                                         ct, ncs, initr, C, red, blk, partA, partB);
-        if (DORD == 4 && m - 2 >= bot) {
-            prefetch(m - 2);
-            inv_step<NCH, 0, SIDE, PAIR>(m - 2, L, nx, n, an, good, ms, ring0, nreg, nsw, lane, w, W, lb, X, Y, E, fast,
-                                         ct, ncs, initr, C, red, blk, partA, partB);
-            if (m - 3 >= bot)
-                inv_step<NCH, 1, SIDE, PAIR>(m - 3, L, nx, n, an, good, ms, ring0, nreg, nsw, lane, w, W, lb, X, Y, E,
-                                             fast, ct, ncs, initr, C, red, blk, partA, partB);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < DORD; ++q)
-            if (m - q >= bot)
-                inv_reduce<SIDE, PAIR>(m - q, L, W, good, ms, ring0, nreg, nsw,
-                                       red + (size_t)((m - q) & (NBUF - 1)) * SL, blk, partA, partB);
-    }
-    asm volatile("" ::"v"(pf));
-}
-
-// ------------------------------------------------------------------ forward d-stage
-// Lanes = 64 consecutive l (group g); each wave owns 2 x SG contiguous ring
-// slots (ring rbase + k; rings past the last regular ring are inert: zero
-// lambda, zero H, never initialised); waves of a workgroup share the l-group
-// and split the rings.  A workgroup runs group p then group G-1-p so all
-// workgroups carry equal work.  At order m:
-//   acc(l) = g_m^l sum_{slots} e * H[m][ring]   (e unscaled; see renorm),
-// reduced over the waves in LDS (rotating reducers) and written to
-// QA/QB[blk][l][m].  kappa and g of the next order are loaded one step ahead.
-
-// LDS reduction buffers of the forward sweep.  A two-sided run keeps the four
-// components of an order (A re, A im, B re, B im; W x 4 x 64 sums) in buffer m mod 4;
-// a one-sided run (SIDE 1 / 2) keeps its two (re, im) in buffer m mod 8 of half the
-// size, so the same LDS holds eight orders and its main loop reduces four orders per
-// barrier.  A buffer is rewritten only after a barrier that follows its reduction:
-// two consecutive barrier intervals never span more orders than there are buffers.
-// fwd_boff1: offset of a one-sided run's buffer for order m.
-__device__ __forceinline__ size_t fwd_boff1(int m, int W)
-{
-    return (size_t)(m & 7) * W * 2 * 64;
-}
-
-// A one-sided run's sums of this order to its LDS buffer (wave w, lane).
-template <int SIDE>
-__device__ __forceinline__ void fwd_put1(double *red, int m, int w, int W, int lane, double g, double aAr, double aAi,
-                                         double aBr, double aBi)
-{
-    double *rb = red + fwd_boff1(m, W);
-    rb[(w * 2 + 0) * 64 + lane] = (SIDE == 1 ? aAr : aBr) * g;
-    rb[(w * 2 + 1) * 64 + lane] = (SIDE == 1 ? aAi : aBi) * g;
-}
-
-__device__ __forceinline__ const double2 *init_tab_ptr(const double2 *init, int r0, int m, int L)
-{
-    return init + (size_t)r0 * L + m;
-}
-
-template <int PAR, bool HEAD, bool REAL = false, int SIDE = 0>
-__device__ __forceinline__ void fwd_chunk(double (&X)[SG], double (&Y)[SG], int (&E)[SG], const double *__restrict__ Lm,
-                                          const double *__restrict__ HA, const double *__restrict__ HB, double kk,
-                                          bool init, int nval, const double2 *__restrict__ iv, int istride, double &aAr,
-                                          double &aAi, double &aBr, double &aBi)
-{
-#pragma unroll
-    for (int k = 0; k < SG; ++k) {
-        double &nw = PAR == 0 ? Y[k] : X[k];
-        double &od = PAR == 0 ? X[k] : Y[k];
-        nw = fma(kk * Lm[k], od, -nw);
-        if constexpr (HEAD) {
-            if (init && k < nval) {                      // l == m starts at slot k's ring (a swept ring)
-                const double2 v = iv[(size_t)k * istride];
-                nw = v.x;
-                E[k] = (int)v.y;
-                od = 0.0;
-            }
-        }
-        const double t = nw;                             // unscaled (see renorm)
-        const double *ha = HA + k * 4;                   // components chosen by the caller's offsets
-        const double *hb = HB + k * 4;
-        if constexpr (SIDE != 2) {
-            aAr = fma(t, ha[0], aAr);
-            aAi = fma(t, ha[1], aAi);
-        }
-        if constexpr (SIDE != 1) {
-            aBr = fma(t, hb[0], aBr);
-            aBi = fma(t, hb[1], aBi);
-        }
-    }
-}
-
-// HEAD: degrees of the group start in this pair of orders.  MAIN: m >= |n|
-// (no low-order copies, no continuation outputs).  SAME (with MAIN, m > 0): both
-// sides read one spectra array (run n = 0), so a ring's four components form one
-// contiguous record and the wave's row is fetched with wide scalar loads.
-// REAL (with MAIN): every chunk is realised (all E == 0), which stays so in the
-// main loop since no degree starts there: no scaling and no renormalisation.
-// SIDE 1 / 2: only the A side (order +m) or only the B side (order -m) is
-// accumulated (a real signal's run n = 0, whose order -m is the conjugate; a
-// spin-s sphere run, which feeds one side of its slice).
-// PAIRF (run n = 0, N/S-symmetric sampling): the slots are the northern rings,
-// the lanes of group g hold degrees of one parity (l = 128 (g/2) + 2 lane + g%2),
-// and by d^l_{m,0}(pi - theta) = (-1)^{l+m} d^l_{m,0}(theta) a slot contributes
-// d (H(ring) + (-1)^{l+m} H(mirror)): HA holds the sums and HB the differences of
-// the two rings' spectra, and l + m has one parity across the wave at each order.
-template <int NCH, int PAR, bool HEAD, bool MAIN = false, bool SAME = false, bool REAL = false, int SIDE = 0,
-          bool PAIRF = false>
-__device__ __forceinline__ void fwd_step(int m, int mend, int g, int l, int L, int nxp, int n, int an, int lane, int w,
-                                         int W, int hstride, int lstride, int nreg, int rbase, double (&X)[NCH][SG],
-                                         double (&Y)[NCH][SG], int (&E)[NCH][SG], uint32_t &real, double &kk, double &gm,
-                                         const double *__restrict__ lam, const double2 *__restrict__ init,
-                                         const double *__restrict__ kap, const double *__restrict__ gtab,
-                                         const double *__restrict__ HA, const double *__restrict__ HB,
-                                         const double *__restrict__ HxA, const double *__restrict__ HxB, double *red,
-                                         int blk, double *__restrict__ QA, double *__restrict__ QB,
-                                         double *__restrict__ QxA, double *__restrict__ QxB)
-{
-    // kappa / g of this order were loaded one step ahead; fetch the next order's now
-    const double kcur = kk, gcur = gm;
-    if (m - 1 >= mend) {
-        const int mn = m - 1;
-        const int lc = min(l, L - 1);
-        kk = (l > mn && l < L) ? kap[(ptrdiff_t)mn * L + lc] : 0.0;
-        gm = (l >= mn && l < L) ? gtab[(ptrdiff_t)mn * L + lc] : 0.0;
-    }
-    const bool starts = HEAD && (l == m) && (l >= an);
-    // start values of slot k: init[rbase + k][m] (rings past nreg stay zero)
-    double aAr = 0.0, aAi = 0.0, aBr = 0.0, aBi = 0.0;
-    const double *Lm = lam + (ptrdiff_t)m * lstride + rbase;
-    // Ring spectra of the two sides.  Orders below |n| read copies in which the
-    // rings where this run is unstable are zero (the other run covers them); the
-    // continuation (m <= 0) reads the A slice at order m < 0 (components 2,3) and
-    // the B slice at order -m >= 0 (components 0,1).
-    const int am = MAIN ? m : (m < 0 ? -m : m);
-    const bool low = !MAIN && m < an;
-    const double *HAm, *HBm;
-    if constexpr (PAIRF) {
-        HAm = (((m + g) & 1) ? HB : HA) + ((size_t)am * hstride + rbase) * 4;
-        HBm = HAm + 2;
-    } else {
-        HAm = (low ? HxA : HA) + ((size_t)am * hstride + rbase) * 4 + (!MAIN && m < 0 ? 2 : 0);
-        HBm = SAME ? HAm + 2 : (low ? HxB : HB) + ((size_t)am * hstride + rbase) * 4 + (m > 0 ? 2 : 0);
-    }
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-        const double *Lc = Lm + c * SG;
-        const double *Ac = HAm + c * SG * 4;
-        const double *Bc = HBm + c * SG * 4;
-        if (HEAD) {
-            const int r0 = min(rbase + c * SG, nreg - 1);
-            // slots at or past the last swept ring (MW south pole, padding) are never
-            // started: they stay zero, and their start values lie outside the table
-            const int nval = nreg - (rbase + c * SG);
-            const bool ok = starts && nval > 0;
-            fwd_chunk<PAR, true, false, SIDE>(X[c], Y[c], E[c], Lc, Ac, Bc, kcur, ok, nval,
-                                              init_tab_ptr(init, r0, m < 0 ? 0 : m, L), L, aAr, aAi, aBr, aBi);
-        } else {
-            fwd_chunk<PAR, false, REAL, SIDE>(X[c], Y[c], E[c], Lc, Ac, Bc, kcur, false, 0, nullptr, 0, aAr, aAi, aBr,
-                                              aBi);
-        }
-    }
-    if (HEAD) real = 0u;                                  // degrees start in this group: not realised
-    if (!REAL && (m & (RN - 1)) == 0) renorm_chunks<NCH>(X, Y, E, NCH, real);
-    // this order's sums go to its LDS buffer; the caller reduces two orders after
-    // one barrier (fwd_reduce2)
-    if constexpr (SIDE == 0) {
-        double *rb = red + (size_t)(m & 3) * W * 4 * 64;
-        rb[(w * 4 + 0) * 64 + lane] = aAr * gcur;
-        rb[(w * 4 + 1) * 64 + lane] = aAi * gcur;
-        rb[(w * 4 + 2) * 64 + lane] = aBr * gcur;
-        rb[(w * 4 + 3) * 64 + lane] = aBi * gcur;
-    } else {
-        fwd_put1<SIDE>(red, m, w, W, lane, gcur, aAr, aAi, aBr, aBi);
-    }
-}
-
-// The main-loop order of a run whose two sides read one spectra array (SAME: run
-// n = 0, m > 0; a paired sweep reads the sums or the differences by the order's
-// parity, and the caller passes the row of the array that this order reads): the
-// wave's lambda and spectra rows and the lane's kappa and g are reached through
-// pointers that step back (hstep: the spectra row's step per call), so an order
-// carries no index arithmetic, and kappa and g of the next order are plain loads (in
-// the main loop every lane's degree has started, l > m; lanes past L read row
-// entries of L - 1 and are never stored).
-template <int NCH, int PAR, bool REAL, int SIDE>
-__device__ __forceinline__ void fwd_step_same(int m, int lane, int w, int W, int L, double (&X)[NCH][SG],
-                                              double (&Y)[NCH][SG], int (&E)[NCH][SG], uint32_t &real, double &kk,
-                                              double &gm, const double *__restrict__ &Lp,
-                                              const double *__restrict__ &Hp, const double *__restrict__ &kp,
-                                              const double *__restrict__ &gp, int lstride, int hstep, double *red)
-{
-    const double kcur = kk, gcur = gm;
-    kp -= L;
-    gp -= L;
-    kk = *kp;                                            // order m - 1
-    gm = *gp;
-    double aAr = 0.0, aAi = 0.0, aBr = 0.0, aBi = 0.0;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c)
-        fwd_chunk<PAR, false, REAL, SIDE>(X[c], Y[c], E[c], Lp + c * SG, Hp + c * SG * 4, Hp + c * SG * 4 + 2, kcur,
-                                          false, 0, nullptr, 0, aAr, aAi, aBr, aBi);
-    Lp -= lstride;
-    Hp -= hstep;
-    if (!REAL && (m & (RN - 1)) == 0) renorm_chunks<NCH>(X, Y, E, NCH, real);
-    if constexpr (SIDE == 0) {
-        double *rb = red + (size_t)(m & 3) * W * 4 * 64;
-        rb[(w * 4 + 0) * 64 + lane] = aAr * gcur;
-        rb[(w * 4 + 1) * 64 + lane] = aAi * gcur;
-        rb[(w * 4 + 2) * 64 + lane] = aBr * gcur;
-        rb[(w * 4 + 3) * 64 + lane] = aBi * gcur;
-    } else {
-        fwd_put1<SIDE>(red, m, w, W, lane, gcur, aAr, aAi, aBr, aBi);
-    }
-}
-
-// Sum of order m's partials over the WT waves (its LDS buffer) and its store to
-// QA/QB[blk][l][m] (continuation orders m < 0: QxA/QxB).
-template <int WT, bool MAIN, int SIDE, bool PAIRF>
-__device__ __forceinline__ void fwd_reduce(int m, int g, int L, int nxp, int n, int an, const double *red, int blk,
-                                           double *__restrict__ QA, double *__restrict__ QB, double *__restrict__ QxA,
-                                           double *__restrict__ QxB)
-{
-    const double *rb = SIDE == 0 ? red + (size_t)(m & 3) * WT * 4 * 64 : red + fwd_boff1(m, WT);
-    const int am = MAIN ? m : (m < 0 ? -m : m);
-    const int tr = (int)threadIdx.x - 256 * reducer_group(m, WT);
-    if (tr >= 0 && tr < 256 && (SIDE == 0 || (SIDE == 1) == (tr < 128))) {
-        const int ll = tr & 63, comp = tr >> 6;
-        const int lo = PAIRF ? 128 * (g >> 1) + 2 * ll + (g & 1) : 64 * g + ll;
-        double s;
-        if constexpr (SIDE == 0) s = wave_sum<WT>(rb, comp, ll, WT);
-        else s = wave_sum<WT, 2>(rb, comp & 1, ll, WT);
-        if (MAIN) {
-            if (lo < L && lo >= m && (m > 0 || comp < 2)) {
-                double *dst = comp < 2 ? QA : QB;
-                if (dst) dst[(((size_t)blk * L + lo) * L + m) * 4 + comp] = s;
-            }
-        } else if (lo < L && lo >= m) {
-            if (m > 0 || comp < 2) {
-                if (m >= 0) {
-                    double *dst = comp < 2 ? QA : QB;
-                    if (dst) dst[(((size_t)blk * L + lo) * L + m) * 4 + comp] = s;
-                } else if (QxA) {
-                    // A slice at order m < 0; the sign cancels the one the finish applies to m < 0
-                    const double sg = ((am + n) & 1) ? -s : s;
-                    QxA[(((size_t)blk * L + lo) * nxp + am) * 4 + comp + 2] = sg;
-                }
-            } else if (an > 0 && QxB) {
-                // B slice at order -m >= 0: d^l_{-m,-n} = (-1)^{m-n} d^l_{m,n}
-                const double sg = ((am + n) & 1) ? -s : s;
-                QxB[(((size_t)blk * L + lo) * nxp + am) * 4 + comp - 2] = sg;
-            }
-        }
-    }
-}
-
-// One barrier, then the reductions of orders m and (two) m - 1, whose buffers are
-// next written two iterations on or later, after the next barrier, which every
-// reducer reaches only once done here.  With 8 or 16 waves the two orders go to
-// different reducer groups.
-template <int WT, bool MAIN, int SIDE, bool PAIRF>
-__device__ __forceinline__ void fwd_reduce2(int m, bool two, int g, int L, int nxp, int n, int an, const double *red,
-                                            int blk, double *__restrict__ QA, double *__restrict__ QB,
-                                            double *__restrict__ QxA, double *__restrict__ QxB)
-{
-    __syncthreads();
-    fwd_reduce<WT, MAIN, SIDE, PAIRF>(m, g, L, nxp, n, an, red, blk, QA, QB, QxA, QxB);
-    if (two) fwd_reduce<WT, MAIN, SIDE, PAIRF>(m - 1, g, L, nxp, n, an, red, blk, QA, QB, QxA, QxB);
-}
-
-template <int NCH, bool SAME, int WT, int SIDE = 0, bool PAIRF = false>
-__global__ __launch_bounds__(64 * WT) void k_dstage_fwd(
-    int gx, int gy, int gz, bool xcd, int L, int nxp, int nreg, int hstride, int lstride, int n, int G,
-    const double *__restrict__ lam, const double2 *__restrict__ init, const double *__restrict__ kap,
-    const double *__restrict__ gtab, const double *__restrict__ HA, const double *__restrict__ HB,
-    const double *__restrict__ HxA, const double *__restrict__ HxB, double *__restrict__ QA, double *__restrict__ QB,
-    double *__restrict__ QxA, double *__restrict__ QxB, OrderTiles ot)
-{
-    __shared__ double red[4 * WT * 4 * 64];         // four order buffers of WT x 4 x 64 sums
-    const int an = n < 0 ? -n : n;
-    const int mend = an > 1 ? -(an - 1) : 0;            // continuation below m = 0
-    const int lane = threadIdx.x & 63;
-    const int w = ufl(threadIdx.x >> 6);
-    constexpr int W = WT;                                // waves per workgroup (== blockDim.x / 64)
-    // l-group pair p, ring block blk, order tile bz (xcd: each XCD takes contiguous
-    // pairs, so the workgroups of one ring block read its spectra rows through one L2)
-    int p, blk, bz;
-    if (!xcd_tile(gx, gy, gz, p, blk, bz, xcd)) return;
-    // this wave's rings: rbase .. rbase + NCH SG - 1 (contiguous; >= nreg inert)
-    const int rbase = (blk * W + w) * NCH * SG;
-    // order tile bz: orders ctop - 1 .. lo
-    const int tile = bz;
-    const int ctop = tile == 0 ? L : ot.c[tile];
-    const int lo = tile + 1 < ot.nt ? ot.c[tile + 1] : mend;
-
-    for (int pass = 0; pass < 2; ++pass) {
-        const int g = pass == 0 ? p : G - 1 - p;
-        if (pass == 1 && g == p) break;
-        const int lmin = PAIRF ? 128 * (g >> 1) + (g & 1) : 64 * g;     // lowest degree of the group
-        const int l = PAIRF ? lmin + 2 * lane : lmin + lane;
-        double X[NCH][SG], Y[NCH][SG];
-        int E[NCH][SG];
-#pragma unroll
-        for (int c = 0; c < NCH; ++c)
-#pragma unroll
-            for (int k = 0; k < SG; ++k) { X[c][k] = 0.0; Y[c][k] = 0.0; E[c][k] = 0; }
-        uint32_t real = 0u;
-        const int mstart = min(PAIRF ? lmin + 126 : lmin + 63, L - 1);
-        // head: the orders at which lanes of this group start (an even number of
-        // steps so the register roles line up with the main loop)
-        const int hend = ((mstart - lmin + 1) % 2 == 0) ? lmin : lmin - 1;
-        int m = min(mstart, ctop - 1);
-        if (m < lo) continue;                            // the group's degrees lie below the tile
-        if (tile > 0 && l >= ctop && l < L) {
-            // lanes whose degree started above the tile resume from the stored state
-            // (PAR 0 at order ctop - 1: X holds e_{ctop}); slots past the swept rings stay zero
-            const double *q = ot.ck + ot.off[tile] + (size_t)(l - ctop) * 3 * ot.rp + rbase;
-#pragma unroll
-            for (int c = 0; c < NCH; ++c)
-#pragma unroll
-                for (int k = 0; k < SG; ++k)
-                    if (rbase + c * SG + k < nreg) {
-                        X[c][k] = q[c * SG + k];
-                        Y[c][k] = q[ot.rp + c * SG + k];
-                        E[c][k] = (int)q[2 * ot.rp + c * SG + k];
-                    }
-        }
-        const int lc = min(l, L - 1);
-        double kk = (l > m && l < L) ? kap[(ptrdiff_t)m * L + lc] : 0.0;
-        double gm = (l >= m && l < L) ? gtab[(ptrdiff_t)m * L + lc] : 0.0;
-        // Pull the wave's lambda and spectra rows of orders m - PFF, m - PFF - 1 toward
-        // the caches (one dword per 128-byte line, PQ lanes per order); the result is
-        // consumed only at the next pair of orders, so the latency overlaps their work.
-        constexpr int HL = NCH * SG * 4 * 8 / 128;           // 128-byte lines of one side's spectra row
-        constexpr int PQ = 1 + 2 * HL;
-        constexpr int PFF = PFD;
-        int pf = 0;
-        auto prefetch = [&](int mm) {
-            asm volatile("" ::"v"(pf));
-            const int mp = mm - PFF - (lane >= PQ ? 1 : 0);
-            const int q = lane % PQ;
-            if (lane < 2 * PQ && mp >= an) {
-                // q = 0: the wave's lambdas; q = 1..HL / HL+1..2HL: the spectra rows of the two sides
-                const int *a;
-                if (q == 0) a = reinterpret_cast<const int *>(lam + (ptrdiff_t)mp * lstride + rbase);
-                else if (q <= HL) a = reinterpret_cast<const int *>(HA + ((size_t)mp * hstride + rbase) * 4) + (q - 1) * 32;
-                else a = reinterpret_cast<const int *>(HB + ((size_t)mp * hstride + rbase) * 4) + (q - 1 - HL) * 32;
-                pf = *a;
-            }
-        };
-        for (; m >= hend && m >= lo; m -= 2) {
-            prefetch(m);
-            fwd_step<NCH, 0, true, false, false, false, SIDE, PAIRF>(m, mend, g, l, L, nxp, n, an, lane, w, W, hstride,
-                                                              lstride, nreg, rbase, X, Y, E, real, kk, gm, lam, init,
-                                                              kap, gtab, HA, HB, HxA, HxB, red, blk, QA, QB, QxA, QxB);
-            if (m - 1 >= lo)
-                fwd_step<NCH, 1, true, false, false, false, SIDE, PAIRF>(m - 1, mend, g, l, L, nxp, n, an, lane, w, W,
-                                                                  hstride, lstride, nreg, rbase, X, Y, E, real, kk, gm,
-                                                                  lam, init, kap, gtab, HA, HB, HxA, HxB, red, blk, QA,
-                                                                  QB, QxA, QxB);
-            fwd_reduce2<WT, false, SIDE, PAIRF>(m, m - 1 >= lo, g, L, nxp, n, an, red, blk, QA, QB, QxA, QxB);
-        }
-        // both orders of the pair >= |n| (and > 0 when the sides share one array) and
-        // in the tile
-        constexpr uint32_t ALL = (1u << NCH) - 1u;
-        const int mlo = max(SAME ? max(an, 1) : an, lo);
-        if constexpr (SAME) {
-            // Main loop with every per-order address stepped, not recomputed: the wave's
-            // lambda and spectra rows, the lane's kappa / g, the prefetch lanes' lines and
-            // each reducer thread's output column move back one order per step.
-            // PAIRF: order m reads the sums (HA) or the differences (HB) by the parity of
-            // m + g; the loop takes two orders per iteration, so each of its two steps
-            // keeps one array and steps its row back two orders at a time.
-            const bool hodd = PAIRF && ((m + g) & 1);
-            const double *Lp = lam + (ptrdiff_t)m * lstride + rbase;
-            const double *Hp = (hodd ? HB : HA) + ((size_t)m * hstride + rbase) * 4;
-            const double *Hq = PAIRF ? (hodd ? HA : HB) + ((ptrdiff_t)(m - 1) * hstride + rbase) * 4 : nullptr;
-            const double *kp = kap + (ptrdiff_t)m * L + lc;      // kk, gm hold order m already
-            const double *gp = gtab + (ptrdiff_t)m * L + lc;
-            const int hstep = hstride * 4;
-            // prefetch: lanes [0, PS) pull the rows of order m - PFF, lanes [PS, 2 PS) those
-            // of order m - PFF - 1 (lane q of a row: the lambdas for q = 0, else one
-            // 128-byte line of the spectra row); both sides share the spectra
-            constexpr int PS = 1 + HL;
-            const int q = lane % PS;
-            int pm = m - PFF - (lane >= PS ? 1 : 0);
-            const double *HP = (PAIRF && ((pm + g) & 1)) ? HB : HA;    // a lane's rows keep their parity
-            const char *pa = q == 0 ? reinterpret_cast<const char *>(lam + (ptrdiff_t)pm * lstride + rbase)
-                                    : reinterpret_cast<const char *>(HP + ((ptrdiff_t)pm * hstride + rbase) * 4) +
-                                          (q - 1) * 128;
-            const ptrdiff_t pstep = q == 0 ? 2 * (ptrdiff_t)lstride * 8 : 2 * (ptrdiff_t)hstride * 32;
-            const bool plane = lane < 2 * PS;
-            // reducer thread (group threadIdx / 256, component, lane): its output column
-            // at order m is dcol[m * 4] (every order of the main loop is > 0 and < l)
-            const int rgrp = (int)threadIdx.x >> 8;
-            const int rcomp = ((int)threadIdx.x >> 6) & 3;
-            const int lo = PAIRF ? 128 * (g >> 1) + 2 * lane + (g & 1) : 64 * g + lane;
-            double *dbase = rcomp < 2 ? QA : QB;
-            const bool rok = lo < L && dbase != nullptr && (SIDE == 0 || (SIDE == 1) == (rcomp < 2));
-            double *dcol = rok ? dbase + (((size_t)blk * L + lo) * L) * 4 + rcomp : nullptr;
-            auto reduce_pair = [&](int mm) {
-                __syncthreads();
-#pragma unroll
-                for (int o = 0; o < 2; ++o) {
-                    const int mo = mm - o;
-                    if (rok && rgrp == reducer_group(mo, WT)) {
-                        if constexpr (SIDE == 0) {
-                            const double *rb = red + (size_t)(mo & 3) * WT * 4 * 64;
-                            dcol[(size_t)mo * 4] = wave_sum<WT>(rb, rcomp, lane, WT);
-                        } else {
-                            dcol[(size_t)mo * 4] = wave_sum<WT, 2>(red + fwd_boff1(mo, WT), rcomp & 1, lane, WT);
-                        }
-                    }
-                }
-            };
-            // one-sided runs: one barrier, then the reductions of four orders (a rolled
-            // loop, so that the loads of one order's sum are live at a time)
-            auto reduce_quad = [&](int mm) {
-                __syncthreads();
-#pragma unroll 1
-                for (int o = 0; o < 4; ++o) {
-                    const int mo = mm - o;
-                    if (rok && rgrp == reducer_group(mo, WT)) {
-                        dcol[(size_t)mo * 4] = wave_sum<WT, 2>(red + fwd_boff1(mo, WT), rcomp & 1, lane, WT);
-                    }
-                }
-            };
-            auto pull = [&]() {
-                asm volatile("" ::"v"(pf));
-                if (plane && pm >= an) pf = *reinterpret_cast<const int *>(pa);
-                pa -= pstep;
-                pm -= 2;
-            };
-            // one order's step; PAIRF: the second order of each pair reads Hq
-            constexpr int HST = PAIRF ? 2 : 1;
-            // two orders per iteration; a one-sided run reduces after every second
-            // iteration (four orders per barrier), the last pair pending at most (not
-            // the paired one-sided run: there the deferral costs registers and spills)
-            bool pend = false;
-            for (; m - 1 >= mlo && real != ALL; m -= 2) {
-                pull();
-                fwd_step_same<NCH, 0, false, SIDE>(m, lane, w, W, L, X, Y, E, real, kk, gm, Lp, Hp, kp, gp, lstride,
-                                                   HST * hstep, red);
-                fwd_step_same<NCH, 1, false, SIDE>(m - 1, lane, w, W, L, X, Y, E, real, kk, gm, Lp, PAIRF ? Hq : Hp,
-                                                   kp, gp, lstride, HST * hstep, red);
-                if constexpr (SIDE == 0 || PAIRF) {
-                    reduce_pair(m);
-                } else {
-                    if (pend) reduce_quad(m + 2);
-                    pend = !pend;
-                }
-            }
-            for (; m - 1 >= mlo; m -= 2) {               // realised: plain contributions
-                pull();
-                fwd_step_same<NCH, 0, true, SIDE>(m, lane, w, W, L, X, Y, E, real, kk, gm, Lp, Hp, kp, gp, lstride,
-                                                  HST * hstep, red);
-                fwd_step_same<NCH, 1, true, SIDE>(m - 1, lane, w, W, L, X, Y, E, real, kk, gm, Lp, PAIRF ? Hq : Hp,
-                                                  kp, gp, lstride, HST * hstep, red);
-                if constexpr (SIDE == 0 || PAIRF) {
-                    reduce_pair(m);
-                } else {
-                    if (pend) reduce_quad(m + 2);
-                    pend = !pend;
-                }
-            }
-            if constexpr (SIDE != 0 && !PAIRF)
-                if (pend) reduce_pair(m + 2);            // the last pair's orders m + 2, m + 1
-        }
-        for (; m - 1 >= mlo && real != ALL; m -= 2) {
-            prefetch(m);
-            fwd_step<NCH, 0, false, true, SAME, false, SIDE, PAIRF>(m, mend, g, l, L, nxp, n, an, lane, w, W, hstride,
-                                                             lstride, nreg, rbase, X, Y, E, real, kk, gm, lam, init,
-                                                             kap, gtab, HA, HB, HxA, HxB, red, blk, QA, QB, QxA, QxB);
-            fwd_step<NCH, 1, false, true, SAME, false, SIDE, PAIRF>(m - 1, mend, g, l, L, nxp, n, an, lane, w, W, hstride,
-                                                             lstride, nreg, rbase, X, Y, E, real, kk, gm, lam, init,
-                                                             kap, gtab, HA, HB, HxA, HxB, red, blk, QA, QB, QxA, QxB);
-            fwd_reduce2<WT, true, SIDE, PAIRF>(m, true, g, L, nxp, n, an, red, blk, QA, QB, QxA, QxB);
-        }
-        for (; m - 1 >= mlo; m -= 2) {                   // realised: plain contributions
-            prefetch(m);
-            fwd_step<NCH, 0, false, true, SAME, true, SIDE, PAIRF>(m, mend, g, l, L, nxp, n, an, lane, w, W, hstride,
-                                                            lstride, nreg, rbase, X, Y, E, real, kk, gm, lam, init,
-                                                            kap, gtab, HA, HB, HxA, HxB, red, blk, QA, QB, QxA, QxB);
-            fwd_step<NCH, 1, false, true, SAME, true, SIDE, PAIRF>(m - 1, mend, g, l, L, nxp, n, an, lane, w, W, hstride,
-                                                            lstride, nreg, rbase, X, Y, E, real, kk, gm, lam, init,
-                                                            kap, gtab, HA, HB, HxA, HxB, red, blk, QA, QB, QxA, QxB);
-            fwd_reduce2<WT, true, SIDE, PAIRF>(m, true, g, L, nxp, n, an, red, blk, QA, QB, QxA, QxB);
-        }
-        for (; m >= lo; m -= 2) {
-            prefetch(m);
-            fwd_step<NCH, 0, false, false, false, false, SIDE, PAIRF>(m, mend, g, l, L, nxp, n, an, lane, w, W, hstride,
-                                                               lstride, nreg, rbase, X, Y, E, real, kk, gm, lam, init,
-                                                               kap, gtab, HA, HB, HxA, HxB, red, blk, QA, QB, QxA, QxB);
-            if (m - 1 >= lo)
-                fwd_step<NCH, 1, false, false, false, false, SIDE, PAIRF>(m - 1, mend, g, l, L, nxp, n, an, lane, w, W,
-                                                                   hstride, lstride, nreg, rbase, X, Y, E, real, kk,
-                                                                   gm, lam, init, kap, gtab, HA, HB, HxA, HxB, red,
-                                                                   blk, QA, QB, QxA, QxB);
-            fwd_reduce2<WT, false, SIDE, PAIRF>(m, m - 1 >= lo, g, L, nxp, n, an, red, blk, QA, QB, QxA, QxB);
-        }
-        asm volatile("" ::"v"(pf));
-        __syncthreads();   // the LDS buffers are reused by the next pass
-    }
-}
-
 // Sums and differences of the spectra of a ring and its mirror for the paired
 // forward sweep: S[m][i] = H[m][i] + H[m][nreg-1-i], D[m][i] = H[m][i] -
 // H[m][nreg-1-i] over whole 32-byte records (both sides); a ring that is its own
 // mirror (the equator) enters once: S = D = H.  Pairs past nsw are zero padding.
 __global__ void k_pair_spectra(int L, int nreg, int nsw, int hstride, int pstride, const double *__restrict__ H,
-                               double *__restrict__ S, double *__restrict__ D)
+                               double *__restrict__ S, double *__restrict__ D, long long wsd)
 {
+    H += blockIdx.y * wsd;
+    S += blockIdx.y * wsd;
+    D += blockIdx.y * wsd;
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (size_t)L * pstride) return;
     const int m = (int)(i / pstride), r = (int)(i % pstride);
@@ -1071,12 +129,20 @@ __global__ void k_pair_spectra(int L, int nreg, int nsw, int hstride, int pstrid
 // components 2,3 at mu > 0) where the run is stable or mu >= ms, and the
 // continuation orders (A components 2,3 = A slice at -mu, B components 0,1 = B
 // slice at +mu) where the run is the stable one and mu < ms.  Other entries 0.
-__global__ void k_mask_low(int an_run, int n, int nreg, int hstride, const double *__restrict__ cot,
-                           const double *__restrict__ csc, const double *__restrict__ FA,
-                           const double *__restrict__ FB, double *__restrict__ HxA, double *__restrict__ HxB)
+__global__ void k_mask_low(int nrun, const SweepRun *__restrict__ runs, int nreg, int hstride,
+                           const double *__restrict__ cot, const double *__restrict__ csc,
+                           const double *__restrict__ F, double *__restrict__ Hx, long long wsd, long long nF,
+                           long long nHx)
 {
+    const int map = blockIdx.y / nrun, ri = blockIdx.y % nrun;
+    const SweepRun run = runs[ri];
+    const int n = run.n, an_run = n < 0 ? -n : n;
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (size_t)an_run * hstride) return;
+    const double *FA = F + map * wsd + (size_t)(run.sliceA >= 0 ? run.sliceA : run.sliceB) * nF;
+    const double *FB = F + map * wsd + (size_t)(run.sliceB >= 0 ? run.sliceB : run.sliceA) * nF;
+    double *HxA = Hx + map * wsd + (size_t)ri * 2 * nHx;
+    double *HxB = HxA + nHx;
     const int r = (int)(i % hstride), mu = (int)(i / hstride);
     bool own = false, ext = false;
     if (r < nreg) {
@@ -1096,18 +162,6 @@ __global__ void k_mask_low(int an_run, int n, int nreg, int hstride, const doubl
     HxB[i * 4 + 3] = own ? FB[i * 4 + 3] : 0.0;
 }
 
-// 2 lambda table for the forward sweep: lam[m][r] = n csc_r - (m+1) cot_r
-// (the same FMA the inverse sweep evaluates inline).
-// Rows are padded to lstride rings; padding rings get lambda = 0 (inert).
-__global__ void k_lambda_table(int L, int nx, int nreg, int lstride, int n, const double *__restrict__ cot,
-                               const double *__restrict__ csc, double *__restrict__ lam)
-{
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;   // rows m in [-nx, L), lam at row 0
-    if (i >= (size_t)(L + nx) * lstride) return;
-    const int m = (int)(i / lstride) - nx, r = (int)(i % lstride);
-    lam[(ptrdiff_t)m * lstride + r] = r < nreg ? fma(-(double)(m + 1), cot[r], (double)n * csc[r]) : 0.0;
-}
-
 // ------------------------------------------------------------------ phi-DFT: inverse
 // One workgroup per (map, ring).  X_k = ftilde at orders m == k mod nphi
 // (summed over the d-stage blocks), times the ring's half-pixel phase, then an
@@ -1115,9 +169,8 @@ __global__ void k_lambda_table(int L, int nx, int nreg, int lstride, int n, cons
 // one-to-one onto the bins.  The MW south pole (ring == nreg) has the closed
 // form d^l_{m,-s}(pi) = (-1)^{l+m} delta_{m,s} (Eq. 29).
 __global__ __launch_bounds__(1024) void k_phi_inv(
-    int L, int nreg, int nblk, int spin, const double *__restrict__ part, const int *__restrict__ mtop,
-    const double2 *__restrict__ flm,
-    const double *__restrict__ wl, const int *__restrict__ ring_nphi, const long long *__restrict__ ring_start,
+    int L, int nreg, int nblk, Items it, Strides sp, Strides sf, Strides sm, const double *__restrict__ part,
+    const int *__restrict__ mtop, const double2 *__restrict__ flm, const double *__restrict__ wl, const int *__restrict__ ring_nphi, const long long *__restrict__ ring_start,
     const int *__restrict__ ring_shift, const int *__restrict__ ring_fft, const FftArgs *__restrict__ ffts,
     double2 *__restrict__ map, double2 *__restrict__ fscr)
 {
@@ -1125,6 +178,12 @@ __global__ __launch_bounds__(1024) void k_phi_inv(
     __shared__ double2 red[1024];
     const int r = blockIdx.x;
     const int T = blockDim.x, tid = threadIdx.x;
+    const int item = it.item0 + blockIdx.y, map_i = item / it.nslice, slice = item % it.nslice;
+    const int spin = it.spin[slice];
+    part += map_i * sp.map + slice * sp.slice;
+    flm += map_i * sf.map + slice * sf.slice;
+    map += map_i * sm.map + slice * sm.slice;
+    wl += (size_t)slice * L;
     const int nphi = ring_nphi[r];
     const FftArgs *f = ffts + ring_fft[r];
     const int shift = ring_shift[r];
@@ -1229,14 +288,20 @@ __global__ __launch_bounds__(1024) void k_phi_inv(
 // for |m| < L (the periodic repeat of Sec. 4.2 for short HEALPix rings), written
 // to F[m][ring] = {ftilde_m, ftilde_-m}.
 __global__ __launch_bounds__(1024) void k_phi_fwd(
-    int L, int nring, int hstride, double q, const double2 *__restrict__ map, const int *__restrict__ ring_nphi,
+    int L, int nring, int hstride, double q, Items it, Strides sm, Strides sF, const double2 *__restrict__ map, const int *__restrict__ ring_nphi,
     const long long *__restrict__ ring_start, const int *__restrict__ ring_shift,
     const int *__restrict__ ring_fft, const FftArgs *__restrict__ ffts, const double *__restrict__ ringq,
     double *__restrict__ F, double2 *__restrict__ fscr)
 {
     extern __shared__ double2 buf[];
-    const int r = blockIdx.x;
+    // a row of F holds a ring's 32-byte record per order: four rings share a 128-byte line,
+    // so they go to one XCD (workgroup i to XCD i mod 8), whose L2 joins their stores
+    const int bi = blockIdx.x, b32 = bi & ~31;
+    const int r = b32 + 32 <= (int)gridDim.x ? b32 + (bi & 7) * 4 + ((bi >> 3) & 3) : bi;
     const int T = blockDim.x, tid = threadIdx.x;
+    const int item = it.item0 + blockIdx.y, map_i = item / it.nslice, slice = item % it.nslice;
+    map += map_i * sm.map + slice * sm.slice;
+    F += map_i * sF.map + slice * sF.slice;
     if (r >= nring) {                       // padding rings of the forward sweep: zeros
         for (int m = tid; m < L; m += T) {
             double *o = F + ((size_t)m * hstride + r) * 4;
@@ -1284,7 +349,7 @@ __global__ __launch_bounds__(1024) void k_phi_fwd(
 // bins; other rings sum the orders of each bin (HEALPix repeat) with the
 // half-pixel phase.
 __global__ __launch_bounds__(1024) void k_phi_inv_real(
-    int L, int nreg, int nblk, const int *__restrict__ pairs, const double *__restrict__ part,
+    int L, int nreg, int nblk, int item0, long long sp, long long sf, long long sm, const int *__restrict__ pairs, const double *__restrict__ part,
     const int *__restrict__ mtop, const double2 *__restrict__ flm, const double *__restrict__ wl,
     const int *__restrict__ ring_nphi, const long long *__restrict__ ring_start, const int *__restrict__ ring_shift,
     const int *__restrict__ ring_fft, const FftArgs *__restrict__ ffts, double *__restrict__ map,
@@ -1292,6 +357,10 @@ __global__ __launch_bounds__(1024) void k_phi_inv_real(
 {
     extern __shared__ double2 buf[];
     __shared__ double2 red[1024];
+    const int map_i = item0 + blockIdx.y;
+    part += map_i * sp;
+    flm += map_i * sf;
+    map += map_i * sm;
     const int r1 = pairs[2 * blockIdx.x], r2 = pairs[2 * blockIdx.x + 1];
     const int T = blockDim.x, tid = threadIdx.x;
     const int M = 2 * L - 1;
@@ -1388,13 +457,16 @@ __global__ __launch_bounds__(1024) void k_phi_inv_real(
 // of the complex phi-DFT).  Workgroups past the pairs zero the sweep's padding
 // rings nring .. hstride-1, two per workgroup.
 __global__ __launch_bounds__(1024) void k_phi_fwd_real(
-    int L, int nring, int hstride, int npair, double q, const int *__restrict__ pairs, const double *__restrict__ map,
+    int L, int nring, int hstride, int npair, double q, int item0, long long sm, long long sF,
+    const int *__restrict__ pairs, const double *__restrict__ map,
     const int *__restrict__ ring_nphi, const long long *__restrict__ ring_start, const int *__restrict__ ring_shift,
     const int *__restrict__ ring_fft, const FftArgs *__restrict__ ffts, const double *__restrict__ ringq,
     double *__restrict__ F, double2 *__restrict__ fscr)
 {
     extern __shared__ double2 buf[];
     const int T = blockDim.x, tid = threadIdx.x;
+    map += (item0 + (int)blockIdx.y) * sm;
+    F += (item0 + (int)blockIdx.y) * sF;
     if ((int)blockIdx.x >= npair) {
         const int r0 = nring + 2 * ((int)blockIdx.x - npair);
         for (int m = tid; m < L; m += T)
@@ -1471,16 +543,22 @@ __device__ __forceinline__ int torus_ring(int t, int L, int N, int ss, bool *mir
     return u == 0 ? L : u - 1;
 }
 
-__global__ __launch_bounds__(1024) void k_mw_filter(int L, int ss, int hstride, int spin, const FftArgs *__restrict__ fN,
-                                                    const double *__restrict__ wq, const double *__restrict__ ph,
-                                                    double *__restrict__ F, double2 *__restrict__ hpole,
-                                                    double2 *__restrict__ hpoleN, double2 *__restrict__ fscr,
-                                                    int half, int adj, const FftArgs *__restrict__ fconv)
+__global__ __launch_bounds__(1024) void k_mw_filter(int L, int ss, int hstride, Items it, Strides sF, Strides sh,
+                                                    const FftArgs *__restrict__ fN, const double *__restrict__ wq,
+                                                    const double *__restrict__ ph, double *__restrict__ F,
+                                                    double2 *__restrict__ hpole, double2 *__restrict__ hpoleN,
+                                                    double2 *__restrict__ fscr, int half, int adj,
+                                                    const FftArgs *__restrict__ fconv)
 {
     extern __shared__ double2 buf[];
     __shared__ double2 nyq;
     __shared__ double2 wpart[16];                          // per-wave partial sums (<= 1024 threads)
     const int m = blockIdx.x;
+    const int item = it.item0 + blockIdx.y, map_i = item / it.nslice, slice = item % it.nslice;
+    const int spin = it.spin[slice];
+    F += map_i * sF.map + slice * sF.slice;
+    hpole += map_i * sh.map + slice * sh.slice;
+    if (hpoleN) hpoleN += map_i * sh.map + slice * sh.slice;
     const int N = ss ? 2 * L : 2 * L - 1;
     const int T = blockDim.x, tid = threadIdx.x;
     const double par = ((m + spin) & 1) ? -1.0 : 1.0;
@@ -1603,10 +681,16 @@ __global__ __launch_bounds__(1024) void k_mw_filter(int L, int ss, int hstride, 
 // MWSS (ss): the rows are the L-1 regular rings, the south pole (row L-1) and the
 // north pole (row L, the forward's w_l h~_{-s}(0) at order -s), and the adjoint
 // filter runs in between.
-__global__ void k_fadj_gather(int L, int ss, int nblk, int spin, const double *__restrict__ part,
+__global__ void k_fadj_gather(int L, int ss, int nblk, Items it, Strides sp, Strides sf, Strides sF, const double *__restrict__ part,
                               const int *__restrict__ mtop, const double2 *__restrict__ flm,
                               const double *__restrict__ wl, int hstride, double *__restrict__ F)
 {
+    const int item = it.item0 + blockIdx.y, map_i = item / it.nslice, slice = item % it.nslice;
+    const int spin = it.spin[slice];
+    part += map_i * sp.map + slice * sp.slice;
+    flm += map_i * sf.map + slice * sf.slice;
+    F += map_i * sF.map + slice * sF.slice;
+    wl += (size_t)slice * L;
     const int nrow = L + ss;
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (size_t)L * nrow) return;
@@ -1646,10 +730,16 @@ __global__ void k_fadj_gather(int L, int ss, int nblk, int spin, const double *_
     for (int c = 0; c < 4; ++c) dst[c] = v[c];
 }
 
-__global__ void k_fadj_scatter(int L, int ss, int hstride, double q, const double *__restrict__ F,
+__global__ void k_fadj_scatter(int L, int ss, int hstride, double q, Items it, Strides sF, Strides sh, Strides so,
+                               const double *__restrict__ F,
                                const double2 *__restrict__ hpole, const double2 *__restrict__ hpoleN,
                                double *__restrict__ out)
 {
+    const int item = it.item0 + blockIdx.y, map_i = item / it.nslice, slice = item % it.nslice;
+    F += map_i * sF.map + slice * sF.slice;
+    hpole += map_i * sh.map + slice * sh.slice;
+    if (hpoleN) hpoleN += map_i * sh.map + slice * sh.slice;
+    out += map_i * so.map + slice * so.slice;
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (size_t)(L + ss) * L) return;
     const int t = (int)(i / L), m = (int)(i % L);
@@ -1670,7 +760,9 @@ __global__ void k_fadj_scatter(int L, int ss, int hstride, double q, const doubl
 }
 
 // ------------------------------------------------------------------ forward finish
-// flm[l][m] = w_l * (sum_b Q[b][l][|m|].side + Qx[b][l][|m|].side) * ((-1)^{|m|-nB} for m < 0)
+// flm[l][m] = w_l * (g sum_b Q[b][l][|m|].side + g' sum_b Qx[b][l][|m|].side) * ((-1)^{|m|-nB} for m < 0)
+//           (g = g_{|m|}^l, g' = g_{-|m|}^l: the sweeps leave the recursion's scale to here;
+//           gtab null: already applied)
 //           + south pole: w_l (-1)^{l+s} h~_s(pi) at m = s  (Eq. 29)
 //           + north pole (MWSS): w_l h~_{-s}(0) at m = -s.
 // Zero where l < max(|m|, |spin|).  One thread per (l, |m|) reads whole 32-byte
@@ -1680,11 +772,20 @@ __global__ void k_fadj_scatter(int L, int ss, int hstride, double q, const doubl
 // half = 2 (gradient of the real-signal inverse with respect to its complex
 // input, whose orders m > 0 enter twice and order 0 through its real part):
 // 2 x side A at m > 0, its real part at m = 0, zero at m < 0.
-__global__ void k_finish_fwd(int L, int nblk, int spin, int nB, const double *__restrict__ Q,
+__global__ void k_finish_fwd(int L, int nblk, Items it, Strides sQ, Strides sQx, Strides sh, Strides sf,
+                             const double *__restrict__ gtab, const double *__restrict__ Q,
                              const double *__restrict__ Qx, int nxp, const double *__restrict__ wl,
                              const double2 *__restrict__ hpole, const double2 *__restrict__ hpoleN,
                              double2 *__restrict__ flm, int half)
 {
+    const int item = it.item0 + blockIdx.y, map_i = item / it.nslice, slice = item % it.nslice;
+    const int spin = it.spin[slice], nB = spin;
+    Q += map_i * sQ.map + slice * sQ.slice;
+    if (Qx) Qx += map_i * sQx.map + slice * sQx.slice;
+    if (hpole) hpole += map_i * sh.map + slice * sh.slice;
+    if (hpoleN) hpoleN += map_i * sh.map + slice * sh.slice;
+    flm += map_i * sf.map + slice * sf.slice;
+    wl += (size_t)slice * L;
     const int M = 2 * L - 1;
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (size_t)L * L) return;
@@ -1696,11 +797,22 @@ __global__ void k_finish_fwd(int L, int nblk, int spin, int nB, const double *__
             const double2 *q = reinterpret_cast<const double2 *>(Q + (((size_t)bb * L + l) * L + am) * 4);
             a = cadd(a, q[0]);
             if (!half) b = cadd(b, q[1]);
-            if (Qx && am < nxp) {                      // orders below |n| from the other run's continuation
+        }
+        if (gtab) {
+            const double g = gtab[(size_t)am * L + l];
+            a = make_double2(g * a.x, g * a.y);
+            b = make_double2(g * b.x, g * b.y);
+        }
+        if (Qx && am < nxp) {                          // orders below |n| from the other run's continuation
+            double2 ax = make_double2(0.0, 0.0), bx = ax;
+            for (int bb = 0; bb < nblk; ++bb) {
                 const double2 *qx = reinterpret_cast<const double2 *>(Qx + (((size_t)bb * L + l) * nxp + am) * 4);
-                a = cadd(a, qx[0]);
-                b = cadd(b, qx[1]);
+                ax = cadd(ax, qx[0]);
+                bx = cadd(bx, qx[1]);
             }
+            const double gx = gtab ? gtab[-(ptrdiff_t)am * L + l] : 1.0;
+            a = make_double2(fma(gx, ax.x, a.x), fma(gx, ax.y, a.y));
+            b = make_double2(fma(gx, bx.x, b.x), fma(gx, bx.y, b.y));
         }
         const double w = wl[l];
         const double wb = ((am - nB) & 1) ? -w : w;
@@ -1741,8 +853,10 @@ __global__ void k_finish_fwd(int L, int nblk, int spin, int nB, const double *__
 
 // ------------------------------------------------------------------ ring scaling
 // map[t][p] *= w[t] for rings of nphi samples each (adjoint of a ring-weighted quadrature)
-__global__ void k_ring_scale(int nring, int nphi, const double *__restrict__ w, double2 *__restrict__ map)
+__global__ void k_ring_scale(int nring, int nphi, const double *__restrict__ w, double2 *__restrict__ map,
+                             long long sm)
 {
+    map += blockIdx.y * sm;
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (size_t)nring * nphi) return;
     const double s = w[i / nphi];
@@ -1752,10 +866,11 @@ __global__ void k_ring_scale(int nring, int nphi, const double *__restrict__ w, 
 // real maps: map[t][p] *= w[t] over rings given by their start and length
 __global__ void k_ring_scale_real(int nring, const long long *__restrict__ ring_start,
                                   const int *__restrict__ ring_nphi, const double *__restrict__ w,
-                                  double *__restrict__ map)
+                                  double *__restrict__ map, long long sm)
 {
     const int r = blockIdx.x;
     if (r >= nring) return;
+    map += blockIdx.y * sm;
     double *row = map + ring_start[r];
     const double s = w[r];
     for (int k = threadIdx.x; k < ring_nphi[r]; k += blockDim.x) row[k] *= s;
@@ -1765,8 +880,11 @@ __global__ void k_ring_scale_real(int nring, const long long *__restrict__ ring_
 // h_m = (G[l][m] + (-1)^m conj G[l][-m]) / 2 (m > 0), h_0 = Re G[l][0], with
 // out[l][-m] = (-1)^m conj h_m.  For a real map x and the forward transform F,
 // Re <G, F x> = <h, F x>: the real-signal adjoint of the forward sees only h.
-__global__ void k_hermitian_part(int L, const double2 *__restrict__ G, double2 *__restrict__ out)
+__global__ void k_hermitian_part(int L, const double2 *__restrict__ G, double2 *__restrict__ out, long long sG,
+                                 long long so)
 {
+    G += blockIdx.y * sG;
+    out += blockIdx.y * so;
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (size_t)L * L) return;
     const int l = (int)(i / L), am = (int)(i % L);
@@ -1788,8 +906,10 @@ __global__ void k_hermitian_part(int L, const double2 *__restrict__ G, double2 *
 // ------------------------------------------------------------------ SO(3) gamma DFT
 // inverse: out[k][i] = sum_n e^{i n gamma_k} in[n][i];  forward: out[n][i] = q sum_k e^{-i n gamma_k} in[k][i]
 __global__ void k_gamma_dft(int N, long long nper, int sign, double q, const double *__restrict__ roots,
-                            const double2 *__restrict__ in, double2 *__restrict__ out)
+                            const double2 *__restrict__ in, double2 *__restrict__ out, long long si, long long so)
 {
+    in += blockIdx.y * si;
+    out += blockIdx.y * so;
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nper) return;
     const int G = 2 * N - 1;
@@ -1946,8 +1066,12 @@ __global__ __launch_bounds__(1024) void k_bluestein_prep(const FftArgs *__restri
 }
 
 // pole[(L-1) + m] = F[|m|][ring].side(m): the MW south-pole ring's Fourier line
-__global__ void k_pole_from_F(int L, int hstride, int ring, const double *__restrict__ F, double2 *__restrict__ pole)
+__global__ void k_pole_from_F(int L, int hstride, int ring, Items it, Strides sF, Strides sh,
+                              const double *__restrict__ F, double2 *__restrict__ pole)
 {
+    const int item = it.item0 + blockIdx.y, map_i = item / it.nslice, slice = item % it.nslice;
+    F += map_i * sF.map + slice * sF.slice;
+    pole += map_i * sh.map + slice * sh.slice;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= 2 * L - 1) return;
     const int m = i - (L - 1), am = m < 0 ? -m : m;
@@ -1955,135 +1079,23 @@ __global__ void k_pole_from_F(int L, int hstride, int ring, const double *__rest
     pole[i] = make_double2(src[0], src[1]);
 }
 
+// p[0 .. n) of every map = 0
+__global__ void k_zero_maps(double *__restrict__ p, size_t n, long long wsd)
+{
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[blockIdx.y * wsd + i] = 0.0;
+}
+
 // ------------------------------------------------------------------ launchers
 #define S2_LAUNCH_CHECK() do { hipError_t _e = hipGetLastError(); if (_e != hipSuccess) return _e; } while (0)
 
-hipError_t launch_pack_inv(hipStream_t st, int L, int nx, int n, int nblk, int slots_per_blk, const int *lslot,
-                           const double2 *flmA, const double2 *flmB, const double *wA, const double *wB,
-                           const double *kap, const double *gtab, double *C, int half)
-{   // half: 0 both sides, 1 the A side only, 2 the B side only
-    const int nslot = nblk * slots_per_blk;
-    dim3 grid((nslot + 255) / 256, L + nx);
-    // side 1: A only (flmB not read), side 2: B only (flmA absent)
-    if ((half == 1 && !flmA) || (half == 2 && (flmA || !flmB))) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_pack_inv, grid, dim3(256), 0, st, L, nx, n, nslot, slots_per_blk, half ? 3 : 5, lslot, flmA,
-                       half == 1 ? nullptr : flmB, wA, wB, kap, gtab, C);
-    S2_LAUNCH_CHECK();
-    return hipSuccess;
-}
-
-hipError_t launch_dstage_inv(hipStream_t st, int nwaves, int nblk, int L, int nx, int nreg, int n, const double *cot,
-                             const double *csc, const double2 *init, const double *C, const int *lchunk,
-                             const int *mtop, double *partA, double *partB, int side, int nsw,
-                             const OrderTiles &ot)
-{
-    if (ot.nt < 1 || ot.nt > MAX_ORDER_TILES || (ot.nt > 1 && !ot.ck)) return hipErrorInvalidValue;
-    if (nwaves != 4 && nwaves != 8) return hipErrorInvalidValue;   // reducer rotation: one or two groups of 4
-    if (side < 0 || side > 2 || (side == 1 && !partA) || (side == 2 && !partB) || (side == 0 && (!partA || !partB)))
-        return hipErrorInvalidValue;                                // the side(s) swept must have outputs
-    if (nsw <= 0) nsw = nreg;
-    const bool pair = nsw < nreg;                                   // mirror rings from the northern sweep
-    if (nsw > nreg || (pair && (n != 0 || side == 2 || 2 * nsw < nreg))) return hipErrorInvalidValue;
-    dim3 grid((nsw + 63) / 64, nblk, ot.nt);
-    // wave count, the real-signal half and the ring pairing as template arguments
-    auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, grid, dim3(64 * nwaves), 0, st, L, nx, nreg, nsw, n, cot, csc, init, C, lchunk, mtop,
-                           partA, partB, ot);
-    };
-    if (nwaves == 8) {
-        if (pair) side ? go(k_dstage_inv<INV_NCH, 8, 1, true>) : go(k_dstage_inv<INV_NCH, 8, 0, true>);
-        else if (side == 1) go(k_dstage_inv<INV_NCH, 8, 1>);
-        else if (side == 2) go(k_dstage_inv<INV_NCH, 8, 2>);
-        else go(k_dstage_inv<INV_NCH, 8, 0>);
-    } else {
-        if (pair) side ? go(k_dstage_inv<INV_NCH, 4, 1, true>) : go(k_dstage_inv<INV_NCH, 4, 0, true>);
-        else if (side == 1) go(k_dstage_inv<INV_NCH, 4, 1>);
-        else if (side == 2) go(k_dstage_inv<INV_NCH, 4, 2>);
-        else go(k_dstage_inv<INV_NCH, 4, 0>);
-    }
-    S2_LAUNCH_CHECK();
-    return hipSuccess;
-}
-
-hipError_t launch_dstage_fwd(hipStream_t st, int nwaves, int nblk, int G, int L, int nxp, int nreg, int hstride,
-                             int lstride, int n, const double *lam, const double2 *init, const double *kap,
-                             const double *gtab, const double *HA, const double *HB, const double *HxA,
-                             const double *HxB, double *QA, double *QB, double *QxA, double *QxB, int side, int pair,
-                             const OrderTiles &ot)
-{
-    if (ot.nt < 1 || ot.nt > MAX_ORDER_TILES || (ot.nt > 1 && !ot.ck)) return hipErrorInvalidValue;
-    if ((nwaves != 4 && nwaves != 8 && nwaves != 16) || nwaves > FWD_MAX_WAVES)
-        return hipErrorInvalidValue;                                // reducer rotation: 1, 2 or 4 groups of 4
-    if (pair && (n != 0 || HA == HB || HxA || HxB || side == 2)) return hipErrorInvalidValue;   // mirror rings: n = 0
-    // one side: both sides read one spectra array (the run's slice), and that side has outputs
-    if (side && !pair && (HA != HB || (side == 1 && !QA) || (side == 2 && !QB))) return hipErrorInvalidValue;
-    // XCD-aware tile order when the untiled grid is resident in one round (every
-    // workgroup of a ring block then runs beside the others that read its spectra rows,
-    // in step through one L2).  Measured (one map): MW L = 2048 forward 2.94 -> 2.82 ms
-    // (spin 2: 5.43 -> 5.05 ms), HEALPix nside 1024 3.95 -> 3.80 ms, spectra read from
-    // HBM 3.04 -> 1.58 GB; grids of several rounds were slower in that order (L = 3072
-    // 10.7 -> 12.4 ms, L = 4096 19.5 -> 28.1 ms, L = 1024 in 8 order tiles 0.59 -> 0.75
-    // ms) and keep the plain one.  The inverse sweep was slower in XCD order at every size
-    // tried (L = 1024: 0.47 -> 0.79 ms; L = 2048 spin 2: 4.5 -> 5.1 ms).
-    const int gx = (G + 1) / 2, gy = nblk, gz = ot.nt, T = gx * gy * gz;
-    // (a failed query only selects the plain order; its error is cleared, not reported)
-    int dev = 0, ncu = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) !=
-        hipSuccess) {
-        ncu = 0;
-        (void)hipGetLastError();
-    }
-    // the wave count is a template argument: the reducer rotation and the wave sum
-    // then compile to fixed code; HA == HB (run n = 0) selects the one-array path
-    auto go = [&](auto kern) {
-        int per_cu = 0;
-        if (ncu && hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64 * nwaves, 0) != hipSuccess) {
-            per_cu = 0;
-            (void)hipGetLastError();
-        }
-        const bool xcd = ot.nt == 1 && T <= per_cu * ncu;
-        const dim3 grid((unsigned)(xcd ? (T + NXCD - 1) / NXCD * NXCD : T));
-        hipLaunchKernelGGL(kern, grid, dim3(64 * nwaves), 0, st, gx, gy, gz, xcd, L, nxp, nreg, hstride, lstride, n,
-                           G, lam, init, kap, gtab, HA, HB, HxA, HxB, QA, QB, QxA, QxB, ot);
-    };
-    const bool same = HA == HB;
-    if (pair) {
-        if (nwaves == 16) side ? go(k_dstage_fwd<FWD_NCH, true, 16, 1, true>) : go(k_dstage_fwd<FWD_NCH, true, 16, 0, true>);
-        else if (nwaves == 8) side ? go(k_dstage_fwd<FWD_NCH, true, 8, 1, true>) : go(k_dstage_fwd<FWD_NCH, true, 8, 0, true>);
-        else side ? go(k_dstage_fwd<FWD_NCH, true, 4, 1, true>) : go(k_dstage_fwd<FWD_NCH, true, 4, 0, true>);
-    } else if (side == 1) {
-        if (nwaves == 16) go(k_dstage_fwd<FWD_NCH, true, 16, 1>);
-        else if (nwaves == 8) go(k_dstage_fwd<FWD_NCH, true, 8, 1>);
-        else go(k_dstage_fwd<FWD_NCH, true, 4, 1>);
-    } else if (side == 2) {
-        if (nwaves == 16) go(k_dstage_fwd<FWD_NCH, true, 16, 2>);
-        else if (nwaves == 8) go(k_dstage_fwd<FWD_NCH, true, 8, 2>);
-        else go(k_dstage_fwd<FWD_NCH, true, 4, 2>);
-    } else if (nwaves == 16) same ? go(k_dstage_fwd<FWD_NCH, true, 16>) : go(k_dstage_fwd<FWD_NCH, false, 16>);
-    else if (nwaves == 8) same ? go(k_dstage_fwd<FWD_NCH, true, 8>) : go(k_dstage_fwd<FWD_NCH, false, 8>);
-    else same ? go(k_dstage_fwd<FWD_NCH, true, 4>) : go(k_dstage_fwd<FWD_NCH, false, 4>);
-    S2_LAUNCH_CHECK();
-    return hipSuccess;
-}
-
-hipError_t launch_order_ckpt(hipStream_t st, int L, int nreg, int n, const double *cot, const double *csc,
-                             const double2 *init, const double *kap, const OrderTiles &ot, double *ck)
-{
-    if (ot.nt < 2) return hipSuccess;
-    if (ot.nt > MAX_ORDER_TILES || !ck || ot.rp < nreg) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_order_ckpt, dim3((ot.rp + 63) / 64, L), dim3(64), 0, st, L, nreg, n, cot, csc, init, kap, ot,
-                       ck);
-    S2_LAUNCH_CHECK();
-    return hipSuccess;
-}
-
-hipError_t launch_pair_spectra(hipStream_t st, int L, int nreg, int nsw, int hstride, int pstride, const double *H,
-                               double *S, double *D)
+hipError_t launch_pair_spectra(hipStream_t st, int nmap, long long wsd, int L, int nreg, int nsw, int hstride,
+                               int pstride, const double *H, double *S, double *D)
 {
     if (nsw > pstride || 2 * nsw < nreg || nreg > hstride) return hipErrorInvalidValue;
     const size_t tot = (size_t)L * pstride;
-    hipLaunchKernelGGL(k_pair_spectra, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, L, nreg, nsw, hstride,
-                       pstride, H, S, D);
+    hipLaunchKernelGGL(k_pair_spectra, dim3((unsigned)((tot + 255) / 256), nmap), dim3(256), 0, st, L, nreg, nsw,
+                       hstride, pstride, H, S, D, wsd);
     S2_LAUNCH_CHECK();
     return hipSuccess;
 }
@@ -2098,121 +1110,133 @@ hipError_t launch_init_table(hipStream_t st, int L, int nreg, int n, const doubl
     return hipSuccess;
 }
 
-hipError_t launch_lambda_table(hipStream_t st, int L, int nx, int nreg, int lstride, int n, const double *cot,
-                               const double *csc, double *lam)
+// The DFT kernels of a plan whose rings need global scratch (fscr) run one item per
+// launch, so that the items share it.
+template <typename F>
+static hipError_t over_items(int nitem, bool one_by_one, F go)
 {
-    const size_t tot = (size_t)(L + nx) * lstride;
-    hipLaunchKernelGGL(k_lambda_table, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, L, nx, nreg, lstride, n,
-                       cot, csc, lam);
-    S2_LAUNCH_CHECK();
+    const int step = one_by_one ? 1 : 32768;             // grid.y limit
+    for (int i = 0; i < nitem; i += step) {
+        go(i, nitem - i < step ? nitem - i : step);
+        S2_LAUNCH_CHECK();
+    }
     return hipSuccess;
 }
 
-hipError_t launch_phi_inv(hipStream_t st, int nthreads, size_t lds, int nring, int L, int nreg, int nblk, int spin,
-                          const double *part, const int *mtop, const double2 *flm, const double *wl,
-                          const int *ring_nphi, const long long *ring_start, const int *ring_shift,
-                          const int *ring_fft, const FftArgs *ffts, double2 *map, double2 *fscr)
-{
-    hipLaunchKernelGGL(k_phi_inv, dim3(nring), dim3(nthreads), lds, st, L, nreg, nblk, spin, part, mtop, flm, wl,
-                       ring_nphi, ring_start, ring_shift, ring_fft, ffts, map, fscr);
-    S2_LAUNCH_CHECK();
-    return hipSuccess;
-}
-
-hipError_t launch_phi_fwd(hipStream_t st, int nthreads, size_t lds, int nring, int hstride, int L, double q,
-                          const double2 *map, const int *ring_nphi, const long long *ring_start, const int *ring_shift,
-                          const int *ring_fft, const FftArgs *ffts, const double *ringq, double *F,
+hipError_t launch_phi_inv(hipStream_t st, int nthreads, size_t lds, int nring, int L, int nreg, int nblk, Items it,
+                          int nitem, Strides sp, Strides sf, Strides sm, const double *part, const int *mtop,
+                          const double2 *flm, const double *wl, const int *ring_nphi, const long long *ring_start,
+                          const int *ring_shift, const int *ring_fft, const FftArgs *ffts, double2 *map,
                           double2 *fscr)
 {
-    hipLaunchKernelGGL(k_phi_fwd, dim3(hstride), dim3(nthreads), lds, st, L, nring, hstride, q, map, ring_nphi,
-                       ring_start, ring_shift, ring_fft, ffts, ringq, F, fscr);
-    S2_LAUNCH_CHECK();
-    return hipSuccess;
+    return over_items(nitem, fscr != nullptr, [&](int i, int ny) {
+        it.item0 = i;
+        hipLaunchKernelGGL(k_phi_inv, dim3(nring, ny), dim3(nthreads), lds, st, L, nreg, nblk, it, sp, sf, sm, part,
+                           mtop, flm, wl, ring_nphi, ring_start, ring_shift, ring_fft, ffts, map, fscr);
+    });
 }
 
-hipError_t launch_phi_inv_real(hipStream_t st, int nthreads, size_t lds, int npair, int L, int nreg, int nblk,
-                               const int *pairs, const double *part, const int *mtop, const double2 *flm,
-                               const double *wl, const int *ring_nphi, const long long *ring_start,
-                               const int *ring_shift, const int *ring_fft, const FftArgs *ffts, double *map,
-                               double2 *fscr)
+hipError_t launch_phi_fwd(hipStream_t st, int nthreads, size_t lds, int nring, int hstride, int L, double q, Items it,
+                          int nitem, Strides sm, Strides sF, const double2 *map, const int *ring_nphi,
+                          const long long *ring_start, const int *ring_shift, const int *ring_fft, const FftArgs *ffts,
+                          const double *ringq, double *F, double2 *fscr)
+{
+    return over_items(nitem, fscr != nullptr, [&](int i, int ny) {
+        it.item0 = i;
+        hipLaunchKernelGGL(k_phi_fwd, dim3(hstride, ny), dim3(nthreads), lds, st, L, nring, hstride, q, it, sm, sF, map,
+                           ring_nphi, ring_start, ring_shift, ring_fft, ffts, ringq, F, fscr);
+    });
+}
+
+hipError_t launch_phi_inv_real(hipStream_t st, int nthreads, size_t lds, int npair, int L, int nreg, int nblk, int nmap,
+                               long long sp, long long sf, long long sm, const int *pairs, const double *part,
+                               const int *mtop, const double2 *flm, const double *wl, const int *ring_nphi,
+                               const long long *ring_start, const int *ring_shift, const int *ring_fft,
+                               const FftArgs *ffts, double *map, double2 *fscr)
 {
     if (nthreads > 1024 || npair < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_phi_inv_real, dim3(npair), dim3(nthreads), lds, st, L, nreg, nblk, pairs, part, mtop, flm, wl,
-                       ring_nphi, ring_start, ring_shift, ring_fft, ffts, map, fscr);
-    S2_LAUNCH_CHECK();
-    return hipSuccess;
+    return over_items(nmap, fscr != nullptr, [&](int i, int ny) {
+        hipLaunchKernelGGL(k_phi_inv_real, dim3(npair, ny), dim3(nthreads), lds, st, L, nreg, nblk, i, sp, sf, sm,
+                           pairs, part, mtop, flm, wl, ring_nphi, ring_start, ring_shift, ring_fft, ffts, map, fscr);
+    });
 }
 
 hipError_t launch_phi_fwd_real(hipStream_t st, int nthreads, size_t lds, int nring, int hstride, int npair, int L,
-                               double q, const int *pairs, const double *map, const int *ring_nphi,
-                               const long long *ring_start, const int *ring_shift, const int *ring_fft,
-                               const FftArgs *ffts, const double *ringq, double *F, double2 *fscr)
+                               double q, int nmap, long long sm, long long sF, const int *pairs, const double *map,
+                               const int *ring_nphi, const long long *ring_start, const int *ring_shift,
+                               const int *ring_fft, const FftArgs *ffts, const double *ringq, double *F, double2 *fscr)
 {
     if (nthreads > 1024 || hstride < nring || npair < 1) return hipErrorInvalidValue;
     const int nblocks = npair + (hstride - nring + 1) / 2;
-    hipLaunchKernelGGL(k_phi_fwd_real, dim3(nblocks), dim3(nthreads), lds, st, L, nring, hstride, npair, q, pairs, map,
-                       ring_nphi, ring_start, ring_shift, ring_fft, ffts, ringq, F, fscr);
-    S2_LAUNCH_CHECK();
-    return hipSuccess;
+    return over_items(nmap, fscr != nullptr, [&](int i, int ny) {
+        hipLaunchKernelGGL(k_phi_fwd_real, dim3(nblocks, ny), dim3(nthreads), lds, st, L, nring, hstride, npair, q, i,
+                           sm, sF, pairs, map, ring_nphi, ring_start, ring_shift, ring_fft, ffts, ringq, F, fscr);
+    });
 }
 
-hipError_t launch_mw_filter(hipStream_t st, int nthreads, size_t lds, int L, int ss, int hstride, int spin,
-                            const FftArgs *fN, const double *wq, const double *ph, double *F, double2 *hpole,
-                            double2 *hpoleN, double2 *fscr, int half, int adj, const FftArgs *fconv)
+hipError_t launch_mw_filter(hipStream_t st, int nthreads, size_t lds, int L, int ss, int hstride, Items it, int nitem,
+                            Strides sF, Strides sh, const FftArgs *fN, const double *wq, const double *ph, double *F,
+                            double2 *hpole, double2 *hpoleN, double2 *fscr, int half, int adj, const FftArgs *fconv)
 {
     if ((ss && !hpoleN) || nthreads > 1024) return hipErrorInvalidValue;
     if (fconv && ss) return hipErrorInvalidValue;               // the convolution form is MW's
-    hipLaunchKernelGGL(k_mw_filter, dim3(L), dim3(nthreads), lds, st, L, ss, hstride, spin, fN, wq, ph, F, hpole,
-                       hpoleN, fscr, half, adj, fconv);
-    S2_LAUNCH_CHECK();
-    return hipSuccess;
+    return over_items(nitem, fscr != nullptr, [&](int i, int ny) {
+        it.item0 = i;
+        hipLaunchKernelGGL(k_mw_filter, dim3(L, ny), dim3(nthreads), lds, st, L, ss, hstride, it, sF, sh, fN, wq, ph, F,
+                           hpole, hpoleN, fscr, half, adj, fconv);
+    });
 }
 
-hipError_t launch_ring_scale_real(hipStream_t st, int nring, const long long *ring_start, const int *ring_nphi,
-                                  const double *w, double *map)
+hipError_t launch_ring_scale_real(hipStream_t st, int nmap, long long sm, int nring, const long long *ring_start,
+                                  const int *ring_nphi, const double *w, double *map)
 {
     if (nring < 1) return hipSuccess;
-    hipLaunchKernelGGL(k_ring_scale_real, dim3(nring), dim3(256), 0, st, nring, ring_start, ring_nphi, w, map);
-    S2_LAUNCH_CHECK();
-    return hipSuccess;
+    return over_items(nmap, false, [&](int i, int ny) {
+        hipLaunchKernelGGL(k_ring_scale_real, dim3(nring, ny), dim3(256), 0, st, nring, ring_start, ring_nphi, w,
+                           map + i * sm, sm);
+    });
 }
 
-hipError_t launch_hermitian_part(hipStream_t st, int L, const double2 *G, double2 *out)
+hipError_t launch_hermitian_part(hipStream_t st, int nmap, long long sG, long long so, int L, const double2 *G,
+                                 double2 *out)
 {
     const size_t tot = (size_t)L * L;
-    hipLaunchKernelGGL(k_hermitian_part, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, L, G, out);
-    S2_LAUNCH_CHECK();
-    return hipSuccess;
+    return over_items(nmap, false, [&](int i, int ny) {
+        hipLaunchKernelGGL(k_hermitian_part, dim3((unsigned)((tot + 255) / 256), ny), dim3(256), 0, st, L, G + i * sG,
+                           out + i * so, sG, so);
+    });
 }
 
-hipError_t launch_ring_scale(hipStream_t st, int nring, int nphi, const double *w, double2 *map)
+hipError_t launch_ring_scale(hipStream_t st, int nmap, long long sm, int nring, int nphi, const double *w, double2 *map)
 {
     const size_t tot = (size_t)nring * nphi;
     if (tot == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_ring_scale, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, nring, nphi, w, map);
-    S2_LAUNCH_CHECK();
-    return hipSuccess;
+    return over_items(nmap, false, [&](int i, int ny) {
+        hipLaunchKernelGGL(k_ring_scale, dim3((unsigned)((tot + 255) / 256), ny), dim3(256), 0, st, nring, nphi, w,
+                           map + i * sm, sm);
+    });
 }
 
-hipError_t launch_finish_fwd(hipStream_t st, int L, int nblk, int spin, int nB, const double *Q, const double *Qx,
-                             int nxp, const double *wl, const double2 *hpole, const double2 *hpoleN, double2 *flm,
-                             int half)
+hipError_t launch_finish_fwd(hipStream_t st, int L, int nblk, Items it, int nitem, Strides sQ, Strides sQx, Strides sh,
+                             Strides sf, const double *gtab, const double *Q, const double *Qx, int nxp,
+                             const double *wl, const double2 *hpole, const double2 *hpoleN, double2 *flm, int half)
 {
-    if (half && (spin != 0 || Qx)) return hipErrorInvalidValue;   // real signals: spin 0
+    if (half && Qx) return hipErrorInvalidValue;                  // real signals: spin 0
     const size_t tot = (size_t)L * L;
-    hipLaunchKernelGGL(k_finish_fwd, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, L, nblk, spin, nB, Q, Qx,
-                       nxp, wl, hpole, hpoleN, flm, half);
-    S2_LAUNCH_CHECK();
-    return hipSuccess;
+    return over_items(nitem, false, [&](int i, int ny) {
+        it.item0 = i;
+        hipLaunchKernelGGL(k_finish_fwd, dim3((unsigned)((tot + 255) / 256), ny), dim3(256), 0, st, L, nblk, it, sQ,
+                           sQx, sh, sf, gtab, Q, Qx, nxp, wl, hpole, hpoleN, flm, half);
+    });
 }
 
-hipError_t launch_gamma_dft(hipStream_t st, int N, long long nper, int sign, double q, const double *roots,
-                            const double2 *in, double2 *out)
+hipError_t launch_gamma_dft(hipStream_t st, int nmap, long long si, long long so, int N, long long nper, int sign,
+                            double q, const double *roots, const double2 *in, double2 *out)
 {
-    hipLaunchKernelGGL(k_gamma_dft, dim3((unsigned)((nper + 255) / 256)), dim3(256), 0, st, N, nper, sign, q, roots,
-                       in, out);
-    S2_LAUNCH_CHECK();
-    return hipSuccess;
+    return over_items(nmap, false, [&](int i, int ny) {
+        hipLaunchKernelGGL(k_gamma_dft, dim3((unsigned)((nper + 255) / 256), ny), dim3(256), 0, st, N, nper, sign, q,
+                           roots, in + i * si, out + i * so, si, so);
+    });
 }
 
 hipError_t launch_unitarity(hipStream_t st, int L, int n, int nsel, const int *rsel, const double *cot,
@@ -2244,44 +1268,60 @@ hipError_t launch_bluestein_filter(hipStream_t st, int nfft, const FftArgs *ffts
     return hipSuccess;
 }
 
-hipError_t launch_fadj_gather(hipStream_t st, int L, int ss, int nblk, int spin, const double *part, const int *mtop,
-                              const double2 *flm, const double *wl, int hstride, double *F)
+hipError_t launch_fadj_gather(hipStream_t st, int L, int ss, int nblk, Items it, int nitem, Strides sp, Strides sf,
+                              Strides sF, const double *part, const int *mtop, const double2 *flm, const double *wl,
+                              int hstride, double *F)
 {
     if (hstride < L + ss) return hipErrorInvalidValue;
     const size_t tot = (size_t)L * (L + ss);
-    hipLaunchKernelGGL(k_fadj_gather, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, L, ss, nblk, spin, part,
-                       mtop, flm, wl, hstride, F);
-    S2_LAUNCH_CHECK();
-    return hipSuccess;
+    return over_items(nitem, false, [&](int i, int ny) {
+        it.item0 = i;
+        hipLaunchKernelGGL(k_fadj_gather, dim3((unsigned)((tot + 255) / 256), ny), dim3(256), 0, st, L, ss, nblk, it, sp,
+                           sf, sF, part, mtop, flm, wl, hstride, F);
+    });
 }
 
-hipError_t launch_fadj_scatter(hipStream_t st, int L, int ss, int hstride, double q, const double *F,
-                               const double2 *hpole, const double2 *hpoleN, double *out)
+hipError_t launch_fadj_scatter(hipStream_t st, int L, int ss, int hstride, double q, Items it, int nitem, Strides sF,
+                               Strides sh, Strides so, const double *F, const double2 *hpole, const double2 *hpoleN,
+                               double *out)
 {
     if (ss && !hpoleN) return hipErrorInvalidValue;
     const size_t tot = (size_t)(L + ss) * L;
-    hipLaunchKernelGGL(k_fadj_scatter, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, L, ss, hstride, q, F,
-                       hpole, hpoleN, out);
-    S2_LAUNCH_CHECK();
-    return hipSuccess;
+    return over_items(nitem, false, [&](int i, int ny) {
+        it.item0 = i;
+        hipLaunchKernelGGL(k_fadj_scatter, dim3((unsigned)((tot + 255) / 256), ny), dim3(256), 0, st, L, ss, hstride, q,
+                           it, sF, sh, so, F, hpole, hpoleN, out);
+    });
 }
 
-hipError_t launch_mask_low(hipStream_t st, int an, int n, int nreg, int hstride, const double *cot, const double *csc,
-                           const double *FA, const double *FB, double *HxA, double *HxB)
+hipError_t launch_mask_low(hipStream_t st, int nmap, int nrun, const SweepRun *runs, int anmax, int nreg, int hstride,
+                           const double *cot, const double *csc, const double *F, double *Hx, long long wsd,
+                           long long nF, long long nHx)
 {
-    const size_t tot = (size_t)an * hstride;
+    const size_t tot = (size_t)anmax * hstride;
     if (tot == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mask_low, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, an, n, nreg, hstride, cot, csc,
-                       FA, FB, HxA, HxB);
+    hipLaunchKernelGGL(k_mask_low, dim3((unsigned)((tot + 255) / 256), nmap * nrun), dim3(256), 0, st, nrun, runs, nreg,
+                       hstride, cot, csc, F, Hx, wsd, nF, nHx);
     S2_LAUNCH_CHECK();
     return hipSuccess;
 }
 
-hipError_t launch_pole_from_F(hipStream_t st, int L, int hstride, int ring, const double *F, double2 *pole)
+hipError_t launch_zero_maps(hipStream_t st, int nmap, long long wsd, double *p, size_t n)
 {
-    hipLaunchKernelGGL(k_pole_from_F, dim3((2 * L - 1 + 255) / 256), dim3(256), 0, st, L, hstride, ring, F, pole);
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_zero_maps, dim3((unsigned)((n + 255) / 256), nmap), dim3(256), 0, st, p, n, wsd);
     S2_LAUNCH_CHECK();
     return hipSuccess;
+}
+
+hipError_t launch_pole_from_F(hipStream_t st, int L, int hstride, int ring, Items it, int nitem, Strides sF, Strides sh,
+                              const double *F, double2 *pole)
+{
+    return over_items(nitem, false, [&](int i, int ny) {
+        it.item0 = i;
+        hipLaunchKernelGGL(k_pole_from_F, dim3((2 * L - 1 + 255) / 256, ny), dim3(256), 0, st, L, hstride, ring, it, sF,
+                           sh, F, pole);
+    });
 }
 
 // Kernels with large dynamic LDS need the per-kernel limit raised.
