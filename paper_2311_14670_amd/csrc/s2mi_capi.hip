@@ -825,7 +825,7 @@ static int plan_create_impl(s2_plan_t *out, int L, int spin, int N, s2_sampling_
         for (const FftArgs &f : P->ffts_h) split = split || (f.blue && f.split);
         // one FFT_SCRATCH slice per workgroup of the phi-DFT (hstride), inverse phi-DFT
         // (nring) and MW filter (L) launches of one item (items then run one by one)
-        P->sz_fscr = split ? (size_t)std::max({P->hstride, P->nring, L}) * FFT_SCRATCH * sizeof(double2) : 0;
+        P->sz_fscr = split ? (size_t)std::max({P->hstride, P->nring, L + 16}) * FFT_SCRATCH * sizeof(double2) : 0;
         P->off_fscr = o; o += align256(P->sz_fscr);
         P->ws_bytes = o;
     }

@@ -263,23 +263,27 @@ void host_chirp(int n, std::vector<double> *out)
 
 // MW theta filter constants for N = 2L-1 torus points theta_t = (2t+1) pi/N and
 // midpoints mu_t = theta_t + pi/N:
-//   wq[t], wq[N + t]  = P_{2L-2}[sin(theta) 1_[0,pi]] at theta_t and mu_t.  The
-//       Fourier coefficients c_d = (1/2pi) int_0^pi sin(th) e^{-i d th} are
+//   wq[t], wq[N + t]  = P_{2L-2}[|sin(theta)| / 2] at theta_t and mu_t, the even part of
+//       the weight sin(theta) 1_[0,pi] (the filter folds its result onto the parity of
+//       the input, to which the odd part sin / 2 adds only vs below).  The Fourier
+//       coefficients of the weight c_d = (1/2pi) int_0^pi sin(th) e^{-i d th} are
 //       c_{+-1} = -+ i/4, c_d = 1/(pi (1 - d^2)) for even d, 0 for other odd d
-//       (Eq. 42 up to the 2pi normalisation and the sign of d), so
-//       P[...](th) = sin(th)/2 + c_0 + 2 sum_{even d >= 2} c_d cos(d th);
+//       (Eq. 42 up to the 2pi normalisation and the sign of d), so the even part is
+//       P[...](th) = c_0 + 2 sum_{even d >= 2} c_d cos(d th);
+//   wq[2N + t] = vs_t, t <= L: what sin / 2 makes of a unit sample at the south pole,
+//       folded with odd parity: (2 pi/N^2) (-1)^L sin((L-1) theta_t);
 //   ph[k] = e^{i k' pi / N} / N for DFT bin k with signed frequency
 //       k' = k (k <= L-1) or k - N (k >= L): the half-sample shift.
 void host_mw_filter(int L, bool ss, std::vector<double> *wq, std::vector<double> *ph)
 {
     const int N = ss ? 2 * L : 2 * L - 1;
     const long double pi = 3.141592653589793238462643383279502884L;
-    wq->assign(2 * (size_t)N, 0.0);
+    wq->assign(2 * (size_t)N + L + 1, 0.0);
     for (int which = 0; which < 2; ++which) {
         for (int t = 0; t < N; ++t) {
             // MW theta_t = (2t+1) pi/N, MWSS theta_t = 2t pi/N; midpoints one half-step on
             const long double th = (2.0L * t + (ss ? 0.0L : 1.0L) + which) * pi / (long double)N;
-            long double acc = 1.0L / pi + 0.5L * sinl(th);
+            long double acc = 1.0L / pi;           // |sin| / 2: the odd part sin / 2 is vs below
             const long double c2 = cosl(2.0L * th);
             long double cprev = 1.0L, ccur = c2;   // cos(0 th), cos(2 th)
             for (int d = 2; d <= 2 * L - 2; d += 2) {
@@ -293,6 +297,11 @@ void host_mw_filter(int L, bool ss, std::vector<double> *wq, std::vector<double>
             }
             (*wq)[(size_t)which * N + t] = (double)acc;
         }
+    }
+    for (int t = 0; t <= L; ++t) {
+        const long long num = (long long)(L - 1) * (ss ? 2 * t : 2 * t + 1) % (2 * N);   // (L-1) theta_t / (pi/N)
+        (*wq)[2 * (size_t)N + t] =
+            (double)((L & 1 ? -2.0L : 2.0L) * pi / ((long double)N * N) * sinl((long double)num * pi / (long double)N));
     }
     ph->resize(2 * (size_t)N);
     for (int k = 0; k < N; ++k) {

@@ -512,8 +512,8 @@ __global__ __launch_bounds__(1024) void k_phi_fwd_real(
 }
 
 // ------------------------------------------------------------------ MW / MWSS theta filter
-// One workgroup per order m >= 0, both signs.  For g = the torus extension of
-// ftilde_{+-m} (g(2pi - th) = (-1)^{m+s} g(th)), on the N torus points
+// For g = the torus extension of ftilde_{+-m} (g(2pi - th) = (-1)^{m+s} g(th)), on the
+// N torus points
 // (MW: N = 2L-1, theta_t = (2t+1) pi/N; MWSS: N = 2L, theta_t = 2 pi t/N)
 //   h = P_{L-1}[g w'],   w' = P_{2L-2}[sin(theta) 1_[0,pi]],
 // folded onto the rings: h~(theta_t) = (2pi/N) [h(theta_t) + (-1)^{m+s} h(mirror t)]
@@ -527,7 +527,25 @@ __global__ __launch_bounds__(1024) void k_phi_fwd_real(
 // Torus point t <-> ring: MW t < L: ring t (t = L-1: south pole), MWSS t = 0:
 // north pole (ring L), 0 < t < L: ring t-1, t = L: south pole (ring L-1).  In
 // place: F[m][ring] -> H[m][ring] for the swept rings; the pole values go to
-// hpole[(L-1) +- m] (south) and hpoleN (north, MWSS).  half (real signals):
+// hpole[(L-1) +- m] (south) and hpoleN (north, MWSS).
+//
+// Two orders per workgroup.  Of the weight only the even part |sin| / 2 of
+// sin 1_[0,pi] = (|sin| + sin) / 2 reaches the fold of an extension (which has the fold's
+// own parity), and with it the filter commutes with the mirror map; consecutive orders
+// have extensions of opposite parity.  So one pass over the sum z of the extensions of
+// orders 2j and 2j + 1 gives both, h~_m = sc (h(t) + (-1)^{m+s} h(mirror t)) keeping each
+// order's own part.  (Half the transforms of one order at a time: MW L = 2048
+// 0.50 -> 0.28 ms, L = 4096 5.2 -> 2.8 ms, L = 64 0.036 -> 0.022 ms;
+// both orders come from, or go into, the same ring DFTs, so their rounding is relative to
+// one another anyway.)  The one thing an extension of odd parity holds beyond that is its
+// sample at a fixed point of the mirror (a pole): it is even, and the odd part sin / 2 of
+// the weight carries it to the rings: P_{L-1}[sin / 2 times the interpolant of a unit
+// sample] = (-1)^L sin((L-1) theta) / (2N) (without (-1)^L for the north pole), since all
+// other frequencies cancel.  So an odd order's pole sample is left out of z and added as
+// vs[t] g_pole, and the adjoint (adj) gives its pole the sum of vs[t] g(t); the values at
+// odd poles that nothing reads (the finish uses |m| = |s|, even) are 0.  The sides +m and
+// -m are workgroups of their own, on one XCD (their values interleave in 32-byte
+// records).  half (real signals):
 // only the side of order +m is filtered, the filter being real and the side
 // of order -m the conjugate.
 // adj (MWSS): the Hermitian adjoint of the filter.  With the Nyquist projector
@@ -553,7 +571,14 @@ __global__ __launch_bounds__(1024) void k_mw_filter(int L, int ss, int hstride, 
     extern __shared__ double2 buf[];
     __shared__ double2 nyq;
     __shared__ double2 wpart[16];                          // per-wave partial sums (<= 1024 threads)
-    const int m = blockIdx.x;
+    // workgroup -> (pair of orders, side): both sides of a pair at distance 8
+    const int bx = blockIdx.x;
+    const int side = half ? 0 : (bx >> 3) & 1;
+    const int pair = half ? bx : ((bx >> 4) << 3) + (bx & 7);
+    const int m0 = 2 * pair, m1 = m0 + 1;
+    if (m0 >= L) return;
+    const bool has0 = side == 0 || m0 > 0, has1 = m1 < L;    // (side -m exists for m > 0)
+    if (!has0 && !has1) return;
     const int item = it.item0 + blockIdx.y, map_i = item / it.nslice, slice = item % it.nslice;
     const int spin = it.spin[slice];
     F += map_i * sF.map + slice * sF.slice;
@@ -561,19 +586,41 @@ __global__ __launch_bounds__(1024) void k_mw_filter(int L, int ss, int hstride, 
     if (hpoleN) hpoleN += map_i * sh.map + slice * sh.slice;
     const int N = ss ? 2 * L : 2 * L - 1;
     const int T = blockDim.x, tid = threadIdx.x;
-    const double par = ((m + spin) & 1) ? -1.0 : 1.0;
+    const double par = ((m0 + spin) & 1) ? -1.0 : 1.0;       // parity of m0; m1 has the other
     const double2 *phc = reinterpret_cast<const double2 *>(ph);
     double2 *scr = fscr ? fscr + (size_t)blockIdx.x * FFT_SCRATCH : nullptr;
-    for (int side = 0; side < 2; ++side) {
-        if (side == 1 && (m == 0 || half)) break;
+    const double *F0 = F + (size_t)m0 * hstride * 4 + 2 * side;
+    const double *F1 = F + (size_t)m1 * hstride * 4 + 2 * side;
+    // z(t): the two orders' extensions
+    auto sample = [&](int t) {
+        bool mir;
+        const int r = torus_ring(t, L, N, ss, &mir);
+        const bool pole = ss ? (t == 0 || t == L) : t == L - 1;
+        double2 a = make_double2(0.0, 0.0), b = a;
+        if (has0 && !(pole && par < 0.0)) a = *reinterpret_cast<const double2 *>(F0 + (size_t)r * 4);
+        if (has1 && !(pole && par > 0.0)) b = *reinterpret_cast<const double2 *>(F1 + (size_t)r * 4);
+        const double s = mir ? par : 1.0, q = mir ? -par : 1.0;
+        return make_double2(fma(s, a.x, q * b.x), fma(s, a.y, q * b.y));
+    };
+    // the odd-parity order: its pole samples (south, plus the north one signed for MWSS)
+    // reach the rings through vs; adj: the rings reach its poles (sums of vs g)
+    const double *vs = wq + 2 * (size_t)N;
+    const bool hasO = par < 0.0 ? has0 : has1;
+    const double *FO = par < 0.0 ? F0 : F1;
+    const double sgN = (L & 1) ? -1.0 : 1.0;                 // vs of the north pole: (-1)^L vs
+    double2 gpo = make_double2(0.0, 0.0);
+    if (hasO) {
+        gpo = *reinterpret_cast<const double2 *>(FO + (size_t)(L - 1) * 4);
+        if (ss) {
+            const double2 gn = *reinterpret_cast<const double2 *>(FO + (size_t)L * 4);
+            gpo = make_double2(fma(sgN, gn.x, gpo.x), fma(sgN, gn.y, gpo.y));
+        }
+    }
+    {
         // torus samples
-        double2 acc = make_double2(0.0, 0.0);                // adj: sum_t (-1)^t w'_theta g
+        double2 acc = make_double2(0.0, 0.0);                // adj: sum_t (-1)^t w'_theta z
         for (int t = tid; t < N; t += T) {
-            bool mir;
-            const int r = torus_ring(t, L, N, ss, &mir);
-            const double *src = F + ((size_t)m * hstride + r) * 4 + 2 * side;
-            double2 g = make_double2(src[0], src[1]);
-            if (mir) { g.x *= par; g.y *= par; }
+            const double2 g = sample(t);
             buf[t] = g;
             if (ss && adj) {
                 const double sw = (t & 1) ? -wq[t] : wq[t];
@@ -591,8 +638,26 @@ __global__ __launch_bounds__(1024) void k_mw_filter(int L, int ss, int hstride, 
             if (tid == 0) {
                 double2 tot = make_double2(0.0, 0.0);
                 for (int w = 0; w < (T + 63) / 64; ++w) tot = cadd(tot, wpart[w]);
-                nyq = make_double2(tot.x / N, tot.y / N);   // Nyquist component of g w'_theta
+                nyq = make_double2(tot.x / N, tot.y / N);   // Nyquist component of z w'_theta
             }
+        }
+        double2 po = make_double2(0.0, 0.0);                // adj: the odd order's pole value
+        if (adj && hasO) {                                  // uniform over the workgroup
+            for (int r = tid; r < L - 1; r += T) {
+                const double2 g = *reinterpret_cast<const double2 *>(FO + (size_t)r * 4);
+                const double v = vs[ss ? r + 1 : r];
+                po.x = fma(v, g.x, po.x);
+                po.y = fma(v, g.y, po.y);
+            }
+            for (int o = 32; o > 0; o >>= 1) {
+                po.x += __shfl_xor(po.x, o, 64);
+                po.y += __shfl_xor(po.y, o, 64);
+            }
+            __syncthreads();                                // wpart is free again
+            if ((tid & 63) == 0) wpart[tid >> 6] = po;
+            __syncthreads();
+            po = make_double2(0.0, 0.0);
+            for (int w = 0; w < (T + 63) / 64; ++w) po = cadd(po, wpart[w]);
         }
         // the midpoint samples S g times the weights w'', moved back: S^{-1} (w'' S g).
         // DFT form: four engine passes (forward, shift, inverse: midpoints; weights;
@@ -624,20 +689,16 @@ __global__ __launch_bounds__(1024) void k_mw_filter(int L, int ss, int hstride, 
             }
             __syncthreads();
         }
-        for (int t = tid; t < N; t += T) {          // + g w'_theta (g re-read: F is rewritten only below)
-            bool mir;
-            const int r = torus_ring(t, L, N, ss, &mir);
-            const double *src = F + ((size_t)m * hstride + r) * 4 + 2 * side;
-            double2 g = make_double2(src[0], src[1]);
-            if (mir) { g.x *= par; g.y *= par; }
+        for (int t = tid; t < N; t += T) {          // + z w'_theta (z re-read: F is rewritten only below)
+            double2 g = sample(t);
             const double wv = wq[t];
             const double sg = (t & 1) ? -1.0 : 1.0;
-            if (ss && !adj) {                                // P g, then times w'
+            if (ss && !adj) {                                // P z, then times w'
                 g.x -= sg * nyq.x;
                 g.y -= sg * nyq.y;
             }
             double2 gw = make_double2(g.x * wv, g.y * wv);
-            if (ss && adj) {                                 // P (g w')
+            if (ss && adj) {                                 // P (z w')
                 gw.x -= sg * nyq.x;
                 gw.y -= sg * nyq.y;
             }
@@ -645,28 +706,27 @@ __global__ __launch_bounds__(1024) void k_mw_filter(int L, int ss, int hstride, 
         }
         __syncthreads();
         const double sc = 2.0 * M_PI / (double)N;
-        const int hidx = side == 0 ? (L - 1) + m : (L - 1) - m;
         for (int t = tid; t < (ss ? L + 1 : L); t += T) {
-            double2 h = buf[t];
-            const bool pole = ss ? (t == 0 || t == L) : (t == L - 1);
-            if (!pole) {
+            const double2 h = buf[t];
+            if (!(ss ? (t == 0 || t == L) : (t == L - 1))) {
                 const double2 hr = buf[ss ? N - t : N - 1 - t];
-                h.x += par * hr.x;
-                h.y += par * hr.y;
-            }
-            h.x *= sc;
-            h.y *= sc;
-            if (!pole) {
-                double *dst = F + ((size_t)m * hstride + (ss ? t - 1 : t)) * 4 + 2 * side;
-                dst[0] = h.x;
-                dst[1] = h.y;
-            } else if (ss && t == 0) {
-                hpoleN[hidx] = h;
+                const size_t o = (size_t)(ss ? t - 1 : t) * 4;
+                const double v = vs[t];
+                const double v0 = par < 0.0 ? v : 0.0, v1 = par < 0.0 ? 0.0 : v;
+                if (has0)
+                    *reinterpret_cast<double2 *>(const_cast<double *>(F0) + o) =
+                        make_double2(fma(v0, gpo.x, sc * fma(par, hr.x, h.x)), fma(v0, gpo.y, sc * fma(par, hr.y, h.y)));
+                if (has1)
+                    *reinterpret_cast<double2 *>(const_cast<double *>(F1) + o) =
+                        make_double2(fma(v1, gpo.x, sc * fma(-par, hr.x, h.x)), fma(v1, gpo.y, sc * fma(-par, hr.y, h.y)));
             } else {
-                hpole[hidx] = h;
+                double2 *hp = ss && t == 0 ? hpoleN : hpole;
+                const double so = ss && t == 0 ? sgN : 1.0;
+                const double2 v = make_double2(sc * h.x, sc * h.y), z = make_double2(so * po.x, so * po.y);
+                if (has0) hp[side == 0 ? (L - 1) + m0 : (L - 1) - m0] = par > 0.0 ? v : z;
+                if (has1) hp[side == 0 ? (L - 1) + m1 : (L - 1) - m1] = par < 0.0 ? v : z;
             }
         }
-        __syncthreads();
     }
 }
 
@@ -1182,7 +1242,8 @@ hipError_t launch_mw_filter(hipStream_t st, int nthreads, size_t lds, int L, int
     if (fconv && ss) return hipErrorInvalidValue;               // the convolution form is MW's
     return over_items(nitem, fscr != nullptr, [&](int i, int ny) {
         it.item0 = i;
-        hipLaunchKernelGGL(k_mw_filter, dim3(L, ny), dim3(nthreads), lds, st, L, ss, hstride, it, sF, sh, fN, wq, ph, F,
+        const int np = (L + 1) / 2;                      // pairs of orders, and their two sides
+        hipLaunchKernelGGL(k_mw_filter, dim3(half ? np : (np + 7) / 8 * 16, ny), dim3(nthreads), lds, st, L, ss, hstride, it, sF, sh, fN, wq, ph, F,
                            hpole, hpoleN, fscr, half, adj, fconv);
     });
 }
