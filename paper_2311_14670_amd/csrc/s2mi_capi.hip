@@ -1100,7 +1100,7 @@ int run_forward_dstage(s2_plan_t P, bool poles, double2 *flm, int nm, const doub
 {
     const int L = P->L;
     FwdArgs a{};
-    a.L = L; a.nxp = std::max(P->nxp, 1); a.nreg = P->nsw; a.hstride = P->fwd_pair ? P->pstride : P->hstride;
+    a.L = L; a.nxp = std::max(P->nxp, 1); a.nx = P->nx; a.nreg = P->nsw; a.hstride = P->fwd_pair ? P->pstride : P->hstride;
     a.nrun = (int)P->runs.size(); a.half = half ? 1 : 0;
     a.rb = P->fwd.tiles; a.nk = P->fwd.nk; a.nslot = P->fwd.nslot; a.rp = P->fwd.rp;
     a.merge = merge_slots(P->fwd, (long long)nm * a.nrun, P->ncu);

@@ -34,6 +34,7 @@ struct InvArgs {
 
 struct FwdArgs {
     int L, nxp;               // band-limit, orders of the continuation sums
+    int nx;                   // negative orders held in the tables
     int nreg, hstride;        // rings swept, ring stride of the spectra rows
     int nrun, half;
     int rb, nk;               // ring blocks, four-ring steps per wave

@@ -12,8 +12,8 @@ constexpr int SG = 8;     // degrees (or rings) per register chunk
 // Renormalisation period of the recursion (orders; a power of two).  The state grows
 // by at most |kappa lambda| + 1 < 2^20 per order for L <= 4096 (|lambda| sin theta <=
 // |n| + m + 1 with kappa (|n| + m + 1) <= 181 over every degree below 4096, and
-// sin theta >= 1.9e-4 on every grid's swept rings), so between passes a pair scaled
-// near 2^-RT stays below 2^-275: far from overflow, and its unscaled contribution
+// sin theta >= 1.9e-4 on every grid's swept rings), so between passes a pair left at or
+// below 2^-500 stays below 2^-180: far from overflow, and its unscaled contribution
 // negligible (see renorm).
 constexpr int RN = 16;
 
@@ -50,33 +50,35 @@ __device__ __forceinline__ bool xcd_tile(int gx, int gy, int gz, int &bx, int &b
 }
 
 // State of one recursion slot: the pair (e, ep) and an int E, the slot's values
-// being e 2^E and ep 2^E.  Realised (E = 0): e is the value itself.  Not yet realised
-// (value below 2^-RT): E < 0 and the pair is kept scaled near 2^-RT, so a sweep can use
-// e unscaled in its contraction -- such a slot then contributes at most about
-// 2^(325 - RT) times its record (the growth between two passes of the sweeps is below
-// 2^320) instead of its exact (equally negligible) value, and no exponent scaling is
-// needed per step.  A slot that has not started holds zeros
-// with E = 0.
+// being e 2^E and ep 2^E.  Realised (E = 0): e is the value itself.  Not yet realised:
+// E < 0 and the pair is kept scaled to at most 2^-500 at each pass, so a sweep can use
+// e unscaled in its contraction -- such a slot then contributes at most 2^-180 times its
+// record (the growth between two passes of the sweeps is below 2^320) instead of its
+// exact (equally negligible) value, and no exponent scaling is needed per step.  A slot
+// that has not started holds zeros with E = 0.
 
 // Exact power-of-two renormalisation of the pair (e, ep) carrying exponent E
-// (running renormalisation, Sec. 3.4): a pair whose value is below 2^-RT is rescaled
-// so its larger entry is in [2^-RT, 2^(4-RT)), E absorbing the change; a pair whose
-// value is at least 2^-RT is realised (E = 0, values unscaled from then on).  Every
+// (running renormalisation, Sec. 3.4).  Nothing is due while the pair is below 2^-500
+// (its value then is below that too).  Above, a pair whose value is below 2^-RT is
+// rescaled so its larger entry is in [2^-RT, 2^(4-RT)), E absorbing the change, and one
+// whose value is at least 2^-RT is realised (E = 0, unscaled from then on).  Every
 // scaling is by a power of two, so the values themselves never change; every E is a
 // multiple of 4 (the sweeps store E / 4 in 16 bits: log2 of a start value is at least
 // 2 l log2 sin(theta / 2) > -2^17 for L <= 4096 on every grid's swept rings).
 __device__ __forceinline__ void renorm(double &e, double &ep, int &E)
 {
     const double mx = fmax(fabs(e), fabs(ep));
-    // floor(log2 mx) = frexp exponent - 1 (mx is finite: the state grows by a bounded
-    // factor between passes); a not-yet-started (zero) state keeps E
-    const int k = mx > 0.0 ? __builtin_amdgcn_frexp_exp(mx) - 1 : 0;
-    const bool real = (E + k >= -RT);                   // the value's exponent is E + k
-    const int k4 = k & ~3;
-    const int sh = real ? E : -k4 - RT;
-    e = ldexp(e, sh);
-    ep = ldexp(ep, sh);
-    E = real ? 0 : E + k4 + RT;                          // < 0: E + k < -RT
+    if (E < 0 && mx > 0x1p-500) {
+        // floor(log2 mx) = frexp exponent - 1 (mx is finite: the state grows by a bounded
+        // factor between passes)
+        const int k = __builtin_amdgcn_frexp_exp(mx) - 1;
+        const bool real = (E + k >= -RT);               // the value's exponent is E + k
+        const int k4 = k & ~3;
+        const int sh = real ? E : -k4 - RT;
+        e = ldexp(e, sh);
+        ep = ldexp(ep, sh);
+        E = real ? 0 : E + k4 + RT;                      // < 0: E + k < -RT
+    }
 }
 
 // Stable-direction switch for runs with n != 0.  At a ring the descending

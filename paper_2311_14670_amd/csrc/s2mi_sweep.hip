@@ -32,10 +32,19 @@
 // loads, and one wave holds 4 x 16 rows, so the sums that cross the waves of a
 // workgroup are 1/32 of the d values.
 //
+// A third of the vector instructions were not FP64 at first: addresses, the sums over
+// the waves, the renormalisation.  So the operands and kappa are buffer loads and the
+// partial sums buffer stores at scalar offsets (the lane's part of an address is fixed
+// for a piece), one half of the waves reduces an iteration's orders after the first of
+// the next iteration and the other half after the third (the matrix unit of a SIMD is
+// left to the other wave meanwhile), and only values beyond 2^-500 lose exponent.
+//
 // Measured on MI355X (one map, spin 0, MW L = 2048): inverse sweep 2.58 -> 1.65 ms,
-// forward 2.70 -> 1.93 ms against the vector form with scalar record loads; HEALPix nside
-// 1024, L = 2048, real signal 2.68 -> 2.14 and 2.73 -> 1.98 ms; L = 512, 16 maps in one
-// launch instead of 16 in turn 2.95 -> 0.89 and 3.50 -> 0.81 ms.
+// forward 2.70 -> 1.93 ms against the vector form with scalar record loads, and 1.56
+// and 1.75 ms with scalar offsets and the two halves apart; HEALPix nside 1024, L =
+// 2048, real signal 2.68 -> 1.82 and 2.73 -> 2.00 ms; MW L = 4096 19.3 -> 10.5 and
+// 19.0 -> 12.3 ms; L = 512, 16 maps in one launch instead of 16 in turn 2.95 -> 0.88
+// and 3.50 -> 0.74 ms.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -257,12 +266,30 @@ struct InvLane {
     unsigned okap, ocoef;       // byte offsets of the lane's values in a record row
 };
 
-template <int RS>
-__device__ __forceinline__ void inv_load(const double *Cq, int m, const InvLane &ln, double2 &kq, double2 &cq)
+// (buffer loads: the row is a scalar offset, so a load needs no vector address arithmetic)
+typedef int v4i __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ double2 buf_load2(__amdgpu_buffer_rsrc_t rs, unsigned lane_off, unsigned row_off)
 {
-    const char *row = reinterpret_cast<const char *>(Cq + (ptrdiff_t)m * RS);
-    kq = *reinterpret_cast<const double2 *>(row + ln.okap);
-    cq = *reinterpret_cast<const double2 *>(row + ln.ocoef);
+    return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(rs, lane_off, row_off, 0));
+}
+
+__device__ __forceinline__ double buf_load1(__amdgpu_buffer_rsrc_t rs, unsigned lane_off, unsigned row_off)
+{
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, lane_off, row_off, 0));
+}
+__device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t rs, unsigned lane_off, unsigned row_off, double v)
+{
+    typedef unsigned v2u __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, v), rs, lane_off, row_off, 0);
+}
+
+template <int RS>
+__device__ __forceinline__ void inv_load(__amdgpu_buffer_rsrc_t rs, unsigned Cq, int m, const InvLane &ln, double2 &kq,
+                                         double2 &cq)
+{
+    const unsigned row = Cq + (unsigned)(m * (RS * 8));
+    kq = buf_load2(rs, ln.okap, row);
+    cq = buf_load2(rs, ln.ocoef, row);
 }
 
 // One order of the started chunks (bits of act): recursion, products, and the load of
@@ -272,7 +299,8 @@ __device__ __forceinline__ void inv_load(const double *Cq, int m, const InvLane 
 // that the compiler can count the loads in flight: behind a branch it would wait for all
 // of them at every chunk.)
 template <int PAR, bool ONE, bool PAIR>
-__device__ __forceinline__ void inv_step(int m, uint32_t act, int nx, const int (&cb)[4], const double *const (&Cq)[4], const InvLane &ln,
+__device__ __forceinline__ void inv_step(int m, uint32_t act, int nx, const int (&cb)[4], __amdgpu_buffer_rsrc_t rsrc,
+                                         const unsigned (&Cq)[4], const InvLane &ln,
                                          double (&X)[4][2][4], double (&Y)[4][2][4], double2 (&kq)[4],
                                          double2 (&cq)[4], double *rb)
 {
@@ -310,11 +338,27 @@ __device__ __forceinline__ void inv_step(int m, uint32_t act, int nx, const int 
             }
         }
         }
-        inv_load<RS>(Cq[c], max(min(m - 1, cb[c] + 7), -nx), ln, kq[c], cq[c]);
+        inv_load<RS>(rsrc, Cq[c], max(min(m - 1, cb[c] + 7), -nx), ln, kq[c], cq[c]);
         __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
     for (int i = 0; i < NA; ++i) rb[i * 64] = acc[i];
+}
+
+// One buffer descriptor for the main sums of both sides: from the lower of the two
+// slices (the same one, one of them null, or two of an SO(3) run) to the end of the
+// higher one, a side's slice as an offset of the lane.  The descriptor has to be the
+// same in every lane.  base null: beyond the 4 GiB of a descriptor, stores by pointer.
+struct OutSpan {
+    double *base;
+    unsigned off, bytes;
+};
+__device__ inline OutSpan out_span(double *A, double *B, int comp, size_t bytes)
+{
+    double *lo = !A ? B : !B || A <= B ? A : B;
+    const ptrdiff_t da = A ? (A - lo) * 8 : 0, db = B ? (B - lo) * 8 : 0;
+    const size_t all = (size_t)(da > db ? da : db) + bytes;
+    return {all < (1ull << 32) ? lo : nullptr, (unsigned)(comp < 2 ? da : db), (unsigned)all};
 }
 
 template <bool ONE, bool PAIR>
@@ -339,7 +383,6 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_inv(InvArgs a, const do
     const SweepRun r = a.runs[ri];
     const int n = r.n, an = n < 0 ? -n : n, side = run_side(r, a.half);
     const int mend = an > 1 ? -(an - 1) : 0;             // continuation below m = 0
-    const double *C = a.C + (size_t)map * a.wsd + (size_t)ri * a.nC;
     double *PA = side != 2 ? a.P + (size_t)map * a.wsd + (size_t)r.sliceA * a.nP : nullptr;
     double *PB = side != 1 ? a.P + (size_t)map * a.wsd + (size_t)r.sliceB * a.nP : nullptr;
     InvLane ln;
@@ -366,13 +409,98 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_inv(InvArgs a, const do
         const int ms = switch_order(n, cot[rr], csc[rr]);
         msg[i] = ring_good(n, cot[rr]) ? ~ms : ms;
     }
+    // its place in an order's buffer (the wave and the second row are fixed offsets), and
+    // its byte offset in a block's partial sums for order mb - DORD + 1
+    const int r16 = row0 & 15;
+    const int rpos = (row0 >> 4) * 64 + 16 * (r16 & 3) + 4 * (r16 >> 2) + rc;
+    const OutSpan po = out_span(PA, PB, comp, (size_t)a.nreg * L * 32);
+    const unsigned ooff = ((unsigned)(ring0 + row0) * L + (DORD - 1 - rq)) * 32 + comp * 8 + po.off;
+    const unsigned moff = ((unsigned)(a.nreg - 1 - ring0 - row0) * L + (DORD - 1 - rq)) * 32 + comp * 8 + po.off;   // mirror
+    const bool reducer = row0 < 64;
     short *ex = expo + (size_t)w * 32 * 64 + lane;       // exponent of slot (c, h, g) at 64 (8 c + 4 h + g)
     double X[4][2][4], Y[4][2][4];
     double2 kq[4], cq[4];
     int cb[4];
-    const double *Cq[4];
+    unsigned Cq[4];                                      // byte offset of a chunk's row of order 0
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        a.C + (size_t)map * a.wsd + (size_t)ri * a.nC, 0, (int)(a.nC * 8), 0x00027000);
     uint32_t fast = 0;
     int it = 0, pblk = -1, pm = -1;
+    // Adds the waves' sums of the orders m1 .. m1 - DORD + 1 (buffer half `hf`) and stores
+    // them to block blk's partial sums.
+    auto reduce = [&](int blk, int hf, int m1, int mhi, int bot) {
+        if (!reducer) return;
+        const double *rb0 = red + (size_t)(hf * DORD + rq) * OB + (rpos & ~63) + ((rpos + 4 * ((m1 & 2 ? 0 : 2) * EO + rq)) & 63);
+        double s[NR], s2[NR];
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const double *rb = rb0 + i * ROWS / 16 * 64;
+            s[i] = 0.0;
+            s2[i] = 0.0;
+            if constexpr (PAIR && ONE) {                    // columns 2, 3: two doubles on
+#pragma unroll
+                for (int ww = 0; ww < SW_WAVES; ++ww) {
+                    s[i] += rb[ww * NA * 64];
+                    s2[i] += rb[ww * NA * 64 + 2];
+                }
+                s2[i] = ((m1 - rq) & 1) ? -s2[i] : s2[i];
+            } else if constexpr (PAIR) {
+                double se = 0.0, so = 0.0;
+#pragma unroll
+                for (int ww = 0; ww < SW_WAVES; ++ww) {
+                    se += rb[ww * NA * 64];
+                    so += rb[(ww * NA + 4) * 64];
+                }
+                s[i] = se + so;                             // ring ring0 + row
+                s2[i] = ((m1 - rq) & 1) ? so - se : se - so;   // its mirror
+            } else {
+#pragma unroll
+                for (int ww = 0; ww < SW_WAVES; ++ww) s[i] += rb[ww * NA * 64];
+            }
+        }
+        const size_t bo = (size_t)blk * a.nreg * L * 4;
+        const int m3 = m1 - (DORD - 1);
+        if (po.base && m1 <= mhi && m3 >= bot && m3 >= (an > 1 ? an : 1)) {
+            // main orders: every ring's own sides, at scalar offsets (no vector addresses)
+            const __amdgpu_buffer_rsrc_t rs =
+                __builtin_amdgcn_make_buffer_rsrc(po.base + bo, 0, (int)po.bytes, 0x00027000);
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                if (ring0 + row0 + ROWS * i >= a.nsw) continue;
+                buf_store(rs, ooff, m3 * 32 + i * ROWS * L * 32, s[i]);
+                if (PAIR && a.nreg - 1 != 2 * (ring0 + row0 + ROWS * i))
+                    buf_store(rs, moff - i * ROWS * L * 32, m3 * 32, s2[i]);
+            }
+            return;
+        }
+        const int m = m1 - rq;
+        if (m > mhi || m < bot) return;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            // Orders below the ring's switch order ms come from the run that is
+            // stable there (n cos(theta) < 0): it writes its own sides at m >= 0
+            // and, from its continuation to m > -ms, the A slice at order m < 0
+            // (components 2,3 at |m|) and the B slice at order -m >= 0 (components
+            // 0,1 at |m|).  The other run writes nothing below ms.
+            const bool good = msg[i] < 0;
+            const int ms = good ? ~msg[i] : msg[i];
+            double *dst = nullptr;
+            int mo = m, co = comp;
+            const bool ext = good && m <= 0 && -m < ms;
+            if (comp < 2) {
+                if (m >= 0 && (good || m >= ms)) dst = PA;
+                else if (m < 0 && ext) { dst = PA; mo = -m; co = comp + 2; }
+            } else {
+                if (m > 0 && (good || m >= ms)) dst = PB;
+                else if (ext) { dst = PB; mo = -m; co = comp - 2; }
+            }
+            const int rr = ring0 + row0 + ROWS * i;
+            if (dst && rr < a.nsw) {
+                dst[bo + ((size_t)rr * L + mo) * 4 + co] = s[i];
+                if (PAIR && a.nreg - 1 - rr != rr) dst[bo + ((size_t)(a.nreg - 1 - rr) * L + mo) * 4 + co] = s2[i];
+            }
+        }
+    };
     const int e1 = a.first[min((t + 1) * a.merge, a.nslot)];
 #pragma unroll 1
     for (int e = a.first[t * a.merge]; e < e1; ++e) {
@@ -388,7 +516,7 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_inv(InvArgs a, const do
                 const int j = c - (4 - nv), q = q0 + w + 8 * j;
                 const bool ok = j >= 0;
                 cb[c] = ok ? 8 * q : -(1 << 20);
-                Cq[c] = C + rec_row(ok ? q : 0, 0, nx) * RS;
+                Cq[c] = (unsigned)rec_row(ok ? q : 0, 0, nx) * (RS * 8);
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -405,7 +533,7 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_inv(InvArgs a, const do
                         Y[c][h][g] = prev;                // order mhi + 1, Y receives mhi
                         ex[64 * (8 * c + 4 * h + g)] = (short)((int)E >> 2);
                     }
-                inv_load<RS>(Cq[c], max(min(mhi | 3, cb[c] + 7), -nx), ln, kq[c], cq[c]);
+                inv_load<RS>(rsrc, Cq[c], max(min(mhi | 3, cb[c] + 7), -nx), ln, kq[c], cq[c]);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -418,7 +546,7 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_inv(InvArgs a, const do
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 if (cb[c] != (mb & ~7)) continue;
-                if (mb & 4) inv_load<RS>(Cq[c], mb, ln, kq[c], cq[c]);
+                if (mb & 4) inv_load<RS>(rsrc, Cq[c], mb, ln, kq[c], cq[c]);
                 fast &= ~(1u << c);
                 const int l0 = cb[c] + 2 * ln.ks;
                 const double sgn = (ln.ks & 1) ? -1.0 : 1.0;
@@ -444,71 +572,25 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_inv(InvArgs a, const do
                 constexpr int q = decltype(Q)::value;
                 double *wb = red + (size_t)(EO ? (it & 1) * 2 + (q & 1) : (it & 1) * 4 + q) * OB + w * NA * 64 +
                              ((lane + 4 * q) & 63);
-                inv_step<q & 1, ONE, PAIR>(mb - q, act, nx, cb, Cq, ln, X, Y, kq, cq, wb);
+                inv_step<q & 1, ONE, PAIR>(mb - q, act, nx, cb, rsrc, Cq, ln, X, Y, kq, cq, wb);
             };
-            auto reduce = [&](int q0) {                  // orders mb - q0 .. mb - q0 - DORD + 1
-                __syncthreads();
-                const int m = mb - q0 - rq;
-                if (m > mhi || m < bot || row0 >= 64) return;
-                const double *ib = red + (size_t)((it & 1) * DORD + rq) * OB;
-#pragma unroll
-                for (int i = 0; i < NR; ++i) {
-                    const int row = row0 + ROWS * i, r16 = row & 15;
-                    const double *rb = ib + (row >> 4) * 64 + ((16 * (r16 & 3) + 4 * (r16 >> 2) + rc + 4 * (q0 + rq)) & 63);
-                    double s = 0.0, s2 = 0.0;
-                    if constexpr (PAIR && ONE) {            // columns 2, 3: two doubles on
-#pragma unroll
-                        for (int ww = 0; ww < SW_WAVES; ++ww) {
-                            s += rb[ww * NA * 64];
-                            s2 += rb[ww * NA * 64 + 2];
-                        }
-                        s2 = (m & 1) ? -s2 : s2;
-                    } else if constexpr (PAIR) {
-                        double se = 0.0, so = 0.0;
-#pragma unroll
-                        for (int ww = 0; ww < SW_WAVES; ++ww) {
-                            se += rb[ww * NA * 64];
-                            so += rb[(ww * NA + 4) * 64];
-                        }
-                        s = se + so;                        // ring ring0 + row
-                        s2 = (m & 1) ? so - se : se - so;   // its mirror
-                    } else {
-#pragma unroll
-                        for (int ww = 0; ww < SW_WAVES; ++ww) s += rb[ww * NA * 64];
-                    }
-                    // Orders below the ring's switch order ms come from the run that is
-                    // stable there (n cos(theta) < 0): it writes its own sides at m >= 0
-                    // and, from its continuation to m > -ms, the A slice at order m < 0
-                    // (components 2,3 at |m|) and the B slice at order -m >= 0 (components
-                    // 0,1 at |m|).  The other run writes nothing below ms.
-                    const bool good = msg[i] < 0;
-                    const int ms = good ? ~msg[i] : msg[i];
-                    double *dst = nullptr;
-                    int mo = m, co = comp;
-                    const bool ext = good && m <= 0 && -m < ms;
-                    if (comp < 2) {
-                        if (m >= 0 && (good || m >= ms)) dst = PA;
-                        else if (m < 0 && ext) { dst = PA; mo = -m; co = comp + 2; }
-                    } else {
-                        if (m > 0 && (good || m >= ms)) dst = PB;
-                        else if (ext) { dst = PB; mo = -m; co = comp - 2; }
-                    }
-                    const int rr = ring0 + row;
-                    if (dst && rr < a.nsw) {
-                        dst[(((size_t)blk * a.nreg + rr) * L + mo) * 4 + co] = s;
-                        if (PAIR && a.nreg - 1 - rr != rr)
-                            dst[(((size_t)blk * a.nreg + (a.nreg - 1 - rr)) * L + mo) * 4 + co] = s2;
-                    }
-                }
-            };
+            // The sums of the last iteration (EO: half iteration) are added in this one, by
+            // half of the waves after its first order and by the others, which share their
+            // SIMDs, after its third (EO: second): while one wave of a SIMD adds, the other
+            // has products to issue.  After the next barrier that half is free again.
             step(std::integral_constant<int, 0>());
+            if (w < SW_WAVES / 2 && mb + DORD <= (mhi | 3)) reduce(blk, (it & 1) ^ 1, mb + DORD, mhi, bot);
             step(std::integral_constant<int, 1>());
             if constexpr (EO) {
-                reduce(0);
+                if (w >= SW_WAVES / 2 && mb + DORD <= (mhi | 3)) reduce(blk, (it & 1) ^ 1, mb + DORD, mhi, bot);
+                __syncthreads();
                 ++it;
             }
             step(std::integral_constant<int, 2>());
+            if (EO ? w < SW_WAVES / 2 : w >= SW_WAVES / 2 && mb + DORD <= (mhi | 3))
+                reduce(blk, (it & 1) ^ 1, EO ? mb : mb + DORD, mhi, bot);
             step(std::integral_constant<int, 3>());
+            if (EO && w >= SW_WAVES / 2) reduce(blk, (it & 1) ^ 1, mb, mhi, bot);
             // renormalisation every RN orders of the started chunks not yet realised
             if ((m3 & (RN - 1)) == 0) {
 #pragma unroll
@@ -528,9 +610,11 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_inv(InvArgs a, const do
                     if (__all(z) && m3 <= cb[c]) fast |= 1u << c;
                 }
             }
-            reduce(EO ? 2 : 0);
+            __syncthreads();
             ++it;
         }
+        // the last iteration's sums (the next piece writes the other half first)
+        reduce(blk, (it & 1) ^ 1, ((bot + 4096) & ~3) - 4096 + DORD - 1, mhi, bot);
     }
 }
 
@@ -564,14 +648,14 @@ __device__ __forceinline__ const double *fwd_row(int m, int an, int hstride, int
 // One order.  hrow, kapn: the next order's rows.
 template <int PAR>
 __device__ __forceinline__ void fwd_step(int m, int nk, const double (&ct)[FWD_KS], const double (&ncs)[FWD_KS],
-                                         const double *__restrict__ kapn, const int (&lc)[4],
+                                         __amdgpu_buffer_rsrc_t krs, unsigned krow, const unsigned (&lc)[4],
                                          const double *__restrict__ hrow, double (&X)[FWD_KS][4], double (&Y)[FWD_KS][4],
                                          double (&kp)[4], double (&hq)[FWD_KS], double *rb)
 {
     const double mm = -(double)(m + 1);
     double kn[4];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) kn[g] = kapn[lc[g]];
+    for (int g = 0; g < 4; ++g) kn[g] = buf_load1(krs, lc[g], krow);
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int s = 0; s < FWD_KS; ++s) {
@@ -648,19 +732,73 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_fwd(FwdArgs a, const do
         ct[s] = ok ? cot[rr] : 0.0;
         ncs[s] = ok ? (double)n * csc[rr] : 0.0;
     }
+    const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<double *>(kap - (ptrdiff_t)a.nx * L), 0, (int)((unsigned)(L + a.nx) * L * 8), 0x00027000);
     constexpr int NC = ONE ? 2 : 4;
     const int tid = threadIdx.x;
     const int rc = tid & (NC - 1), rq = (tid / NC) & (DORD - 1), row0 = tid / (NC * DORD);
     constexpr int ROWS = 64 * SW_WAVES / (NC * DORD);    // 32 or 64
     constexpr int NR = 64 / ROWS;
     const int comp = rc + (ONE && side == 2 ? 2 : 0);
+    constexpr int lsh = PAIRF ? 1 : 0;                   // log2 of a group's degree stride
+    const int r16 = row0 & 15;
+    const int rpos = (row0 >> 4) * 64 + ((16 * (r16 & 3) + 4 * (r16 >> 2) + rc + 4 * rq) & 63);
+    const OutSpan qo = out_span(QA, QB, comp, (size_t)L * L * 32);
+    const unsigned ooff = ((unsigned)(row0 << lsh) * L + (DORD - 1 - rq)) * 32 + comp * 8 + qo.off;
+    // Adds the waves' sums of the orders m1 .. m1 - 3 of group lmin (buffer half `hf`)
+    // and stores them to the block's partial sums.
+    auto reduce = [&](int lmin, int hf, int m1, int mhi, int bot) {
+        const double *rb0 = red + (size_t)(hf * DORD + rq) * OB + rpos;
+        double s[NR];
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            s[i] = 0.0;
+#pragma unroll
+            for (int ww = 0; ww < SW_WAVES; ++ww) s[i] += rb0[ww * 256 + i * ROWS / 16 * 64];
+        }
+        const size_t bo = (size_t)blk * L * L * 4;
+        const int m3 = m1 - (DORD - 1);
+        if (qo.base && m1 <= mhi && m1 <= lmin && m3 >= bot && m3 >= (an > 1 ? an : 1)) {
+            // main orders below the group's degrees, at scalar offsets
+            const __amdgpu_buffer_rsrc_t rs =
+                __builtin_amdgcn_make_buffer_rsrc(qo.base + bo, 0, (int)qo.bytes, 0x00027000);
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                if (lmin + ((row0 + ROWS * i) << lsh) >= L) continue;
+                buf_store(rs, ooff, (unsigned)((lmin + ((ROWS * i) << lsh)) * L + m3) * 32, s[i]);
+            }
+            return;
+        }
+        const int m = m1 - rq;
+        if (m > mhi || m < bot) return;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const int lo = lmin + ((row0 + ROWS * i) << lsh);
+            if (lo >= L || lo < m) continue;
+            const int am = m < 0 ? -m : m;
+            // continuation orders: the A slice at order m < 0 (the sign cancels the
+            // one the finish applies there) and the B slice at order -m >= 0,
+            // d^l_{-m,-n} = (-1)^{m-n} d^l_{m,n}
+            const double sx = ((am + n) & 1) ? -s[i] : s[i];
+            if (comp < 2) {
+                if (m >= 0) {
+                    if (QA) QA[bo + ((size_t)lo * L + m) * 4 + comp] = s[i];
+                } else if (QxA) {
+                    QxA[(((size_t)blk * L + lo) * a.nxp + am) * 4 + comp + 2] = sx;
+                }
+            } else if (m > 0) {
+                if (QB) QB[bo + ((size_t)lo * L + m) * 4 + comp] = s[i];
+            } else if (an > 0 && QxB) {
+                QxB[(((size_t)blk * L + lo) * a.nxp + am) * 4 + comp - 2] = sx;
+            }
+        }
+    };
     short *ex = expo + (size_t)w * 32 * 64 + lane;       // exponent of slot (s, g) at 64 (4 s + g)
     double X[FWD_KS][4], Y[FWD_KS][4];
     double hq[FWD_KS], kp[4];
-    int lc[4];                                           // the lane's degrees (clamped into the tables)
+    unsigned lc[4];                                      // byte offsets of the lane's degrees (clamped into the table)
     uint32_t fast = 0;
     int it = 0, pg = -1, pm = -1, lmin = 0;
-    constexpr int lsh = PAIRF ? 1 : 0;                   // log2 of a group's degree stride
     // operand row of order m (pair: sums or differences by the parity of m + group)
     auto row_of = [&](int m, int G) -> const double * {
         if constexpr (PAIRF) {
@@ -678,7 +816,7 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_fwd(FwdArgs a, const do
         if (G != pg || mhi != pm) {                      // not a continuation of the last piece
             lmin = PAIRF ? 128 * (G >> 1) + (G & 1) : 64 * G;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) lc[g] = min(lmin + ((16 * g + i16) << lsh), L - 1);
+            for (int g = 0; g < 4; ++g) lc[g] = 8 * min(lmin + ((16 * g + i16) << lsh), L - 1);
             fast = 0;
             const double *h = row_of(min(mhi | 3, L - 1), G);
 #pragma unroll
@@ -701,7 +839,7 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_fwd(FwdArgs a, const do
                 __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
-            for (int g = 0; g < 4; ++g) kp[g] = kap[(ptrdiff_t)min(mhi | 3, L - 1) * L + lc[g]];
+            for (int g = 0; g < 4; ++g) kp[g] = buf_load1(krs, lc[g], (unsigned)((min(mhi | 3, L - 1) + a.nx) * L) * 8);
         }
         pg = G;
         pm = bot - 1;
@@ -733,10 +871,17 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_fwd(FwdArgs a, const do
 #define S2_FWD_STEP(Q)                                                                                                \
     {                                                                                                                 \
         const int mn = max(min(mb - (Q) - 1, L - 1), mend);                                                           \
-        fwd_step<(Q) & 1>(mb - (Q), nk, ct, ncs, kap + (ptrdiff_t)mn * L, lc, row_of(mn, G), X, Y, kp, hq,      \
+        fwd_step<(Q) & 1>(mb - (Q), nk, ct, ncs, krs, (unsigned)((mn + a.nx) * L) * 8, lc, row_of(mn, G), X, Y, \
+                          kp, hq,                                                                                     \
                                 wb + (Q) * OB + ((lane + 4 * (Q)) & 63));                                             \
     }
-            S2_FWD_STEP(0) S2_FWD_STEP(1) S2_FWD_STEP(2) S2_FWD_STEP(3)
+            // (the last iteration's sums are added in this one, in turn by the two waves of
+            // a SIMD: see the inverse)
+            S2_FWD_STEP(0)
+            if (w < SW_WAVES / 2 && mb + 4 <= (mhi | 3)) reduce(lmin, (it & 1) ^ 1, mb + 4, mhi, bot);
+            S2_FWD_STEP(1) S2_FWD_STEP(2)
+            if (w >= SW_WAVES / 2 && mb + 4 <= (mhi | 3)) reduce(lmin, (it & 1) ^ 1, mb + 4, mhi, bot);
+            S2_FWD_STEP(3)
 #undef S2_FWD_STEP
             const int ml = mb - (DORD - 1);
             if ((ml & (RN - 1)) == 0) {                   // renormalisation of the steps not yet realised
@@ -756,38 +901,9 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_fwd(FwdArgs a, const do
                 }
             }
             __syncthreads();
-            const int m = mb - rq;
-            if (m <= mhi && m >= bot) {
-                const double *ib = red + (size_t)((it & 1) * DORD + rq) * OB;
-#pragma unroll
-                for (int i = 0; i < NR; ++i) {
-                    const int row = row0 + ROWS * i, r16 = row & 15;
-                    const double *rb = ib + (row >> 4) * 64 + ((16 * (r16 & 3) + 4 * (r16 >> 2) + rc + 4 * rq) & 63);
-                    double s = 0.0;
-#pragma unroll
-                    for (int ww = 0; ww < SW_WAVES; ++ww) s += rb[ww * 256];
-                    const int lo = lmin + (row << lsh);
-                    if (lo >= L || lo < m) continue;
-                    const int am = m < 0 ? -m : m;
-                    // continuation orders: the A slice at order m < 0 (the sign cancels the
-                    // one the finish applies there) and the B slice at order -m >= 0,
-                    // d^l_{-m,-n} = (-1)^{m-n} d^l_{m,n}
-                    const double sx = ((am + n) & 1) ? -s : s;
-                    if (comp < 2) {
-                        if (m >= 0) {
-                            if (QA) QA[(((size_t)blk * L + lo) * L + m) * 4 + comp] = s;
-                        } else if (QxA) {
-                            QxA[(((size_t)blk * L + lo) * a.nxp + am) * 4 + comp + 2] = sx;
-                        }
-                    } else if (m > 0) {
-                        if (QB) QB[(((size_t)blk * L + lo) * L + m) * 4 + comp] = s;
-                    } else if (an > 0 && QxB) {
-                        QxB[(((size_t)blk * L + lo) * a.nxp + am) * 4 + comp - 2] = sx;
-                    }
-                }
-            }
             ++it;
         }
+        reduce(lmin, (it & 1) ^ 1, ((bot + 4096) & ~3) - 4096 + DORD - 1, mhi, bot);
     }
 }
 
