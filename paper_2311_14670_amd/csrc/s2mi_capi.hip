@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "../../include/s2mi.h"
+#include "s2mi_conv.h"
 #include "s2mi_internal.h"
 #include "s2mi_kernels.h"
 #include "s2mi_mfma.h"
@@ -201,12 +202,9 @@ struct s2_plan_s {
     // FFT
     std::vector<FftArgs> ffts_h;
     FftArgs *ffts = nullptr;
-    int fft_threads = 64;
-    size_t fft_lds = 0;
+    DftShape dft{64, 0, 0, 0};
     FftArgs fN{};                          // MW ring / theta-torus length 2L-1
     double *wq = nullptr, *ph = nullptr;   // MW theta filter
-    int conv_idx = -1;                     // MW, 2L - 1 not 13-smooth: the filter's two shifts as cyclic
-                                           // convolutions (FftArgs conv_idx and conv_idx + 1)
     double *ringq = nullptr;               // DH / GL: forward quadrature weight of each ring (phi rule included)
     double *groots = nullptr;              // e^{-2 pi i k/(2N-1)}
     // d-stage work assignment
@@ -571,34 +569,47 @@ static int plan_create_impl(s2_plan_t *out, int L, int spin, int N, s2_sampling_
             P->ffts_h.push_back(f);
             maxlen = std::max(maxlen, f.len);
         }
+        // rings of one length that needs Bluestein's identity: the register engine
+        if (lens.size() == 1 && P->ffts_h[0].blue) {
+            FftArgs &f = P->ffts_h[0];
+            f.perm = 1;
+            P->dft.conv = (f.split ? 2 : 1) * f.len;
+            P->dft.n = f.n;
+        }
         if (sampling == S2_MW || sampling == S2_MWSS) P->fN = P->ffts_h[0];
         // MW with a ring length N = 2L - 1 that needs Bluestein's identity: the theta
         // filter's two half-step shifts are circular convolutions of length N, each run
-        // by the Bluestein driver as one cyclic convolution of the same length M (unit
-        // chirp, the shift kernel's spectrum as the filter; two FFTs of M points, or four
-        // of M/2 where the driver splits it) instead of two Bluestein DFTs
+        // as one convolution of the same length M instead of two Bluestein DFTs
         if (sampling == S2_MW && P->fN.blue) {
             const int M = P->fN.split ? 2 * P->fN.len : P->fN.len;
             stg.d.emplace_back();
-            host_shift_spectra(L, M, &stg.d.back());
+            std::vector<double> nat;
+            host_shift_spectra(L, M, &nat);
+            stg.d.back().resize(nat.size());
+            const int len = P->fN.len;
+            for (int which = 0; which < 2; ++which)
+                for (int k = 0; k < M; ++k) {
+                    const int at = P->fN.split ? (k & 1) * len + conv_index(len, k / 2) : conv_index(len, k);
+                    for (int c = 0; c < 2; ++c)
+                        stg.d.back()[2 * ((size_t)which * M + at) + c] = nat[2 * ((size_t)which * M + k) + c];
+                }
             double *cs;
             if ((rc = upload(P, &cs, stg.d.back(), st, "theta filter shift spectra"))) return bail(rc);
-            FftArgs f = P->fN;                             // same engine; its chirp is never applied
+            FftArgs f = P->fN;                             // same engine; entries 1 and 2
             f.conv = 1;
-            P->conv_idx = (int)P->ffts_h.size();
             f.bflt = cs;
             P->ffts_h.push_back(f);
             f.bflt = cs + 2 * (size_t)M;
             P->ffts_h.push_back(f);
         }
-        P->fft_threads = fft_threads_for(maxlen);
-        P->fft_lds = (size_t)maxlen * sizeof(double2);
+        P->dft.threads = fft_threads_for(maxlen);
+        P->dft.lds = (size_t)maxlen * sizeof(double2);
         if ((rc = upload(P, &P->ring_fft, rf, st, "ring_fft"))) return bail(rc);
         if ((rc = upload(P, &P->ffts, P->ffts_h, st, "fft table"))) return bail(rc);
-        PLANCHK(set_kernel_lds_limits(P->fft_lds), "LDS limits");
+        PLANCHK(set_kernel_lds_limits(P->dft), "LDS limits");
         int nblue = 0;
         for (auto &f : P->ffts_h) nblue += f.blue;
-        if (nblue) PLANCHK(launch_bluestein_filter(st, (int)P->ffts_h.size(), P->ffts, P->fft_threads, P->fft_lds), "bluestein filters");
+        if (nblue) PLANCHK(launch_bluestein_filter(st, (int)P->ffts_h.size(), P->ffts, P->dft.threads, P->dft.lds), "bluestein filters");
     }
     if (sampling == S2_MW || sampling == S2_MWSS) {
         stg.d.emplace_back(); std::vector<double> &wq = stg.d.back();
@@ -822,7 +833,7 @@ static int plan_create_impl(s2_plan_t *out, int L, int spin, int N, s2_sampling_
         }
         o *= P->group;
         bool split = false;
-        for (const FftArgs &f : P->ffts_h) split = split || (f.blue && f.split);
+        for (const FftArgs &f : P->ffts_h) split = split || (f.blue && f.split && !f.perm);
         // one FFT_SCRATCH slice per workgroup of the phi-DFT (hstride), inverse phi-DFT
         // (nring) and MW filter (L) launches of one item (items then run one by one)
         P->sz_fscr = split ? (size_t)std::max({P->hstride, P->nring, L + 16}) * FFT_SCRATCH * sizeof(double2) : 0;
@@ -965,7 +976,6 @@ int check_call(const char *fn, s2_plan_t P, const void *in, const void *out, int
 }
 
 // the theta filter's convolution form: its FFT, kernel spectra and length (none: nullptr)
-#define CONV_ARGS(P) ((P)->conv_idx >= 0 ? (P)->ffts + (P)->conv_idx : nullptr)
 
 // the workspace's split-Bluestein scratch (nullptr when no DFT of the plan needs it)
 double2 *fft_scratch(const s2_plan_s *P, char *ws)
@@ -1022,7 +1032,7 @@ int run_inverse(s2_plan_t P, const double2 *flm, double2 *maps, Strides sm, int 
     int rc = run_inverse_dstage(P, flm, sf.map, nm, wl, ws, st);
     if (rc) return rc;
     TIMED(S2_STAGE_PHI_INV);
-    HIPCHK(launch_phi_inv(st, P->fft_threads, P->fft_lds, P->nring, P->L, P->nreg, P->inv.nblk, all_slices(P),
+    HIPCHK(launch_phi_inv(st, P->dft, P->nring, P->L, P->nreg, P->inv.nblk, all_slices(P),
                           nm * P->nslice, ws_strides(P, P->szP), sf, sm, (const double *)(ws + P->off_P), P->mtop, flm,
                           wl, P->ring_nphi, P->ring_start, P->ring_shift, P->ring_fft, P->ffts, maps,
                           tight && P->sz_fscr ? (double2 *)(ws + align256(P->off_P + P->szP * P->nslice))
@@ -1037,9 +1047,9 @@ int run_theta(s2_plan_t P, int nm, char *ws, hipStream_t st, int half, int adj)
     const int L = P->L, ss = P->sampling == S2_MWSS;
     double2 *hp = (double2 *)(ws + P->off_hpole);
     double2 *hpN = ss ? hp + (size_t)P->nslice * (2 * L - 1) : nullptr;
-    HIPCHK(launch_mw_filter(st, P->fft_threads, P->fft_lds, L, ss, P->hstride, all_slices(P), nm * P->nslice,
+    HIPCHK(launch_mw_filter(st, P->dft, L, ss, P->hstride, all_slices(P), nm * P->nslice,
                             ws_strides(P, P->szF), pole_strides(P), P->ffts, P->wq, P->ph, (double *)(ws + P->off_F), hp,
-                            hpN, fft_scratch(P, ws), half, adj, CONV_ARGS(P)), "MW theta filter");
+                            hpN, fft_scratch(P, ws), half, adj), "MW theta filter");
     return S2_OK;
 }
 
@@ -1087,7 +1097,7 @@ int run_forward_adjoint_mw(s2_plan_t P, const double2 *G, double2 *maps, Strides
     int rc = run_inverse_dstage(P, G, sf.map, nm, wl, ws, st);
     if (rc || (rc = run_theta_adjoint(P, G, sf, nm, wl, ws, st, 0))) return rc;
     TIMED(S2_STAGE_PHI_INV);
-    HIPCHK(launch_phi_inv(st, P->fft_threads, P->fft_lds, P->nring, P->L, P->nring, 1, all_slices(P), nm * P->nslice,
+    HIPCHK(launch_phi_inv(st, P->dft, P->nring, P->L, P->nring, 1, all_slices(P), nm * P->nslice,
                           ws_strides(P, P->szQ), sf, sm, (const double *)(ws + P->off_Q), P->mtop1, G, wl, P->ring_nphi,
                           P->ring_start, P->ring_shift, P->ring_fft, P->ffts, maps, fft_scratch(P, ws)),
            "adjoint phi-DFT");
@@ -1157,7 +1167,7 @@ int run_forward(s2_plan_t P, const double2 *maps, Strides sm, double2 *flm, int 
     const bool mw = P->sampling == S2_MW || P->sampling == S2_MWSS;   // theta-torus samplings
     {
         TIMED(S2_STAGE_PHI_FWD);
-        HIPCHK(launch_phi_fwd(st, P->fft_threads, P->fft_lds, P->nring, P->hstride, P->L, phi_weight(P, adjoint),
+        HIPCHK(launch_phi_fwd(st, P->dft, P->nring, P->hstride, P->L, phi_weight(P, adjoint),
                               all_slices(P), nm * P->nslice, sm, ws_strides(P, P->szF), maps, P->ring_nphi,
                               P->ring_start, P->ring_shift, P->ring_fft, P->ffts, adjoint ? nullptr : P->ringq,
                               (double *)(ws + P->off_F), fft_scratch(P, ws)), "forward phi-DFT");
@@ -1178,7 +1188,7 @@ int run_inverse_real(s2_plan_t P, const double2 *flm, long long fstride, double 
     int rc = run_inverse_dstage(P, flm, fstride, nm, wl, ws, st, 1);
     if (rc) return rc;
     TIMED(S2_STAGE_PHI_INV);
-    HIPCHK(launch_phi_inv_real(st, P->fft_threads, P->fft_lds, P->npair, P->L, P->nreg, P->inv.nblk, nm, wsd(P),
+    HIPCHK(launch_phi_inv_real(st, P->dft, P->npair, P->L, P->nreg, P->inv.nblk, nm, wsd(P),
                                fstride, P->nsamp, P->ring_pairs, (const double *)(ws + P->off_P), P->mtop, flm, wl,
                                P->ring_nphi, P->ring_start, P->ring_shift, P->ring_fft, P->ffts, map,
                                fft_scratch(P, ws)), "real inverse phi-DFT");
@@ -1194,7 +1204,7 @@ int run_forward_real(s2_plan_t P, const double *map, double2 *flm, int nm, char 
     const bool mw = P->sampling == S2_MW || P->sampling == S2_MWSS;   // theta-torus samplings
     {
         TIMED(S2_STAGE_PHI_FWD);
-        HIPCHK(launch_phi_fwd_real(st, P->fft_threads, P->fft_lds, P->nring, P->hstride, P->npair, P->L,
+        HIPCHK(launch_phi_fwd_real(st, P->dft, P->nring, P->hstride, P->npair, P->L,
                                    phi_weight(P, vjp), nm, P->nsamp, wsd(P), P->ring_pairs, map, P->ring_nphi,
                                    P->ring_start, P->ring_shift, P->ring_fft, P->ffts, vjp ? nullptr : P->ringq,
                                    (double *)(ws + P->off_F), fft_scratch(P, ws)), "real forward phi-DFT");
@@ -1229,7 +1239,7 @@ int run_forward_real_adjoint(s2_plan_t P, const double2 *G, double *map, int nm,
     if ((rc = run_inverse_dstage(P, H, hs, nm, P->w_sht, ws, st, 1))) return rc;
     if ((rc = run_theta_adjoint(P, H, Strides{hs, 0}, nm, P->w_sht, ws, st, 1))) return rc;
     TIMED(S2_STAGE_PHI_INV);
-    HIPCHK(launch_phi_inv_real(st, P->fft_threads, P->fft_lds, P->npair, P->L, P->nring, 1, nm, wsd(P), hs, P->nsamp,
+    HIPCHK(launch_phi_inv_real(st, P->dft, P->npair, P->L, P->nring, 1, nm, wsd(P), hs, P->nsamp,
                                P->ring_pairs, (const double *)(ws + P->off_Q), P->mtop1, H, P->w_sht, P->ring_nphi,
                                P->ring_start, P->ring_shift, P->ring_fft, P->ffts, map, fft_scratch(P, ws)),
            "real adjoint phi-DFT");
@@ -1291,7 +1301,7 @@ int run_inverse_mfma(s2_plan_t P, const double2 *flm, int B, double2 *maps, cons
         }
     }
     TIMED(S2_STAGE_PHI_INV);
-    HIPCHK(launch_phi_inv(st, P->fft_threads, P->fft_lds, P->nring, L, P->nreg, 1, all_slices(P), B * S,
+    HIPCHK(launch_phi_inv(st, P->dft, P->nring, L, P->nreg, 1, all_slices(P), B * S,
                           Strides{(long long)(S * nP1), (long long)nP1}, coef_strides(P), map_strides(P), Pm, P->mtop1, flm,
                           wl, P->ring_nphi, P->ring_start, P->ring_shift, P->ring_fft, P->ffts, maps,
                           fft_scratch(P, ws)), "inverse phi-DFT");
@@ -1324,7 +1334,7 @@ int run_forward_mfma(s2_plan_t P, const double2 *maps, int B, double2 *flm, cons
     const Strides sF{(long long)(S * nF), (long long)nF}, sh{(long long)S * (2 * L - 1), 2 * L - 1};
     {
         TIMED(S2_STAGE_PHI_FWD);
-        HIPCHK(launch_phi_fwd(st, P->fft_threads, P->fft_lds, P->nring, P->hstride, L, phi_weight(P, adjoint),
+        HIPCHK(launch_phi_fwd(st, P->dft, P->nring, P->hstride, L, phi_weight(P, adjoint),
                               all_slices(P), B * S, map_strides(P), sF, maps, P->ring_nphi, P->ring_start, P->ring_shift,
                               P->ring_fft, P->ffts, adjoint ? nullptr : P->ringq, Fm, fft_scratch(P, ws)),
                "forward phi-DFT");
@@ -1332,8 +1342,8 @@ int run_forward_mfma(s2_plan_t P, const double2 *maps, int B, double2 *flm, cons
     if (mw) {
         TIMED(S2_STAGE_MW_THETA);
         if (!adjoint) {
-            HIPCHK(launch_mw_filter(st, P->fft_threads, P->fft_lds, L, ss, P->hstride, all_slices(P), B * S, sF, sh,
-                                    P->ffts, P->wq, P->ph, Fm, hp, hpN, fft_scratch(P, ws), 0, 0, CONV_ARGS(P)),
+            HIPCHK(launch_mw_filter(st, P->dft, L, ss, P->hstride, all_slices(P), B * S, sF, sh,
+                                    P->ffts, P->wq, P->ph, Fm, hp, hpN, fft_scratch(P, ws), 0, 0),
                    "MW theta filter");
         } else {
             HIPCHK(launch_pole_from_F(st, L, P->hstride, L - 1, all_slices(P), B * S, sF, sh, Fm, hp), "pole line");

@@ -75,18 +75,26 @@ struct Strides {
 hipError_t launch_pair_spectra(hipStream_t st, int nmap, long long wsd, int L, int nreg, int nsw, int hstride,
                                int pstride, const double *H, double *S, double *D);
 // weights wl: [slice][L]
-hipError_t launch_phi_inv(hipStream_t st, int nthreads, size_t lds, int nring, int L, int nreg, int nblk, Items it,
+// the DFT engine of a plan's rings (and of its theta filter)
+struct DftShape {
+    int threads;      // LDS engine: threads and LDS of a workgroup
+    size_t lds;
+    int conv;         // convolution length where every ring has the length n and that needs
+    int n;            // Bluestein's identity (register engine); 0: LDS engine
+};
+
+hipError_t launch_phi_inv(hipStream_t st, const DftShape &dft, int nring, int L, int nreg, int nblk, Items it,
                           int nitem, Strides sp, Strides sf, Strides sm, const double *part, const int *mtop,
                           const double2 *flm, const double *wl, const int *ring_nphi, const long long *ring_start,
                           const int *ring_shift, const int *ring_fft, const FftArgs *ffts, double2 *map,
                           double2 *fscr);
-hipError_t launch_phi_fwd(hipStream_t st, int nthreads, size_t lds, int nring, int hstride, int L, double q, Items it,
+hipError_t launch_phi_fwd(hipStream_t st, const DftShape &dft, int nring, int hstride, int L, double q, Items it,
                           int nitem, Strides sm, Strides sF, const double2 *map, const int *ring_nphi,
                           const long long *ring_start, const int *ring_shift, const int *ring_fft, const FftArgs *ffts,
                           const double *ringq, double *F, double2 *fscr);
-hipError_t launch_mw_filter(hipStream_t st, int nthreads, size_t lds, int L, int ss, int hstride, Items it, int nitem,
+hipError_t launch_mw_filter(hipStream_t st, const DftShape &dft, int L, int ss, int hstride, Items it, int nitem,
                             Strides sF, Strides sh, const FftArgs *fN, const double *wq, const double *ph, double *F,
-                            double2 *hpole, double2 *hpoleN, double2 *fscr, int half, int adj, const FftArgs *fconv);
+                            double2 *hpole, double2 *hpoleN, double2 *fscr, int half, int adj);
 hipError_t launch_ring_scale(hipStream_t st, int nmap, long long sm, int nring, int nphi, const double *w,
                              double2 *map);
 hipError_t launch_ring_scale_real(hipStream_t st, int nmap, long long sm, int nring, const long long *ring_start,
@@ -99,12 +107,12 @@ hipError_t launch_finish_fwd(hipStream_t st, int L, int nblk, Items it, int nite
                              const double *wl, const double2 *hpole, const double2 *hpoleN, double2 *flm,
                              int half = 0);
 // real signals (spin 0): pairs of rings share one complex DFT; maps are real doubles
-hipError_t launch_phi_inv_real(hipStream_t st, int nthreads, size_t lds, int npair, int L, int nreg, int nblk, int nmap,
+hipError_t launch_phi_inv_real(hipStream_t st, const DftShape &dft, int npair, int L, int nreg, int nblk, int nmap,
                                long long sp, long long sf, long long sm, const int *pairs, const double *part,
                                const int *mtop, const double2 *flm, const double *wl, const int *ring_nphi,
                                const long long *ring_start, const int *ring_shift, const int *ring_fft,
                                const FftArgs *ffts, double *map, double2 *fscr);
-hipError_t launch_phi_fwd_real(hipStream_t st, int nthreads, size_t lds, int nring, int hstride, int npair, int L,
+hipError_t launch_phi_fwd_real(hipStream_t st, const DftShape &dft, int nring, int hstride, int npair, int L,
                                double q, int nmap, long long sm, long long sF, const int *pairs, const double *map,
                                const int *ring_nphi, const long long *ring_start, const int *ring_shift,
                                const int *ring_fft, const FftArgs *ffts, const double *ringq, double *F, double2 *fscr);
@@ -130,6 +138,6 @@ hipError_t launch_mask_low(hipStream_t st, int nmap, int nrun, const SweepRun *r
 hipError_t launch_zero_maps(hipStream_t st, int nmap, long long wsd, double *p, size_t n);
 hipError_t launch_pole_from_F(hipStream_t st, int L, int hstride, int ring, Items it, int nitem, Strides sF, Strides sh,
                               const double *F, double2 *pole);
-hipError_t set_kernel_lds_limits(size_t max_dyn);
+hipError_t set_kernel_lds_limits(const DftShape &dft);
 
 }  // namespace s2mi

@@ -16,7 +16,7 @@
 
 #include <cstdint>
 
-#include "s2mi_fft.h"
+#include "s2mi_conv.h"
 #include "s2mi_internal.h"
 #include "s2mi_kernels.h"
 #include "s2mi_recur.h"
@@ -168,14 +168,15 @@ __global__ void k_mask_low(int nrun, const SweepRun *__restrict__ runs, int nreg
 // inverse DFT of length nphi.  MW rings: nphi = 2L-1 and the order line maps
 // one-to-one onto the bins.  The MW south pole (ring == nreg) has the closed
 // form d^l_{m,-s}(pi) = (-1)^{l+m} delta_{m,s} (Eq. 29).
-__global__ __launch_bounds__(1024) void k_phi_inv(
+template <class E>
+__global__ __launch_bounds__(E::MAXT, E::WPE) void k_phi_inv(
     int L, int nreg, int nblk, Items it, Strides sp, Strides sf, Strides sm, const double *__restrict__ part,
     const int *__restrict__ mtop, const double2 *__restrict__ flm, const double *__restrict__ wl, const int *__restrict__ ring_nphi, const long long *__restrict__ ring_start,
     const int *__restrict__ ring_shift, const int *__restrict__ ring_fft, const FftArgs *__restrict__ ffts,
     double2 *__restrict__ map, double2 *__restrict__ fscr)
 {
     extern __shared__ double2 buf[];
-    __shared__ double2 red[1024];
+    __shared__ double2 red[E::MAXT];
     const int r = blockIdx.x;
     const int T = blockDim.x, tid = threadIdx.x;
     const int item = it.item0 + blockIdx.y, map_i = item / it.nslice, slice = item % it.nslice;
@@ -278,16 +279,18 @@ __global__ __launch_bounds__(1024) void k_phi_inv(
         if (tid == 0) buf[((mp % nphi) + nphi) % nphi] = red[0];
     }
     __syncthreads();
-    dft_lds(buf, f, +1, fscr ? fscr + (size_t)blockIdx.x * FFT_SCRATCH : nullptr);
     double2 *out = map + ring_start[r];
-    for (int k = tid; k < nphi; k += T) out[k] = buf[k];
+    E::template dft<false, false>(
+        buf, f, +1, fscr ? fscr + (size_t)blockIdx.x * FFT_SCRATCH : nullptr, [&](int k) { return buf[k]; },
+        [&](int k, double2 v) { out[k] = v; });
 }
 
 // ------------------------------------------------------------------ phi-DFT: forward
 // One workgroup per (map, ring): X = DFT_nphi(ring); ftilde_m = q e^{-i pi m s_r/nphi} X[m mod nphi]
 // for |m| < L (the periodic repeat of Sec. 4.2 for short HEALPix rings), written
 // to F[m][ring] = {ftilde_m, ftilde_-m}.
-__global__ __launch_bounds__(1024) void k_phi_fwd(
+template <class E>
+__global__ __launch_bounds__(E::MAXT, E::WPE) void k_phi_fwd(
     int L, int nring, int hstride, double q, Items it, Strides sm, Strides sF, const double2 *__restrict__ map, const int *__restrict__ ring_nphi,
     const long long *__restrict__ ring_start, const int *__restrict__ ring_shift,
     const int *__restrict__ ring_fft, const FftArgs *__restrict__ ffts, const double *__restrict__ ringq,
@@ -315,9 +318,9 @@ __global__ __launch_bounds__(1024) void k_phi_fwd(
     const int shift = ring_shift[r];
     if (ringq) q = ringq[r];                     // per-ring quadrature weight (DH, GL)
     const double2 *in = map + ring_start[r];
-    for (int k = tid; k < nphi; k += T) buf[k] = in[k];
-    __syncthreads();
-    dft_lds(buf, f, -1, fscr ? fscr + (size_t)blockIdx.x * FFT_SCRATCH : nullptr);
+    E::template dft<true, true>(
+        buf, f, -1, fscr ? fscr + (size_t)blockIdx.x * FFT_SCRATCH : nullptr, [&](int k) { return in[k]; },
+        [](int, double2) {});
     for (int m = tid; m < L; m += T) {
         double2 a = buf[m % nphi];
         double2 b = buf[(nphi - (m % nphi)) % nphi];
@@ -348,7 +351,8 @@ __global__ __launch_bounds__(1024) void k_phi_fwd(
 // m >= 0.  Rings of 2L-1 samples without offset map orders one-to-one onto
 // bins; other rings sum the orders of each bin (HEALPix repeat) with the
 // half-pixel phase.
-__global__ __launch_bounds__(1024) void k_phi_inv_real(
+template <class E>
+__global__ __launch_bounds__(E::MAXT, E::WPE) void k_phi_inv_real(
     int L, int nreg, int nblk, int item0, long long sp, long long sf, long long sm, const int *__restrict__ pairs, const double *__restrict__ part,
     const int *__restrict__ mtop, const double2 *__restrict__ flm, const double *__restrict__ wl,
     const int *__restrict__ ring_nphi, const long long *__restrict__ ring_start, const int *__restrict__ ring_shift,
@@ -356,7 +360,7 @@ __global__ __launch_bounds__(1024) void k_phi_inv_real(
     double2 *__restrict__ fscr)
 {
     extern __shared__ double2 buf[];
-    __shared__ double2 red[1024];
+    __shared__ double2 red[E::MAXT];
     const int map_i = item0 + blockIdx.y;
     part += map_i * sp;
     flm += map_i * sf;
@@ -442,13 +446,14 @@ __global__ __launch_bounds__(1024) void k_phi_inv_real(
         }
     }
     __syncthreads();
-    dft_lds(buf, f, +1, fscr ? fscr + (size_t)blockIdx.x * FFT_SCRATCH : nullptr);
     double *o1 = map + ring_start[r1];
     double *o2 = r2 >= 0 ? map + ring_start[r2] : nullptr;
-    for (int k = tid; k < nphi; k += T) {
-        o1[k] = buf[k].x;
-        if (o2) o2[k] = buf[k].y;
-    }
+    E::template dft<false, false>(
+        buf, f, +1, fscr ? fscr + (size_t)blockIdx.x * FFT_SCRATCH : nullptr, [&](int k) { return buf[k]; },
+        [&](int k, double2 v) {
+            o1[k] = v.x;
+            if (o2) o2[k] = v.y;
+        });
 }
 
 // Forward: Z = DFT(x1 + i x2), X1[k] = (Z[k] + conj Z[-k]) / 2, X2[k] = (Z[k] -
@@ -456,7 +461,8 @@ __global__ __launch_bounds__(1024) void k_phi_inv_real(
 // (q per ring for DH / GL), written as F[m][ring] = {X_m, conj X_m} (the layout
 // of the complex phi-DFT).  Workgroups past the pairs zero the sweep's padding
 // rings nring .. hstride-1, two per workgroup.
-__global__ __launch_bounds__(1024) void k_phi_fwd_real(
+template <class E>
+__global__ __launch_bounds__(E::MAXT, E::WPE) void k_phi_fwd_real(
     int L, int nring, int hstride, int npair, double q, int item0, long long sm, long long sF,
     const int *__restrict__ pairs, const double *__restrict__ map,
     const int *__restrict__ ring_nphi, const long long *__restrict__ ring_start, const int *__restrict__ ring_shift,
@@ -485,9 +491,9 @@ __global__ __launch_bounds__(1024) void k_phi_fwd_real(
     const double q2 = 0.5 * (ringq && r2 >= 0 ? ringq[r2] : q);
     const double *x1 = map + ring_start[r1];
     const double *x2 = r2 >= 0 ? map + ring_start[r2] : nullptr;
-    for (int k = tid; k < nphi; k += T) buf[k] = make_double2(x1[k], x2 ? x2[k] : 0.0);
-    __syncthreads();
-    dft_lds(buf, f, -1, fscr ? fscr + (size_t)blockIdx.x * FFT_SCRATCH : nullptr);
+    E::template dft<true, true>(
+        buf, f, -1, fscr ? fscr + (size_t)blockIdx.x * FFT_SCRATCH : nullptr,
+        [&](int k) { return make_double2(x1[k], x2 ? x2[k] : 0.0); }, [](int, double2) {});
     for (int m = tid; m < L; m += T) {
         const int b = m % nphi;
         const double2 z = buf[b];
@@ -561,12 +567,12 @@ __device__ __forceinline__ int torus_ring(int t, int L, int N, int ss, bool *mir
     return u == 0 ? L : u - 1;
 }
 
-__global__ __launch_bounds__(1024) void k_mw_filter(int L, int ss, int hstride, Items it, Strides sF, Strides sh,
+template <class E, bool ss>
+__global__ __launch_bounds__(E::MAXT, E::WPE) void k_mw_filter(int L, int hstride, Items it, Strides sF, Strides sh,
                                                     const FftArgs *__restrict__ fN, const double *__restrict__ wq,
                                                     const double *__restrict__ ph, double *__restrict__ F,
                                                     double2 *__restrict__ hpole, double2 *__restrict__ hpoleN,
-                                                    double2 *__restrict__ fscr, int half, int adj,
-                                                    const FftArgs *__restrict__ fconv)
+                                                    double2 *__restrict__ fscr, int half, int adj)
 {
     extern __shared__ double2 buf[];
     __shared__ double2 nyq;
@@ -616,10 +622,11 @@ __global__ __launch_bounds__(1024) void k_mw_filter(int L, int ss, int hstride, 
             gpo = make_double2(fma(sgN, gn.x, gpo.x), fma(sgN, gn.y, gpo.y));
         }
     }
+    constexpr bool conv = E::CONV && !ss;                  // see below
     {
         // torus samples
         double2 acc = make_double2(0.0, 0.0);                // adj: sum_t (-1)^t w'_theta z
-        for (int t = tid; t < N; t += T) {
+        for (int t = tid; !conv && t < N; t += T) {
             const double2 g = sample(t);
             buf[t] = g;
             if (ss && adj) {
@@ -659,50 +666,85 @@ __global__ __launch_bounds__(1024) void k_mw_filter(int L, int ss, int hstride, 
             po = make_double2(0.0, 0.0);
             for (int w = 0; w < (T + 63) / 64; ++w) po = cadd(po, wpart[w]);
         }
-        // the midpoint samples S g times the weights w'', moved back: S^{-1} (w'' S g).
-        // DFT form: four engine passes (forward, shift, inverse: midpoints; weights;
-        // forward, shift back, inverse).  Convolution form (MW, N not 13-smooth, fconv:
-        // the two shifts' FftArgs): each shift is a circular convolution of length N
-        // with a fixed kernel, run by the Bluestein driver with a unit chirp and the
-        // kernel's spectrum as its filter (one cyclic convolution, two FFTs or four
-        // half-length ones where the engine splits it, instead of two Bluestein DFTs);
-        // its result is at t < N.  One call site, so the engine is inlined once.
-        const bool conv = fconv != nullptr;
-        __syncthreads();                             // the torus samples are in LDS
-#pragma nounroll
-        for (int pass = 0; pass < 4; ++pass) {
-            if (!conv || !(pass & 1))
-                dft_lds(buf, conv ? fconv + (pass >> 1) : fN, conv ? -1 : ((pass & 1) ? +1 : -1), scr);
-            if (pass == 0 && !conv) {
-                for (int k = tid; k < N; k += T) {                                 // shift +pi/N
-                    if (ss && !adj && k == L) nyq = make_double2(buf[k].x / N, buf[k].y / N);   // ghat_L (MWSS), read first
-                    buf[k] = cmul(buf[k], phc[k]);
+        // the midpoint samples S g times the weights w'', moved back: S^{-1} (w'' S g), and
+        // z w'_theta added (z re-read: F is rewritten only below).
+        if constexpr (conv) {
+            // MW, N not 13-smooth: each shift is a circular convolution of length N with a fixed
+            // kernel (fN + 1 and fN + 2: the two shifts' FftArgs), and the whole filter
+            // stays in registers.
+            double2 v[E::V];
+            int t0 = E::first_point();
+#pragma unroll
+            for (int i = 0; i < E::V; ++i) {
+                const int t = t0 + E::T * i;
+                v[i] = t < N ? sample(t) : make_double2(0.0, 0.0);
+                E::few_loads(i);
+            }
+#pragma unroll 1
+            for (int pass = 0; pass < 2; ++pass) {
+                E::convolve(v, reinterpret_cast<double *>(buf), fN + 1 + pass);
+                if (pass == 0) {
+                    t0 = E::first_point();
+#pragma unroll
+                    for (int i = 0; i < E::V; ++i) {
+                        const int t = t0 + E::T * i;
+                        const double wv = t < N ? wq[N + t] : 0.0;
+                        v[i] = make_double2(v[i].x * wv, v[i].y * wv);
+                        E::few_loads(i);
+                    }
                 }
-            } else if (pass == 1) {
-                for (int t = tid; t < N; t += T) {
-                    const double wv = wq[N + t];
-                    buf[t].x *= wv;
-                    buf[t].y *= wv;
-                }
-            } else if (pass == 2 && !conv) {
-                for (int k = tid; k < N; k += T) buf[k] = cmulc(buf[k], phc[k]);   // shift -pi/N
             }
             __syncthreads();
-        }
-        for (int t = tid; t < N; t += T) {          // + z w'_theta (z re-read: F is rewritten only below)
-            double2 g = sample(t);
-            const double wv = wq[t];
-            const double sg = (t & 1) ? -1.0 : 1.0;
-            if (ss && !adj) {                                // P z, then times w'
-                g.x -= sg * nyq.x;
-                g.y -= sg * nyq.y;
+            t0 = E::first_point();
+#pragma unroll
+            for (int i = 0; i < E::V; ++i) {
+                const int t = t0 + E::T * i;
+                if (t < N) {
+                    const double2 g = sample(t);
+                    const double wv = wq[t];
+                    buf[t] = make_double2(0.5 * fma(g.x, wv, v[i].x), 0.5 * fma(g.y, wv, v[i].y));
+                }
+                E::few_loads(i);
             }
-            double2 gw = make_double2(g.x * wv, g.y * wv);
-            if (ss && adj) {                                 // P (z w')
-                gw.x -= sg * nyq.x;
-                gw.y -= sg * nyq.y;
+        } else {
+            // four engine passes (forward, shift, inverse: midpoints; weights; forward, shift
+            // back, inverse) from one call site, so the engine is inlined once
+            __syncthreads();                             // the torus samples are in LDS
+#pragma nounroll
+            for (int pass = 0; pass < 4; ++pass) {
+                E::template dft<false, true>(
+                    buf, fN, (pass & 1) ? +1 : -1, scr, [&](int k) { return buf[k]; }, [](int, double2) {});
+                if (pass == 0) {
+                    for (int k = tid; k < N; k += T) {                                 // shift +pi/N
+                        if (ss && !adj && k == L) nyq = make_double2(buf[k].x / N, buf[k].y / N);   // ghat_L (MWSS), read first
+                        buf[k] = cmul(buf[k], phc[k]);
+                    }
+                } else if (pass == 1) {
+                    for (int t = tid; t < N; t += T) {
+                        const double wv = wq[N + t];
+                        buf[t].x *= wv;
+                        buf[t].y *= wv;
+                    }
+                } else if (pass == 2) {
+                    for (int k = tid; k < N; k += T) buf[k] = cmulc(buf[k], phc[k]);   // shift -pi/N
+                }
+                __syncthreads();
             }
-            buf[t] = make_double2(0.5 * (gw.x + buf[t].x), 0.5 * (gw.y + buf[t].y));
+            for (int t = tid; t < N; t += T) {
+                double2 g = sample(t);
+                const double wv = wq[t];
+                const double sg = (t & 1) ? -1.0 : 1.0;
+                if (ss && !adj) {                                // P z, then times w'
+                    g.x -= sg * nyq.x;
+                    g.y -= sg * nyq.y;
+                }
+                double2 gw = make_double2(g.x * wv, g.y * wv);
+                if (ss && adj) {                                 // P (z w')
+                    gw.x -= sg * nyq.x;
+                    gw.y -= sg * nyq.y;
+                }
+                buf[t] = make_double2(0.5 * (gw.x + buf[t].x), 0.5 * (gw.y + buf[t].y));
+            }
         }
         __syncthreads();
         const double sc = 2.0 * M_PI / (double)N;
@@ -1091,7 +1133,7 @@ __global__ __launch_bounds__(1024) void k_bluestein_prep(const FftArgs *__restri
 {
     extern __shared__ double2 buf[];
     const FftArgs *f = ffts + blockIdx.x;
-    if (!f->blue || f->conv) return;                    // convolutions carry their own filter
+    if (!f->blue || f->conv) return;                    // the theta filter's kernels carry their own spectra
     const int n = f->n, len = f->len;
     const double2 *ch = reinterpret_cast<const double2 *>(f->chirp);
     if (f->split) {
@@ -1107,7 +1149,7 @@ __global__ __launch_bounds__(1024) void k_bluestein_prep(const FftArgs *__restri
             __syncthreads();
             fft_engine(buf, f, -1);
             for (int k = threadIdx.x; k < len; k += blockDim.x)
-                out[2 * k + half] = make_double2(buf[k].x * inv, buf[k].y * inv);
+                out[f->perm ? half * len + conv_index(len, k) : 2 * k + half] = make_double2(buf[k].x * inv, buf[k].y * inv);
             __syncthreads();
         }
         return;
@@ -1122,7 +1164,8 @@ __global__ __launch_bounds__(1024) void k_bluestein_prep(const FftArgs *__restri
     fft_engine(buf, f, -1);
     double2 *out = reinterpret_cast<double2 *>(const_cast<double *>(f->bflt));
     const double inv = 1.0 / (double)len;
-    for (int i = threadIdx.x; i < len; i += blockDim.x) out[i] = make_double2(buf[i].x * inv, buf[i].y * inv);
+    for (int i = threadIdx.x; i < len; i += blockDim.x)
+        out[f->perm ? conv_index(len, i) : i] = make_double2(buf[i].x * inv, buf[i].y * inv);
 }
 
 // pole[(L-1) + m] = F[|m|][ring].side(m): the MW south-pole ring's Fourier line
@@ -1183,68 +1226,102 @@ static hipError_t over_items(int nitem, bool one_by_one, F go)
     return hipSuccess;
 }
 
-hipError_t launch_phi_inv(hipStream_t st, int nthreads, size_t lds, int nring, int L, int nreg, int nblk, Items it,
+// DFT kernels over the engine of a plan: go(engine, threads, LDS bytes).  conv: the
+// convolution length where all rings share one length that needs Bluestein's identity.
+template <typename F>
+static hipError_t with_engine(const DftShape &d, F go)
+{
+    auto conv = [&](auto e) {
+        using E = decltype(e);
+        return go(e, E::T, std::max(d.n * sizeof(double2), (size_t)(E::T * E::V) * sizeof(double)));
+    };
+    switch (d.conv) {
+    case 0: return d.threads > 1024 ? hipErrorInvalidValue : go(LdsDft{}, d.threads, d.lds);
+    case 64: return conv(ConvDft<64, false>{});
+    case 128: return conv(ConvDft<128, false>{});
+    case 256: return conv(ConvDft<256, false>{});
+    case 512: return conv(ConvDft<512, false>{});
+    case 1024: return conv(ConvDft<1024, false>{});
+    case 2048: return conv(ConvDft<2048, false>{});
+    case 4096: return conv(ConvDft<4096, false>{});
+    case 8192: return conv(ConvDft<8192, false>{});
+    case 16384: return conv(ConvDft<8192, true>{});
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_phi_inv(hipStream_t st, const DftShape &dft, int nring, int L, int nreg, int nblk, Items it,
                           int nitem, Strides sp, Strides sf, Strides sm, const double *part, const int *mtop,
                           const double2 *flm, const double *wl, const int *ring_nphi, const long long *ring_start,
                           const int *ring_shift, const int *ring_fft, const FftArgs *ffts, double2 *map,
                           double2 *fscr)
 {
-    return over_items(nitem, fscr != nullptr, [&](int i, int ny) {
-        it.item0 = i;
-        hipLaunchKernelGGL(k_phi_inv, dim3(nring, ny), dim3(nthreads), lds, st, L, nreg, nblk, it, sp, sf, sm, part,
-                           mtop, flm, wl, ring_nphi, ring_start, ring_shift, ring_fft, ffts, map, fscr);
+    return with_engine(dft, [&](auto e, int nt, size_t lds) {
+        return over_items(nitem, fscr != nullptr, [&](int i, int ny) {
+            it.item0 = i;
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_phi_inv<decltype(e)>), dim3(nring, ny), dim3(nt), lds, st, L, nreg, nblk, it, sp, sf, sm, part,
+                               mtop, flm, wl, ring_nphi, ring_start, ring_shift, ring_fft, ffts, map, fscr);
+        });
     });
 }
 
-hipError_t launch_phi_fwd(hipStream_t st, int nthreads, size_t lds, int nring, int hstride, int L, double q, Items it,
+hipError_t launch_phi_fwd(hipStream_t st, const DftShape &dft, int nring, int hstride, int L, double q, Items it,
                           int nitem, Strides sm, Strides sF, const double2 *map, const int *ring_nphi,
                           const long long *ring_start, const int *ring_shift, const int *ring_fft, const FftArgs *ffts,
                           const double *ringq, double *F, double2 *fscr)
 {
-    return over_items(nitem, fscr != nullptr, [&](int i, int ny) {
-        it.item0 = i;
-        hipLaunchKernelGGL(k_phi_fwd, dim3(hstride, ny), dim3(nthreads), lds, st, L, nring, hstride, q, it, sm, sF, map,
-                           ring_nphi, ring_start, ring_shift, ring_fft, ffts, ringq, F, fscr);
+    return with_engine(dft, [&](auto e, int nt, size_t lds) {
+        return over_items(nitem, fscr != nullptr, [&](int i, int ny) {
+            it.item0 = i;
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_phi_fwd<decltype(e)>), dim3(hstride, ny), dim3(nt), lds, st, L, nring, hstride, q, it, sm, sF, map,
+                               ring_nphi, ring_start, ring_shift, ring_fft, ffts, ringq, F, fscr);
+        });
     });
 }
 
-hipError_t launch_phi_inv_real(hipStream_t st, int nthreads, size_t lds, int npair, int L, int nreg, int nblk, int nmap,
+hipError_t launch_phi_inv_real(hipStream_t st, const DftShape &dft, int npair, int L, int nreg, int nblk, int nmap,
                                long long sp, long long sf, long long sm, const int *pairs, const double *part,
                                const int *mtop, const double2 *flm, const double *wl, const int *ring_nphi,
                                const long long *ring_start, const int *ring_shift, const int *ring_fft,
                                const FftArgs *ffts, double *map, double2 *fscr)
 {
-    if (nthreads > 1024 || npair < 1) return hipErrorInvalidValue;
-    return over_items(nmap, fscr != nullptr, [&](int i, int ny) {
-        hipLaunchKernelGGL(k_phi_inv_real, dim3(npair, ny), dim3(nthreads), lds, st, L, nreg, nblk, i, sp, sf, sm,
-                           pairs, part, mtop, flm, wl, ring_nphi, ring_start, ring_shift, ring_fft, ffts, map, fscr);
+    if (npair < 1) return hipErrorInvalidValue;
+    return with_engine(dft, [&](auto e, int nt, size_t lds) {
+        return over_items(nmap, fscr != nullptr, [&](int i, int ny) {
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_phi_inv_real<decltype(e)>), dim3(npair, ny), dim3(nt), lds, st, L, nreg, nblk, i, sp, sf, sm,
+                               pairs, part, mtop, flm, wl, ring_nphi, ring_start, ring_shift, ring_fft, ffts, map, fscr);
+        });
     });
 }
 
-hipError_t launch_phi_fwd_real(hipStream_t st, int nthreads, size_t lds, int nring, int hstride, int npair, int L,
+hipError_t launch_phi_fwd_real(hipStream_t st, const DftShape &dft, int nring, int hstride, int npair, int L,
                                double q, int nmap, long long sm, long long sF, const int *pairs, const double *map,
                                const int *ring_nphi, const long long *ring_start, const int *ring_shift,
                                const int *ring_fft, const FftArgs *ffts, const double *ringq, double *F, double2 *fscr)
 {
-    if (nthreads > 1024 || hstride < nring || npair < 1) return hipErrorInvalidValue;
+    if (hstride < nring || npair < 1) return hipErrorInvalidValue;
     const int nblocks = npair + (hstride - nring + 1) / 2;
-    return over_items(nmap, fscr != nullptr, [&](int i, int ny) {
-        hipLaunchKernelGGL(k_phi_fwd_real, dim3(nblocks, ny), dim3(nthreads), lds, st, L, nring, hstride, npair, q, i,
-                           sm, sF, pairs, map, ring_nphi, ring_start, ring_shift, ring_fft, ffts, ringq, F, fscr);
+    return with_engine(dft, [&](auto e, int nt, size_t lds) {
+        return over_items(nmap, fscr != nullptr, [&](int i, int ny) {
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_phi_fwd_real<decltype(e)>), dim3(nblocks, ny), dim3(nt), lds, st, L, nring, hstride, npair, q, i,
+                               sm, sF, pairs, map, ring_nphi, ring_start, ring_shift, ring_fft, ffts, ringq, F, fscr);
+        });
     });
 }
 
-hipError_t launch_mw_filter(hipStream_t st, int nthreads, size_t lds, int L, int ss, int hstride, Items it, int nitem,
+hipError_t launch_mw_filter(hipStream_t st, const DftShape &dft, int L, int ss, int hstride, Items it, int nitem,
                             Strides sF, Strides sh, const FftArgs *fN, const double *wq, const double *ph, double *F,
-                            double2 *hpole, double2 *hpoleN, double2 *fscr, int half, int adj, const FftArgs *fconv)
+                            double2 *hpole, double2 *hpoleN, double2 *fscr, int half, int adj)
 {
-    if ((ss && !hpoleN) || nthreads > 1024) return hipErrorInvalidValue;
-    if (fconv && ss) return hipErrorInvalidValue;               // the convolution form is MW's
-    return over_items(nitem, fscr != nullptr, [&](int i, int ny) {
-        it.item0 = i;
-        const int np = (L + 1) / 2;                      // pairs of orders, and their two sides
-        hipLaunchKernelGGL(k_mw_filter, dim3(half ? np : (np + 7) / 8 * 16, ny), dim3(nthreads), lds, st, L, ss, hstride, it, sF, sh, fN, wq, ph, F,
-                           hpole, hpoleN, fscr, half, adj, fconv);
+    if (ss && !hpoleN) return hipErrorInvalidValue;
+    return with_engine(dft, [&](auto e, int nt, size_t lds) {
+        return over_items(nitem, fscr != nullptr, [&](int i, int ny) {
+            it.item0 = i;
+            const int np = (L + 1) / 2;                      // pairs of orders, and their two sides
+            auto *k = ss ? k_mw_filter<decltype(e), true> : k_mw_filter<decltype(e), false>;
+            hipLaunchKernelGGL(k, dim3(half ? np : (np + 7) / 8 * 16, ny), dim3(nt), lds, st, L, hstride, it, sF, sh,
+                               fN, wq, ph, F, hpole, hpoleN, fscr, half, adj);
+        });
     });
 }
 
@@ -1386,16 +1463,23 @@ hipError_t launch_pole_from_F(hipStream_t st, int L, int hstride, int ring, Item
 }
 
 // Kernels with large dynamic LDS need the per-kernel limit raised.
-hipError_t set_kernel_lds_limits(size_t max_dyn)
+hipError_t set_kernel_lds_limits(const DftShape &dft)
 {
-    hipError_t e;
-    if ((e = hipFuncSetAttribute((const void *)k_phi_inv, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_dyn)) != hipSuccess) return e;
-    if ((e = hipFuncSetAttribute((const void *)k_phi_fwd, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_dyn)) != hipSuccess) return e;
-    if ((e = hipFuncSetAttribute((const void *)k_mw_filter, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_dyn)) != hipSuccess) return e;
-    if ((e = hipFuncSetAttribute((const void *)k_bluestein_prep, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_dyn)) != hipSuccess) return e;
-    if ((e = hipFuncSetAttribute((const void *)k_phi_inv_real, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_dyn)) != hipSuccess) return e;
-    if ((e = hipFuncSetAttribute((const void *)k_phi_fwd_real, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_dyn)) != hipSuccess) return e;
-    return hipSuccess;
+    auto raise = [](const void *k, size_t lds) {
+        return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    };
+    const hipError_t rc = raise((const void *)k_bluestein_prep, dft.lds);
+    if (rc != hipSuccess) return rc;
+    return with_engine(dft, [&](auto e, int, size_t lds) {
+        using E = decltype(e);
+        for (const void *k : {(const void *)k_phi_inv<E>, (const void *)k_phi_fwd<E>, (const void *)k_phi_inv_real<E>,
+                              (const void *)k_phi_fwd_real<E>, (const void *)k_mw_filter<E, false>,
+                              (const void *)k_mw_filter<E, true>}) {
+            const hipError_t rk = raise(k, lds);
+            if (rk != hipSuccess) return rk;
+        }
+        return hipSuccess;
+    });
 }
 
 }  // namespace s2mi
