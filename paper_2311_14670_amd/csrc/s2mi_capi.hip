@@ -76,16 +76,21 @@ struct Work {
 
 namespace {
 
-// Orders per piece that a slot's fixed cost (state load, start of the pipeline)
-// amounts to, and the shortest piece worth a cut.
-constexpr int PIECE_COST = 10, PIECE_MIN = 16;
+// Orders that a slot's fixed cost (state load, start of the pipeline) amounts to, and the
+// shortest slot.  A workgroup that runs several slots sweeps a block's consecutive
+// pieces as one, so slots may be short: where the grid is small (few rings and degrees) the
+// launch takes about 10 us and 1 us per order of a slot, waiting for memory.
+// (Measured on MI355X, inverse / forward sweep, us, shortest slot of 16 orders with pieces
+// run one by one -> 8 -> 4 orders: MW L = 64 spin 2 34 / 44 -> 21 / 28 -> 19 / 25; HEALPix
+// nside 64, L = 128, 8 maps 46 / 75 -> 28 / 46 -> 27 / 39; SO(3) L = 96, N = 4 50 / 62 -> 30 / 43
+// -> 32 / 44; MW L = 512, 16 maps, where pieces merge, 882 / 742 -> 537 / 498 -> 545 / 499;
+// no difference from L = 1024 on.  The fixed cost at 5 or 20: within 2 %.)
+constexpr int PIECE_COST = 10, PIECE_MIN = 4;
 
-// (Measured, pair of MW L = 64 spin 2: 342 us with one workgroup per run over all orders,
-// 136 us with the orders in four pieces and both runs in one launch.)
 // Fills seg / first / cuts for blocks of `orders[b]` orders (largest work last), so
 // that `items` runs sharing a launch of `tiles` ring tiles each fill `ncu` compute
 // units: the slot count that minimises (rounds of workgroups) x (orders per slot +
-// fixed cost).  force > 0: every block in `force` pieces (as far as 16 orders go).
+// fixed cost).  force > 0: every block in `force` pieces (of at least 16 orders).
 void deal_work(Work &W, const std::vector<int> &orders, int items, int ncu, int force)
 {
     const int nb = (int)orders.size();
@@ -98,7 +103,7 @@ void deal_work(Work &W, const std::vector<int> &orders, int items, int ncu, int 
     std::vector<std::vector<int>> cut_of(nb);
     if (force > 0) {
         for (int b = nb - 1; b >= 0; --b) {
-            const int k = std::max(1, std::min(force, orders[b] / PIECE_MIN));
+            const int k = std::max(1, std::min(force, orders[b] / 16));
             int hi = orders[b] - 1;
             for (int j = k - 1; j >= 0; --j) {
                 const int lo = j == 0 ? 0 : orders[b] * j / k / 4 * 4;
@@ -118,19 +123,17 @@ void deal_work(Work &W, const std::vector<int> &orders, int items, int ncu, int 
             const double c = (double)((wg1 * s + ncu - 1) / ncu) * ((double)total / s + PIECE_COST);
             if (c < cost * 0.999) { cost = c; best = s; }
         }
-        W.quota = std::max(PIECE_MIN, (int)((total + best - 1) / best + 3) / 4 * 4);
+        W.quota = std::max(PIECE_MIN, (int)((total + best - 1) / best));
         int room = W.quota;
         for (int b = nb - 1; b >= 0; --b) {
             int hi = orders[b] - 1;
             while (hi >= 0) {
-                int lo = hi + 1 - room;
-                lo = lo <= 7 ? 0 : (lo + 3) / 4 * 4;     // cuts at multiples of 4; no short rest
-                if (lo > hi) lo = hi / 4 * 4;
+                const int lo = std::max(0, hi + 1 - room) / 4 * 4;       // cuts at multiples of 4
                 W.seg.push_back(make_int4(b, hi, lo, hi == orders[b] - 1 ? -1 : 0));
                 if (lo > 0) cut_of[b].push_back(lo);
                 room -= hi - lo + 1;
                 hi = lo - 1;
-                if (room <= 7) {
+                if (room < PIECE_MIN) {
                     W.first.push_back((int)W.seg.size());
                     room = W.quota;
                 }

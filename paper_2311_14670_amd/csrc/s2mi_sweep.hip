@@ -345,6 +345,15 @@ __device__ __forceinline__ void inv_step(int m, uint32_t act, int nx, const int 
     for (int i = 0; i < NA; ++i) rb[i * 64] = acc[i];
 }
 
+// The last order of piece e, taken on through the next pieces of the workgroup where they
+// continue its block (their first state is then at hand); e: the last piece taken.
+__device__ __forceinline__ int piece_end(const int4 *__restrict__ seg, int4 sg, int &e, int e1, int mend)
+{
+    int bot = sg.z;
+    while (e + 1 < e1 && seg[e + 1].x == sg.x) bot = seg[++e].z;
+    return bot == 0 ? mend : bot;
+}
+
 // One buffer descriptor for the main sums of both sides: from the lower of the two
 // slices (the same one, one of them null, or two of an SO(3) run) to the end of the
 // higher one, a side's slice as an offset of the lane.  The descriptor has to be the
@@ -425,7 +434,7 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_inv(InvArgs a, const do
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         a.C + (size_t)map * a.wsd + (size_t)ri * a.nC, 0, (int)(a.nC * 8), 0x00027000);
     uint32_t fast = 0;
-    int it = 0, pblk = -1, pm = -1;
+    int it = 0;
     // Adds the waves' sums of the orders m1 .. m1 - DORD + 1 (buffer half `hf`) and stores
     // them to block blk's partial sums.
     auto reduce = [&](int blk, int hf, int m1, int mhi, int bot) {
@@ -505,8 +514,8 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_inv(InvArgs a, const do
 #pragma unroll 1
     for (int e = a.first[t * a.merge]; e < e1; ++e) {
         const int4 sg = a.seg[e];
-        const int blk = sg.x, mhi = sg.y, bot = sg.z == 0 ? mend : sg.z;
-        if (blk != pblk || mhi != pm) {                  // not a continuation of the last piece
+        const int blk = sg.x, mhi = sg.y, bot = piece_end(a.seg, sg, e, e1, mend);
+        {
             fast = 0;
             const int q0 = blk * a.cb, nq = min(a.cb, (L + 7) / 8 - q0);   // chunks of the block
             const int nv = nq > w ? (nq - w + 7) / 8 : 0;                    // and of this wave
@@ -537,8 +546,6 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_inv(InvArgs a, const do
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        pblk = blk;
-        pm = bot - 1;
 #pragma unroll 1
         for (int mb = mhi | 3; mb >= bot; mb -= 4) {
             // starts: the degrees mb .. mb - 3 belong to one chunk of one wave, in the lane
@@ -798,7 +805,7 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_fwd(FwdArgs a, const do
     double hq[FWD_KS], kp[4];
     unsigned lc[4];                                      // byte offsets of the lane's degrees (clamped into the table)
     uint32_t fast = 0;
-    int it = 0, pg = -1, pm = -1, lmin = 0;
+    int it = 0;
     // operand row of order m (pair: sums or differences by the parity of m + group)
     auto row_of = [&](int m, int G) -> const double * {
         if constexpr (PAIRF) {
@@ -812,9 +819,9 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_fwd(FwdArgs a, const do
 #pragma unroll 1
     for (int e = a.first[t * a.merge]; e < e1; ++e) {
         const int4 sg = a.seg[e];
-        const int G = sg.x, mhi = sg.y, bot = sg.z == 0 ? mend : sg.z;
-        if (G != pg || mhi != pm) {                      // not a continuation of the last piece
-            lmin = PAIRF ? 128 * (G >> 1) + (G & 1) : 64 * G;
+        const int G = sg.x, mhi = sg.y, bot = piece_end(a.seg, sg, e, e1, mend);
+        const int lmin = PAIRF ? 128 * (G >> 1) + (G & 1) : 64 * G;
+        {
 #pragma unroll
             for (int g = 0; g < 4; ++g) lc[g] = 8 * min(lmin + ((16 * g + i16) << lsh), L - 1);
             fast = 0;
@@ -841,8 +848,6 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_fwd(FwdArgs a, const do
 #pragma unroll
             for (int g = 0; g < 4; ++g) kp[g] = buf_load1(krs, lc[g], (unsigned)((min(mhi | 3, L - 1) + a.nx) * L) * 8);
         }
-        pg = G;
-        pm = bot - 1;
 #pragma unroll 1
         for (int mb = mhi | 3; mb >= bot; mb -= 4) {
             if (mb >= lmin) {                             // degrees mb .. mb - 3 of the group start
