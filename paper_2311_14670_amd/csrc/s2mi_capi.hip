@@ -1126,7 +1126,6 @@ int run_forward_dstage(s2_plan_t P, bool poles, double2 *flm, int nm, const doub
     double *Hx = P->nxp > 0 ? (double *)(ws + P->off_Hx) : nullptr;
     a.Hx = Hx;
     a.Qx = P->nxp > 0 ? (double *)(ws + P->off_Qx) : nullptr;
-    if (a.Qx) HIPCHK(launch_zero_maps(st, nm, a.wsd, a.Qx, P->szQx * P->nslice / sizeof(double)), "continuation sums clear");
     const bool one = P->one || half;
     {
         TIMED(S2_STAGE_DSTAGE_FWD);
@@ -1140,7 +1139,8 @@ int run_forward_dstage(s2_plan_t P, bool poles, double2 *flm, int nm, const doub
             a.D = D;
         } else if (P->nxp > 0) {
             HIPCHK(launch_mask_low(st, nm, a.nrun, P->runs_d, P->nxp, P->nreg, P->hstride, P->cot, P->csc, a.F, Hx,
-                                   a.wsd, a.nF, a.nHx), "low-order spectra");
+                                   a.wsd, a.nF, a.nHx, a.Qx, (long long)(P->szQx * P->nslice / sizeof(double))),
+                   "low-order spectra, continuation sums clear");
         }
         HIPCHK(launch_sweep_fwd(st, a, nm, one, P->cot, P->csc, P->kap), "forward d-stage");
     }

@@ -134,8 +134,7 @@ hipError_t launch_fadj_scatter(hipStream_t st, int L, int ss, int hstride, doubl
                                double *out);
 hipError_t launch_mask_low(hipStream_t st, int nmap, int nrun, const SweepRun *runs, int anmax, int nreg, int hstride,
                            const double *cot, const double *csc, const double *F, double *Hx, long long wsd,
-                           long long nF, long long nHx);
-hipError_t launch_zero_maps(hipStream_t st, int nmap, long long wsd, double *p, size_t n);
+                           long long nF, long long nHx, double *Qx, long long nz);
 hipError_t launch_pole_from_F(hipStream_t st, int L, int hstride, int ring, Items it, int nitem, Strides sF, Strides sh,
                               const double *F, double2 *pole);
 hipError_t set_kernel_lds_limits(const DftShape &dft);

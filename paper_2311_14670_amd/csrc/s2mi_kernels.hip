@@ -128,13 +128,17 @@ __global__ void k_pair_spectra(int L, int nreg, int nsw, int hstride, int pstrid
 // order ms of the ring): the own orders (A components 0,1 at mu >= 0, B
 // components 2,3 at mu > 0) where the run is stable or mu >= ms, and the
 // continuation orders (A components 2,3 = A slice at -mu, B components 0,1 = B
-// slice at +mu) where the run is the stable one and mu < ms.  Other entries 0.
+// slice at +mu) where the run is the stable one and mu < ms.  Other entries 0.  Clears
+// the map's nz continuation sums Qx too (a launch of its own took 5 us).
 __global__ void k_mask_low(int nrun, const SweepRun *__restrict__ runs, int nreg, int hstride,
                            const double *__restrict__ cot, const double *__restrict__ csc,
                            const double *__restrict__ F, double *__restrict__ Hx, long long wsd, long long nF,
-                           long long nHx)
+                           long long nHx, double *__restrict__ Qx, long long nz)
 {
     const int map = blockIdx.y / nrun, ri = blockIdx.y % nrun;
+    for (long long j = ((long long)ri * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x; j < nz;
+         j += (long long)nrun * gridDim.x * blockDim.x)
+        Qx[map * wsd + j] = 0.0;
     const SweepRun run = runs[ri];
     const int n = run.n, an_run = n < 0 ? -n : n;
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1007,28 +1011,38 @@ __global__ void k_hermitian_part(int L, const double2 *__restrict__ G, double2 *
 
 // ------------------------------------------------------------------ SO(3) gamma DFT
 // inverse: out[k][i] = sum_n e^{i n gamma_k} in[n][i];  forward: out[n][i] = q sum_k e^{-i n gamma_k} in[k][i]
-__global__ void k_gamma_dft(int N, long long nper, int sign, double q, const double *__restrict__ roots,
-                            const double2 *__restrict__ in, double2 *__restrict__ out, long long si, long long so)
+// Bound by the latency of a few loads: the 2N - 1 roots are the same for every thread and,
+// with N known to the compiler, sit in scalar registers at fixed places (indexed by a
+// remainder per product, the products took 21 us of L = 96, N = 4 against 6).
+template <int N>
+__global__ __launch_bounds__(128) void k_gamma_dft(long long nper, int sign, double q, const double *__restrict__ roots,
+                                                   const double2 *__restrict__ in, double2 *__restrict__ out,
+                                                   long long si, long long so)
 {
+    constexpr int G = 2 * N - 1;
     in += blockIdx.y * si;
     out += blockIdx.y * so;
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nper) return;
-    const int G = 2 * N - 1;
-    double2 v[15];
+    double2 v[G];
+#pragma unroll
     for (int a = 0; a < G; ++a) v[a] = in[(size_t)a * nper + i];
-    for (int b = 0; b < G; ++b) {
-        double2 acc = make_double2(0.0, 0.0);
-        for (int a = 0; a < G; ++a) {
-            // sign = +1 (inverse): a = n index (n = a-(N-1)), b = k;  sign = -1: a = k, b = n index
-            const int nn = (sign > 0 ? a : b) - (N - 1);
-            const int kk = sign > 0 ? b : a;
-            const int idx = (int)((((long long)nn * kk) % G + G) % G);
-            const double2 rt = ldroot(roots, idx, sign);
-            acc = cadd(acc, cmul(v[a], rt));
+    // sign = +1 (inverse): v is indexed by n + N - 1, the result by k; -1: the reverse
+    auto sums = [&](auto inverse) {
+#pragma unroll
+        for (int b = 0; b < G; ++b) {
+            double2 acc = make_double2(0.0, 0.0);
+#pragma unroll
+            for (int a = 0; a < G; ++a) {
+                constexpr bool inv = decltype(inverse)::value;
+                const int e = ((inv ? a : b) - (N - 1)) * (inv ? b : a);
+                acc = cadd(acc, cmul(v[a], ldroot(roots, (e % G + G) % G, inv ? 1 : -1)));
+            }
+            out[(size_t)b * nper + i] = make_double2(q * acc.x, q * acc.y);
         }
-        out[(size_t)b * nper + i] = make_double2(q * acc.x, q * acc.y);
-    }
+    };
+    if (sign > 0) sums(std::true_type());
+    else sums(std::false_type());
 }
 
 // ------------------------------------------------------------------ debug export of d
@@ -1180,13 +1194,6 @@ __global__ void k_pole_from_F(int L, int hstride, int ring, Items it, Strides sF
     const int m = i - (L - 1), am = m < 0 ? -m : m;
     const double *src = F + ((size_t)am * hstride + ring) * 4 + (m < 0 ? 2 : 0);
     pole[i] = make_double2(src[0], src[1]);
-}
-
-// p[0 .. n) of every map = 0
-__global__ void k_zero_maps(double *__restrict__ p, size_t n, long long wsd)
-{
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[blockIdx.y * wsd + i] = 0.0;
 }
 
 // ------------------------------------------------------------------ launchers
@@ -1372,8 +1379,20 @@ hipError_t launch_gamma_dft(hipStream_t st, int nmap, long long si, long long so
                             double q, const double *roots, const double2 *in, double2 *out)
 {
     return over_items(nmap, false, [&](int i, int ny) {
-        hipLaunchKernelGGL(k_gamma_dft, dim3((unsigned)((nper + 255) / 256), ny), dim3(256), 0, st, N, nper, sign, q,
-                           roots, in + i * si, out + i * so, si, so);
+        auto go = [&](auto *k) {
+            hipLaunchKernelGGL(k, dim3((unsigned)((nper + 127) / 128), ny), dim3(128), 0, st, nper, sign, q, roots,
+                               in + i * si, out + i * so, si, so);
+        };
+        switch (N) {
+        case 1: return go(k_gamma_dft<1>);
+        case 2: return go(k_gamma_dft<2>);
+        case 3: return go(k_gamma_dft<3>);
+        case 4: return go(k_gamma_dft<4>);
+        case 5: return go(k_gamma_dft<5>);
+        case 6: return go(k_gamma_dft<6>);
+        case 7: return go(k_gamma_dft<7>);
+        default: return go(k_gamma_dft<8>);
+        }
     });
 }
 
@@ -1434,20 +1453,12 @@ hipError_t launch_fadj_scatter(hipStream_t st, int L, int ss, int hstride, doubl
 
 hipError_t launch_mask_low(hipStream_t st, int nmap, int nrun, const SweepRun *runs, int anmax, int nreg, int hstride,
                            const double *cot, const double *csc, const double *F, double *Hx, long long wsd,
-                           long long nF, long long nHx)
+                           long long nF, long long nHx, double *Qx, long long nz)
 {
     const size_t tot = (size_t)anmax * hstride;
     if (tot == 0) return hipSuccess;
     hipLaunchKernelGGL(k_mask_low, dim3((unsigned)((tot + 255) / 256), nmap * nrun), dim3(256), 0, st, nrun, runs, nreg,
-                       hstride, cot, csc, F, Hx, wsd, nF, nHx);
-    S2_LAUNCH_CHECK();
-    return hipSuccess;
-}
-
-hipError_t launch_zero_maps(hipStream_t st, int nmap, long long wsd, double *p, size_t n)
-{
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zero_maps, dim3((unsigned)((n + 255) / 256), nmap), dim3(256), 0, st, p, n, wsd);
+                       hstride, cot, csc, F, Hx, wsd, nF, nHx, Qx, nz);
     S2_LAUNCH_CHECK();
     return hipSuccess;
 }
