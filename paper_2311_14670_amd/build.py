@@ -28,9 +28,12 @@ def _run(cmd):
 def build(verbose=True):
     os.makedirs(BUILD, exist_ok=True)
     objs = []
+    # the DFT kernels hold one loop per stage radix: the constants of all radices hoisted out
+    # of all those loops spill (MW L = 2048 theta filter, 64 maps: 13.6 -> 13.1 ms without)
+    extra = {"s2mi_kernels.hip": ["-mllvm", "-disable-machine-licm"]}
     for src in ["s2mi_kernels.hip", "s2mi_sweep.hip", "s2mi_mfma.hip", "s2mi_capi.hip"]:
         obj = os.path.join(BUILD, src.replace(".hip", ".o"))
-        _run(["hipcc", "-c", "-x", "hip"] + HIP_FLAGS + [os.path.join(CSRC, src), "-o", obj])
+        _run(["hipcc", "-c", "-x", "hip"] + HIP_FLAGS + extra.get(src, []) + [os.path.join(CSRC, src), "-o", obj])
         objs.append(obj)
     obj = os.path.join(BUILD, "s2mi_consts.o")
     _run(["g++", "-c", "-O2", "-fPIC", "-std=gnu++17", "-I", CSRC, os.path.join(CSRC, "s2mi_consts.cpp"), "-o", obj])

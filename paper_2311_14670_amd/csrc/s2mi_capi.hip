@@ -290,6 +290,7 @@ int factor_radices(int n, std::vector<int> &rad)
 struct Staging {
     std::deque<std::vector<double>> d;
     std::deque<std::vector<int>> i;
+    std::deque<std::vector<uint16_t>> u16;
     std::deque<std::vector<long long>> ll;
     std::vector<SweepRun> sr;
 };
@@ -301,6 +302,14 @@ int upload(s2_plan_s *P, T **dst, const std::vector<T> &src, hipStream_t st, con
     if (rc) return rc;
     if (!src.empty()) HIPCHK(hipMemcpyAsync(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice, st), what);
     return S2_OK;
+}
+
+// position of frequency k in the order that the engine's forward stages leave
+int fft_position(const FftArgs &f, int k)
+{
+    int p = 0;
+    for (int s = 0; s < f.nst; k /= f.stage[s].rad, ++s) p += k % f.stage[s].rad * f.stage[s].sub;
+    return p;
 }
 
 int build_fft(s2_plan_s *P, int n, Staging &stg, hipStream_t st, FftArgs *out)
@@ -327,11 +336,33 @@ int build_fft(s2_plan_s *P, int n, Staging &stg, hipStream_t st, FftArgs *out)
         return fail(S2_ERR_UNSUPPORTED, "DFT length %d needs an engine of %d points (> %d)", n, f.len, FFT_MAX_LEN);
     if ((int)rad.size() > FFT_MAX_STAGES) return fail(S2_ERR_UNSUPPORTED, "too many FFT stages for %d", n);
     f.nst = (int)rad.size();
-    for (int s = 0; s < f.nst; ++s) f.rad[s] = rad[s];
+    for (int s = f.nst - 1, q = 1; s >= 0; --s) {
+        FftStage &g = f.stage[s];
+        g.rad = rad[s];
+        g.sub = q;
+        g.nbf = f.len / rad[s];
+        g.tstep = g.nbf / q;
+        g.msub = q > 1 ? 0xffffffffu / (unsigned)q + 1u : 0u;
+        g.mrad = 0xffffffffu / (unsigned)rad[s] + 1u;
+        q *= rad[s];
+    }
+    f.mix = f.len % 16 == 0 ? 15 : f.len % 8 == 0 ? 7 : 0;
+    int rc;
+    if (!f.blue) {
+        std::vector<uint16_t> slot(n);
+        for (int k = 0; k < n; ++k) {
+            const int p = fft_position(f, k);
+            slot[k] = (uint16_t)(p ^ ((p >> 3) & f.mix));
+        }
+        stg.u16.push_back(std::move(slot));
+        uint16_t *sl;
+        if ((rc = upload(P, &sl, stg.u16.back(), st, "fft bin places"))) return rc;
+        f.slot = sl;
+    }
     stg.d.emplace_back();
     host_roots(f.len, &stg.d.back());
     double *tw;
-    int rc = upload(P, &tw, stg.d.back(), st, "fft twiddles");
+    rc = upload(P, &tw, stg.d.back(), st, "fft twiddles");
     if (rc) return rc;
     f.tw = tw;
     if (f.blue) {
@@ -619,6 +650,15 @@ static int plan_create_impl(s2_plan_t *out, int L, int spin, int N, s2_sampling_
         stg.d.emplace_back(); std::vector<double> &ph = stg.d.back();
         host_mw_filter(L, sampling == S2_MWSS, &wq, &ph);
         if ((rc = upload(P, &P->wq, wq, st, "mw filter weights"))) return bail(rc);
+        if (!P->dft.conv) {                                // in the order of the LDS engine's positions
+            const std::vector<double> nat(ph);
+            const FftArgs &f = P->fN;
+            for (int k = 0; k < f.n; ++k) {
+                const int p = fft_position(f, k);
+                ph[2 * p] = nat[2 * k];
+                ph[2 * p + 1] = nat[2 * k + 1];
+            }
+        }
         if ((rc = upload(P, &P->ph, ph, st, "mw half-shift phases"))) return bail(rc);
     }
     if (sampling == S2_MW && spin == 0) {

@@ -44,67 +44,6 @@ __host__ __device__ inline int conv_index(int M, int k)
     return (p % V) * (M / V) + p / V;
 }
 
-// In-place DFT of N = 2, 4, 8, 16 registers, natural order: v_q = sum_r v_r e^{S 2 pi i r q / N}.
-template <int N, int S>
-__device__ __forceinline__ void dft_reg(double2 *v)
-{
-    if constexpr (N == 2) {
-        const double2 a = v[0];
-        v[0] = cadd(a, v[1]);
-        v[1] = csub(a, v[1]);
-    } else if constexpr (N == 4) {
-        const double2 a0 = cadd(v[0], v[2]), a1 = csub(v[0], v[2]);
-        const double2 b0 = cadd(v[1], v[3]), b1 = cmuli(csub(v[1], v[3]), S);
-        v[0] = cadd(a0, b0);
-        v[1] = cadd(a1, b1);
-        v[2] = csub(a0, b0);
-        v[3] = csub(a1, b1);
-    } else if constexpr (N == 8) {
-        double2 e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
-        dft_reg<4, S>(e);
-        dft_reg<4, S>(o);
-        constexpr double h = 0.70710678118654752440;
-        const double2 o1 = make_double2(h * (o[1].x - S * o[1].y), h * (o[1].y + S * o[1].x));
-        const double2 o3 = make_double2(h * (-o[3].x - S * o[3].y), h * (-o[3].y + S * o[3].x));
-        o[2] = cmuli(o[2], S);
-        v[0] = cadd(e[0], o[0]);
-        v[4] = csub(e[0], o[0]);
-        v[1] = cadd(e[1], o1);
-        v[5] = csub(e[1], o1);
-        v[2] = cadd(e[2], o[2]);
-        v[6] = csub(e[2], o[2]);
-        v[3] = cadd(e[3], o3);
-        v[7] = csub(e[3], o3);
-    } else {
-        // r = r0 + 4 r1, q = q0 + 4 q1
-        constexpr double c1 = 0.92387953251128675613, s1 = 0.38268343236508977173, h = 0.70710678118654752440;
-        double2 a[4][4];                                 // [r0][q0]
-#pragma unroll
-        for (int r0 = 0; r0 < 4; ++r0) {
-#pragma unroll
-            for (int r1 = 0; r1 < 4; ++r1) a[r0][r1] = v[r0 + 4 * r1];
-            dft_reg<4, S>(a[r0]);
-        }
-        auto mul8 = [](double2 x) { return make_double2(h * (x.x - S * x.y), h * (x.y + S * x.x)); };   // e^{S i pi/4}
-        a[1][1] = cmul(a[1][1], make_double2(c1, S * s1));
-        a[1][2] = mul8(a[1][2]);
-        a[1][3] = cmul(a[1][3], make_double2(s1, S * c1));
-        a[2][1] = mul8(a[2][1]);
-        a[2][2] = cmuli(a[2][2], S);
-        a[2][3] = cmuli(mul8(a[2][3]), S);
-        a[3][1] = cmul(a[3][1], make_double2(s1, S * c1));
-        a[3][2] = cmuli(mul8(a[3][2]), S);
-        a[3][3] = cmul(a[3][3], make_double2(-c1, -S * s1));
-#pragma unroll
-        for (int q0 = 0; q0 < 4; ++q0) {
-            double2 b[4] = {a[0][q0], a[1][q0], a[2][q0], a[3][q0]};
-            dft_reg<4, S>(b);
-#pragma unroll
-            for (int q1 = 0; q1 < 4; ++q1) v[q0 + 4 * q1] = b[q1];
-        }
-    }
-}
-
 // The engine: M points of which a sequence occupies the first n <= (M + 1) / 2 (SPLIT: a
 // convolution of 2 M points of which n < M are occupied, as two of M: the even samples of
 // the spectrum are the transform of u, the odd ones that of u w^j, w = e^{-pi i / M}, and the
@@ -160,20 +99,6 @@ struct ConvDft {
         }
     }
 
-    // v[q] times w^q, q < V, w = e^{S 2 pi i j / B} (from the roots of M points); the
-    // powers as products of two lower ones, so their rounding grows with log2 q
-    template <int S>
-    static __device__ __forceinline__ void twiddle(double2 (&v)[V], const double *tw, int idx)
-    {
-        double2 w[V];
-        w[1] = ldroot(tw, idx, S);
-#pragma unroll
-        for (int q = 1; q < V; ++q) {
-            if (q > 1) w[q] = cmul(w[q / 2], w[q - q / 2]);
-            v[q] = cmul(v[q], w[q]);
-        }
-    }
-
     template <int B>
     static __device__ __forceinline__ void forward(double2 (&v)[V], double *xb, const double *tw)
     {
@@ -182,7 +107,7 @@ struct ConvDft {
         dft_reg<V, -1>(v);
         if constexpr (Q > 1) {
             const int j = t & (Q - 1), b = t / Q * B;
-            twiddle<-1>(v, tw, j * (M / B));
+            twiddle<V, -1>(v, tw, j * (M / B));
             if constexpr (Q >= V) {
                 exchange<Q, Q / V>(v, xb, b + j, t / (Q / V) * Q + (t & (Q / V - 1)));
                 forward<Q>(v, xb, tw);
@@ -209,7 +134,7 @@ struct ConvDft {
                 for (int s = 0; s < V; s += Q) dft_reg<Q, 1>(v + s);
                 exchange<1, Q>(v, xb, t * V, b + j);
             }
-            twiddle<1>(v, tw, j * (M / B));
+            twiddle<V, 1>(v, tw, j * (M / B));
         }
         dft_reg<V, 1>(v);
     }
@@ -257,11 +182,15 @@ struct ConvDft {
         }
     }
 
-    // DFT of get(k), k < n = f->n: KEEP: into buf (natural order), else handed to
-    // put(k, value).  get may read buf.
-    template <bool FILL, bool KEEP, class Get, class Put>
-    static __device__ __forceinline__ void dft(double2 *buf, const FftArgs *f, int sign, double2 *, Get get, Put put)
+    static __device__ __forceinline__ int slot(const FftArgs *, int k) { return k; }
+    static __device__ __forceinline__ int point(const FftArgs *, int t) { return t; }
+
+    // sign = -1: DFT of get(k), k < n = f->n, into the bins' slots of buf; +1: of the bins in their
+    // slots, handed to put(k, value) (LDS: which stores into buf)
+    template <int SIGN, bool LDS, class Get, class Put>
+    static __device__ __forceinline__ void dft(double2 *buf, const FftArgs *f, double2 *, Get get, Put put)
     {
+        constexpr bool KEEP = SIGN < 0;
         const int n = f->n;
         const double2 *ch = reinterpret_cast<const double2 *>(f->chirp);
         double2 v[V];
@@ -271,27 +200,25 @@ struct ConvDft {
             const int k = t + T * i;
             v[i] = make_double2(0.0, 0.0);
             if (k < n) {
-                double2 x = get(k);
-                if (sign > 0) x.y = -x.y;
+                const double2 x = KEEP ? get(k) : cconj(buf[k]);
                 v[i] = cmulc(x, ch[k]);
             }
             few_loads(i);
         }
         convolve(v, reinterpret_cast<double *>(buf), f);
-        if (KEEP) __syncthreads();
+        if (KEEP || LDS) __syncthreads();
         t = first_point();
 #pragma unroll
         for (int i = 0; i < V; ++i) {
             const int k = t + T * i;
             if (k < n) {
-                double2 y = cmulc(v[i], ch[k]);
-                if (sign > 0) y.y = -y.y;
+                const double2 y = cmulc(v[i], ch[k]);
                 if constexpr (KEEP) buf[k] = y;
-                else put(k, y);
+                else put(k, cconj(y));
             }
             few_loads(i);
         }
-        if (KEEP) __syncthreads();
+        if (KEEP || LDS) __syncthreads();
     }
 };
 
@@ -300,17 +227,13 @@ struct LdsDft {
     static constexpr int MAXT = 1024, WPE = 4;
     static constexpr bool CONV = false;
 
-    template <bool FILL, bool KEEP, class Get, class Put>
-    static __device__ __forceinline__ void dft(double2 *buf, const FftArgs *f, int sign, double2 *scr, Get get, Put put)
+    static __device__ __forceinline__ int slot(const FftArgs *f, int k) { return fft_slot(f, k); }
+    static __device__ __forceinline__ int point(const FftArgs *f, int t) { return fft_place(f, t); }
+
+    template <int SIGN, bool LDS, class Get, class Put>
+    static __device__ __forceinline__ void dft(double2 *buf, const FftArgs *f, double2 *scr, Get get, Put put)
     {
-        const int n = f->n;
-        if constexpr (FILL) {
-            for (int k = threadIdx.x; k < n; k += blockDim.x) buf[k] = get(k);
-            __syncthreads();
-        }
-        dft_lds(buf, f, sign, scr);
-        if constexpr (!KEEP)
-            for (int k = threadIdx.x; k < n; k += blockDim.x) put(k, buf[k]);
+        dft_lds<SIGN>(buf, f, scr, get, put);
     }
 };
 

@@ -2,15 +2,30 @@
 // in LDS.  Used for the per-ring phi-DFTs (Eqs. 31-32) and the MW theta
 // half-sample shifts.
 //
-// Engine: self-sorting (Stockham) mixed-radix FFT over radices
-// {2,3,4,5,7,8,9,11,13}, in place in LDS: every stage reads all its butterfly
-// inputs into registers, synchronises, then writes.  Lengths with a larger
+// Engine: mixed-radix FFT over radices {2,3,4,5,7,8,9,11,13}, every butterfly in place
+// in LDS.  Forward (sign -1) by decimation in frequency: natural order in, the spectrum
+// at fft_pos(k); inverse (sign +1) by decimation in time, the same stages backwards.  So a
+// stage is one read and one write of the sequence and one barrier, a thread holds one
+// butterfly at a time, a forward transform followed by an inverse one never reorders, and
+// its innermost two stages (with a product in between) are one pass, as are an inverse's
+// last stage and the first of the forward that follows.  First loads and last stores go
+// straight to their source and target.  Lengths with a larger
 // prime factor go through Bluestein's chirp-z identity
 //   X_k = conj(c_k) sum_j (x_j conj(c_j)) c_{k-j},  c_j = e^{i pi j^2 / n},
-// evaluated as a power-of-two circular convolution.
+// evaluated as a power-of-two circular convolution (rings of one length: s2mi_conv.h).
+//
+// What bounds it: latency (barriers, first loads of a stage) and the FP64 work of the
+// butterflies; 64 KiB of LDS at 4095 points leave two workgroups on a compute unit.
+// Measured on MI355X, ms, self-sorting stages with a barrier on both sides of each -> this
+// form: 4095 points (MW L = 2048, one map / 64 maps) inverse phi-DFT 0.178 / 4.6 -> 0.176 /
+// 4.6, forward 0.113 / 7.9 -> 0.097 / 6.5, theta filter 0.253 / 15.0 -> 0.221 / 13.1; HEALPix
+// nside 1024, L = 2048, real 0.54, 0.32 -> 0.48, 0.24; nside 64, L = 128, 8 maps 0.026, 0.021
+// -> 0.023, 0.017.  (The filter's rings kept in registers to its end: no gain, spills.)
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "s2mi_internal.h"
 
@@ -81,75 +96,166 @@ template <> struct OddRoots<13> {
                                      -0.9927088740980539928, -0.82298386589365639458, -0.46472317204376854566};
 };
 
-// Small DFT y_q = sum_r v_r e^{sign 2 pi i r q / R}, stored to out[q * os].
-// Odd R: with a_r = v_r + v_{R-r}, b_r = v_r - v_{R-r} (r <= (R-1)/2),
-//   y_q, y_{R-q} = v_0 + sum_r a_r cos(2 pi rq/R) +- sign i sum_r b_r sin(2 pi rq/R).
-template <int R>
-__device__ __forceinline__ void dft_small_store(double2 (&v)[R], int sign, double2 *out, int os)
+// In-place DFT of N = 2, 4, 8, 16 registers, natural order: v_q = sum_r v_r e^{S 2 pi i r q / N}.
+template <int N, int S>
+__device__ __forceinline__ void dft_reg(double2 *v)
 {
-    if constexpr (R == 2) {
-        out[0] = cadd(v[0], v[1]);
-        out[os] = csub(v[0], v[1]);
-    } else if constexpr (R == 4) {
+    if constexpr (N == 2) {
+        const double2 a = v[0];
+        v[0] = cadd(a, v[1]);
+        v[1] = csub(a, v[1]);
+    } else if constexpr (N == 4) {
         const double2 a0 = cadd(v[0], v[2]), a1 = csub(v[0], v[2]);
-        const double2 b0 = cadd(v[1], v[3]), b1 = cmuli(csub(v[1], v[3]), sign);
-        out[0] = cadd(a0, b0);
-        out[2 * os] = csub(a0, b0);
-        out[os] = cadd(a1, b1);
-        out[3 * os] = csub(a1, b1);
-    } else if constexpr (R == 8) {
-        // two radix-4 on even/odd, then combine with e^{sign 2 pi i k/8}
-        const double2 e0 = cadd(v[0], v[4]), e1 = csub(v[0], v[4]);
-        const double2 e2 = cadd(v[2], v[6]), e3 = cmuli(csub(v[2], v[6]), sign);
-        const double2 E0 = cadd(e0, e2), E2 = csub(e0, e2), E1 = cadd(e1, e3), E3 = csub(e1, e3);
-        const double2 o0 = cadd(v[1], v[5]), o1 = csub(v[1], v[5]);
-        const double2 o2 = cadd(v[3], v[7]), o3 = cmuli(csub(v[3], v[7]), sign);
-        const double2 O0 = cadd(o0, o2), O2 = csub(o0, o2), O1 = cadd(o1, o3), O3 = csub(o1, o3);
-        const double h = 0.70710678118654752440;
-        const double2 t1 = make_double2(h * (O1.x - sign * O1.y), h * (O1.y + sign * O1.x));
-        const double2 t2 = cmuli(O2, sign);
-        const double2 t3 = make_double2(h * (-O3.x - sign * O3.y), h * (-O3.y + sign * O3.x));
-        out[0] = cadd(E0, O0);
-        out[4 * os] = csub(E0, O0);
-        out[os] = cadd(E1, t1);
-        out[5 * os] = csub(E1, t1);
-        out[2 * os] = cadd(E2, t2);
-        out[6 * os] = csub(E2, t2);
-        out[3 * os] = cadd(E3, t3);
-        out[7 * os] = csub(E3, t3);
-    } else if constexpr (R == 9) {
-        // 9 = 3 x 3: with r = 3j + k and q = p + 3s, y_q = sum_k w9^{kp} w3^{ks}
-        // (sum_j v_{3j+k} w3^{jp}): three radix-3 DFTs, twiddles, three more
-        constexpr double c3 = -0.5, s3 = 0.86602540378443864676;   // cos, sin of 2 pi / 3
-        auto dft3 = [sign](double2 a, double2 b, double2 c, double2 &y0, double2 &y1, double2 &y2) {
-            const double2 t = cadd(b, c), d = csub(b, c);
-            y0 = cadd(a, t);
-            const double2 mid = make_double2(fma(c3, t.x, a.x), fma(c3, t.y, a.y));
-            const double2 rot = cmuli(make_double2(s3 * d.x, s3 * d.y), sign);   // sign i s3 (b - c)
-            y1 = cadd(mid, rot);
-            y2 = csub(mid, rot);
-        };
-        double2 t[3][3];                                  // t[k][p]
-#pragma unroll
-        for (int k = 0; k < 3; ++k) dft3(v[k], v[3 + k], v[6 + k], t[k][0], t[k][1], t[k][2]);
-        const double sg = sign < 0 ? -1.0 : 1.0;          // w9^e = cos(2 pi e / 9) + sign i sin(2 pi e / 9)
-        const double2 w1 = make_double2(0.76604444311897803520, sg * 0.64278760968653932632);
-        const double2 w2 = make_double2(0.17364817766693034885, sg * 0.98480775301220805937);
-        const double2 w4 = make_double2(-0.93969262078590838405, sg * 0.34202014332566873304);
-        t[1][1] = cmul(t[1][1], w1);
-        t[1][2] = cmul(t[1][2], w2);
-        t[2][1] = cmul(t[2][1], w2);
-        t[2][2] = cmul(t[2][2], w4);
-#pragma unroll
-        for (int p = 0; p < 3; ++p) {
-            double2 y0, y1, y2;
-            dft3(t[0][p], t[1][p], t[2][p], y0, y1, y2);
-            out[p * os] = y0;
-            out[(p + 3) * os] = y1;
-            out[(p + 6) * os] = y2;
-        }
+        const double2 b0 = cadd(v[1], v[3]), b1 = cmuli(csub(v[1], v[3]), S);
+        v[0] = cadd(a0, b0);
+        v[1] = cadd(a1, b1);
+        v[2] = csub(a0, b0);
+        v[3] = csub(a1, b1);
+    } else if constexpr (N == 8) {
+        double2 e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
+        dft_reg<4, S>(e);
+        dft_reg<4, S>(o);
+        constexpr double h = 0.70710678118654752440;
+        const double2 o1 = make_double2(h * (o[1].x - S * o[1].y), h * (o[1].y + S * o[1].x));
+        const double2 o3 = make_double2(h * (-o[3].x - S * o[3].y), h * (-o[3].y + S * o[3].x));
+        o[2] = cmuli(o[2], S);
+        v[0] = cadd(e[0], o[0]);
+        v[4] = csub(e[0], o[0]);
+        v[1] = cadd(e[1], o1);
+        v[5] = csub(e[1], o1);
+        v[2] = cadd(e[2], o[2]);
+        v[6] = csub(e[2], o[2]);
+        v[3] = cadd(e[3], o3);
+        v[7] = csub(e[3], o3);
     } else {
-        constexpr int H = (R - 1) / 2;
+        // r = r0 + 4 r1, q = q0 + 4 q1
+        constexpr double c1 = 0.92387953251128675613, s1 = 0.38268343236508977173, h = 0.70710678118654752440;
+        double2 a[4][4];                                 // [r0][q0]
+#pragma unroll
+        for (int r0 = 0; r0 < 4; ++r0) {
+#pragma unroll
+            for (int r1 = 0; r1 < 4; ++r1) a[r0][r1] = v[r0 + 4 * r1];
+            dft_reg<4, S>(a[r0]);
+        }
+        auto mul8 = [](double2 x) { return make_double2(h * (x.x - S * x.y), h * (x.y + S * x.x)); };   // e^{S i pi/4}
+        a[1][1] = cmul(a[1][1], make_double2(c1, S * s1));
+        a[1][2] = mul8(a[1][2]);
+        a[1][3] = cmul(a[1][3], make_double2(s1, S * c1));
+        a[2][1] = mul8(a[2][1]);
+        a[2][2] = cmuli(a[2][2], S);
+        a[2][3] = cmuli(mul8(a[2][3]), S);
+        a[3][1] = cmul(a[3][1], make_double2(s1, S * c1));
+        a[3][2] = cmuli(mul8(a[3][2]), S);
+        a[3][3] = cmul(a[3][3], make_double2(-c1, -S * s1));
+#pragma unroll
+        for (int q0 = 0; q0 < 4; ++q0) {
+            double2 b[4] = {a[0][q0], a[1][q0], a[2][q0], a[3][q0]};
+            dft_reg<4, S>(b);
+#pragma unroll
+            for (int q1 = 0; q1 < 4; ++q1) v[q0 + 4 * q1] = b[q1];
+        }
+    }
+}
+
+// The same for R = 9.
+template <int S>
+__device__ __forceinline__ void dft_nine(double2 (&v)[9])
+{
+    // 9 = 3 x 3: with r = 3j + k and q = p + 3s, y_q = sum_k w9^{kp} w3^{ks}
+    // (sum_j v_{3j+k} w3^{jp}): three radix-3 DFTs, twiddles, three more
+    constexpr double c3 = -0.5, s3 = 0.86602540378443864676;   // cos, sin of 2 pi / 3
+    auto dft3 = [](double2 a, double2 b, double2 c, double2 &y0, double2 &y1, double2 &y2) {
+        const double2 t = cadd(b, c), d = csub(b, c);
+        y0 = cadd(a, t);
+        const double2 mid = make_double2(fma(c3, t.x, a.x), fma(c3, t.y, a.y));
+        const double2 rot = cmuli(make_double2(s3 * d.x, s3 * d.y), S);   // S i s3 (b - c)
+        y1 = cadd(mid, rot);
+        y2 = csub(mid, rot);
+    };
+    double2 t[3][3];                                  // t[k][p]
+#pragma unroll
+    for (int k = 0; k < 3; ++k) dft3(v[k], v[3 + k], v[6 + k], t[k][0], t[k][1], t[k][2]);
+    constexpr double sg = S;                          // w9^e = cos(2 pi e / 9) + S i sin(2 pi e / 9)
+    const double2 w1 = make_double2(0.76604444311897803520, sg * 0.64278760968653932632);
+    const double2 w2 = make_double2(0.17364817766693034885, sg * 0.98480775301220805937);
+    const double2 w4 = make_double2(-0.93969262078590838405, sg * 0.34202014332566873304);
+    t[1][1] = cmul(t[1][1], w1);
+    t[1][2] = cmul(t[1][2], w2);
+    t[2][1] = cmul(t[2][1], w2);
+    t[2][2] = cmul(t[2][2], w4);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        double2 y0, y1, y2;
+        dft3(t[0][p], t[1][p], t[2][p], y0, y1, y2);
+        v[p] = y0;
+        v[p + 3] = y1;
+        v[p + 6] = y2;
+    }
+}
+
+// v[q] times w^q, q < R, w = e^{S 2 pi i idx / len}; the powers as products of two lower
+// ones, so their rounding grows with log2 q
+template <int R, int S>
+__device__ __forceinline__ void twiddle(double2 (&v)[R], const double *tw, int idx)
+{
+    double2 w[R];
+    w[1] = ldroot(tw, idx, S);
+#pragma unroll
+    for (int q = 1; q < R; ++q) {
+        if (q > 1) w[q] = cmul(w[q / 2], w[q - q / 2]);
+        v[q] = cmul(v[q], w[q]);
+    }
+}
+
+// One butterfly of radix R: the twiddled or plain inputs and outputs of a stage.
+template <int R, bool PAIRS = (R % 2 == 1 && R != 9)>
+struct Butterfly {                                       // 2, 4, 8, 9
+    double2 v[R];
+    template <int S>
+    __device__ __forceinline__ void twiddle_in(const double *tw, int idx)
+    {
+        twiddle<R, S>(v, tw, idx);
+    }
+    // out(q, y_q w^q), w = e^{S 2 pi i idx / len} (TW; else w = 1)
+    template <int S, bool TW, class Out>
+    __device__ __forceinline__ void run(const double *tw, int idx, Out out)
+    {
+        if constexpr (R == 9) dft_nine<S>(v);
+        else dft_reg<R, S>(v);
+        if (TW && idx > 0) twiddle<R, S>(v, tw, idx);
+#pragma unroll
+        for (int q = 0; q < R; ++q) out(q, v[q]);
+    }
+};
+
+// Odd R: with a_r = v_r + v_{R-r}, b_r = v_r - v_{R-r} (r <= (R-1)/2),
+//   y_q, y_{R-q} = v_0 + sum_r a_r cos(2 pi rq/R) +- S i sum_r b_r sin(2 pi rq/R),
+// a pair at a time, so that the outputs need no registers of their own; the twiddles of a
+// pair are w^q, by repeated products, and w^{R-q} = w^R conj(w^q), w^R from the table.
+template <int R>
+struct Butterfly<R, true> {
+    static constexpr int H = (R - 1) / 2;
+    double2 v[R];
+    template <int S>
+    __device__ __forceinline__ void twiddle_in(const double *tw, int idx)
+    {
+        const double2 w1 = ldroot(tw, idx, S), wR = ldroot(tw, R * idx, S);
+        double2 w = w1;
+#pragma unroll
+        for (int r = 1; r <= H; ++r) {
+            if (r > 1) w = cmul(w, w1);
+            v[r] = cmul(v[r], w);
+            v[R - r] = cmul(v[R - r], cmulc(wR, w));
+        }
+    }
+    template <int S, bool TW, class Out>
+    __device__ __forceinline__ void run(const double *tw, int idx, Out out)
+    {
+        double2 w1, wR, w;
+        if constexpr (TW) {
+            w1 = ldroot(tw, idx, S);
+            wR = ldroot(tw, R * idx, S);
+        }
         double2 y0 = v[0];
 #pragma unroll
         for (int r = 1; r <= H; ++r) {
@@ -158,7 +264,7 @@ __device__ __forceinline__ void dft_small_store(double2 (&v)[R], int sign, doubl
             v[R - r] = b;
             y0 = cadd(y0, a);
         }
-        out[0] = y0;
+        out(0, y0);
 #pragma unroll
         for (int q = 1; q <= H; ++q) {
             double2 A = v[0], B = make_double2(0.0, 0.0);
@@ -170,105 +276,183 @@ __device__ __forceinline__ void dft_small_store(double2 (&v)[R], int sign, doubl
                 B.x = fma(v[R - r].x, s, B.x);
                 B.y = fma(v[R - r].y, s, B.y);
             }
-            const double2 iB = cmuli(B, sign);
-            out[q * os] = cadd(A, iB);
-            out[(R - q) * os] = csub(A, iB);
+            const double2 iB = cmuli(B, S);
+            if constexpr (TW) {
+                w = q > 1 ? cmul(w, w1) : w1;
+                out(q, cmul(cadd(A, iB), w));
+                out(R - q, cmul(csub(A, iB), cmulc(wR, w)));
+            } else {
+                out(q, cadd(A, iB));
+                out(R - q, csub(A, iB));
+            }
         }
+    }
+};
+
+// LDS place of point i: in lengths with enough factors of two the low bits are mixed with
+// the next ones, so that a last stage of radix 8 (a thread's points side by side) meets
+// the banks without conflict.
+__device__ __forceinline__ int fft_place(const FftArgs *f, int i) { return i ^ ((i >> 3) & f->mix); }
+
+// position of frequency k in the order the forward stages leave
+__device__ __forceinline__ int fft_pos(const FftArgs *f, int k)
+{
+    int p = 0;
+    for (int s = 0; s < f->nst; ++s) {
+        const int q = (int)__umulhi((unsigned)k, f->stage[s].mrad);   // k / rad
+        p += (k - q * f->stage[s].rad) * f->stage[s].sub;
+        k = q;
+    }
+    return p;
+}
+
+// P2: lengths that are powers of two; SMALL: radices up to 9
+template <bool P2, bool SMALL, class G>
+__device__ __forceinline__ void fft_radix(int R, G g)
+{
+    if constexpr (P2) {
+        if (R == 8) g(std::integral_constant<int, 8>());
+        else if (R == 4) g(std::integral_constant<int, 4>());
+        else g(std::integral_constant<int, 2>());
+        return;
+    }
+    switch (R) {
+    case 2: g(std::integral_constant<int, 2>()); break;
+    case 3: g(std::integral_constant<int, 3>()); break;
+    case 4: g(std::integral_constant<int, 4>()); break;
+    case 5: g(std::integral_constant<int, 5>()); break;
+    case 7: g(std::integral_constant<int, 7>()); break;
+    case 8: g(std::integral_constant<int, 8>()); break;
+    case 9: g(std::integral_constant<int, 9>()); break;
+    default: break;
+    }
+    if constexpr (!SMALL) switch (R) {
+    case 11: g(std::integral_constant<int, 11>()); break;
+    case 13: g(std::integral_constant<int, 13>()); break;
+    default: break;
     }
 }
 
-// One Stockham stage of radix R; NB butterflies per thread at most.
-template <int R, int NB>
-__device__ __forceinline__ void fft_stage(double2 *buf, int len, int Ns, const double *tw, int sign)
+// Stage s over the sequence: a butterfly's points i = base + sub r come from load(i) and go
+// to store(i, v).
+//   FWD: stage s of the forward transform (butterfly, twiddles)
+//   INV: of the inverse (twiddles, butterfly)
+//   TURN, s = 0: the last inverse and the first forward stage, mid(i, v) on the points between
+//   INNER, s = nst - 1: the last forward and the first inverse stage, mid(p, v) on the
+//   positions of the spectrum
+enum { FFT_FWD, FFT_INV, FFT_TURN, FFT_INNER };
+template <int KIND, bool P2 = false, class Load, class Mid, class Store>
+__device__ __forceinline__ void fft_stage(const FftArgs *f, int s, Load load, Mid mid, Store store)
 {
-    const int T = blockDim.x, tid = threadIdx.x;
-    const int nbf = len / R;
-    double2 v[NB][R];
+    const FftStage *g = f->stage + s;
+    const double *tw = f->tw;
+    const int sub = g->sub, nbf = g->nbf, tstep = g->tstep, T = blockDim.x;
+    const unsigned msub = g->msub;                           // j / sub = umulhi(j, msub), sub > 1
+    fft_radix<P2, KIND == FFT_TURN || KIND == FFT_INNER>(g->rad, [&](auto Rc) {
+        constexpr int R = decltype(Rc)::value;
+        const int B = sub * R;
+#pragma unroll 1
+        for (int j = threadIdx.x; j < nbf; j += T) {
+            const int blk = sub > 1 ? (int)__umulhi((unsigned)j, msub) : j, jj = j - blk * sub;
+            const int base = blk * B + jj;
+            const int idx = jj * tstep;
+            Butterfly<R> x;
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int j = tid + b * T;
-        if (j < nbf) {
-#pragma unroll
-            for (int r = 0; r < R; ++r) v[b][r] = buf[j + r * nbf];
-        }
-    }
-    __syncthreads();
-    const int tstep = len / (Ns * R);
-    // j / Ns by one high multiply with ceil(2^32 / Ns): exact for j < 2^16, Ns <= 2^13
-    // (the error j (ceil(2^32/Ns) - 2^32/Ns) / 2^32 < 2^-19 stays below 1/Ns)
-    const unsigned mag = Ns > 1 ? 0xffffffffu / (unsigned)Ns + 1u : 0u;
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int j = tid + b * T;
-        if (j < nbf) {
-            const int jq = Ns > 1 ? (int)__umulhi((unsigned)j, mag) : j;   // j / Ns
-            const int k = j - jq * Ns;                                      // j % Ns
-            if (Ns > 1) {
-                // twiddles w^r, r < R, by repeated multiplication from one table read (the
-                // R-1 reads at stride r lanes apart touched a line each; rounding grows
-                // like r ulp, r <= 12)
-                const double2 w1 = ldroot(tw, k * tstep, sign);
-                double2 w = w1;
-                v[b][1] = cmul(v[b][1], w);
-#pragma unroll
-                for (int r = 2; r < R; ++r) {
-                    w = cmul(w, w1);
-                    v[b][r] = cmul(v[b][r], w);
+            for (int r = 0; r < R; ++r) x.v[r] = load(base + sub * r);
+            auto out = [&](int q, double2 y) { store(base + sub * q, y); };
+            if constexpr (KIND == FFT_FWD) {
+                x.template run<-1, true>(tw, idx, out);
+            } else if constexpr (KIND == FFT_INV) {
+                if (sub > 1) x.template twiddle_in<1>(tw, idx);
+                x.template run<1, false>(tw, 0, out);
+            } else {
+                Butterfly<R> y;
+                auto turn = [&](int q, double2 z) { y.v[q] = mid(base + sub * q, z); };
+                if constexpr (KIND == FFT_INNER) {
+                    x.template run<-1, false>(tw, 0, turn);
+                    y.template run<1, false>(tw, 0, out);
+                } else {
+                    if (sub > 1) x.template twiddle_in<1>(tw, idx);
+                    x.template run<1, false>(tw, 0, turn);
+                    y.template run<-1, true>(tw, idx, out);
                 }
             }
-            const int o = jq * Ns * R + k;
-            dft_small_store<R>(v[b], sign, buf + o, Ns);
         }
-    }
+    });
     __syncthreads();
 }
 
-// With blockDim.x >= len/8 (plan-time rule) a thread holds at most 8 values,
-// i.e. NB <= ceil(8/R) butterflies; only those variants are instantiated.
-template <int R>
-__device__ __forceinline__ void fft_stage_nb(double2 *buf, int len, int Ns, const double *tw, int sign)
+// INNER and TURN for any radix: 11 and 13 as two stages (both butterflies at once take more
+// registers than the 128 of a wave with three others)
+template <class Load, class Mid, class Store>
+__device__ __forceinline__ void fft_inner(const FftArgs *f, int s, Load load, Mid mid, Store store)
 {
-    constexpr int NBMAX = (8 + R - 1) / R;
-    const int nb = (len / R + blockDim.x - 1) / blockDim.x;
-    if (nb <= 1 || NBMAX == 1) fft_stage<R, 1>(buf, len, Ns, tw, sign);
-    else if (nb == 2 || NBMAX == 2) fft_stage<R, (NBMAX >= 2 ? 2 : 1)>(buf, len, Ns, tw, sign);
-    else if (nb == 3 || NBMAX == 3) fft_stage<R, (NBMAX >= 3 ? 3 : 1)>(buf, len, Ns, tw, sign);
-    else fft_stage<R, (NBMAX >= 4 ? 4 : 1)>(buf, len, Ns, tw, sign);
+    if (f->stage[s].rad <= 9) {
+        fft_stage<FFT_INNER>(f, s, load, mid, store);
+    } else {
+        fft_stage<FFT_FWD>(f, s, load, mid, [&](int i, double2 v) { store(i, mid(i, v)); });
+        fft_stage<FFT_INV>(f, s, load, mid, store);
+    }
 }
-
-// Unnormalised DFT of length f.len in LDS: X_k = sum_j x_j e^{sign 2 pi i jk/len}.
-// Requires blockDim.x * 4 * radix >= len for every stage radix (enforced at plan time).
-// f points at a FftArgs in device memory (uniform): its fields are read with
-// scalar loads, never copied into a private array.
-__device__ __forceinline__ void fft_engine(double2 *buf, const FftArgs *f, int sign)
+template <class Load, class Mid, class Store>
+__device__ __forceinline__ void fft_turn(const FftArgs *f, Load load, Mid mid, Store store)
 {
-    const int len = f->len, nst = f->nst;
-    const double *tw = f->tw;
-    int Ns = 1;
-    for (int s = 0; s < nst; ++s) {
-        const int R = f->rad[s];
-        switch (R) {
-        case 2: fft_stage_nb<2>(buf, len, Ns, tw, sign); break;
-        case 3: fft_stage_nb<3>(buf, len, Ns, tw, sign); break;
-        case 4: fft_stage_nb<4>(buf, len, Ns, tw, sign); break;
-        case 5: fft_stage_nb<5>(buf, len, Ns, tw, sign); break;
-        case 7: fft_stage_nb<7>(buf, len, Ns, tw, sign); break;
-        case 8: fft_stage_nb<8>(buf, len, Ns, tw, sign); break;
-        case 9: fft_stage_nb<9>(buf, len, Ns, tw, sign); break;
-        case 11: fft_stage_nb<11>(buf, len, Ns, tw, sign); break;
-        default: fft_stage_nb<13>(buf, len, Ns, tw, sign); break;
-        }
-        Ns *= R;
+    if (f->stage[0].rad <= 9) {
+        fft_stage<FFT_TURN>(f, 0, load, mid, store);
+    } else {
+        fft_stage<FFT_INV>(f, 0, load, mid, [&](int i, double2 v) { store(i, mid(i, v)); });
+        fft_stage<FFT_FWD>(f, 0, load, mid, store);
     }
 }
 
-// Unnormalised DFT of length f.n of buf[0..n) in LDS (buf must hold f.len
-// entries).  sign = -1: forward, +1: inverse.  Leaves the result in buf[0..n).
+struct FftNone {
+    __device__ double2 operator()(int) const { return make_double2(0.0, 0.0); }
+    __device__ double2 operator()(int, double2 v) const { return v; }
+};
+
+// forward stages a .. b - 1 in LDS (inverse: b - 1 down to a)
+template <bool P2 = false>
+__device__ __forceinline__ void fft_forward(double2 *buf, const FftArgs *f, int a, int b)
+{
+    auto get = [&](int i) { return buf[fft_place(f, i)]; };
+    auto put = [&](int i, double2 v) { buf[fft_place(f, i)] = v; };
+#pragma unroll 1
+    for (int s = a; s < b; ++s) fft_stage<FFT_FWD, P2>(f, s, get, FftNone(), put);
+}
+template <bool P2 = false>
+__device__ __forceinline__ void fft_inverse(double2 *buf, const FftArgs *f, int a, int b)
+{
+    auto get = [&](int i) { return buf[fft_place(f, i)]; };
+    auto put = [&](int i, double2 v) { buf[fft_place(f, i)] = v; };
+#pragma unroll 1
+    for (int s = b - 1; s >= a; --s) fft_stage<FFT_INV, P2>(f, s, get, FftNone(), put);
+}
+
+// The cyclic convolution of len points, a power of two above 8, in LDS: load(i) -> spectrum ->
+// mid(position, value) -> store(i, value).
+template <class Load, class Mid, class Store>
+__device__ __forceinline__ void fft_convolve(double2 *buf, const FftArgs *f, Load load, Mid mid, Store store)
+{
+    const int last = f->nst - 1;
+    auto get = [&](int i) { return buf[fft_place(f, i)]; };
+    auto put = [&](int i, double2 v) { buf[fft_place(f, i)] = v; };
+    fft_stage<FFT_FWD, true>(f, 0, load, FftNone(), put);
+    fft_forward<true>(buf, f, 1, last);
+    fft_stage<FFT_INNER, true>(f, last, get, mid, put);
+    fft_inverse<true>(buf, f, 1, last);
+    fft_stage<FFT_INV, true>(f, 0, get, FftNone(), store);
+}
+
+// Where bin k of the spectrum (not Bluestein: the order of the stages) lies in LDS.  (From a
+// table: the digits of k by multiplications took 6 % of a phi-DFT of 4095 points.)
+__device__ __forceinline__ int fft_slot(const FftArgs *f, int k) { return f->blue ? fft_place(f, k) : f->slot[k]; }
+
+// DFTs of length n = f->n in LDS (f->len places).  sign = -1: of load(k), k < n, the result in
+// the slots of its bins; sign = +1: of the bins in their slots, the result to store(k, value).
+// load may read buf at point k's place.
 //
-// Bluestein (lengths with a prime factor above 13): the inverse is
-// conj(DFT(conj(x))); the chirped input u_j = x_j conj(c_j) is convolved with
-// the chirp by a forward FFT, a product with the filter spectrum and an inverse
-// FFT, then de-chirped.
+// Bluestein: the inverse is conj(DFT(conj(x))); the chirped input u_j = x_j conj(c_j) is
+// convolved with the chirp, then de-chirped.
 //
 // Split Bluestein (convolution length M = 2H, H = f.len the LDS engine length,
 // n < H): u is zero past n < H, so the even spectrum samples U[2k] are
@@ -278,52 +462,53 @@ __device__ __forceinline__ void fft_engine(double2 *buf, const FftArgs *f, int s
 // other in the same LDS buffer; u and the even result wait in scr (2H entries
 // of this workgroup's global scratch, each read back only by the thread that
 // wrote it).
-//
-// All forms run as one loop over engine passes, so the engine is inlined once
-// per call site.
-__device__ __forceinline__ void dft_lds(double2 *buf, const FftArgs *f, int sign, double2 *scr = nullptr)
+template <int SIGN, class Load, class Store>
+__device__ __forceinline__ void dft_lds(double2 *buf, const FftArgs *f, double2 *scr, Load load, Store store)
 {
-    const int T = blockDim.x, tid = threadIdx.x;
-    const int n = f->n, len = f->len;
-    const int blue = f->blue, split = blue && f->split;
+    const int n = f->n, len = f->len, nst = f->nst;
+    auto get = [&](int i) { return buf[fft_place(f, i)]; };
+    auto put = [&](int i, double2 v) { buf[fft_place(f, i)] = v; };
+    if (!f->blue) {
+        if constexpr (SIGN < 0) {
+            fft_stage<FFT_FWD>(f, 0, load, FftNone(), put);
+            fft_forward(buf, f, 1, nst);
+        } else {
+            fft_inverse(buf, f, 1, nst);
+            fft_stage<FFT_INV>(f, 0, get, FftNone(), store);
+        }
+        return;
+    }
     const double2 *ch = reinterpret_cast<const double2 *>(f->chirp);
     const double2 *bf = reinterpret_cast<const double2 *>(f->bflt);
     const double2 *wm = reinterpret_cast<const double2 *>(f->twm);
-    const int npass = !blue ? 1 : (split ? 4 : 2);
+    const int split = f->split;
 #pragma unroll 1
-    for (int pass = 0; pass < npass; ++pass) {
-        if (blue) {
-            if (pass == 0) {                                 // chirp (zero-padded to len)
-                for (int i = tid; i < len; i += T) {
-                    double2 v = make_double2(0.0, 0.0);
-                    if (i < n) {
-                        double2 x = buf[i];
-                        if (sign > 0) x.y = -x.y;
-                        v = cmulc(x, ch[i]);
-                    }
-                    if (split) scr[i] = v;
-                    buf[i] = v;
+    for (int half = 0; half <= split; ++half) {
+        const double2 *b = bf + half * len;
+        fft_convolve(
+            buf, f,
+            [&](int i) {
+                if (half) return cmul(scr[i], wm[i]);
+                double2 x = make_double2(0.0, 0.0);
+                if (i < n) {
+                    x = SIGN > 0 ? cconj(get(i)) : load(i);
+                    x = cmulc(x, ch[i]);
                 }
-            } else if (pass == 2) {                          // split: odd half input u w^j
-                for (int i = tid; i < len; i += T) buf[i] = cmul(scr[i], wm[i]);
-            } else {                                         // filter spectrum (split: even / odd samples)
-                const int stp = split ? 2 : 1, off = pass == 3 ? 1 : 0;
-                for (int i = tid; i < len; i += T) buf[i] = cmul(buf[i], bf[stp * i + off]);
-            }
-            __syncthreads();
-        }
-        fft_engine(buf, f, !blue ? sign : ((pass & 1) ? +1 : -1));
-        if (split && pass == 1)                              // keep the even half's result
-            for (int i = tid; i < len; i += T) scr[len + i] = buf[i];
-    }
-    if (blue) {                                              // (combine and) de-chirp
-        for (int i = tid; i < n; i += T) {
-            const double2 v = split ? cadd(scr[len + i], cmulc(buf[i], wm[i])) : buf[i];
-            double2 y = cmulc(v, ch[i]);
-            if (sign > 0) y.y = -y.y;
-            buf[i] = y;
-        }
-        __syncthreads();
+                if (split) scr[i] = x;
+                return x;
+            },
+            [&](int p, double2 v) { return cmul(v, b[p]); },
+            [&](int i, double2 v) {
+                if (split && !half) {
+                    scr[len + i] = v;
+                    return;
+                }
+                if (i >= n) return;
+                if (split) v = cadd(scr[len + i], cmulc(v, wm[i]));
+                v = cmulc(v, ch[i]);
+                if constexpr (SIGN > 0) store(i, cconj(v));
+                else put(i, v);
+            });
     }
 }
 

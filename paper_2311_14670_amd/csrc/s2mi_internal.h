@@ -40,6 +40,17 @@ constexpr int FFT_MAX_LEN = 8192;        // LDS-resident engine length (complex 
 constexpr int FFT_THREADS = 1024;
 constexpr size_t FFT_SCRATCH = 2 * (size_t)FFT_MAX_LEN;   // split Bluestein: complex scratch entries per workgroup
 
+// One engine stage (quotients of numbers below 2^16 by one high multiplication: the error
+// stays below 1 / 2^13)
+struct FftStage {
+    int rad;
+    int sub;          // size of a block of the stage over its radix: the product of the later radices
+    int nbf;          // butterflies, len / rad
+    int tstep;        // nbf / sub
+    unsigned msub;    // ceil(2^32 / sub)
+    unsigned mrad;    // ceil(2^32 / rad)
+};
+
 // Everything a kernel needs to run one DFT of length n in LDS (passed by value).
 struct FftArgs {
     int n;            // logical DFT length
@@ -48,7 +59,9 @@ struct FftArgs {
     int blue;         // 1: Bluestein
     int split;        // 1: Bluestein convolution of length 2 len done as two LDS-resident halves
     int nst;          // engine stages
-    int rad[FFT_MAX_STAGES];
+    FftStage stage[FFT_MAX_STAGES];
+    int mix;          // LDS places: the bits of (i >> 3) that are mixed into i (below 16, len a multiple of it + 1)
+    const uint16_t *slot; // not Bluestein: LDS place of bin k of the spectrum
     const double *tw;     // e^{-2 pi i k/len}, k < len (interleaved)
     const double *chirp;  // Bluestein: e^{+i pi k^2/n}, k < n
     const double *bflt;   // Bluestein: FFT of the chirp filter over the convolution length, divided by it

@@ -198,7 +198,7 @@ __global__ __launch_bounds__(E::MAXT, E::WPE) void k_phi_inv(
         // belt, DH, MWSS): a thread per |m| reads whole 32-byte records (order +|m| in
         // components 0,1, order -|m| in 2,3) and fills bins |m| and nphi - |m|; the bins
         // L .. nphi - L that no order reaches are zero
-        for (int k = L + tid; k <= nphi - L; k += T) buf[k] = make_double2(0.0, 0.0);
+        for (int k = L + tid; k <= nphi - L; k += T) buf[E::slot(f, k)] = make_double2(0.0, 0.0);
         const double *pr = part + (size_t)r * L * 4;
         const size_t bstride = (size_t)nreg * L * 4;
         for (int am = tid; am < L; am += T) {
@@ -215,8 +215,8 @@ __global__ __launch_bounds__(E::MAXT, E::WPE) void k_phi_inv(
                 va = cmul(va, make_double2(c, s));
                 vb = cmul(vb, make_double2(c, -s));
             }
-            buf[am] = va;
-            if (am > 0) buf[nphi - am] = vb;
+            buf[E::slot(f, am)] = va;
+            if (am > 0) buf[E::slot(f, nphi - am)] = vb;
         }
     } else if (r < nreg) {
         // Bin k sums the orders m = k + q nphi within [-(L-1), L-1].  A short ring (nphi
@@ -247,14 +247,14 @@ __global__ __launch_bounds__(E::MAXT, E::WPE) void k_phi_inv(
             return acc;
         };
         if (per == 1) {
-            for (int k = tid; k < nphi; k += T) buf[k] = bin_sum(k, 0);
+            for (int k = tid; k < nphi; k += T) buf[E::slot(f, k)] = bin_sum(k, 0);
         } else {                                               // uniform over the workgroup
             if (tid < per * nphi) red[tid] = bin_sum(tid % nphi, tid / nphi);
             __syncthreads();
             for (int k = tid; k < nphi; k += T) {
                 double2 acc = red[k];
                 for (int j = 1; j < per; ++j) acc = cadd(acc, red[k + j * nphi]);
-                buf[k] = acc;
+                buf[E::slot(f, k)] = acc;
             }
         }
     } else {
@@ -278,14 +278,14 @@ __global__ __launch_bounds__(E::MAXT, E::WPE) void k_phi_inv(
             if (tid < s && tid + s < T) red[tid] = cadd(red[tid], red[tid + s]);
             __syncthreads();
         }
-        for (int k = tid; k < nphi; k += T) buf[k] = make_double2(0.0, 0.0);
+        for (int k = tid; k < nphi; k += T) buf[E::slot(f, k)] = make_double2(0.0, 0.0);
         __syncthreads();
-        if (tid == 0) buf[((mp % nphi) + nphi) % nphi] = red[0];
+        if (tid == 0) buf[E::slot(f, ((mp % nphi) + nphi) % nphi)] = red[0];
     }
     __syncthreads();
     double2 *out = map + ring_start[r];
-    E::template dft<false, false>(
-        buf, f, +1, fscr ? fscr + (size_t)blockIdx.x * FFT_SCRATCH : nullptr, [&](int k) { return buf[k]; },
+    E::template dft<+1, false>(
+        buf, f, fscr ? fscr + (size_t)blockIdx.x * FFT_SCRATCH : nullptr, FftNone(),
         [&](int k, double2 v) { out[k] = v; });
 }
 
@@ -322,12 +322,12 @@ __global__ __launch_bounds__(E::MAXT, E::WPE) void k_phi_fwd(
     const int shift = ring_shift[r];
     if (ringq) q = ringq[r];                     // per-ring quadrature weight (DH, GL)
     const double2 *in = map + ring_start[r];
-    E::template dft<true, true>(
-        buf, f, -1, fscr ? fscr + (size_t)blockIdx.x * FFT_SCRATCH : nullptr, [&](int k) { return in[k]; },
-        [](int, double2) {});
+    E::template dft<-1, false>(
+        buf, f, fscr ? fscr + (size_t)blockIdx.x * FFT_SCRATCH : nullptr, [&](int k) { return in[k]; },
+        FftNone());
     for (int m = tid; m < L; m += T) {
-        double2 a = buf[m % nphi];
-        double2 b = buf[(nphi - (m % nphi)) % nphi];
+        double2 a = buf[E::slot(f, m % nphi)];
+        double2 b = buf[E::slot(f, (nphi - (m % nphi)) % nphi)];
         if (shift) {
             double s, c;   // e^{-i pi m / nphi}
             sincospi((double)(m % (2 * nphi)) / (double)nphi, &s, &c);
@@ -412,8 +412,8 @@ __global__ __launch_bounds__(E::MAXT, E::WPE) void k_phi_inv_real(
     if (nphi == M && !shift) {
         for (int am = tid; am < L; am += T) {
             const double2 x1 = spec(r1, am), x2 = spec(r2, am);
-            buf[am] = make_double2(x1.x - x2.y, x1.y + x2.x);                      // X1 + i X2
-            if (am > 0) buf[M - am] = make_double2(x1.x + x2.y, x2.x - x1.y);     // conj X1 + i conj X2
+            buf[E::slot(f, am)] = make_double2(x1.x - x2.y, x1.y + x2.x);                      // X1 + i X2
+            if (am > 0) buf[E::slot(f, M - am)] = make_double2(x1.x + x2.y, x2.x - x1.y);     // conj X1 + i conj X2
         }
     } else {
         // bins sum the orders = k mod nphi; short rings spread a bin over `per` threads
@@ -437,7 +437,7 @@ __global__ __launch_bounds__(E::MAXT, E::WPE) void k_phi_inv_real(
             return z;
         };
         if (per == 1) {
-            for (int k = tid; k < nphi; k += T) buf[k] = bin_sum(k, 0);
+            for (int k = tid; k < nphi; k += T) buf[E::slot(f, k)] = bin_sum(k, 0);
         } else {
             __syncthreads();                                   // red may still hold the pole sums
             if (tid < per * nphi) red[tid] = bin_sum(tid % nphi, tid / nphi);
@@ -445,15 +445,15 @@ __global__ __launch_bounds__(E::MAXT, E::WPE) void k_phi_inv_real(
             for (int k = tid; k < nphi; k += T) {
                 double2 z = red[k];
                 for (int j = 1; j < per; ++j) z = cadd(z, red[k + j * nphi]);
-                buf[k] = z;
+                buf[E::slot(f, k)] = z;
             }
         }
     }
     __syncthreads();
     double *o1 = map + ring_start[r1];
     double *o2 = r2 >= 0 ? map + ring_start[r2] : nullptr;
-    E::template dft<false, false>(
-        buf, f, +1, fscr ? fscr + (size_t)blockIdx.x * FFT_SCRATCH : nullptr, [&](int k) { return buf[k]; },
+    E::template dft<+1, false>(
+        buf, f, fscr ? fscr + (size_t)blockIdx.x * FFT_SCRATCH : nullptr, FftNone(),
         [&](int k, double2 v) {
             o1[k] = v.x;
             if (o2) o2[k] = v.y;
@@ -495,13 +495,13 @@ __global__ __launch_bounds__(E::MAXT, E::WPE) void k_phi_fwd_real(
     const double q2 = 0.5 * (ringq && r2 >= 0 ? ringq[r2] : q);
     const double *x1 = map + ring_start[r1];
     const double *x2 = r2 >= 0 ? map + ring_start[r2] : nullptr;
-    E::template dft<true, true>(
-        buf, f, -1, fscr ? fscr + (size_t)blockIdx.x * FFT_SCRATCH : nullptr,
-        [&](int k) { return make_double2(x1[k], x2 ? x2[k] : 0.0); }, [](int, double2) {});
+    E::template dft<-1, false>(
+        buf, f, fscr ? fscr + (size_t)blockIdx.x * FFT_SCRATCH : nullptr,
+        [&](int k) { return make_double2(x1[k], x2 ? x2[k] : 0.0); }, FftNone());
     for (int m = tid; m < L; m += T) {
         const int b = m % nphi;
-        const double2 z = buf[b];
-        const double2 zc = cconj(buf[b == 0 ? 0 : nphi - b]);
+        const double2 z = buf[E::slot(f, b)];
+        const double2 zc = cconj(buf[E::slot(f, b == 0 ? 0 : nphi - b)]);
         double2 a = make_double2(q1 * (z.x + zc.x), q1 * (z.y + zc.y));     // q X1[m]
         double2 c = make_double2(q2 * (z.y - zc.y), -q2 * (z.x - zc.x));    // q X2[m]
         if (shift) {
@@ -601,14 +601,17 @@ __global__ __launch_bounds__(E::MAXT, E::WPE) void k_mw_filter(int L, int hstrid
     double2 *scr = fscr ? fscr + (size_t)blockIdx.x * FFT_SCRATCH : nullptr;
     const double *F0 = F + (size_t)m0 * hstride * 4 + 2 * side;
     const double *F1 = F + (size_t)m1 * hstride * 4 + 2 * side;
-    // z(t): the two orders' extensions
+    // z(t): the two orders' extensions; their values at ring r
+    auto rings = [&](int r, bool pole, double2 &a, double2 &b) {
+        a = b = make_double2(0.0, 0.0);
+        if (has0 && !(pole && par < 0.0)) a = *reinterpret_cast<const double2 *>(F0 + (size_t)r * 4);
+        if (has1 && !(pole && par > 0.0)) b = *reinterpret_cast<const double2 *>(F1 + (size_t)r * 4);
+    };
     auto sample = [&](int t) {
         bool mir;
         const int r = torus_ring(t, L, N, ss, &mir);
-        const bool pole = ss ? (t == 0 || t == L) : t == L - 1;
-        double2 a = make_double2(0.0, 0.0), b = a;
-        if (has0 && !(pole && par < 0.0)) a = *reinterpret_cast<const double2 *>(F0 + (size_t)r * 4);
-        if (has1 && !(pole && par > 0.0)) b = *reinterpret_cast<const double2 *>(F1 + (size_t)r * 4);
+        double2 a, b;
+        rings(r, ss ? (t == 0 || t == L) : t == L - 1, a, b);
         const double s = mir ? par : 1.0, q = mir ? -par : 1.0;
         return make_double2(fma(s, a.x, q * b.x), fma(s, a.y, q * b.y));
     };
@@ -630,9 +633,9 @@ __global__ __launch_bounds__(E::MAXT, E::WPE) void k_mw_filter(int L, int hstrid
     {
         // torus samples
         double2 acc = make_double2(0.0, 0.0);                // adj: sum_t (-1)^t w'_theta z
-        for (int t = tid; !conv && t < N; t += T) {
+        for (int t = tid; ((E::CONV && ss) || (ss && adj)) && t < N; t += T) {
             const double2 g = sample(t);
-            buf[t] = g;
+            if (E::CONV) buf[t] = g;
             if (ss && adj) {
                 const double sw = (t & 1) ? -wq[t] : wq[t];
                 acc.x = fma(sw, g.x, acc.x);
@@ -670,8 +673,7 @@ __global__ __launch_bounds__(E::MAXT, E::WPE) void k_mw_filter(int L, int hstrid
             po = make_double2(0.0, 0.0);
             for (int w = 0; w < (T + 63) / 64; ++w) po = cadd(po, wpart[w]);
         }
-        // the midpoint samples S g times the weights w'', moved back: S^{-1} (w'' S g), and
-        // z w'_theta added (z re-read: F is rewritten only below).
+        // the midpoint samples S g times the weights w'', moved back: S^{-1} (w'' S g)
         if constexpr (conv) {
             // MW, N not 13-smooth: each shift is a circular convolution of length N with a fixed
             // kernel (fN + 1 and fN + 2: the two shifts' FftArgs), and the whole filter
@@ -701,43 +703,73 @@ __global__ __launch_bounds__(E::MAXT, E::WPE) void k_mw_filter(int L, int hstrid
             __syncthreads();
             t0 = E::first_point();
 #pragma unroll
-            for (int i = 0; i < E::V; ++i) {
-                const int t = t0 + E::T * i;
-                if (t < N) {
-                    const double2 g = sample(t);
-                    const double wv = wq[t];
-                    buf[t] = make_double2(0.5 * fma(g.x, wv, v[i].x), 0.5 * fma(g.y, wv, v[i].y));
-                }
-                E::few_loads(i);
-            }
+            for (int i = 0; i < E::V; ++i)
+                if (t0 + E::T * i < N) buf[t0 + E::T * i] = v[i];
         } else {
-            // four engine passes (forward, shift, inverse: midpoints; weights; forward, shift
-            // back, inverse) from one call site, so the engine is inlined once
-            __syncthreads();                             // the torus samples are in LDS
-#pragma nounroll
-            for (int pass = 0; pass < 4; ++pass) {
-                E::template dft<false, true>(
-                    buf, fN, (pass & 1) ? +1 : -1, scr, [&](int k) { return buf[k]; }, [](int, double2) {});
-                if (pass == 0) {
-                    for (int k = tid; k < N; k += T) {                                 // shift +pi/N
-                        if (ss && !adj && k == L) nyq = make_double2(buf[k].x / N, buf[k].y / N);   // ghat_L (MWSS), read first
-                        buf[k] = cmul(buf[k], phc[k]);
+            // forward, shift, inverse: midpoints; weights; forward, shift back, inverse
+            auto shift = [&](int pass, double2 v, double2 w) { return pass ? cmulc(v, w) : cmul(v, w); };
+            auto weigh = [&](int t, double2 v) { return make_double2(v.x * wq[N + t], v.y * wq[N + t]); };
+            __syncthreads();
+            if constexpr (E::CONV) {
+                // MWSS, 2L not 13-smooth: four DFTs of the samples in LDS
+#pragma unroll 1
+                for (int pass = 0; pass < 2; ++pass) {
+                    E::template dft<-1, true>(buf, fN, scr, [&](int k) { return buf[k]; }, FftNone());
+                    for (int k = tid; k < N; k += T) {
+                        if (ss && !adj && pass == 0 && k == L) nyq = make_double2(buf[k].x / N, buf[k].y / N);   // ghat_L
+                        buf[k] = shift(pass, buf[k], phc[k]);
                     }
-                } else if (pass == 1) {
-                    for (int t = tid; t < N; t += T) {
-                        const double wv = wq[N + t];
-                        buf[t].x *= wv;
-                        buf[t].y *= wv;
-                    }
-                } else if (pass == 2) {
-                    for (int k = tid; k < N; k += T) buf[k] = cmulc(buf[k], phc[k]);   // shift -pi/N
+                    __syncthreads();
+                    E::template dft<+1, true>(
+                        buf, fN, scr, FftNone(),
+                        [&](int t, double2 v) { buf[t] = pass ? v : weigh(t, v); });
                 }
-                __syncthreads();
+            } else {
+                // one pass over LDS per stage; the shifts (phc in the order of the positions)
+                // between the two innermost stages, the weights between the last inverse and
+                // the first forward stage
+                const int nst = fN->nst, last = nst - 1;
+                const int pL = ss ? fft_pos(fN, L) : -1;
+                auto get = [&](int i) { return buf[fft_place(fN, i)]; };
+                auto put = [&](int i, double2 v) { buf[fft_place(fN, i)] = v; };
+                if (last) {
+                    fft_stage<FFT_FWD>(fN, 0, sample, FftNone(), put);
+                } else {                                         // one stage alone: from LDS
+                    for (int t = tid; t < N; t += T) put(t, sample(t));
+                    __syncthreads();
+                }
+#pragma unroll 1
+                for (int pass = 0; pass < 2; ++pass) {
+                    fft_forward(buf, fN, 1, last);
+                    fft_inner(
+                        fN, last, get,
+                        [&](int p, double2 v) {
+                            if (ss && !adj && pass == 0 && p == pL) nyq = make_double2(v.x / N, v.y / N);   // ghat_L
+                            return shift(pass, v, phc[p]);
+                        },
+                        put);
+                    fft_inverse(buf, fN, 1, last);
+                    if (pass) break;
+                    if (last) {
+                        fft_turn(fN, get, weigh, put);
+                    } else {                                     // one stage alone
+                        for (int t = tid; t < N; t += T) put(t, weigh(t, get(t)));
+                        __syncthreads();
+                    }
+                }
+                if (last) fft_stage<FFT_INV>(fN, 0, get, FftNone(), put);
             }
-            for (int t = tid; t < N; t += T) {
-                double2 g = sample(t);
-                const double wv = wq[t];
-                const double sg = (t & 1) ? -1.0 : 1.0;
+        }
+        __syncthreads();
+        const double sc = 2.0 * M_PI / (double)N;
+        // + z w'_theta, folded onto the rings: z at a ring and at its mirror are the sum and
+        // the difference of the same two values
+        auto fold = [&](int t, double2 za, double2 zb) {
+            const bool pole = ss ? (t == 0 || t == L) : t == L - 1;
+            const int mt = pole ? t : ss ? N - t : N - 1 - t;
+            auto value = [&](int u, double2 g) {
+                const double wv = wq[u], sg = (u & 1) ? -1.0 : 1.0;
+                const double2 v = buf[E::point(fN, u)];
                 if (ss && !adj) {                                // P z, then times w'
                     g.x -= sg * nyq.x;
                     g.y -= sg * nyq.y;
@@ -747,15 +779,12 @@ __global__ __launch_bounds__(E::MAXT, E::WPE) void k_mw_filter(int L, int hstrid
                     gw.x -= sg * nyq.x;
                     gw.y -= sg * nyq.y;
                 }
-                buf[t] = make_double2(0.5 * (gw.x + buf[t].x), 0.5 * (gw.y + buf[t].y));
-            }
-        }
-        __syncthreads();
-        const double sc = 2.0 * M_PI / (double)N;
-        for (int t = tid; t < (ss ? L + 1 : L); t += T) {
-            const double2 h = buf[t];
-            if (!(ss ? (t == 0 || t == L) : (t == L - 1))) {
-                const double2 hr = buf[ss ? N - t : N - 1 - t];
+                return make_double2(0.5 * (gw.x + v.x), 0.5 * (gw.y + v.y));
+            };
+            const double2 h = value(t, cadd(za, zb));
+            if (!pole) {
+                const double2 d = csub(za, zb);
+                const double2 hr = value(mt, make_double2(par * d.x, par * d.y));
                 const size_t o = (size_t)(ss ? t - 1 : t) * 4;
                 const double v = vs[t];
                 const double v0 = par < 0.0 ? v : 0.0, v1 = par < 0.0 ? 0.0 : v;
@@ -772,6 +801,11 @@ __global__ __launch_bounds__(E::MAXT, E::WPE) void k_mw_filter(int L, int hstrid
                 if (has0) hp[side == 0 ? (L - 1) + m0 : (L - 1) - m0] = par > 0.0 ? v : z;
                 if (has1) hp[side == 0 ? (L - 1) + m1 : (L - 1) - m1] = par < 0.0 ? v : z;
             }
+        };
+        for (int t = tid; t < (ss ? L + 1 : L); t += T) {
+            double2 za, zb;
+            rings(!ss ? t : t == 0 ? L : t - 1, ss ? (t == 0 || t == L) : t == L - 1, za, zb);
+            fold(t, za, zb);
         }
     }
 }
@@ -1158,12 +1192,15 @@ __global__ __launch_bounds__(1024) void k_bluestein_prep(const FftArgs *__restri
             for (int j = threadIdx.x; j < len; j += blockDim.x) {
                 const double2 lo = j < n ? ch[j] : make_double2(0.0, 0.0);
                 const double2 hi = (j > len - n) ? ch[len - j] : make_double2(0.0, 0.0);
-                buf[j] = half == 0 ? cadd(lo, hi) : cmul(csub(lo, hi), wm[j]);
+                buf[fft_place(f, j)] = half == 0 ? cadd(lo, hi) : cmul(csub(lo, hi), wm[j]);
             }
             __syncthreads();
-            fft_engine(buf, f, -1);
-            for (int k = threadIdx.x; k < len; k += blockDim.x)
-                out[f->perm ? half * len + conv_index(len, k) : 2 * k + half] = make_double2(buf[k].x * inv, buf[k].y * inv);
+            fft_forward<true>(buf, f, 0, f->nst);
+            for (int k = threadIdx.x; k < len; k += blockDim.x) {
+                const int p = fft_pos(f, k);
+                const double2 v = buf[fft_place(f, p)];
+                out[half * len + (f->perm ? conv_index(len, k) : p)] = make_double2(v.x * inv, v.y * inv);
+            }
             __syncthreads();
         }
         return;
@@ -1172,14 +1209,17 @@ __global__ __launch_bounds__(1024) void k_bluestein_prep(const FftArgs *__restri
         double2 v = make_double2(0.0, 0.0);
         if (i < n) v = ch[i];
         else if (i > len - n) v = ch[len - i];
-        buf[i] = v;
+        buf[fft_place(f, i)] = v;
     }
     __syncthreads();
-    fft_engine(buf, f, -1);
+    fft_forward<true>(buf, f, 0, f->nst);
     double2 *out = reinterpret_cast<double2 *>(const_cast<double *>(f->bflt));
     const double inv = 1.0 / (double)len;
-    for (int i = threadIdx.x; i < len; i += blockDim.x)
-        out[f->perm ? conv_index(len, i) : i] = make_double2(buf[i].x * inv, buf[i].y * inv);
+    for (int k = threadIdx.x; k < len; k += blockDim.x) {
+        const int p = fft_pos(f, k);
+        const double2 v = buf[fft_place(f, p)];
+        out[f->perm ? conv_index(len, k) : p] = make_double2(v.x * inv, v.y * inv);
+    }
 }
 
 // pole[(L-1) + m] = F[|m|][ring].side(m): the MW south-pole ring's Fourier line
