@@ -239,7 +239,7 @@ struct s2_plan_s {
     MfmaGeom mg{};
     int mch = 1;                           // orders per generated d chunk
     int gen_nblk = 1, gen_waves = 1;
-    int *gen_lchunk = nullptr, *gen_mtop = nullptr, *mtop1 = nullptr;
+    int *gen_lchunk = nullptr, *mtop1 = nullptr;
     double2 *kg = nullptr;                 // [m][lrow] {kappa, g}
     size_t nslots = 0;                     // recursion state slots (l) of the generator
     size_t off_D = 0, off_S = 0, off_AH = 0, off_mP = 0, off_mF = 0, off_mQ = 0, off_mhp = 0, off_mmaps = 0;
@@ -388,36 +388,6 @@ int build_fft(s2_plan_s *P, int n, Staging &stg, hipStream_t st, FftArgs *out)
 }
 
 int fft_threads_for(int len) { return std::min(1024, std::max(64, ((len / 8 + 63) / 64) * 64)); }
-
-// Inverse d-stage: l is cut into chunks of 8 consecutive degrees; chunks are
-// dealt in decreasing order of work (work of chunk c ~ c) over the (block,
-// wave) bins in snake order, two per wave, so every wave's sum_l (l + 1) is
-// balanced.  lchunk[bin] = {base of chunk A, base of chunk B} (or -1);
-// lslot[bin][16] = the degree of each slot (slot j of a chunk: base + 7 - j),
-// -1 where the chunk runs past L-1.
-void assign_inverse(int L, int nblk, int W, int nchw, std::vector<int> &lchunk, std::vector<int> &lslot,
-                    std::vector<int> &mtop)
-{
-    const int nbin = nblk * W;
-    const int jw = 8 * nchw;
-    const int nch = (L + 7) / 8;
-    lchunk.assign((size_t)nbin * nchw, -1);
-    lslot.assign((size_t)nbin * jw, -1);
-    std::vector<int> fill(nbin, 0);
-    for (int idx = 0, c = nch - 1; c >= 0; --c, ++idx) {
-        const int round = idx / nbin, pos = idx % nbin;
-        const int bin = (round % 2 == 0) ? pos : nbin - 1 - pos;
-        const int g = fill[bin]++;
-        lchunk[(size_t)bin * nchw + g] = 8 * c;
-        for (int j = 0; j < 8; ++j) {
-            const int l = 8 * c + 7 - j;
-            lslot[(size_t)bin * jw + g * 8 + j] = l < L ? l : -1;
-        }
-    }
-    mtop.assign(nblk, 0);
-    for (int b = 0; b < nblk; ++b)
-        for (int k = 0; k < W * jw; ++k) mtop[b] = std::max(mtop[b], lslot[(size_t)b * W * jw + k]);
-}
 
 }  // namespace
 
@@ -913,16 +883,14 @@ static int plan_create_impl(s2_plan_t *out, int L, int spin, int N, s2_sampling_
         g.rows = (4 * max_batch + 31) / 32 * 32;
         {
             const int nch = g.kc;
-            const int per_blk = DSTAGE_MAX_WAVES * GEN_NCH;
-            P->gen_nblk = (nch + per_blk - 1) / per_blk;
-            P->gen_waves = std::max(1, (nch + GEN_NCH * P->gen_nblk - 1) / (GEN_NCH * P->gen_nblk));
-            stg.i.emplace_back(); std::vector<int> &lch = stg.i.back();
-            stg.i.emplace_back(); std::vector<int> &ls = stg.i.back();
-            stg.i.emplace_back(); std::vector<int> &mt = stg.i.back();
-            assign_inverse(L, P->gen_nblk, P->gen_waves, GEN_NCH, lch, ls, mt);
-            if ((rc = upload(P, &P->gen_lchunk, lch, st, "generator chunks"))) return bail(rc);
-            if ((rc = upload(P, &P->gen_mtop, mt, st, "generator mtop"))) return bail(rc);
-            P->nslots = (size_t)P->gen_nblk * P->gen_waves * GEN_NCH * 8;
+            // a wave per chunk of 8 degrees, the longest (largest degrees) first
+            P->gen_nblk = (nch + DSTAGE_MAX_WAVES - 1) / DSTAGE_MAX_WAVES;
+            P->gen_waves = (nch + P->gen_nblk - 1) / P->gen_nblk;
+            const int nslot = P->gen_nblk * P->gen_waves;
+            stg.i.emplace_back(nslot, -1);
+            for (int k = 0; k < nch; ++k) stg.i.back()[k] = 8 * (nch - 1 - k);
+            if ((rc = upload(P, &P->gen_lchunk, stg.i.back(), st, "generator chunks"))) return bail(rc);
+            P->nslots = (size_t)nslot * 8;
         }
         if ((rc = P->dalloc(&P->kg, (size_t)(L + P->nx) * g.lrow, "kappa/g table"))) return bail(rc);
         P->kg += (size_t)P->nx * g.lrow;                     // rows m in [-nx, L)
@@ -1329,7 +1297,7 @@ int run_inverse_mfma(s2_plan_t P, const double2 *flm, int B, double2 *maps, cons
             {
             TIMED(S2_STAGE_DGEN);
             HIPCHK(launch_dgen(st, 0, fmt, P->gen_waves, P->gen_nblk, g, r.n, mhi, mlo, P->cot, P->csc, P->init[ri],
-                               P->kg, P->gen_lchunk, P->gen_mtop, SX, SY, SE, D), "d-tile generator");
+                               P->kg, P->gen_lchunk, SX, SY, SE, D), "d-tile generator");
             }
             {
             TIMED(S2_STAGE_PACK);
@@ -1411,7 +1379,7 @@ int run_forward_mfma(s2_plan_t P, const double2 *maps, int B, double2 *flm, cons
             {
             TIMED(S2_STAGE_DGEN);
             HIPCHK(launch_dgen(st, 1, fmt, P->gen_waves, P->gen_nblk, g, r.n, mhi, mlo, P->cot, P->csc, P->init[ri],
-                               P->kg, P->gen_lchunk, P->gen_mtop, SX, SY, SE, D), "d-tile generator");
+                               P->kg, P->gen_lchunk, SX, SY, SE, D), "d-tile generator");
             }
             {
             TIMED(S2_STAGE_PACK);

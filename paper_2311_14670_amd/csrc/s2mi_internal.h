@@ -80,7 +80,6 @@ constexpr int FWD_BLK = 4 * FWD_KS * SW_WAVES;   // rings of a forward block at 
 constexpr int PAIR_MIN_RINGS = 64;      // mirror-ring sweeps from this many rings on
 constexpr double GROUP_ORDERS = 1024;   // a batch's maps share launches up to this much work per compute unit ..
 constexpr size_t GROUP_BYTES = (size_t)2 << 30;   // .. and this much workspace
-constexpr int GEN_NCH = 2;              // 8-degree chunks per wave, d-tile generator (matrix-core path)
 constexpr int DSTAGE_MAX_WAVES = 8;     // d-tile generator workgroups: at most 512 threads
 
 // One recursion run: fixed second index n of d^l_{m,n}; its A side feeds the

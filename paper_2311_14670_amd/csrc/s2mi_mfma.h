@@ -26,7 +26,7 @@ hipError_t launch_kg_table(hipStream_t st, int L, int nx, int lrow, const double
 // layout 0: D[m][l/8][ring][8] (inverse);  layout 1: D[m][ring/8][l][8] (forward)
 hipError_t launch_dgen(hipStream_t st, int layout, int fmt, int nwaves, int nblk, const MfmaGeom &g, int n, int m_hi,
                        int m_lo, const double *cot, const double *csc, const double2 *init,
-                       const double2 *kg, const int *lchunk, const int *mtop, double *SX, double *SY, int *SE,
+                       const double2 *kg, const int *lchunk, double *SX, double *SY, int *SE,
                        uint4 *D);
 hipError_t launch_pack_a(hipStream_t st, int fmt, const MfmaGeom &g, int n, int m_lo, int mcn, int B,
                          long long mstride, const double2 *flmA, const double2 *flmB, const double *wA,

@@ -26,6 +26,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "s2mi_internal.h"
 #include "s2mi_mfma.h"
@@ -135,96 +136,93 @@ __global__ void k_kg_table(int L, int nx, int lrow, const double *__restrict__ k
 }
 
 // ------------------------------------------------------------------ d-tile generator
-// Same sweep geometry as the fused inverse sweep: lanes = 64 rings, each wave
-// owns NCH chunks of 8 consecutive degrees (slot e holds l = base + e).  Runs
+// Lanes are 64 rings, a wave owns a chunk of 8 consecutive degrees (slot e holds
+// l = base + e).  Runs
 // the orders m_hi .. m_lo (register roles fixed by the parity of m so a chunk
 // boundary needs no fix-up; m_lo < 0 continues the run below m = 0), writing
 // realised d values (zero at orders below |n| on rings where the run is the
 // unstable one):
 //   LAY 0 (K = l):    D[m - m_lo][l/8][ring][8 degrees]
 //   LAY 1 (K = ring): D[m - m_lo][ring/8][l][8 rings]   (8x8 transposes through LDS)
-template <int PAR, bool SLOW>
-__device__ __forceinline__ void gen_chunk(double (&X)[SG], double (&Y)[SG], int (&E)[SG], const double2 *__restrict__ rec,
-                                          double lam, int ein, double e0, int E0, float (&dv)[SG])
+// What bounds it: latency.  An order of a chunk is 8 x 64 values in some 100 instructions,
+// and its 256 bytes of kappa and g, the same for all lanes, come through scalar loads from
+// far caches.  So a wave holds one chunk (its state is small enough for four waves on a
+// SIMD), loads the next order's table row while it stores this one, and the rare parts,
+// start of a degree and renormalisation, are branches that change the state in place.
+// Measured on MI355X, both directions, two chunks per wave at 256 registers and one table
+// row loaded where it is used -> this: 64 maps of L = 2048 split BF16 17.1 -> 9.1 ms (33 GB
+// of D written: 3.7 TB/s), 32 maps of L = 1024 FP32 2.77 -> 1.77 ms.
+
+// {kappa, g} of the chunk's degrees at one order, in scalar registers
+__device__ __forceinline__ void gen_load(const double2 *__restrict__ rec, double2 (&kq)[SG])
 {
 #pragma unroll
-    for (int e = 0; e < SG; ++e) {
-        double &nw = PAR == 0 ? Y[e] : X[e];              // receives order m
-        double &od = PAR == 0 ? X[e] : Y[e];              // holds order m+1
-        const double2 kgv = rec[e];
-        nw = fma(kgv.x * lam, od, -nw);
-        double t = nw;
-        if constexpr (SLOW) {
-            if (e == ein) {                               // l == m starts here
-                nw = e0;
-                od = 0.0;
-                E[e] = E0;
-            }
-            renorm(nw, od, E[e]);
-            t = nw;                                       // not yet realised: below 2^-180, 0 as a float
-        }
-        dv[e] = (float)(t * kgv.y);
-    }
+    for (int e = 0; e < SG; ++e) kq[e] = rec[e];
 }
 
-template <int NCH, int LAY, int FMT, int PAR>
+template <int LAY, int FMT, int PAR>
 __device__ __forceinline__ void gen_step(int m, int m_lo, int an, bool good, int ms, int kc_tot, int rpad, int lp,
-                                         int ring0, int lane, int w, const int (&lb)[NCH], double (&X)[NCH][SG], double (&Y)[NCH][SG],
-                                         int (&E)[NCH][SG], uint32_t &fast, double ct, double ncs,
-                                         const double2 *__restrict__ initr, const double2 *__restrict__ kgm,
-                                         float *tr, uint4 *__restrict__ D)
+                                         int ring0, int lane, int base, double (&X)[SG], double (&Y)[SG], int (&E)[SG],
+                                         bool &fast, double ct, double ncs, const double2 *__restrict__ initr,
+                                         const double2 *__restrict__ kgn, double2 (&kq)[SG], float *tr,
+                                         uint4 *__restrict__ D)
 {
+    double (&nw)[SG] = PAR == 0 ? Y : X;                  // receives order m
+    double (&od)[SG] = PAR == 0 ? X : Y;                  // holds order m + 1
     const double lam = fma(-(double)(m + 1), ct, ncs);   // lambda_{m+1}: produces order m
-    const size_t mc = (size_t)(m - m_lo);
 #pragma unroll
-    for (int g = 0; g < NCH; ++g) {
-        const int base = lb[g];
-        if (base < 0 || m > base + SG - 1) continue;     // chunk not started
-        const double2 *rec = kgm + base;
-        float dv[SG];
-        if (m >= base) {                                  // ramp: slot m - base starts at this order
-            const double2 iv = initr[m];                 // d^m_{m,n}(theta_ring), zero if m < |n|
-            gen_chunk<PAR, true>(X[g], Y[g], E[g], rec, lam, m >= an ? m - base : -1, iv.x, (int)iv.y, dv);
-            bool z = true;
+    for (int e = 0; e < SG; ++e) nw[e] = fma(kq[e].x * lam, od[e], -nw[e]);
+    const bool ramp = m >= base;                          // slot m - base starts at this order
+    if (ramp && m >= an) {
+        const double2 iv = initr[m];                     // d^m_{m,n}(theta_ring)
 #pragma unroll
-            for (int e = 0; e < SG; ++e) z = z && (E[g][e] == 0);
-            fast = __all(z) ? (fast | (1u << g)) : (fast & ~(1u << g));
-        } else if (((fast >> g) & 1u) || (m & (RN - 1)) != 0) {
-            // realised, or not a renormalisation order (a value not yet realised
-            // stays below 2^-180 between passes and rounds to a zero float)
-            gen_chunk<PAR, false>(X[g], Y[g], E[g], rec, lam, -1, 0.0, 0, dv);
-        } else {
-            gen_chunk<PAR, true>(X[g], Y[g], E[g], rec, lam, -1, 0.0, 0, dv);
-            bool z = true;
+        for (int e = 0; e < SG; ++e)
+            if (e == m - base) {
+                nw[e] = iv.x;
+                od[e] = 0.0;
+                E[e] = (int)iv.y;
+            }
+    }
+    // a value not yet realised stays below 2^-180 between renormalisations and rounds to a
+    // zero float
+    if (ramp || (!fast && (m & (RN - 1)) == 0)) {
+        bool z = true;
 #pragma unroll
-            for (int e = 0; e < SG; ++e) z = z && (E[g][e] == 0);
-            if (__all(z)) fast |= (1u << g);
+        for (int e = 0; e < SG; ++e) {
+            renorm(nw[e], od[e], E[e]);
+            z = z && (E[e] == 0);
         }
-        if (good ? (m < 0 && -m >= ms) : (m < ms)) {      // values this run does not supply at this ring
+        fast = __all(z);
+    }
+    float dv[SG];
+#pragma unroll
+    for (int e = 0; e < SG; ++e) dv[e] = (float)(nw[e] * kq[e].y);
+    gen_load(kgn, kq);
+    if (good ? (m < 0 && -m >= ms) : (m < ms)) {          // values this run does not supply at this ring
 #pragma unroll                                            // (the other run covers them): emitted as 0
-            for (int e = 0; e < SG; ++e) dv[e] = 0.0f;
-        }
-        if constexpr (LAY == 0) {
-            store_elem<FMT>(D + ((mc * kc_tot + base / SG) * rpad + ring0 + lane) * 2, dv);
-        } else {
+        for (int e = 0; e < SG; ++e) dv[e] = 0.0f;
+    }
+    const size_t mc = (size_t)(m - m_lo);
+    if constexpr (LAY == 0) {
+        store_elem<FMT>(D + ((mc * kc_tot + base / SG) * rpad + ring0 + lane) * 2, dv);
+    } else {
 #pragma unroll
-            for (int e = 0; e < SG; ++e) tr[e * 64 + lane] = dv[e];
-            wave_lds_sync();
-            const int e2 = lane >> 3, rg = lane & 7;
-            float v[SG];
+        for (int e = 0; e < SG; ++e) tr[e * 64 + lane] = dv[e];
+        wave_lds_sync();
+        const int e2 = lane >> 3, rg = lane & 7;
+        float v[SG];
 #pragma unroll
-            for (int k = 0; k < SG; ++k) v[k] = tr[e2 * 64 + rg * SG + k];
-            wave_lds_sync();
-            store_elem<FMT>(D + ((mc * (rpad / SG) + ring0 / SG + rg) * lp + base + e2) * 2, v);
-        }
+        for (int k = 0; k < SG; ++k) v[k] = tr[e2 * 64 + rg * SG + k];
+        wave_lds_sync();
+        store_elem<FMT>(D + ((mc * (rpad / SG) + ring0 / SG + rg) * lp + base + e2) * 2, v);
     }
 }
 
-template <int NCH, int LAY, int FMT>
-__global__ __launch_bounds__(512) void k_dgen(
+template <int LAY, int FMT>
+__global__ __launch_bounds__(512, 4) void k_dgen(
     int L, int nreg, int rpad, int lp, int kc_tot, int lrow, int n, int m_hi, int m_lo,
     const double *__restrict__ cot, const double *__restrict__ csc, const double2 *__restrict__ init,
-    const double2 *__restrict__ kg, const int *__restrict__ lchunk, const int *__restrict__ mtop,
+    const double2 *__restrict__ kg, const int *__restrict__ lchunk,
     double *__restrict__ SX, double *__restrict__ SY, int *__restrict__ SE, uint4 *__restrict__ D)
 {
     __shared__ float trbuf[LAY == 1 ? DSTAGE_MAX_WAVES * SG * 64 : 1];
@@ -232,8 +230,11 @@ __global__ __launch_bounds__(512) void k_dgen(
     const int lane = threadIdx.x & 63;
     const int w = ufl(threadIdx.x >> 6);
     const int W = blockDim.x >> 6;
-    const int blk = blockIdx.y;
+    const int slot = blockIdx.y * W + w;                  // the wave's chunk
+    const int base = ufl(lchunk[slot]);
     const int ring0 = blockIdx.x * 64;
+    int m = min(m_hi, base + SG - 1);                     // orders of the chunk in this launch
+    if (base < 0 || m < m_lo) return;                     // (no barriers below)
     const int ring = min(ring0 + lane, nreg - 1);        // lanes past the last ring duplicate it
     const double ct = cot[ring], cs = csc[ring];
     const double ncs = (double)n * cs;
@@ -242,49 +243,37 @@ __global__ __launch_bounds__(512) void k_dgen(
     const bool good = ring_good(n, ct);                 // this run is the stable one at this ring
     const int ms = switch_order(n, ct, cs);
 
-    int lb[NCH];
-#pragma unroll
-    for (int g = 0; g < NCH; ++g) lb[g] = ufl(lchunk[((size_t)blk * W + w) * NCH + g]);
-    double X[NCH][SG], Y[NCH][SG];
-    int E[NCH][SG];
-    // state of slot (g, e) at SXw[(g SG + e) rpad + lane] (zeroed before a run's first chunk)
-    const size_t sbase = ((((size_t)blk * W + w) * NCH) * SG) * rpad + ring0;
+    double2 kq[SG];
+    gen_load(kg + (ptrdiff_t)m * lrow + base, kq);
+    double X[SG], Y[SG];
+    int E[SG];
+    // state of slot e at SXw[e rpad + lane] (zeroed before a run's first orders)
+    const size_t sbase = (size_t)slot * SG * rpad + ring0 + lane;
     double *SXw = SX + sbase, *SYw = SY + sbase;
     int *SEw = SE + sbase;
 #pragma unroll
-    for (int g = 0; g < NCH; ++g)
-#pragma unroll
-        for (int e = 0; e < SG; ++e) {
-            const int so = (g * SG + e) * rpad + lane;
-            X[g][e] = SXw[so];
-            Y[g][e] = SYw[so];
-            E[g][e] = SEw[so];
-        }
-    uint32_t fast = 0;
-
-    const int mt = ufl(mtop[blk]);
-    int m = min(m_hi, mt);
-    if (m >= m_lo && (m & 1)) {
-        gen_step<NCH, LAY, FMT, 1>(m, m_lo, an, good, ms, kc_tot, rpad, lp, ring0, lane, w, lb, X, Y, E, fast, ct, ncs,
-                                   initr, kg + (ptrdiff_t)m * lrow, tr, D);
-        --m;
+    for (int e = 0; e < SG; ++e) {
+        X[e] = SXw[e * rpad];
+        Y[e] = SYw[e * rpad];
+        E[e] = SEw[e * rpad];
     }
-    for (; m >= m_lo; m -= 2) {
-        gen_step<NCH, LAY, FMT, 0>(m, m_lo, an, good, ms, kc_tot, rpad, lp, ring0, lane, w, lb, X, Y, E, fast, ct, ncs,
-                                   initr, kg + (ptrdiff_t)m * lrow, tr, D);
-        if (m - 1 >= m_lo)
-            gen_step<NCH, LAY, FMT, 1>(m - 1, m_lo, an, good, ms, kc_tot, rpad, lp, ring0, lane, w, lb, X, Y, E, fast, ct,
-                                       ncs, initr, kg + (ptrdiff_t)(m - 1) * lrow, tr, D);
+    bool fast = false;
+    auto step = [&](auto par, int mm) {
+        gen_step<LAY, FMT, decltype(par)::value>(mm, m_lo, an, good, ms, kc_tot, rpad, lp, ring0, lane, base, X, Y, E, fast, ct,
+                                                 ncs, initr, kg + (ptrdiff_t)max(mm - 1, m_lo) * lrow + base, kq, tr, D);
+    };
+    if (m & 1) step(std::integral_constant<int, 1>(), m--);
+    for (; m > m_lo; m -= 2) {
+        step(std::integral_constant<int, 0>(), m);
+        step(std::integral_constant<int, 1>(), m - 1);
     }
+    if (m == m_lo) step(std::integral_constant<int, 0>(), m);
 #pragma unroll
-    for (int g = 0; g < NCH; ++g)
-#pragma unroll
-        for (int e = 0; e < SG; ++e) {
-            const int so = (g * SG + e) * rpad + lane;
-            SXw[so] = X[g][e];
-            SYw[so] = Y[g][e];
-            SEw[so] = E[g][e];
-        }
+    for (int e = 0; e < SG; ++e) {
+        SXw[e * rpad] = X[e];
+        SYw[e * rpad] = Y[e];
+        SEw[e * rpad] = E[e];
+    }
 }
 
 // ------------------------------------------------------------------ operand packs
@@ -624,15 +613,15 @@ hipError_t launch_kg_table(hipStream_t st, int L, int nx, int lrow, const double
 
 hipError_t launch_dgen(hipStream_t st, int layout, int fmt, int nwaves, int nblk, const MfmaGeom &g, int n, int m_hi,
                        int m_lo, const double *cot, const double *csc, const double2 *init,
-                       const double2 *kg, const int *lchunk, const int *mtop, double *SX, double *SY, int *SE,
+                       const double2 *kg, const int *lchunk, double *SX, double *SY, int *SE,
                        uint4 *D)
 {
     if (nwaves < 1 || nwaves > DSTAGE_MAX_WAVES || g.rpad % 64 || m_lo <= -g.L || m_hi >= g.L || m_lo > m_hi)
         return hipErrorInvalidValue;
     dim3 grid((unsigned)(g.rpad / 64), (unsigned)nblk), block((unsigned)(64 * nwaves));
 #define S2_DGEN(LAY, FMT)                                                                                   \
-    hipLaunchKernelGGL((k_dgen<GEN_NCH, LAY, FMT>), grid, block, 0, st, g.L, g.nreg, g.rpad, g.lp, g.kc,    \
-                       g.lrow, n, m_hi, m_lo, cot, csc, init, kg, lchunk, mtop, SX, SY, SE, D)
+    hipLaunchKernelGGL((k_dgen<LAY, FMT>), grid, block, 0, st, g.L, g.nreg, g.rpad, g.lp, g.kc,    \
+                       g.lrow, n, m_hi, m_lo, cot, csc, init, kg, lchunk, SX, SY, SE, D)
     if (layout == 0 && fmt == S2_CONTRACT_FP32) S2_DGEN(0, S2_CONTRACT_FP32);
     else if (layout == 0) S2_DGEN(0, S2_CONTRACT_SPLIT_BF16);
     else if (fmt == S2_CONTRACT_FP32) S2_DGEN(1, S2_CONTRACT_FP32);
