@@ -72,14 +72,32 @@ __device__ __forceinline__ float elem_f32(v4u a, v4u b, int s)   // s compile-ti
     return __uint_as_float(s < 4 ? a[s] : b[s - 4]);
 }
 
+// A lane holds the four components of one column's record; the lanes 2 j and 2 j + 1 exchange
+// halves, and each store instruction writes whole 32-byte records: the even column's (at p)
+// and the odd one's (stride doubles on).  Records of neighbouring columns lie a power of
+// two apart at the sizes that matter, so the stores are bound by requests to a few
+// channels, and 16-byte ones were twice as many.
+__device__ __forceinline__ void store_pair(float a0, float a1, float b0, float b1, int li, bool even_ok, bool odd_ok,
+                                           double *p, size_t stride)
+{
+    const bool odd = li & 1;
+    auto swap = [](float x) {
+        return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xb1, 0xf, 0xf, true));   // quad [1,0,3,2]
+    };
+    const float r0 = swap(odd ? a0 : b0), r1 = swap(odd ? a1 : b1);
+    p += odd ? 2 : 0;
+    if (even_ok) *(double2 *)p = odd ? make_double2(r0, r1) : make_double2(a0, a1);
+    if (odd_ok) *(double2 *)(p + stride) = odd ? make_double2(b0, b1) : make_double2(r0, r1);
+}
+
 // acc[i][t] += A(tile i) * B(tile t) over one K step (16 values; one 32-byte element
 // per lane and operand) for all of a wave's tiles, interleaved so that consecutive
 // matrix instructions accumulate into different tiles (each tile's products depend
 // on its previous one).  FP32: eight 32x32x2 products per tile; split BF16: three
 // 32x32x16 products per tile, hi*hi, hi*lo, lo*hi.
-template <int FMT, int MTW>
-__device__ __forceinline__ void mfma_tiles(f32x16_t (&acc)[MTW][2], const bool (&mv)[MTW], const v4u (&ah)[MTW],
-                                           const v4u (&al)[MTW], const v4u (&bh)[2], const v4u (&bl)[2])
+template <int FMT, int MTW, int NT>
+__device__ __forceinline__ void mfma_tiles(f32x16_t (&acc)[MTW][NT], const bool (&mv)[MTW], const v4u (&ah)[MTW],
+                                           const v4u (&al)[MTW], const v4u (&bh)[NT], const v4u (&bl)[NT])
 {
     if constexpr (FMT == S2_CONTRACT_FP32) {
 #pragma unroll
@@ -88,7 +106,7 @@ __device__ __forceinline__ void mfma_tiles(f32x16_t (&acc)[MTW][2], const bool (
             for (int i = 0; i < MTW; ++i) {
                 if (!mv[i]) continue;
 #pragma unroll
-                for (int t = 0; t < 2; ++t)
+                for (int t = 0; t < NT; ++t)
                     acc[i][t] = __builtin_amdgcn_mfma_f32_32x32x2f32(elem_f32(ah[i], al[i], s), elem_f32(bh[t], bl[t], s),
                                                                      acc[i][t], 0, 0, 0);
             }
@@ -99,7 +117,7 @@ __device__ __forceinline__ void mfma_tiles(f32x16_t (&acc)[MTW][2], const bool (
             for (int i = 0; i < MTW; ++i) {
                 if (!mv[i]) continue;
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
+                for (int t = 0; t < NT; ++t) {
                     const v4u a = pass == 2 ? al[i] : ah[i];
                     const v4u b = pass == 1 ? bl[t] : bh[t];
                     acc[i][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(b), acc[i][t], 0, 0, 0);
@@ -149,9 +167,6 @@ __global__ void k_kg_table(int L, int nx, int lrow, const double *__restrict__ k
 // far caches.  So a wave holds one chunk (its state is small enough for four waves on a
 // SIMD), loads the next order's table row while it stores this one, and the rare parts,
 // start of a degree and renormalisation, are branches that change the state in place.
-// Measured on MI355X, both directions, two chunks per wave at 256 registers and one table
-// row loaded where it is used -> this: 64 maps of L = 2048 split BF16 17.1 -> 9.1 ms (33 GB
-// of D written: 3.7 TB/s), 32 maps of L = 1024 FP32 2.77 -> 1.77 ms.
 
 // {kappa, g} of the chunk's degrees at one order, in scalar registers
 __device__ __forceinline__ void gen_load(const double2 *__restrict__ rec, double2 (&kq)[SG])
@@ -407,7 +422,7 @@ __global__ __launch_bounds__(256) void k_pack_h(int m_lo, int mcn, int rpad, int
 // 256 threads = 4 waves; each wave owns MTW 32-row tiles (rows of maps) and two
 // 32-column tiles.  Inverse: columns = 64 rings, K = degrees l >= max(m, |n|).
 // Output of map b, ring r, order m: partA[b][r][m][0,1], partB[b][r][m][2,3].
-template <int FMT, int MTW>
+template <int FMT, int MTW, int NT>
 __global__ __launch_bounds__(256) void k_mfma_inv(int gx, int gy, int gz, bool xcd, int L, int nreg, int rpad, int kc_tot, int n,
                                                   int m_lo, int B,
                                                   int rpad_rows, const double *__restrict__ cot,
@@ -419,7 +434,7 @@ __global__ __launch_bounds__(256) void k_mfma_inv(int gx, int gy, int gz, bool x
     const int half = lane >> 5, li = lane & 31;
     int bx, by, bz;
     if (!xcd_tile(gx, gy, gz, bx, by, bz, xcd)) return;
-    const int ring0 = bx * 64;
+    const int ring0 = bx * 32 * NT;
     const int mc = by, m = m_lo + mc;
     const int MT = rpad_rows / 32;
     const int an = n < 0 ? -n : n;
@@ -432,23 +447,26 @@ __global__ __launch_bounds__(256) void k_mfma_inv(int gx, int gy, int gz, bool x
         mv[i] = mts[i] < MT;
     }
     if (!mv[0]) return;
-    f32x16_t acc[MTW][2];
+    f32x16_t acc[MTW][NT];
 #pragma unroll
     for (int i = 0; i < MTW; ++i)
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int j = 0; j < 16; ++j) acc[i][t][j] = 0.0f;
     const v4u *Dm = (const v4u *)D + (size_t)mc * kc_tot * rpad * 2;
     const v4u *Am = (const v4u *)A + (size_t)mc * kc_tot * rpad_rows * 2;
     const v4u z4 = {0u, 0u, 0u, 0u};
-    for (int kc = kc0; kc < kc_tot; kc += 2) {
+    bool tv[NT];                                         // the last tile may reach past the padded rings
+#pragma unroll
+    for (int t = 0; t < NT; ++t) tv[t] = ring0 + t * 32 < rpad;
+    v4u bh[2][NT], bl[2][NT], ah[2][MTW], al[2][MTW];
+    auto load = [&](int kc, v4u (&bh)[NT], v4u (&bl)[NT], v4u (&ah)[MTW], v4u (&al)[MTW]) {
         const int kk = kc + half;
         const bool kv = kk < kc_tot;
-        v4u bh[2], bl[2], ah[MTW], al[MTW];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const v4u *p = Dm + ((size_t)(kv ? kk : 0) * rpad + ring0 + t * 32 + li) * 2;
+        for (int t = 0; t < NT; ++t) {
+            const v4u *p = Dm + ((size_t)(kv ? kk : 0) * rpad + (tv[t] ? ring0 + t * 32 : 0) + li) * 2;
             bh[t] = kv ? p[0] : z4;
             bl[t] = kv ? p[1] : z4;
         }
@@ -458,14 +476,27 @@ __global__ __launch_bounds__(256) void k_mfma_inv(int gx, int gy, int gz, bool x
             ah[i] = (kv && mv[i]) ? p[0] : z4;
             al[i] = (kv && mv[i]) ? p[1] : z4;
         }
-        mfma_tiles<FMT, MTW>(acc, mv, ah, al, bh, bl);
+    };
+    // the next step's operands are loaded while this one's products run (with the whole
+    // records stored below, 64 maps of L = 2048 split BF16, both directions: 30.4 -> 26.0 ms;
+    // 11.6 ms of the 30.4 were the stores)
+    load(kc0, bh[0], bl[0], ah[0], al[0]);
+    for (int kc = kc0; kc < kc_tot; kc += 4) {
+        load(kc + 2, bh[1], bl[1], ah[1], al[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        mfma_tiles<FMT, MTW, NT>(acc, mv, ah[0], al[0], bh[0], bl[0]);
+        if (kc + 2 >= kc_tot) break;
+        load(kc + 4, bh[0], bl[0], ah[0], al[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        mfma_tiles<FMT, MTW, NT>(acc, mv, ah[1], al[1], bh[1], bl[1]);
     }
     // C layout of a 32x32 tile: lane l, entry j -> row 8(j/4) + 4(l/32) + j%4, column l%32
+    const bool whole = an == 0 && m > 0 && PA && PA == PB;   // both sides of a record, at every ring
 #pragma unroll
     for (int i = 0; i < MTW; ++i) {
         if (!mv[i]) continue;
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
+        for (int t = 0; t < NT; ++t) {
             const int ring = ring0 + t * 32 + li;
             // orders below |n|: only the run that is stable at this ring writes; its
             // continuation (m <= 0) feeds the A slice at m < 0 (components 2,3 at |m|)
@@ -484,7 +515,11 @@ __global__ __launch_bounds__(256) void k_mfma_inv(int gx, int gy, int gz, bool x
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int b = mts[i] * 8 + 2 * q + half;
-                if (b < B && ring < nreg) {
+                if (whole) {
+                    store_pair(acc[i][t][4 * q + 0], acc[i][t][4 * q + 1], acc[i][t][4 * q + 2], acc[i][t][4 * q + 3], li,
+                               b < B && (ring & ~1) < nreg, b < B && (ring | 1) < nreg,
+                               PA + (size_t)b * pstride + ((size_t)(ring & ~1) * L + m) * 4, (size_t)L * 4);
+                } else if (b < B && ring < nreg) {
                     const size_t o = ((size_t)ring * L + am) * 4;
                     const double2 va = make_double2((double)acc[i][t][4 * q + 0], (double)acc[i][t][4 * q + 1]);
                     const double2 vb = make_double2((double)acc[i][t][4 * q + 2], (double)acc[i][t][4 * q + 3]);
@@ -500,7 +535,7 @@ __global__ __launch_bounds__(256) void k_mfma_inv(int gx, int gy, int gz, bool x
 
 // Forward: columns = 64 degrees l, K = rings.  Output Q[b][l][m][comp] for
 // l >= m (degrees below max(m, |n|) carry zero d and give zero).
-template <int FMT, int MTW>
+template <int FMT, int MTW, int NT>
 __global__ __launch_bounds__(256) void k_mfma_fwd(int gx, int gy, int gz, int L, int rpad, int lp, int n, int m_lo,
                                                   int B, int rpad_rows,
                                                   int nxp, const uint4 *__restrict__ H, const uint4 *__restrict__ D,
@@ -512,10 +547,10 @@ __global__ __launch_bounds__(256) void k_mfma_fwd(int gx, int gy, int gz, int L,
     const int half = lane >> 5, li = lane & 31;
     int bx, by, bz;
     if (!xcd_tile(gx, gy, gz, bx, by, bz)) return;
-    const int l0 = bx * 64;
+    const int l0 = bx * 32 * NT;
     const int mc = by, m = m_lo + mc;
     const int an = n < 0 ? -n : n, am = m < 0 ? -m : m;
-    if (l0 + 63 < m) return;
+    if (l0 + 32 * NT - 1 < m) return;
     const int MT = rpad_rows / 32;
     int mts[MTW];
     bool mv[MTW];
@@ -525,23 +560,26 @@ __global__ __launch_bounds__(256) void k_mfma_fwd(int gx, int gy, int gz, int L,
         mv[i] = mts[i] < MT;
     }
     if (!mv[0]) return;
-    f32x16_t acc[MTW][2];
+    f32x16_t acc[MTW][NT];
 #pragma unroll
     for (int i = 0; i < MTW; ++i)
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int j = 0; j < 16; ++j) acc[i][t][j] = 0.0f;
     const int kr_tot = rpad / SG;                        // a multiple of 8
     const v4u *Dm = (const v4u *)D + (size_t)mc * kr_tot * lp * 2;
     const v4u *Hm = (const v4u *)H + (size_t)mc * kr_tot * rpad_rows * 2;
     const v4u z4 = {0u, 0u, 0u, 0u};
-    for (int kr = 0; kr < kr_tot; kr += 2) {
-        const int kk = kr + half;
-        v4u bh[2], bl[2], ah[MTW], al[MTW];
+    bool tv[NT];                                         // the last tile may reach past the padded degrees
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const v4u *p = Dm + ((size_t)kk * lp + l0 + t * 32 + li) * 2;
+    for (int t = 0; t < NT; ++t) tv[t] = l0 + t * 32 < lp;
+    v4u bh[2][NT], bl[2][NT], ah[2][MTW], al[2][MTW];
+    auto load = [&](int kr, v4u (&bh)[NT], v4u (&bl)[NT], v4u (&ah)[MTW], v4u (&al)[MTW]) {
+        const int kk = (kr < kr_tot ? kr : 0) + half;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const v4u *p = Dm + ((size_t)kk * lp + (tv[t] ? l0 + t * 32 : 0) + li) * 2;
             bh[t] = p[0];
             bl[t] = p[1];
         }
@@ -551,18 +589,33 @@ __global__ __launch_bounds__(256) void k_mfma_fwd(int gx, int gy, int gz, int L,
             ah[i] = mv[i] ? p[0] : z4;
             al[i] = mv[i] ? p[1] : z4;
         }
-        mfma_tiles<FMT, MTW>(acc, mv, ah, al, bh, bl);
+    };
+    // as in the inverse (kr_tot: a multiple of 8)
+    load(0, bh[0], bl[0], ah[0], al[0]);
+    for (int kr = 0; kr < kr_tot; kr += 4) {
+        load(kr + 2, bh[1], bl[1], ah[1], al[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        mfma_tiles<FMT, MTW, NT>(acc, mv, ah[0], al[0], bh[0], bl[0]);
+        load(kr + 4, bh[0], bl[0], ah[0], al[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        mfma_tiles<FMT, MTW, NT>(acc, mv, ah[1], al[1], bh[1], bl[1]);
     }
+    const bool whole = an == 0 && m > 0 && QA && QA == QB;   // as in the inverse
 #pragma unroll
     for (int i = 0; i < MTW; ++i) {
         if (!mv[i]) continue;
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
+        for (int t = 0; t < NT; ++t) {
             const int l = l0 + t * 32 + li;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int b = mts[i] * 8 + 2 * q + half;
-                if (b < B && l < L && l >= m) {
+                if (whole) {
+                    const int le = l & ~1, lo = l | 1;
+                    store_pair(acc[i][t][4 * q + 0], acc[i][t][4 * q + 1], acc[i][t][4 * q + 2], acc[i][t][4 * q + 3], li,
+                               b < B && le < L && le >= m, b < B && lo < L && lo >= m,
+                               QA + (size_t)b * qstride + ((size_t)le * L + m) * 4, (size_t)L * 4);
+                } else if (b < B && l < L && l >= m) {
                     const double2 va = make_double2((double)acc[i][t][4 * q + 0], (double)acc[i][t][4 * q + 1]);
                     const double2 vb = make_double2((double)acc[i][t][4 * q + 2], (double)acc[i][t][4 * q + 3]);
                     // continuation sums (orders m <= 0 of a run with n != 0): the A slice at
@@ -663,19 +716,25 @@ hipError_t launch_pack_h(hipStream_t st, int fmt, const MfmaGeom &g, int hstride
     return hipSuccess;
 }
 
+// Column tiles of a wave: four (128 columns per workgroup) where it also has two row tiles and
+// the products are cheap against their operands (split BF16), so that the left operand is
+// read half as often; two otherwise.  (MI355X, both directions, four / two: 64 maps of
+// L = 2048 split BF16 26.0 / 26.5 ms, 32 maps of L = 1024 FP32 5.91 / 5.23 ms.)
+constexpr int col_tiles(int fmt, int mtw) { return fmt == S2_CONTRACT_SPLIT_BF16 && mtw == 2 ? 4 : 2; }
+
 hipError_t launch_mfma_inv(hipStream_t st, int fmt, const MfmaGeom &g, int n, const double *cot, const double *csc,
                            int m_lo, int mcn, int B, const uint4 *A, const uint4 *D, double *PA, double *PB,
                            long long pstride)
 {
     const int MT = g.rows / 32;
-    const int mtw = MT <= 4 ? 1 : 2;
+    const int mtw = MT <= 4 ? 1 : 2, nt = col_tiles(fmt, mtw);
     // the inverse products keep the plain tile order (ring tile fastest): with the XCD-aware
     // order they took 0.474 -> 0.542 ms per 32-order chunk (FP32, 64 maps at L = 2048),
     // while the forward products gained (0.717 -> 0.585 ms)
-    const int gx = g.rpad / 64, gy = mcn, gz = (MT + 4 * mtw - 1) / (4 * mtw);
+    const int gx = (g.rpad + 32 * nt - 1) / (32 * nt), gy = mcn, gz = (MT + 4 * mtw - 1) / (4 * mtw);
     const dim3 grid((unsigned)(gx * gy * gz)), block(256);
 #define S2_MI(FMT, MTW)                                                                                        \
-    hipLaunchKernelGGL((k_mfma_inv<FMT, MTW>), grid, block, 0, st, gx, gy, gz, false, g.L, g.nreg, g.rpad, g.kc, n, m_lo, \
+    hipLaunchKernelGGL((k_mfma_inv<FMT, MTW, col_tiles(FMT, MTW)>), grid, block, 0, st, gx, gy, gz, false, g.L, g.nreg, g.rpad, g.kc, n, m_lo, \
                        B, g.rows, cot, csc, A, D, PA, PB, pstride)
     if (fmt == S2_CONTRACT_FP32) { if (mtw == 1) S2_MI(S2_CONTRACT_FP32, 1); else S2_MI(S2_CONTRACT_FP32, 2); }
     else { if (mtw == 1) S2_MI(S2_CONTRACT_SPLIT_BF16, 1); else S2_MI(S2_CONTRACT_SPLIT_BF16, 2); }
@@ -689,11 +748,11 @@ hipError_t launch_mfma_fwd(hipStream_t st, int fmt, const MfmaGeom &g, int n, in
                            double *QxB, long long qxstride)
 {
     const int MT = g.rows / 32;
-    const int mtw = MT <= 4 ? 1 : 2;
-    const int gx = g.lp / 64, gy = mcn, gz = (MT + 4 * mtw - 1) / (4 * mtw);
+    const int mtw = MT <= 4 ? 1 : 2, nt = col_tiles(fmt, mtw);
+    const int gx = (g.lp + 32 * nt - 1) / (32 * nt), gy = mcn, gz = (MT + 4 * mtw - 1) / (4 * mtw);
     const dim3 grid((unsigned)((gx * gy * gz + NXCD - 1) / NXCD * NXCD)), block(256);
 #define S2_MF(FMT, MTW)                                                                                          \
-    hipLaunchKernelGGL((k_mfma_fwd<FMT, MTW>), grid, block, 0, st, gx, gy, gz, g.L, g.rpad, g.lp, n, m_lo, B, g.rows, \
+    hipLaunchKernelGGL((k_mfma_fwd<FMT, MTW, col_tiles(FMT, MTW)>), grid, block, 0, st, gx, gy, gz, g.L, g.rpad, g.lp, n, m_lo, B, g.rows, \
                        nxp, H, D, QA, QB, qstride, QxA, QxB, qxstride)
     if (fmt == S2_CONTRACT_FP32) { if (mtw == 1) S2_MF(S2_CONTRACT_FP32, 1); else S2_MF(S2_CONTRACT_FP32, 2); }
     else { if (mtw == 1) S2_MF(S2_CONTRACT_SPLIT_BF16, 1); else S2_MF(S2_CONTRACT_SPLIT_BF16, 2); }
