@@ -77,8 +77,14 @@ constexpr int INV_BLK = 256;            // degrees of an inverse block at most (
 constexpr int FWD_L = 64;               // degrees of a forward group
 constexpr int FWD_KS = 8;               // four-ring steps of a forward wave at most
 constexpr int FWD_BLK = 4 * FWD_KS * SW_WAVES;   // rings of a forward block at most
-constexpr int PAIR_MIN_RINGS = 64;      // mirror-ring sweeps from this many rings on
-constexpr double GROUP_ORDERS = 1024;   // a batch's maps share launches up to this much work per compute unit ..
+// Mirror-ring sweeps from this many rings on: one 64-ring tile instead of two (MI355X, pair of
+// transforms, us, unpaired / paired: DH 48 rings 46.8 / 46.9, HEALPix 63 rings 46.8 / 47.4, DH 64
+// 45.9 / 45.7, GL 64 48.1 / 46.9, DH 96 49.5 / 48.7, GL 100 58.4 / 55.0, HEALPix 127 59.1 / 56.8).
+constexpr int PAIR_MIN_RINGS = 64;
+// A batch's maps share launches up to this much work per compute unit (MI355X, MW L = 512, 16
+// maps, inverse + forward sweep, ms: 256 orders 0.69 + 0.63, 1024 0.54 + 0.50, 4096 0.54 + 0.48,
+// for four times the workspace) ..
+constexpr double GROUP_ORDERS = 1024;
 constexpr size_t GROUP_BYTES = (size_t)2 << 30;   // .. and this much workspace
 constexpr int DSTAGE_MAX_WAVES = 8;     // d-tile generator workgroups: at most 512 threads
 

@@ -545,7 +545,8 @@ __global__ __launch_bounds__(E::MAXT, E::WPE) void k_phi_fwd_real(
 // have extensions of opposite parity.  So one pass over the sum z of the extensions of
 // orders 2j and 2j + 1 gives both, h~_m = sc (h(t) + (-1)^{m+s} h(mirror t)) keeping each
 // order's own part.  (Half the transforms of one order at a time: MW L = 2048
-// 0.50 -> 0.28 ms, L = 4096 5.2 -> 2.8 ms, L = 64 0.036 -> 0.022 ms;
+// 0.50 -> 0.28 ms, L = 4096 5.2 -> 2.8 ms, L = 64 0.036 -> 0.022 ms; with the transforms
+// of s2mi_fft.h and s2mi_conv.h as they are now 0.22, 1.5 and 0.011 ms;
 // both orders come from, or go into, the same ring DFTs, so their rounding is relative to
 // one another anyway.)  The one thing an extension of odd parity holds beyond that is its
 // sample at a fixed point of the mirror (a pole): it is even, and the odd part sin / 2 of

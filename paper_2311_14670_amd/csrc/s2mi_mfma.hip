@@ -72,6 +72,12 @@ __device__ __forceinline__ float elem_f32(v4u a, v4u b, int s)   // s compile-ti
     return __uint_as_float(s < 4 ? a[s] : b[s - 4]);
 }
 
+// FP32 with two row tiles is bound by its 64 products per step, eight times as long as split
+// BF16's per value; a second operand set only takes registers from other waves (64 maps of
+// L = 2048, both directions, one set / two: 46 / 60 ms).  One row tile: 5.7 / 5.2 ms (32 maps of
+// L = 1024).
+constexpr bool operands_ahead(int fmt, int mtw) { return fmt == S2_CONTRACT_SPLIT_BF16 || mtw == 1; }
+
 // A lane holds the four components of one column's record; the lanes 2 j and 2 j + 1 exchange
 // halves, and each store instruction writes whole 32-byte records: the even column's (at p)
 // and the odd one's (stride doubles on).  Records of neighbouring columns lie a power of
@@ -479,16 +485,21 @@ __global__ __launch_bounds__(256) void k_mfma_inv(int gx, int gy, int gz, bool x
     };
     // the next step's operands are loaded while this one's products run (with the whole
     // records stored below, 64 maps of L = 2048 split BF16, both directions: 30.4 -> 26.0 ms;
-    // 11.6 ms of the 30.4 were the stores)
-    load(kc0, bh[0], bl[0], ah[0], al[0]);
-    for (int kc = kc0; kc < kc_tot; kc += 4) {
-        load(kc + 2, bh[1], bl[1], ah[1], al[1]);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_tiles<FMT, MTW, NT>(acc, mv, ah[0], al[0], bh[0], bl[0]);
-        if (kc + 2 >= kc_tot) break;
-        load(kc + 4, bh[0], bl[0], ah[0], al[0]);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_tiles<FMT, MTW, NT>(acc, mv, ah[1], al[1], bh[1], bl[1]);
+    // 11.6 ms of the 30.4 were the stores), but for FP32 with two row tiles (see operands_ahead)
+    if constexpr (operands_ahead(FMT, MTW)) {
+        load(kc0, bh[0], bl[0], ah[0], al[0]);
+        for (int kc = kc0; kc < kc_tot; kc += 4) {
+            load(kc + 2, bh[1], bl[1], ah[1], al[1]);
+            mfma_tiles<FMT, MTW, NT>(acc, mv, ah[0], al[0], bh[0], bl[0]);
+            if (kc + 2 >= kc_tot) break;
+            load(kc + 4, bh[0], bl[0], ah[0], al[0]);
+            mfma_tiles<FMT, MTW, NT>(acc, mv, ah[1], al[1], bh[1], bl[1]);
+        }
+    } else {
+        for (int kc = kc0; kc < kc_tot; kc += 2) {
+            load(kc, bh[0], bl[0], ah[0], al[0]);
+            mfma_tiles<FMT, MTW, NT>(acc, mv, ah[0], al[0], bh[0], bl[0]);
+        }
     }
     // C layout of a 32x32 tile: lane l, entry j -> row 8(j/4) + 4(l/32) + j%4, column l%32
     const bool whole = an == 0 && m > 0 && PA && PA == PB;   // both sides of a record, at every ring
@@ -591,14 +602,19 @@ __global__ __launch_bounds__(256) void k_mfma_fwd(int gx, int gy, int gz, int L,
         }
     };
     // as in the inverse (kr_tot: a multiple of 8)
-    load(0, bh[0], bl[0], ah[0], al[0]);
-    for (int kr = 0; kr < kr_tot; kr += 4) {
-        load(kr + 2, bh[1], bl[1], ah[1], al[1]);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_tiles<FMT, MTW, NT>(acc, mv, ah[0], al[0], bh[0], bl[0]);
-        load(kr + 4, bh[0], bl[0], ah[0], al[0]);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_tiles<FMT, MTW, NT>(acc, mv, ah[1], al[1], bh[1], bl[1]);
+    if constexpr (operands_ahead(FMT, MTW)) {
+        load(0, bh[0], bl[0], ah[0], al[0]);
+        for (int kr = 0; kr < kr_tot; kr += 4) {
+            load(kr + 2, bh[1], bl[1], ah[1], al[1]);
+            mfma_tiles<FMT, MTW, NT>(acc, mv, ah[0], al[0], bh[0], bl[0]);
+            load(kr + 4, bh[0], bl[0], ah[0], al[0]);
+            mfma_tiles<FMT, MTW, NT>(acc, mv, ah[1], al[1], bh[1], bl[1]);
+        }
+    } else {
+        for (int kr = 0; kr < kr_tot; kr += 2) {
+            load(kr, bh[0], bl[0], ah[0], al[0]);
+            mfma_tiles<FMT, MTW, NT>(acc, mv, ah[0], al[0], bh[0], bl[0]);
+        }
     }
     const bool whole = an == 0 && m > 0 && QA && QA == QB;   // as in the inverse
 #pragma unroll
