@@ -105,18 +105,16 @@ typedef struct {
     long long ncoeffs;          /* L * (2L-1) per (map, n-slice): dense layout size  */
     size_t workspace_bytes;     /* device workspace one call needs at max_batch      */
     size_t plan_device_bytes;   /* device memory held by the plan                    */
-    int swept_rings;            /* rings the inverse sweep's lanes run: nrings without
-                                   the poles, or (spin 0, N/S-symmetric samplings,
-                                   when that still fills the device; environment
-                                   S2MI_RING_PAIRING=0/1 forces off/on) the northern
-                                   half, mirror rings following from
-                                   d^l_{m,0}(pi - theta) = (-1)^{l+m} d^l_{m,0}(theta) */
-    int order_tiles;            /* FP64 sweeps: order ranges run as separate slices of
-                                   the grid (1: none), each starting from the Wigner
-                                   recursion's state stored at plan creation; chosen
-                                   when the sweeps' grids would leave the device
-                                   under-filled (environment S2MI_ORDER_TILES=k
-                                   forces k, at most 8)                            */
+    int swept_rings;            /* rings the inverse sweep runs: nrings without the
+                                   poles, or (spin 0, N/S-symmetric samplings, from 64
+                                   rings on; environment S2MI_RING_PAIRING=0/1 forces
+                                   off/on) the northern half, mirror rings following
+                                   from d^l_{m,0}(pi - theta) = (-1)^{l+m} d^l_{m,0}(theta) */
+    int order_tiles;            /* FP64 sweeps: most pieces that a block of degrees has
+                                   its orders cut into (1: none), each starting from the
+                                   Wigner recursion's state stored at plan creation, so
+                                   that the sweeps' workgroups are of equal length
+                                   (environment S2MI_ORDER_TILES=k forces k, at most 8) */
 } s2_plan_info_t;
 
 /*
