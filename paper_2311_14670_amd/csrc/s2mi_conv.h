@@ -68,7 +68,8 @@ struct ConvDft {
     }
 
     // LDS place of a point: the low five bits (the bank of a double) mixed with higher ones
-    // so that every exchange pattern of 32 lanes below meets 32 banks.  Linear in the bits:
+    // so that 32 lanes meet 32 banks in every exchange below (16 in the last one of M = 128).
+    // Linear in the bits:
     // place(a + b) = place(a) ^ place(b) where a and b share none.
     static constexpr __device__ int place(int i)
     {

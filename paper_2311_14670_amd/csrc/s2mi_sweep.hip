@@ -40,11 +40,11 @@
 // left to the other wave meanwhile), and only values beyond 2^-500 lose exponent.
 //
 // Measured on MI355X (one map, spin 0, MW L = 2048): inverse sweep 2.58 -> 1.65 ms,
-// forward 2.70 -> 1.93 ms against the vector form with scalar record loads, and 1.56
-// and 1.75 ms with scalar offsets and the two halves apart; HEALPix nside 1024, L =
-// 2048, real signal 2.68 -> 1.82 and 2.73 -> 2.00 ms; MW L = 4096 19.3 -> 10.5 and
-// 19.0 -> 12.3 ms; L = 512, 16 maps in one launch instead of 16 in turn 2.95 -> 0.88
-// and 3.50 -> 0.74 ms.
+// forward 2.70 -> 1.93 ms against the vector form with scalar record loads, 1.56 and 1.75
+// ms with scalar offsets and the two halves apart, and 1.45 and 1.76 ms with consecutive
+// pieces run as one; HEALPix nside 1024, L = 2048, real signal 2.68 -> 1.82 and 2.73 ->
+// 1.83 ms; MW L = 4096 19.3 -> 10.5 and 19.0 -> 12.2 ms; L = 512, 16 maps in one launch
+// instead of 16 in turn 2.95 -> 0.54 and 3.50 -> 0.50 ms.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
