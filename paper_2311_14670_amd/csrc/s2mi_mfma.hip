@@ -7,7 +7,7 @@
 // from the same FP64 descending-m recursion as the fused FP64 sweeps
 // (Eqs. 25-27, running renormalisation of Sec. 3.4), generated for a chunk of
 // consecutive orders at a time, realised (d = e g; a value not yet realised is
-// below 2^-180 and rounds to zero) and rounded to the
+// below 2^-280 and rounds to zero) and rounded to the
 // contraction format:
 //   FP32        fp32 operands, one MFMA pass, fp32 accumulation;
 //   split BF16  x = hi + lo, hi = bf16(x), lo = bf16(x - hi); three MFMA passes
@@ -204,7 +204,7 @@ __device__ __forceinline__ void gen_step(int m, int m_lo, int an, bool good, int
                 E[e] = (int)iv.y;
             }
     }
-    // a value not yet realised stays below 2^-180 between renormalisations and rounds to a
+    // a value not yet realised stays below 2^-280 between renormalisations and rounds to a
     // zero float
     if (ramp || (!fast && (m & (RN - 1)) == 0)) {
         bool z = true;

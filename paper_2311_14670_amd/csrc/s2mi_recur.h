@@ -7,13 +7,13 @@
 
 namespace s2mi {
 
-constexpr int RT = 600;   // realise once the scale exponent is above -RT (a multiple of 4)
+constexpr int RT = 700;   // realise once the scale exponent is above -RT (a multiple of 4)
 constexpr int SG = 8;     // degrees (or rings) per register chunk
 // Renormalisation period of the recursion (orders; a power of two).  The state grows
 // by at most |kappa lambda| + 1 < 2^20 per order for L <= 4096 (|lambda| sin theta <=
 // |n| + m + 1 with kappa (|n| + m + 1) <= 181 over every degree below 4096, and
 // sin theta >= 1.9e-4 on every grid's swept rings), so between passes a pair left at or
-// below 2^-500 stays below 2^-180: far from overflow, and its unscaled contribution
+// below 2^-600 stays below 2^-280: far from overflow, and its unscaled contribution
 // negligible (see renorm).
 constexpr int RN = 16;
 
@@ -51,15 +51,18 @@ __device__ __forceinline__ bool xcd_tile(int gx, int gy, int gz, int &bx, int &b
 
 // State of one recursion slot: the pair (e, ep) and an int E, the slot's values
 // being e 2^E and ep 2^E.  Realised (E = 0): e is the value itself.  Not yet realised:
-// E < 0 and the pair is kept scaled to at most 2^-500 at each pass, so a sweep can use
-// e unscaled in its contraction -- such a slot then contributes at most 2^-180 times its
+// E < 0 and the pair is kept scaled to at most 2^-600 at each pass, so a sweep can use
+// e unscaled in its contraction -- such a slot then contributes at most 2^-280 times its
 // record (the growth between two passes of the sweeps is below 2^320) instead of its
-// exact (equally negligible) value, and no exponent scaling is needed per step.  A slot
+// exact (equally negligible) value, and no exponent scaling is needed per step.  So
+// records 2^220 times those that matter at a ring are still below rounding there; with
+// both bounds 2^100 higher, at the same cost, 2^120 times them was the limit.  A slot
 // that has not started holds zeros with E = 0.
 
 // Exact power-of-two renormalisation of the pair (e, ep) carrying exponent E
-// (running renormalisation, Sec. 3.4).  Nothing is due while the pair is below 2^-500
-// (its value then is below that too).  Above, a pair whose value is below 2^-RT is
+// (running renormalisation, Sec. 3.4).  Nothing is due while the pair is below 2^-600
+// (its value then is below that too): the 2^100 between that and the scale it is brought
+// back to spares most passes the rescaling.  Above, a pair whose value is below 2^-RT is
 // rescaled so its larger entry is in [2^-RT, 2^(4-RT)), E absorbing the change, and one
 // whose value is at least 2^-RT is realised (E = 0, unscaled from then on).  Every
 // scaling is by a power of two, so the values themselves never change; every E is a
@@ -68,7 +71,7 @@ __device__ __forceinline__ bool xcd_tile(int gx, int gy, int gz, int &bx, int &b
 __device__ __forceinline__ void renorm(double &e, double &ep, int &E)
 {
     const double mx = fmax(fabs(e), fabs(ep));
-    if (E < 0 && mx > 0x1p-500) {
+    if (E < 0 && mx > 0x1p-600) {
         // floor(log2 mx) = frexp exponent - 1 (mx is finite: the state grows by a bounded
         // factor between passes)
         const int k = __builtin_amdgcn_frexp_exp(mx) - 1;
