@@ -572,6 +572,18 @@ __device__ __forceinline__ int torus_ring(int t, int L, int N, int ss, bool *mir
     return u == 0 ? L : u - 1;
 }
 
+// Sum of v over the lanes of a wave, in every lane.  (A workgroup of a small convolution
+// engine is 16 or 32 threads, fewer than a wave; the others are multiples of 64.)
+template <class E>
+__device__ __forceinline__ double2 wave_sum(double2 v)
+{
+    for (int o = (E::MAXT < 64 ? E::MAXT : 64) / 2; o > 0; o >>= 1) {
+        v.x += __shfl_xor(v.x, o, 64);
+        v.y += __shfl_xor(v.y, o, 64);
+    }
+    return v;
+}
+
 template <class E, bool ss>
 __global__ __launch_bounds__(E::MAXT, E::WPE) void k_mw_filter(int L, int hstride, Items it, Strides sF, Strides sh,
                                                     const FftArgs *__restrict__ fN, const double *__restrict__ wq,
@@ -644,10 +656,7 @@ __global__ __launch_bounds__(E::MAXT, E::WPE) void k_mw_filter(int L, int hstrid
             }
         }
         if (ss && adj) {                                    // uniform over the workgroup
-            for (int o = 32; o > 0; o >>= 1) {
-                acc.x += __shfl_xor(acc.x, o, 64);
-                acc.y += __shfl_xor(acc.y, o, 64);
-            }
+            acc = wave_sum<E>(acc);
             if ((tid & 63) == 0) wpart[tid >> 6] = acc;
             __syncthreads();
             if (tid == 0) {
@@ -664,10 +673,7 @@ __global__ __launch_bounds__(E::MAXT, E::WPE) void k_mw_filter(int L, int hstrid
                 po.x = fma(v, g.x, po.x);
                 po.y = fma(v, g.y, po.y);
             }
-            for (int o = 32; o > 0; o >>= 1) {
-                po.x += __shfl_xor(po.x, o, 64);
-                po.y += __shfl_xor(po.y, o, 64);
-            }
+            po = wave_sum<E>(po);
             __syncthreads();                                // wpart is free again
             if ((tid & 63) == 0) wpart[tid >> 6] = po;
             __syncthreads();
