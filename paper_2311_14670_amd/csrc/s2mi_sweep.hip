@@ -356,8 +356,10 @@ __device__ __forceinline__ int piece_end(const int4 *__restrict__ seg, int4 sg, 
 
 // One buffer descriptor for the main sums of both sides: from the lower of the two
 // slices (the same one, one of them null, or two of an SO(3) run) to the end of the
-// higher one, a side's slice as an offset of the lane.  The descriptor has to be the
-// same in every lane.  base null: beyond the 4 GiB of a descriptor, stores by pointer.
+// higher one, a side's slice as an offset of the lane.  base null: beyond the 4 GiB of a
+// descriptor, stores by pointer.  The descriptor has to be the same in every lane (a
+// store through one that differs becomes a loop over the lanes' values): A, B and bytes
+// are, so base and size are taken from the first lane.
 struct OutSpan {
     double *base;
     unsigned off, bytes;
@@ -367,7 +369,9 @@ __device__ inline OutSpan out_span(double *A, double *B, int comp, size_t bytes)
     double *lo = !A ? B : !B || A <= B ? A : B;
     const ptrdiff_t da = A ? (A - lo) * 8 : 0, db = B ? (B - lo) * 8 : 0;
     const size_t all = (size_t)(da > db ? da : db) + bytes;
-    return {all < (1ull << 32) ? lo : nullptr, (unsigned)(comp < 2 ? da : db), (unsigned)all};
+    const uint64_t p = all < (1ull << 32) ? (uint64_t)lo : 0;
+    const uint64_t u = (uint64_t)(uint32_t)ufl((int)(p >> 32)) << 32 | (uint32_t)ufl((int)(uint32_t)p);
+    return {(double *)u, (unsigned)(comp < 2 ? da : db), (unsigned)ufl((int)(unsigned)all)};
 }
 
 template <bool ONE, bool PAIR>
