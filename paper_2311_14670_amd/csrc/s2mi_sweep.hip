@@ -157,6 +157,13 @@ __global__ __launch_bounds__(256) void k_pack_inv(InvArgs a, const double2 *__re
 // Inverse (FWD = false): block b holds degrees b D + i, state ck[cut][i][3][ring];
 // lanes along the rings.  Forward: group b holds degrees b 64 + i or, for a mirror-ring
 // sweep (par), 128 (b / 2) + 2 i + b % 2, state ck[cut][3][ring][i]; lanes along i.
+// What bounds it: kappa.  All lanes of a wave are at the same order (a row of kappa is read
+// at once; degrees below it wait), the rows up to the next renormalisation are loaded
+// together, once every lane has started the steps have no conditions, and forward a wave
+// takes several rings with a row.  (MI355X, one run of MW L = 2048, ms, inverse / forward:
+// each lane at its own order, a row at a time 1.04 / 7.4; one order, rows together - / 3.05;
+// no conditions 0.58 / 2.9; four rings, forward 1.0, with conditions 5.4.)
+constexpr int CUT_RINGS = 4;
 template <bool FWD>
 __global__ __launch_bounds__(64) void k_cut_state(int L, int nreg, int rp, int D, int par, int n,
                                                   const double *__restrict__ cot, const double *__restrict__ csc,
@@ -164,60 +171,96 @@ __global__ __launch_bounds__(64) void k_cut_state(int L, int nreg, int rp, int D
                                                   const int *__restrict__ cfirst, const int2 *__restrict__ cuts,
                                                   double *__restrict__ ck)
 {
-    int r, b, i, l;
+    constexpr int NR = FWD ? CUT_RINGS : 1;              // rings r0 .. of a lane
+    int r0, b, i, l;
     if constexpr (FWD) {
         i = threadIdx.x;
         b = blockIdx.x;
-        r = blockIdx.y;
+        r0 = NR * (int)blockIdx.y;
         l = par ? 128 * (b >> 1) + 2 * i + (b & 1) : 64 * b + i;
     } else {
-        r = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+        r0 = (int)(blockIdx.x * blockDim.x + threadIdx.x);
         l = blockIdx.y;
         b = l / D;
         i = l - b * D;
     }
-    if (r >= rp) return;
     const int c0 = cfirst[b], c1 = cfirst[b + 1];
     const int an = n < 0 ? -n : n;
-    const bool live = r < nreg && l >= an && l < L;
-    double cur = 0.0, prev = 0.0, ct = 0.0, ncs = 0.0;      // e_m, e_{m+1}
-    int E = 0, m = l;
-    if (live) {
-        ct = cot[r];
-        ncs = (double)n * csc[r];
+    const int low = FWD ? (par ? l - 2 * i : l - i) : l;     // first and last degree of the lanes
+    const int top = min(FWD ? low + (par ? 126 : 63) : l, L - 1);
+    double cur[NR], prev[NR], ct[NR], ncs[NR];              // e_m, e_{m+1}
+    double2 start[NR];
+    int E[NR], m = top + 1;
+    const bool deg = l >= an && l < L;
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {                           // (a ring or degree that is not there holds zeros)
+        cur[k] = prev[k] = ct[k] = ncs[k] = 0.0;
+        E[k] = 0;
+        start[k] = make_double2(0.0, 0.0);
+        if (deg && r0 + k < nreg) {
+            ct[k] = cot[r0 + k];
+            ncs[k] = (double)n * csc[r0 + k];
+            start[k] = init[(size_t)(r0 + k) * L + l];
+        }
     }
+    const double *kl = kap + min(l, L - 1);
+    auto step = [&](int k, int mm, double kq) {
+        const double lam = fma(-(double)(mm + 1), ct[k], ncs[k]);
+        const double p = kq * lam;
+        const double nw = fma(p, cur[k], -prev[k]);
+        prev[k] = cur[k];
+        cur[k] = nw;
+    };
     for (int q = c0; q < c1; ++q) {                          // cuts of the block, orders descending
         const int c = cuts[q].x;
-        if (live && c <= l) {
-            if (m == l) {
-                const double2 v = init[(size_t)r * L + l];
-                cur = v.x;
-                E = (int)v.y;
-                prev = 0.0;
+        while (m > c) {                                      // down to the next renormalisation
+            const int hi = m - 1, lo = max(c, hi & ~(RN - 1));
+            double kq[RN];
+#pragma unroll
+            for (int j = 0; j < RN; ++j) kq[j] = kl[(ptrdiff_t)max(hi - j, lo) * L];
+            if (hi - lo == RN - 1 && hi < low) {             // every lane has started
+#pragma unroll
+                for (int j = 0; j < RN; ++j)
+#pragma unroll
+                    for (int k = 0; k < NR; ++k) step(k, hi - j, kq[j]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < RN; ++j) {
+                    const int mm = hi - j;
+                    if (mm < lo || mm > l) continue;
+#pragma unroll
+                    for (int k = 0; k < NR; ++k) {
+                        if (mm == l) {
+                            cur[k] = start[k].x;
+                            E[k] = (int)start[k].y;
+                        } else {
+                            step(k, mm, kq[j]);
+                        }
+                    }
+                }
             }
-            for (int mm = m - 1; mm >= c; --mm) {
-                const double lam = fma(-(double)(mm + 1), ct, ncs);
-                const double p = kap[(ptrdiff_t)mm * L + l] * lam;
-                const double nw = fma(p, cur, -prev);
-                prev = cur;
-                cur = nw;
-                if ((mm & (RN - 1)) == 0) renorm(cur, prev, E);
+            if (lo < l && (lo & (RN - 1)) == 0)
+#pragma unroll
+                for (int k = 0; k < NR; ++k) renorm(cur[k], prev[k], E[k]);
+            m = lo;
+        }
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            if (r0 + k >= rp) continue;
+            const bool have = deg && r0 + k < nreg && c <= l;
+            double *o;
+            size_t st;
+            if constexpr (FWD) {
+                o = ck + ((size_t)cuts[q].y * 3 * rp + r0 + k) * 64 + i;
+                st = (size_t)rp * 64;
+            } else {
+                o = ck + ((size_t)cuts[q].y * D + i) * 3 * rp + r0;
+                st = rp;
             }
-            m = c;
+            o[0] = have ? cur[k] : 0.0;
+            o[st] = have ? prev[k] : 0.0;
+            o[2 * st] = have ? (double)E[k] : 0.0;
         }
-        const bool have = live && c <= l;
-        double *o;
-        size_t st;
-        if constexpr (FWD) {
-            o = ck + ((size_t)cuts[q].y * 3 * rp + r) * 64 + i;
-            st = (size_t)rp * 64;
-        } else {
-            o = ck + ((size_t)cuts[q].y * D + i) * 3 * rp + r;
-            st = rp;
-        }
-        o[0] = have ? cur : 0.0;
-        o[st] = have ? prev : 0.0;
-        o[2 * st] = have ? (double)E : 0.0;
     }
 }
 
@@ -938,8 +981,8 @@ hipError_t launch_cut_state(hipStream_t st, bool fwd, int L, int nreg, int rp, i
 {
     if (rp < nreg || D < 1 || (fwd && D != FWD_L)) return hipErrorInvalidValue;
     if (fwd)
-        hipLaunchKernelGGL(k_cut_state<true>, dim3(nblk, rp), dim3(64), 0, st, L, nreg, rp, D, par, n, cot, csc, init,
-                           kap, cfirst, cuts, ck);
+        hipLaunchKernelGGL(k_cut_state<true>, dim3(nblk, (rp + CUT_RINGS - 1) / CUT_RINGS), dim3(64), 0, st, L, nreg, rp,
+                           D, par, n, cot, csc, init, kap, cfirst, cuts, ck);
     else
         hipLaunchKernelGGL(k_cut_state<false>, dim3((rp + 63) / 64, nblk * D), dim3(64), 0, st, L, nreg, rp, D, par, n,
                            cot, csc, init, kap, cfirst, cuts, ck);
