@@ -103,7 +103,12 @@ typedef struct {
     int nrings;                 /* isolatitude rings of the sphere sampling          */
     long long nsamples;         /* complex samples per map (SO(3): per gamma slice)  */
     long long ncoeffs;          /* L * (2L-1) per (map, n-slice): dense layout size  */
-    size_t workspace_bytes;     /* device workspace one call needs at max_batch      */
+    size_t workspace_bytes;     /* device workspace one call needs at max_batch.  FP64:
+                                   that of as many maps as share the launches, at most
+                                   max_batch and 2 GiB, at least one map's (MW L = 1024:
+                                   0.39 GB for max_batch 1, 1.95 GB for 8); environment
+                                   S2MI_MAP_GROUP=k at plan creation: of at most k maps,
+                                   with the same results.  Matrix-core plans: all maps' */
     size_t plan_device_bytes;   /* device memory held by the plan                    */
     int swept_rings;            /* rings the inverse sweep runs: nrings without the
                                    poles, or (spin 0, N/S-symmetric samplings, from 64
@@ -129,7 +134,8 @@ typedef struct {
  *   sampling   any s2_sampling_t (HEALPix: nside >= 1; L <= 3*nside+1 is not
  *              enforced, the caller picks L, typically 2*nside).  SO(3) plans
  *              require S2_MW.
- *   max_batch  largest batch any call will pass (sizes the workspace), >= 1.
+ *   max_batch  largest batch any call will pass, >= 1; sizes the workspace (see
+ *              s2_plan_info_t), also of calls that pass fewer maps.
  *   prec       contraction arithmetic (see s2_precision_t).
  *   hip_stream stream on which the plan's constants are uploaded and its set-up
  *              kernels run (tables of start values, order-tile states, FFT

@@ -843,6 +843,11 @@ static int plan_create_impl(s2_plan_t *out, int L, int spin, int N, s2_sampling_
             const double want = std::ceil(GROUP_ORDERS / std::max(per, 1e-3));
             P->group = (int)std::max(1.0, std::min({(double)max_batch, want, std::floor((double)GROUP_BYTES / (double)o),
                                                                32768.0 / (double)std::max(S, P->runs.size())}));
+            // S2MI_MAP_GROUP=k: at most k maps (a smaller workspace; tests)
+            if (const char *mg = std::getenv("S2MI_MAP_GROUP")) {
+                const int k = std::atoi(mg);
+                if (k > 0) P->group = std::min(P->group, k);
+            }
         }
         o *= P->group;
         bool split = false;
