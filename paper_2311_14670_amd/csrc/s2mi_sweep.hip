@@ -23,14 +23,14 @@
 //
 // What bounds it.  The matrix instruction takes 16 cycles for 64 d values x 4
 // columns, the recursion 2 FP64 operations (8 cycles); the two share the FP64
-// pipeline, so a slot costs 24 cycles at best (measured alone, two waves per SIMD:
-// 22.7 for one operation and the product, against 29.1 for the same work in five
-// vector operations: the product needs neither four accumulators nor dependent adds
-// close together).  The contraction's other operand and kappa are vector loads that
-// the next order's step has in flight while this one computes (a lane's registers
-// are reloaded as soon as they are used), where the vector form waited for scalar
-// loads, and one wave holds 4 x 16 rows, so the sums that cross the waves of a
-// workgroup are 1/32 of the d values.
+// pipeline, so a slot costs 24 cycles at best.  (Measured in a loop of nothing else, two
+// waves per SIMD: 22.7 for the product and one of the two operations, 27 with both;
+// the product and one operation as five vector operations 29.1: the product needs neither
+// four accumulators nor dependent adds close together.)  The contraction's other operand
+// and kappa are vector loads that the next order's step has in flight while this one
+// computes (a lane's registers are reloaded as soon as they are used), where the vector
+// form waited for scalar loads, and one wave holds 4 x 16 rows, so the sums that cross the
+// waves of a workgroup are 1/32 of the d values.
 //
 // A third of the vector instructions were not FP64 at first: addresses, the sums over
 // the waves, the renormalisation.  So the operands and kappa are buffer loads and the
@@ -401,20 +401,18 @@ __device__ __forceinline__ int piece_end(const int4 *__restrict__ seg, int4 sg, 
 // slices (the same one, one of them null, or two of an SO(3) run) to the end of the
 // higher one, a side's slice as an offset of the lane.  base null: beyond the 4 GiB of a
 // descriptor, stores by pointer.  The descriptor has to be the same in every lane (a
-// store through one that differs becomes a loop over the lanes' values): A, B and bytes
-// are, so base and size are taken from the first lane.
+// store through one that differs becomes a loop over the lanes' values), so nothing of a
+// lane enters here: the lane's offset is offA or offB.
 struct OutSpan {
     double *base;
-    unsigned off, bytes;
+    unsigned offA, offB, bytes;
 };
-__device__ inline OutSpan out_span(double *A, double *B, int comp, size_t bytes)
+__device__ inline OutSpan out_span(double *A, double *B, size_t bytes)
 {
     double *lo = !A ? B : !B || A <= B ? A : B;
     const ptrdiff_t da = A ? (A - lo) * 8 : 0, db = B ? (B - lo) * 8 : 0;
     const size_t all = (size_t)(da > db ? da : db) + bytes;
-    const uint64_t p = all < (1ull << 32) ? (uint64_t)lo : 0;
-    const uint64_t u = (uint64_t)(uint32_t)ufl((int)(p >> 32)) << 32 | (uint32_t)ufl((int)(uint32_t)p);
-    return {(double *)u, (unsigned)(comp < 2 ? da : db), (unsigned)ufl((int)(unsigned)all)};
+    return {all < (1ull << 32) ? lo : nullptr, (unsigned)da, (unsigned)db, (unsigned)all};
 }
 
 template <bool ONE, bool PAIR>
@@ -455,8 +453,8 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_inv(InvArgs a, const do
     constexpr int NC = ONE ? 2 : 4;
     const int tid = threadIdx.x;
     const int rc = tid & (NC - 1), rq = (tid / NC) & (DORD - 1), row0 = tid / (NC * DORD);
-    constexpr int ROWS = 64 * SW_WAVES / (NC * DORD);    // rows covered at once: 32, 64 or 128
-    constexpr int NR = ROWS >= 64 ? 1 : 64 / ROWS;
+    constexpr int ROWS = 64 * SW_WAVES / (NC * DORD);    // rows covered at once: 32 or 64
+    constexpr int NR = 64 / ROWS;
     const int comp = rc + (ONE && side == 2 ? 2 : 0);
     int msg[NR];                                         // switch order of the ring, ~ms where this run is
 #pragma unroll                                           // the stable one
@@ -469,9 +467,13 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_inv(InvArgs a, const do
     // its byte offset in a block's partial sums for order mb - DORD + 1
     const int r16 = row0 & 15;
     const int rpos = (row0 >> 4) * 64 + 16 * (r16 & 3) + 4 * (r16 >> 2) + rc;
-    const OutSpan po = out_span(PA, PB, comp, (size_t)a.nreg * L * 32);
-    const unsigned ooff = ((unsigned)(ring0 + row0) * L + (DORD - 1 - rq)) * 32 + comp * 8 + po.off;
-    const unsigned moff = ((unsigned)(a.nreg - 1 - ring0 - row0) * L + (DORD - 1 - rq)) * 32 + comp * 8 + po.off;   // mirror
+    const OutSpan po = out_span(PA, PB, (size_t)a.nreg * L * 32);
+    const unsigned soff = comp * 8 + (comp < 2 ? po.offA : po.offB);
+    const unsigned ooff = ((unsigned)(ring0 + row0) * L + (DORD - 1 - rq)) * 32 + soff;
+    const unsigned moff = ((unsigned)(a.nreg - 1 - ring0 - row0) * L + (DORD - 1 - rq)) * 32 + soff;   // mirror
+    // Every thread is a reducer.  The branch around the sums stays: without it the compiler
+    // mixes them into the steps, and the one-sided forms get slower (MI355X, us, with /
+    // without: MW L = 2048 spin 2 2620 / 2862, real signal 1340 / 1495, GL L = 301 108 / 114).
     const bool reducer = row0 < 64;
     short *ex = expo + (size_t)w * 32 * 64 + lane;       // exponent of slot (c, h, g) at 64 (8 c + 4 h + g)
     double X[4][2][4], Y[4][2][4];
@@ -797,8 +799,9 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_fwd(FwdArgs a, const do
     constexpr int lsh = PAIRF ? 1 : 0;                   // log2 of a group's degree stride
     const int r16 = row0 & 15;
     const int rpos = (row0 >> 4) * 64 + ((16 * (r16 & 3) + 4 * (r16 >> 2) + rc + 4 * rq) & 63);
-    const OutSpan qo = out_span(QA, QB, comp, (size_t)L * L * 32);
-    const unsigned ooff = ((unsigned)(row0 << lsh) * L + (DORD - 1 - rq)) * 32 + comp * 8 + qo.off;
+    const OutSpan qo = out_span(QA, QB, (size_t)L * L * 32);
+    const unsigned ooff =
+        ((unsigned)(row0 << lsh) * L + (DORD - 1 - rq)) * 32 + comp * 8 + (comp < 2 ? qo.offA : qo.offB);
     // Adds the waves' sums of the orders m1 .. m1 - 3 of group lmin (buffer half `hf`)
     // and stores them to the block's partial sums.
     auto reduce = [&](int lmin, int hf, int m1, int mhi, int bot) {
