@@ -41,7 +41,8 @@ def kernel_source_sha():
     from (the kernel file and the device headers it includes)."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("s2mi_sweep.hip", "s2mi_kernels.hip", "s2mi_recur.h", "s2mi_internal.h", "s2mi_fft.h", "s2mi_conv.h"):
+    for f in ("s2mi_sweep.hip", "s2mi_kernels.hip", "s2mi_kernels.h", "s2mi_recur.h", "s2mi_internal.h", "s2mi_fft.h",
+              "s2mi_conv.h"):
         h.update(open(os.path.join(ROOT, "paper_2311_14670_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 

@@ -29,7 +29,10 @@ def build(verbose=True):
     os.makedirs(BUILD, exist_ok=True)
     objs = []
     # the DFT kernels hold one loop per stage radix: the constants of all radices hoisted out
-    # of all those loops spill (MW L = 2048 theta filter, 64 maps: 13.6 -> 13.1 ms without)
+    # of all those loops spill (MI355X, with / without hoisting, ms: MW L = 2048, 64 maps,
+    # inverse phi-DFT 4.7 / 4.4, forward 6.3 / 5.5, theta filter 13.5 / 13.4, one map's filter
+    # 0.230 / 0.222; HEALPix nside 1024 0.46 + 0.28 / 0.45 + 0.27; MWSS L = 1050 filter, 4 maps,
+    # 0.40 / 0.41; the register engine's kernels, finish and gamma DFT within their noise)
     extra = {"s2mi_kernels.hip": ["-mllvm", "-disable-machine-licm"]}
     for src in ["s2mi_kernels.hip", "s2mi_sweep.hip", "s2mi_mfma.hip", "s2mi_capi.hip"]:
         obj = os.path.join(BUILD, src.replace(".hip", ".o"))

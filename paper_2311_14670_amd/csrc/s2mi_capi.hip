@@ -62,7 +62,7 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // dealt to slots of about equal length (s2mi_sweep.hip).
 struct Work {
     int nblk = 1;                       // blocks (inverse) or degree groups (forward)
-    int tiles = 1, per_item = 1;        // ring tiles (inverse) or ring blocks (forward); workgroups per run: tiles x slots
+    int tiles = 1;                      // ring tiles (inverse) or ring blocks (forward); workgroups per run: tiles x slots
     int cb = 1, nk = 1;                 // inverse: chunks per block; forward: four-ring steps per wave
     int rp = 0;                         // ring stride of a cut's state
     int nslot = 1, quota = 1, pieces = 1;
@@ -720,8 +720,7 @@ static int plan_create_impl(s2_plan_t *out, int L, int spin, int N, s2_sampling_
         if (P->fwd_pair) P->pstride = slots;
         orders.clear();
         const int ng = P->fwd_pair ? 2 * ((L + 127) / 128) : (L + 63) / 64;
-        for (int g = 0; g < ng; ++g)
-            {
+        for (int g = 0; g < ng; ++g) {
             const int lmin = P->fwd_pair ? 128 * (g >> 1) + (g & 1) : 64 * g;
             orders.push_back(lmin < L ? std::min(L, lmin + (P->fwd_pair ? 127 : 64)) : 0);
         }
@@ -990,8 +989,6 @@ int check_call(const char *fn, s2_plan_t P, const void *in, const void *out, int
         return fail(S2_ERR_INVALID_ARG, "%s: batch=%d outside [0, max_batch=%d]", fn, batch, P->max_batch);
     return S2_OK;
 }
-
-// the theta filter's convolution form: its FFT, kernel spectra and length (none: nullptr)
 
 // the workspace's split-Bluestein scratch (nullptr when no DFT of the plan needs it)
 double2 *fft_scratch(const s2_plan_s *P, char *ws)

@@ -37,7 +37,6 @@ void host_weights(int L, int kind, int spin, std::vector<double> *w);
 // ----------------------------------------------------------------- FFT
 constexpr int FFT_MAX_STAGES = 16;
 constexpr int FFT_MAX_LEN = 8192;        // LDS-resident engine length (complex doubles)
-constexpr int FFT_THREADS = 1024;
 constexpr size_t FFT_SCRATCH = 2 * (size_t)FFT_MAX_LEN;   // split Bluestein: complex scratch entries per workgroup
 
 // One engine stage (quotients of numbers below 2^16 by one high multiplication: the error

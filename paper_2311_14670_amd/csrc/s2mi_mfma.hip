@@ -422,11 +422,20 @@ __global__ __launch_bounds__(256) void k_pack_h(int m_lo, int mcn, int rpad, int
 }
 
 // ------------------------------------------------------------------ contractions
-// Contraction tiles are dispatched XCD-aware (xcd_tile): the tiles of one order share
-// that order's coefficient or spectra operand (A_m / H_m, 2 MB at L = 2048, B = 64).
+// The tiles of one order share that order's coefficient or spectra operand (A_m / H_m, 2 MB
+// at L = 2048, B = 64), the row tiles of a column its part of D_m.  The forward products
+// are dispatched XCD-aware (xcd_tile), the inverse ones in plain order, ring tile fastest.
+// Products of all orders on MI355X, ms, XCD-aware / plain order:
+//            inverse FP32    forward FP32    inverse BF16    forward BF16
+//   L = 512,  32 maps   0.46 / 0.31   0.42 / 0.42   0.39 / 0.28   0.34 / 0.33
+//   L = 512,  64        0.82 / 0.62   0.80 / 0.79   0.58 / 0.55   0.43 / 0.45
+//   L = 1024, 32        2.87 / 1.81   2.94 / 2.91   2.11 / 1.40   2.11 / 2.12
+//   L = 1024, 64        5.35 / 3.38   5.31 / 5.38   3.54 / 2.45   2.33 / 2.37
+//   L = 2048, 32        13.6 / 13.0   12.8 / 22.1   9.76 / 9.26   9.52 / 14.9
+//   L = 2048, 64        24.3 / 23.0   22.9 / 39.5   15.7 / 15.0   10.8 / 16.2
 
-// 256 threads = 4 waves; each wave owns MTW 32-row tiles (rows of maps) and two
-// 32-column tiles.  Inverse: columns = 64 rings, K = degrees l >= max(m, |n|).
+// 256 threads = 4 waves; each wave owns MTW 32-row tiles (rows of maps) and NT 32-column
+// tiles.  Inverse: columns = 32 NT rings, K = degrees l >= max(m, |n|).
 // Output of map b, ring r, order m: partA[b][r][m][0,1], partB[b][r][m][2,3].
 template <int FMT, int MTW, int NT>
 __global__ __launch_bounds__(256) void k_mfma_inv(int gx, int gy, int gz, bool xcd, int L, int nreg, int rpad, int kc_tot, int n,
@@ -544,7 +553,7 @@ __global__ __launch_bounds__(256) void k_mfma_inv(int gx, int gy, int gz, bool x
     }
 }
 
-// Forward: columns = 64 degrees l, K = rings.  Output Q[b][l][m][comp] for
+// Forward: columns = 32 NT degrees l, K = rings.  Output Q[b][l][m][comp] for
 // l >= m (degrees below max(m, |n|) carry zero d and give zero).
 template <int FMT, int MTW, int NT>
 __global__ __launch_bounds__(256) void k_mfma_fwd(int gx, int gy, int gz, int L, int rpad, int lp, int n, int m_lo,
@@ -744,9 +753,8 @@ hipError_t launch_mfma_inv(hipStream_t st, int fmt, const MfmaGeom &g, int n, co
 {
     const int MT = g.rows / 32;
     const int mtw = MT <= 4 ? 1 : 2, nt = col_tiles(fmt, mtw);
-    // the inverse products keep the plain tile order (ring tile fastest): with the XCD-aware
-    // order they took 0.474 -> 0.542 ms per 32-order chunk (FP32, 64 maps at L = 2048),
-    // while the forward products gained (0.717 -> 0.585 ms)
+    // plain tile order: the better one at every size, the forward's XCD-aware one there (table
+    // above the kernels)
     const int gx = (g.rpad + 32 * nt - 1) / (32 * nt), gy = mcn, gz = (MT + 4 * mtw - 1) / (4 * mtw);
     const dim3 grid((unsigned)(gx * gy * gz)), block(256);
 #define S2_MI(FMT, MTW)                                                                                        \

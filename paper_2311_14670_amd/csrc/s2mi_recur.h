@@ -1,5 +1,5 @@
 // s2mi_recur.h -- device helpers of the descending-m Wigner recursion shared by
-// the fused FP64 sweeps (s2mi_kernels.hip) and the d-tile generator of the
+// the fused FP64 sweeps (s2mi_sweep.hip) and the d-tile generator of the
 // matrix-core path (s2mi_mfma.hip).
 #pragma once
 
@@ -19,7 +19,7 @@ constexpr int RN = 16;
 
 __device__ __forceinline__ int ufl(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
-// Tile order of the sweeps and contractions.  Workgroups are dispatched round-robin
+// Tile order of the matrix-core contractions.  Workgroups are dispatched round-robin
 // over the 8 XCDs (workgroup i to XCD i mod 8), each with its own L2.  With xcd set, a
 // 1-D grid of ceil(gx gy gz / 8) * 8 workgroups is remapped so that every XCD takes one
 // contiguous run of the tiles, ordered z fastest, then x, then y: tiles that share an
