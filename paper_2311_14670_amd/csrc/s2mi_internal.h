@@ -75,6 +75,7 @@ constexpr int SW_WAVES = 8;             // waves of a sweep workgroup (two per S
 constexpr int INV_BLK = 256;            // degrees of an inverse block at most (8 waves x 4 chunks of 8)
 constexpr int FWD_L = 64;               // degrees of a forward group
 constexpr int FWD_KS = 8;               // four-ring steps of a forward wave at most
+constexpr int FWD_KS_FEW = 2;           // and in the form for few rings
 constexpr int FWD_BLK = 4 * FWD_KS * SW_WAVES;   // rings of a forward block at most
 // Mirror-ring sweeps from this many rings on: one 64-ring tile instead of two (MI355X, pair of
 // transforms, us, unpaired / paired: DH 48 rings 46.8 / 46.9, HEALPix 63 rings 46.8 / 47.4, DH 64

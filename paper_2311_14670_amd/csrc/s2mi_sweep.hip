@@ -300,6 +300,7 @@ __global__ __launch_bounds__(64) void k_cut_state(int L, int nreg, int rp, int D
 // ring r gets E + O and its mirror (-1)^m (E - O).
 // ONE: one side only (columns 2, 3 repeat columns 0, 1); with PAIR the repeated columns
 // take (-1)^l times the coefficient, so columns 0, 1 are E + O and 2, 3 are E - O.
+// NCH: chunks of a wave at most (4, or 1 for small L: see the launcher).
 constexpr int RED_DOUBLES = 8 * SW_WAVES * 256;          // reduction buffers: 8 orders (PAIR: 4) x 8 waves
 constexpr int EXP_SHORTS = SW_WAVES * 32 * 64;           // exponents of every slot and lane
 
@@ -341,11 +342,11 @@ __device__ __forceinline__ void inv_load(__amdgpu_buffer_rsrc_t rs, unsigned Cq,
 // The loads stand outside the branch, at a row that exists for chunks not started, so
 // that the compiler can count the loads in flight: behind a branch it would wait for all
 // of them at every chunk.)
-template <int PAR, bool ONE, bool PAIR>
-__device__ __forceinline__ void inv_step(int m, uint32_t act, int nx, const int (&cb)[4], __amdgpu_buffer_rsrc_t rsrc,
-                                         const unsigned (&Cq)[4], const InvLane &ln,
-                                         double (&X)[4][2][4], double (&Y)[4][2][4], double2 (&kq)[4],
-                                         double2 (&cq)[4], double *rb)
+template <int PAR, bool ONE, bool PAIR, int NCH>
+__device__ __forceinline__ void inv_step(int m, uint32_t act, int nx, const int (&cb)[NCH], __amdgpu_buffer_rsrc_t rsrc,
+                                         const unsigned (&Cq)[NCH], const InvLane &ln,
+                                         double (&X)[NCH][2][4], double (&Y)[NCH][2][4], double2 (&kq)[NCH],
+                                         double2 (&cq)[NCH], double *rb)
 {
     constexpr int RS = rec_doubles(ONE, PAIR);
     constexpr bool EO = PAIR && !ONE;                    // even and odd degrees summed apart
@@ -359,7 +360,7 @@ __device__ __forceinline__ void inv_step(int m, uint32_t act, int nx, const int 
 #pragma unroll
     for (int i = 0; i < NA; ++i) acc[i] = 0.0;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
+    for (int c = 0; c < NCH; ++c) {
         if ((act >> c) & 1u) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -415,7 +416,7 @@ __device__ inline OutSpan out_span(double *A, double *B, size_t bytes)
     return {all < (1ull << 32) ? lo : nullptr, (unsigned)da, (unsigned)db, (unsigned)all};
 }
 
-template <bool ONE, bool PAIR>
+template <bool ONE, bool PAIR, int NCH>
 __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_inv(InvArgs a, const double *__restrict__ cot,
                                                              const double *__restrict__ csc)
 {
@@ -476,10 +477,10 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_inv(InvArgs a, const do
     // without: MW L = 2048 spin 2 2620 / 2862, real signal 1340 / 1495, GL L = 301 108 / 114).
     const bool reducer = row0 < 64;
     short *ex = expo + (size_t)w * 32 * 64 + lane;       // exponent of slot (c, h, g) at 64 (8 c + 4 h + g)
-    double X[4][2][4], Y[4][2][4];
-    double2 kq[4], cq[4];
-    int cb[4];
-    unsigned Cq[4];                                      // byte offset of a chunk's row of order 0
+    double X[NCH][2][4], Y[NCH][2][4];
+    double2 kq[NCH], cq[NCH];
+    int cb[NCH];
+    unsigned Cq[NCH];                                    // byte offset of a chunk's row of order 0
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         a.C + (size_t)map * a.wsd + (size_t)ri * a.nC, 0, (int)(a.nC * 8), 0x00027000);
     uint32_t fast = 0;
@@ -569,9 +570,9 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_inv(InvArgs a, const do
             const int q0 = blk * a.cb, nq = min(a.cb, (L + 7) / 8 - q0);   // chunks of the block
             const int nv = nq > w ? (nq - w + 7) / 8 : 0;                    // and of this wave
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                // the wave's chunks ascend to c = 3; absent ones come first and are never active
-                const int j = c - (4 - nv), q = q0 + w + 8 * j;
+            for (int c = 0; c < NCH; ++c) {
+                // the wave's chunks ascend to the last c; absent ones come first and are never active
+                const int j = c - (NCH - nv), q = q0 + w + 8 * j;
                 const bool ok = j >= 0;
                 cb[c] = ok ? 8 * q : -(1 << 20);
                 Cq[c] = (unsigned)rec_row(ok ? q : 0, 0, nx) * (RS * 8);
@@ -600,7 +601,7 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_inv(InvArgs a, const do
             // starts: the degrees mb .. mb - 3 belong to one chunk of one wave, in the lane
             // groups k0, k0 + 1 (k0 = 2 where the chunk itself starts, at mb = 8 q + 7)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
+            for (int c = 0; c < NCH; ++c) {
                 if (cb[c] != (mb & ~7)) continue;
                 if (mb & 4) inv_load<RS>(rsrc, Cq[c], mb, ln, kq[c], cq[c]);
                 fast &= ~(1u << c);
@@ -623,12 +624,12 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_inv(InvArgs a, const do
             const int m3 = mb - 3;
             uint32_t act = 0;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) act |= (m3 <= cb[c] + 7 ? 1u : 0u) << c;
+            for (int c = 0; c < NCH; ++c) act |= (m3 <= cb[c] + 7 ? 1u : 0u) << c;
             auto step = [&](auto Q) {                    // order mb - Q
                 constexpr int q = decltype(Q)::value;
                 double *wb = red + (size_t)(EO ? (it & 1) * 2 + (q & 1) : (it & 1) * 4 + q) * OB + w * NA * 64 +
                              ((lane + 4 * q) & 63);
-                inv_step<q & 1, ONE, PAIR>(mb - q, act, nx, cb, rsrc, Cq, ln, X, Y, kq, cq, wb);
+                inv_step<q & 1, ONE, PAIR, NCH>(mb - q, act, nx, cb, rsrc, Cq, ln, X, Y, kq, cq, wb);
             };
             // The sums of the last iteration (EO: half iteration) are added in this one, by
             // half of the waves after its first order and by the others, which share their
@@ -650,7 +651,7 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_inv(InvArgs a, const do
             // renormalisation every RN orders of the started chunks not yet realised
             if ((m3 & (RN - 1)) == 0) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
+                for (int c = 0; c < NCH; ++c) {
                     if (m3 > cb[c] + 7 || ((fast >> c) & 1u)) continue;
                     bool z = true;
 #pragma unroll
@@ -687,6 +688,7 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_inv(InvArgs a, const do
 // d^l_{m,0}(pi - theta) = (-1)^{l+m} d^l_{m,0}(theta) a ring contributes d (H(ring) +
 // (-1)^{l+m} H(mirror)): order m reads the sums S or the differences D of the two
 // rings' spectra by the parity of m + G.
+// KS: steps of a wave at most (8, or 2 for few rings: see the launcher).
 
 // The operand row of order m: lane's column of {A re, A im, B re, B im} at its first
 // ring.  Orders below |n| read copies in which the rings where this run is unstable are
@@ -702,11 +704,11 @@ __device__ __forceinline__ const double *fwd_row(int m, int an, int hstride, int
 }
 
 // One order.  hrow, kapn: the next order's rows.
-template <int PAR>
-__device__ __forceinline__ void fwd_step(int m, int nk, const double (&ct)[FWD_KS], const double (&ncs)[FWD_KS],
+template <int PAR, int KS>
+__device__ __forceinline__ void fwd_step(int m, int nk, const double (&ct)[KS], const double (&ncs)[KS],
                                          __amdgpu_buffer_rsrc_t krs, unsigned krow, const unsigned (&lc)[4],
-                                         const double *__restrict__ hrow, double (&X)[FWD_KS][4], double (&Y)[FWD_KS][4],
-                                         double (&kp)[4], double (&hq)[FWD_KS], double *rb)
+                                         const double *__restrict__ hrow, double (&X)[KS][4], double (&Y)[KS][4],
+                                         double (&kp)[4], double (&hq)[KS], double *rb)
 {
     const double mm = -(double)(m + 1);
     double kn[4];
@@ -714,7 +716,7 @@ __device__ __forceinline__ void fwd_step(int m, int nk, const double (&ct)[FWD_K
     for (int g = 0; g < 4; ++g) kn[g] = buf_load1(krs, lc[g], krow);
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int s = 0; s < FWD_KS; ++s) {
+    for (int s = 0; s < KS; ++s) {
         if (s < nk) {
         const double lam = fma(mm, ct[s], ncs[s]);       // lambda_{m+1}: produces order m
         double p[4];
@@ -739,7 +741,7 @@ __device__ __forceinline__ void fwd_step(int m, int nk, const double (&ct)[FWD_K
     for (int g = 0; g < 4; ++g) rb[g * 64] = acc[g];
 }
 
-template <bool ONE, bool PAIRF>
+template <bool ONE, bool PAIRF, int KS>
 __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_fwd(FwdArgs a, const double *__restrict__ cot,
                                                              const double *__restrict__ csc,
                                                              const double *__restrict__ kap)
@@ -780,9 +782,9 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_fwd(FwdArgs a, const do
     const int col = ONE ? (lane & 1) + (side == 2 ? 2 : 0) : lane & 3;
     const int ks = lane >> 4, i16 = lane & 15;           // ring of a step, degree of a group
     const int r0 = rb0 + ks;                             // this lane's first ring (operand rows)
-    double ct[FWD_KS], ncs[FWD_KS];
+    double ct[KS], ncs[KS];
 #pragma unroll
-    for (int s = 0; s < FWD_KS; ++s) {
+    for (int s = 0; s < KS; ++s) {
         const int rr = r0 + 4 * s;
         const bool ok = s < nk && rr < a.nreg;
         ct[s] = ok ? cot[rr] : 0.0;
@@ -851,8 +853,8 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_fwd(FwdArgs a, const do
         }
     };
     short *ex = expo + (size_t)w * 32 * 64 + lane;       // exponent of slot (s, g) at 64 (4 s + g)
-    double X[FWD_KS][4], Y[FWD_KS][4];
-    double hq[FWD_KS], kp[4];
+    double X[KS][4], Y[KS][4];
+    double hq[KS], kp[4];
     unsigned lc[4];                                      // byte offsets of the lane's degrees (clamped into the table)
     uint32_t fast = 0;
     int it = 0;
@@ -877,7 +879,7 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_fwd(FwdArgs a, const do
             fast = 0;
             const double *h = row_of(min(mhi | 3, L - 1), G);
 #pragma unroll
-            for (int s = 0; s < FWD_KS; ++s) {
+            for (int s = 0; s < KS; ++s) {
                 const int rr = r0 + 4 * s;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
@@ -908,7 +910,7 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_fwd(FwdArgs a, const do
                     if (q >= 0 && q < 4 && l >= an && l < L) {
                         const double sgn = q < 2 ? -1.0 : 1.0;
 #pragma unroll
-                        for (int s = 0; s < FWD_KS; ++s) {
+                        for (int s = 0; s < KS; ++s) {
                             const int rr = r0 + 4 * s;
                             if (s < nk && rr < a.nreg) {
                                 const double2 v = r.init[(size_t)rr * L + l];
@@ -926,7 +928,7 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_fwd(FwdArgs a, const do
 #define S2_FWD_STEP(Q)                                                                                                \
     {                                                                                                                 \
         const int mn = max(min(mb - (Q) - 1, L - 1), mend);                                                           \
-        fwd_step<(Q) & 1>(mb - (Q), nk, ct, ncs, krs, (unsigned)((mn + a.nx) * L) * 8, lc, row_of(mn, G), X, Y, \
+        fwd_step<(Q) & 1, KS>(mb - (Q), nk, ct, ncs, krs, (unsigned)((mn + a.nx) * L) * 8, lc, row_of(mn, G), X, Y, \
                           kp, hq,                                                                                     \
                                 wb + (Q) * OB + ((lane + 4 * (Q)) & 63));                                             \
     }
@@ -941,7 +943,7 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_fwd(FwdArgs a, const do
             const int ml = mb - (DORD - 1);
             if ((ml & (RN - 1)) == 0) {                   // renormalisation of the steps not yet realised
 #pragma unroll
-                for (int s = 0; s < FWD_KS; ++s) {
+                for (int s = 0; s < KS; ++s) {
                     if (s >= nk || ((fast >> s) & 1u)) continue;
                     bool z = true;
 #pragma unroll
@@ -1001,13 +1003,21 @@ hipError_t launch_sweep_inv(hipStream_t st, const InvArgs &a, int nmap, bool one
     const long long nt = (a.nslot + a.merge - 1) / a.merge, wg = nt * a.rt * nmap * a.nrun;
     if (wg > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)wg), block(64 * SW_WAVES);
-    if (pair) {
-        if (one) hipLaunchKernelGGL((k_sweep_inv<true, true>), grid, block, 0, st, a, cot, csc);
-        else hipLaunchKernelGGL((k_sweep_inv<false, true>), grid, block, 0, st, a, cot, csc);
-    } else {
-        if (one) hipLaunchKernelGGL((k_sweep_inv<true, false>), grid, block, 0, st, a, cot, csc);
-        else hipLaunchKernelGGL((k_sweep_inv<false, false>), grid, block, 0, st, a, cot, csc);
-    }
+    auto go = [&](auto *k) { hipLaunchKernelGGL(k, grid, block, 0, st, a, cot, csc); };
+    auto form = [&](auto nch) {
+        constexpr int N = decltype(nch)::value;
+        if (pair && one) go(k_sweep_inv<true, true, N>);
+        else if (pair) go(k_sweep_inv<false, true, N>);
+        else if (one) go(k_sweep_inv<true, false, N>);
+        else go(k_sweep_inv<false, false, N>);
+    };
+    // Blocks of at most one chunk per wave (L <= 64) take the form for that: the same sums in
+    // half the code, without scratch.  The form for four chunks costs 7 us more from its first
+    // instruction on (sweep, us, MI355X, form of four / one: MW L = 2 12.1 / 5.4, L = 5 15.0 /
+    // 7.2, L = 16 14.2 / 7.6, L = 64 spin 2 16.3 / 11.9).  From two chunks on the blocks are
+    // long and there are several.
+    if (a.cb <= SW_WAVES) form(std::integral_constant<int, 1>());
+    else form(std::integral_constant<int, INV_BLK / (8 * SW_WAVES)>());
     S2_LAUNCH_CHECK();
     return hipSuccess;
 }
@@ -1022,13 +1032,19 @@ hipError_t launch_sweep_fwd(hipStream_t st, const FwdArgs &a, int nmap, bool one
     const long long nt = (a.nslot + a.merge - 1) / a.merge, wg = nt * a.rb * nmap * a.nrun;
     if (wg > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)wg), block(64 * SW_WAVES);
-    if (pair) {
-        if (one) hipLaunchKernelGGL((k_sweep_fwd<true, true>), grid, block, 0, st, a, cot, csc, kap);
-        else hipLaunchKernelGGL((k_sweep_fwd<false, true>), grid, block, 0, st, a, cot, csc, kap);
-    } else {
-        if (one) hipLaunchKernelGGL((k_sweep_fwd<true, false>), grid, block, 0, st, a, cot, csc, kap);
-        else hipLaunchKernelGGL((k_sweep_fwd<false, false>), grid, block, 0, st, a, cot, csc, kap);
-    }
+    auto go = [&](auto *k) { hipLaunchKernelGGL(k, grid, block, 0, st, a, cot, csc, kap); };
+    auto form = [&](auto ks) {
+        constexpr int N = decltype(ks)::value;
+        if (pair && one) go(k_sweep_fwd<true, true, N>);
+        else if (pair) go(k_sweep_fwd<false, true, N>);
+        else if (one) go(k_sweep_fwd<true, false, N>);
+        else go(k_sweep_fwd<false, false, N>);
+    };
+    // At most 64 rings (per block: 32 a step over the waves) take the form for two steps, as in
+    // the inverse (us, form of eight steps / two: MW L = 2 13.1 / 5.8, L = 5 16.3 / 7.8, L = 16
+    // 14.9 / 6.4, L = 64 spin 2 24.9 / 16.7).
+    if (a.nk <= FWD_KS_FEW) form(std::integral_constant<int, FWD_KS_FEW>());
+    else form(std::integral_constant<int, FWD_KS>());
     S2_LAUNCH_CHECK();
     return hipSuccess;
 }
