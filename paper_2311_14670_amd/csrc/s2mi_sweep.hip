@@ -1012,10 +1012,9 @@ hipError_t launch_sweep_inv(hipStream_t st, const InvArgs &a, int nmap, bool one
         else go(k_sweep_inv<false, false, N>);
     };
     // Blocks of at most one chunk per wave (L <= 64) take the form for that: the same sums in
-    // half the code, without scratch.  The form for four chunks costs 7 us more from its first
-    // instruction on (sweep, us, MI355X, form of four / one: MW L = 2 12.1 / 5.4, L = 5 15.0 /
-    // 7.2, L = 16 14.2 / 7.6, L = 64 spin 2 16.3 / 11.9).  From two chunks on the blocks are
-    // long and there are several.
+    // half the code, without scratch.  A short block runs that code little more than once, from
+    // top to bottom (sweep, us, MI355X, form of four / one: MW L = 2 12.1 / 5.4, L = 5 15.0 /
+    // 7.2, L = 16 14.2 / 7.6, L = 64 spin 2 14.4 / 12.0).
     if (a.cb <= SW_WAVES) form(std::integral_constant<int, 1>());
     else form(std::integral_constant<int, INV_BLK / (8 * SW_WAVES)>());
     S2_LAUNCH_CHECK();
@@ -1042,7 +1041,7 @@ hipError_t launch_sweep_fwd(hipStream_t st, const FwdArgs &a, int nmap, bool one
     };
     // At most 64 rings (per block: 32 a step over the waves) take the form for two steps, as in
     // the inverse (us, form of eight steps / two: MW L = 2 13.1 / 5.8, L = 5 16.3 / 7.8, L = 16
-    // 14.9 / 6.4, L = 64 spin 2 24.9 / 16.7).
+    // 14.9 / 6.4, L = 64 spin 2 19.8 / 11.5).
     if (a.nk <= FWD_KS_FEW) form(std::integral_constant<int, FWD_KS_FEW>());
     else form(std::integral_constant<int, FWD_KS>());
     S2_LAUNCH_CHECK();
