@@ -84,6 +84,18 @@ __device__ __forceinline__ void renorm(double &e, double &ep, int &E)
     }
 }
 
+// A run's values at the rings and orders that the other run supplies (below) are rounding
+// errors grown like the second solution of the recursion, without bound: at more than 51
+// orders of up to 2^20 each they could overflow, and an infinity times the zeros that stand
+// for those rings in the forward sums is NaN.  Runs of |n| > DROP_AN therefore drop a pair
+// beyond 2^400 every RN orders below |n| (a value that is used is at most 1, e within
+// some 2^10 of it), so nothing passes 2^720.
+constexpr int DROP_AN = 32;
+__device__ __forceinline__ void drop_unstable(double &e, double &ep)
+{
+    if (fmax(fabs(e), fabs(ep)) > 0x1p400) e = ep = 0.0;
+}
+
 // Stable-direction switch for runs with n != 0.  At a ring the descending
 // recursion of d^l_{m,n} grows (is stable) down to about m = n cos(theta); for
 // the run with n cos(theta) > 0 the orders m < ms = ceil(|n cos(theta)|) are

@@ -241,7 +241,10 @@ __global__ __launch_bounds__(64) void k_cut_state(int L, int nreg, int rp, int D
             }
             if (lo < l && (lo & (RN - 1)) == 0)
 #pragma unroll
-                for (int k = 0; k < NR; ++k) renorm(cur[k], prev[k], E[k]);
+                for (int k = 0; k < NR; ++k) {
+                    renorm(cur[k], prev[k], E[k]);
+                    if (FWD && an > DROP_AN && lo < an) drop_unstable(cur[k], prev[k]);
+                }
             m = lo;
         }
 #pragma unroll
@@ -956,6 +959,13 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep_fwd(FwdArgs a, const do
                     }
                     if (__all(z) && ml <= lmin) fast |= 1u << s;
                 }
+                if constexpr (ONE && !PAIRF)              // (two-sided runs: |n| < 8)
+                    if (an > DROP_AN && ml < an) {
+#pragma unroll
+                        for (int s = 0; s < KS; ++s)
+#pragma unroll
+                            for (int g = 0; g < 4; ++g) drop_unstable(X[s][g], Y[s][g]);
+                    }
             }
             __syncthreads();
             ++it;
