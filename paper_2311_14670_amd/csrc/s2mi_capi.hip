@@ -290,7 +290,6 @@ int factor_radices(int n, std::vector<int> &rad)
 struct Staging {
     std::deque<std::vector<double>> d;
     std::deque<std::vector<int>> i;
-    std::deque<std::vector<uint16_t>> u16;
     std::deque<std::vector<long long>> ll;
     std::vector<SweepRun> sr;
 };
@@ -348,23 +347,25 @@ int build_fft(s2_plan_s *P, int n, Staging &stg, hipStream_t st, FftArgs *out)
     }
     f.mix = f.len % 16 == 0 ? 15 : f.len % 8 == 0 ? 7 : 0;
     int rc;
+    // twiddles and, behind them, the bins' places: one upload per length (HEALPix plans have
+    // nside of them)
+    stg.d.emplace_back();
+    std::vector<double> &tab = stg.d.back();
+    host_roots(f.len, &tab);
     if (!f.blue) {
         std::vector<uint16_t> slot(n);
         for (int k = 0; k < n; ++k) {
             const int p = fft_position(f, k);
             slot[k] = (uint16_t)(p ^ ((p >> 3) & f.mix));
         }
-        stg.u16.push_back(std::move(slot));
-        uint16_t *sl;
-        if ((rc = upload(P, &sl, stg.u16.back(), st, "fft bin places"))) return rc;
-        f.slot = sl;
+        tab.resize(2 * (size_t)f.len + ((size_t)n + 3) / 4);
+        std::memcpy(tab.data() + 2 * (size_t)f.len, slot.data(), (size_t)n * sizeof(uint16_t));
     }
-    stg.d.emplace_back();
-    host_roots(f.len, &stg.d.back());
     double *tw;
-    rc = upload(P, &tw, stg.d.back(), st, "fft twiddles");
+    rc = upload(P, &tw, tab, st, "fft twiddles");
     if (rc) return rc;
     f.tw = tw;
+    if (!f.blue) f.slot = reinterpret_cast<const uint16_t *>(tw + 2 * (size_t)f.len);
     if (f.blue) {
         stg.d.emplace_back();
         host_chirp(n, &stg.d.back());
@@ -738,26 +739,39 @@ static int plan_create_impl(s2_plan_t *out, int L, int spin, int N, s2_sampling_
         sr.push_back(SweepRun{r.n, r.sliceA, r.sliceB, 0, ini, nullptr, nullptr});
     }
     // the work tables and, per run, the recursion state at each cut
+    const int *cf_d[2] = {};
+    const int2 *cu_d[2] = {};
     for (int f = 0; f < 2 && prec == S2_FP64; ++f) {
         Work &W = f ? P->fwd : P->inv;
         const int D = f ? FWD_L : 8 * W.cb;
-        if ((rc = upload(P, &W.seg_d, W.seg, st, "work pieces"))) return bail(rc);
-        if ((rc = upload(P, &W.first_d, W.first, st, "work slots"))) return bail(rc);
+        // pieces, cuts, slots and first cuts in one upload
+        stg.i.emplace_back();
+        std::vector<int> &tab = stg.i.back();
+        for (const int4 &g : W.seg) tab.insert(tab.end(), {g.x, g.y, g.z, g.w});
+        for (const int2 &c : W.cuts) tab.insert(tab.end(), {c.x, c.y});
+        tab.insert(tab.end(), W.first.begin(), W.first.end());
+        tab.insert(tab.end(), W.cfirst.begin(), W.cfirst.end());
+        int *tab_d;
+        if ((rc = upload(P, &tab_d, tab, st, "work of the sweeps"))) return bail(rc);
+        W.seg_d = reinterpret_cast<int4 *>(tab_d);
+        cu_d[f] = reinterpret_cast<const int2 *>(tab_d + 4 * W.seg.size());
+        W.first_d = tab_d + 4 * W.seg.size() + 2 * W.cuts.size();
+        cf_d[f] = W.first_d + W.first.size();
         if (W.cuts.empty()) continue;
-        int *cf;
-        int2 *cu;
-        if ((rc = upload(P, &cf, W.cfirst, st, "cuts"))) return bail(rc);
-        if ((rc = upload(P, &cu, W.cuts, st, "cuts"))) return bail(rc);
-        for (size_t ri = 0; ri < P->runs.size(); ++ri) {
+        for (SweepRun &s : sr) {
             double *ck;
             if ((rc = P->dalloc(&ck, W.cuts.size() * D * 3 * (size_t)W.rp, "recursion states"))) return bail(rc);
-            PLANCHK(launch_cut_state(st, f == 1, L, P->nsw, W.rp, D, W.nblk, P->fwd_pair, P->runs[ri].n, P->cot, P->csc,
-                                     P->init[ri], P->kap, cf, cu, ck),
-                    "recursion states");
-            (f ? sr[ri].ckF : sr[ri].ckI) = ck;
+            (f ? s.ckF : s.ckI) = ck;
         }
     }
     if ((rc = upload(P, &P->runs_d, sr, st, "runs"))) return bail(rc);
+    for (int f = 0; f < 2 && prec == S2_FP64; ++f) {
+        const Work &W = f ? P->fwd : P->inv;
+        if (!W.cuts.empty())
+            PLANCHK(launch_cut_state(st, f == 1, L, P->nsw, W.rp, f ? FWD_L : 8 * W.cb, W.nblk, P->fwd_pair, nrun,
+                                     P->runs_d, P->cot, P->csc, P->kap, cf_d[f], cu_d[f]),
+                    "recursion states");
+    }
 
     // S2MI_DEBUG_CHECKS=1: check sum_{|m| <= l} (d^l_{m,n})^2 = 1 (d^l is orthogonal) on
     // sampled rings, for every degree and every run whose partner -n is in the plan,

@@ -54,11 +54,11 @@ hipError_t launch_pack_inv(hipStream_t st, const InvArgs &a, int nmap, bool one,
 hipError_t launch_sweep_inv(hipStream_t st, const InvArgs &a, int nmap, bool one, const double *cot, const double *csc);
 hipError_t launch_sweep_fwd(hipStream_t st, const FwdArgs &a, int nmap, bool one, const double *cot, const double *csc,
                             const double *kap);
-// The recursion state at the cuts of one run's inverse (D degrees per block) or
+// The recursion state at the cuts of the runs' inverse (D degrees per block) or
 // forward (groups of 64 degrees) work: rings [0, rp), zero past nreg.
-hipError_t launch_cut_state(hipStream_t st, bool fwd, int L, int nreg, int rp, int D, int nblk, int par, int n,
-                            const double *cot, const double *csc, const double2 *init, const double *kap,
-                            const int *cfirst, const int2 *cuts, double *ck);
+hipError_t launch_cut_state(hipStream_t st, bool fwd, int L, int nreg, int rp, int D, int nblk, int par, int nrun,
+                            const SweepRun *runs, const double *cot, const double *csc, const double *kap,
+                            const int *cfirst, const int2 *cuts);
 hipError_t launch_init_table(hipStream_t st, int L, int nreg, int n, const double *lsin, const double *lcos,
                              const double *lbin, double2 *init);
 

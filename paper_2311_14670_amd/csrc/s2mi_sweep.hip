@@ -165,12 +165,16 @@ __global__ __launch_bounds__(256) void k_pack_inv(InvArgs a, const double2 *__re
 // no conditions 0.58 / 2.9; four rings, forward 1.0, with conditions 5.4.)
 constexpr int CUT_RINGS = 4;
 template <bool FWD>
-__global__ __launch_bounds__(64) void k_cut_state(int L, int nreg, int rp, int D, int par, int n,
+__global__ __launch_bounds__(64) void k_cut_state(int L, int nreg, int rp, int D, int par,
+                                                  const SweepRun *__restrict__ runs,
                                                   const double *__restrict__ cot, const double *__restrict__ csc,
-                                                  const double2 *__restrict__ init, const double *__restrict__ kap,
-                                                  const int *__restrict__ cfirst, const int2 *__restrict__ cuts,
-                                                  double *__restrict__ ck)
+                                                  const double *__restrict__ kap, const int *__restrict__ cfirst,
+                                                  const int2 *__restrict__ cuts)
 {
+    const SweepRun run = runs[blockIdx.z];
+    const int n = run.n;
+    const double2 *init = run.init;
+    double *ck = const_cast<double *>(FWD ? run.ckF : run.ckI);
     constexpr int NR = FWD ? CUT_RINGS : 1;              // rings r0 .. of a lane
     int r0, b, i, l;
     if constexpr (FWD) {
@@ -990,17 +994,17 @@ hipError_t launch_pack_inv(hipStream_t st, const InvArgs &a, int nmap, bool one,
     return hipSuccess;
 }
 
-hipError_t launch_cut_state(hipStream_t st, bool fwd, int L, int nreg, int rp, int D, int nblk, int par, int n,
-                            const double *cot, const double *csc, const double2 *init, const double *kap,
-                            const int *cfirst, const int2 *cuts, double *ck)
+hipError_t launch_cut_state(hipStream_t st, bool fwd, int L, int nreg, int rp, int D, int nblk, int par, int nrun,
+                            const SweepRun *runs, const double *cot, const double *csc, const double *kap,
+                            const int *cfirst, const int2 *cuts)
 {
     if (rp < nreg || D < 1 || (fwd && D != FWD_L)) return hipErrorInvalidValue;
     if (fwd)
-        hipLaunchKernelGGL(k_cut_state<true>, dim3(nblk, (rp + CUT_RINGS - 1) / CUT_RINGS), dim3(64), 0, st, L, nreg, rp,
-                           D, par, n, cot, csc, init, kap, cfirst, cuts, ck);
+        hipLaunchKernelGGL(k_cut_state<true>, dim3(nblk, (rp + CUT_RINGS - 1) / CUT_RINGS, nrun), dim3(64), 0, st, L,
+                           nreg, rp, D, par, runs, cot, csc, kap, cfirst, cuts);
     else
-        hipLaunchKernelGGL(k_cut_state<false>, dim3((rp + 63) / 64, nblk * D), dim3(64), 0, st, L, nreg, rp, D, par, n,
-                           cot, csc, init, kap, cfirst, cuts, ck);
+        hipLaunchKernelGGL(k_cut_state<false>, dim3((rp + 63) / 64, nblk * D, nrun), dim3(64), 0, st, L, nreg, rp, D, par,
+                           runs, cot, csc, kap, cfirst, cuts);
     S2_LAUNCH_CHECK();
     return hipSuccess;
 }
